@@ -177,10 +177,17 @@ int static_scratch(void** out) {
 // Which kernels score a prompt: the single-read kernel (its hand-off words are in use; *F is its plan), the
 // single-read kernel on the front part of a prompt too long for it and streaming passes on the rest (the
 // same, *F = LP->Ff), two streaming passes (the hand-off words stay untouched; *F is their plan), or the
-// 32x32 two-pass kernels.
-enum { kPathNone = 0, kPathFused = 1, kPathStream = 2, kPathLong = 3 };
+// two passes over all window rows of a KV head at once (neither hand-off words nor a plan: F->BH is 1).
+enum { kPathNone = 0, kPathFused = 1, kPathStream = 2, kPathLong = 3, kPathWide = 4 };
+// (the test hook that limits the resident workgroups is for the single-read kernel's long prompts)
+bool use_wide(int dtype, int D, const ScoreGeom& G) { return g_allow_fused && g_fused_slot_cap == 0 && wide_ok(dtype, D, G); }
 int scoring_path(int dtype, int D, const ScoreGeom& G, bool lse_given, bool allow_blocks, bool allow_long,
                  FusedGeom* F, LongPlan* LP) {
+    if (!lse_given && use_wide(dtype, D, G)) {
+        *F = FusedGeom{};
+        F->BH = 1;
+        return kPathWide;
+    }
     if (!lse_given && g_allow_fused) {
         if (fused_plan(dtype, D, G, F, allow_blocks)) return kPathFused;
         if (allow_long && long_plan(dtype, D, G, LP)) {
@@ -204,7 +211,7 @@ bool layers_table_ok(int dtype, int D, const ScoreGeom& G, int kv_heads_per_laye
     probe.count = G.Hkv / kv_heads_per_layer;
     probe.kv_heads = kv_heads_per_layer;
     if (probe.count < 1 || probe.count > kMaxLayerPtrs) return false;
-    if (path == kPathStream) return true;   // nothing there needs a resident grid
+    if (path == kPathStream || path == kPathWide) return true;   // nothing there needs a resident grid
     // (for a long prompt F is the plan of the front part)
     const hipError_t e = launch_score_fused_layers(dtype, D, probe, path == kPathLong ? LP.Gf : G, F, FusedSync{}, nullptr, nullptr, true);
     if (e != hipSuccess) (void)hipGetLastError();
@@ -290,6 +297,22 @@ int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGe
                          : launch_score_lse(dtype, D, q_win, k_rest, ws.lse, LP.Gr, LP.Fr, ws.vote + LP.front, st, rl)) != hipSuccess)
             return SNAPKV_ERR_HIP;
         stage_done(st, kStagePass2);
+        Gp.NV = G.g;
+        Gp.VB = 1;
+    } else if (path == kPathWide) {
+        ScoreGeom Ge = G;
+        WidePrompt P[kMaxWide];
+        const int count = layers ? layers->count : 1;
+        if (count > kMaxWide) return SNAPKV_ERR_UNSUPPORTED;
+        Ge.Hkv = G.Hkv / count;
+        for (int x = 0; x < count; ++x) {
+            P[x].q = layers ? layers->q[x] : q_win;
+            P[x].k = layers ? layers->k[x] : k;
+            P[x].vote = ws.vote + (int64_t)x * Ge.Hkv * G.g * G.vpitch;
+            P[x].part = ws.stat_part + (int64_t)x * (int64_t)(wide_part_bytes(Ge) / sizeof(float2));
+            P[x].G = &Ge;
+        }
+        if (launch_score_wide(dtype, D, count, P, st) != hipSuccess) return SNAPKV_ERR_HIP;
         Gp.NV = G.g;
         Gp.VB = 1;
     } else if (path == kPathStream) {
@@ -441,11 +464,11 @@ int64_t compress_impl(int dtype, const void* q_win, const void* k, const void* v
     }
     if (g_allow_pool_select && pool_select_ok(Gsel, pool_kind, p, C - W)) {   // pooling and selection in one launch
         bool prepared = false;
-        streaming = path == kPathStream;
+        streaming = path == kPathStream || path == kPathWide;
         if (own_scratch && path != kPathNone) {
             int dev = 0;
             if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) {
-                // the streaming path does not touch the hand-off words
+                // the streaming paths do not touch the hand-off words
                 const int64_t nones = streaming ? 0 : fused_sync_pairs(Fp);
                 now.hkv = Hkv;
                 now.hq = Hq;
@@ -546,18 +569,20 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
     ScoreGeom G[kMaxBatch];
     int64_t nmax = 0;
     size_t per_prompt[kMaxBatch], stats = 0, handoff = 0;   // handoff: bytes of hand-off words per prompt
+    bool wide[kMaxBatch];   // scored by the two-pass kernels, as in a call of its own
     for (int i = 0; i < count; ++i) {
         G[i] = make_geom(L[i], Hq, Hkv, D, W);
         G[i].k_rs = row_bytes;
         G[i].k_hs = (int64_t)row_bytes * L[i];
         FusedGeom F;
         if (!lse_plan(dtype, D, G[i], &F)) return 1;   // more window rows than the one-row-per-head kernels take
-        if (g_allow_fused && fused_plan(dtype, D, G[i], &F)) {   // hand-off words this prompt's launch will use
+        wide[i] = use_wide(dtype, D, G[i]);
+        if (g_allow_fused && !wide[i] && fused_plan(dtype, D, G[i], &F)) {   // hand-off words this prompt's launch will use
             const size_t words = (size_t)fused_sync_pairs(F) * sizeof(unsigned long long);
             handoff = words > handoff ? words : handoff;
         }
         nmax = G[i].n > nmax ? G[i].n : nmax;
-        per_prompt[i] = up(stream_stat_bytes(G[i])) + up(sizeof(float) * (size_t)Hq * W);
+        per_prompt[i] = std::max(up(stream_stat_bytes(G[i])), wide_part_bytes(G[i])) + up(sizeof(float) * (size_t)Hq * W);
         stats += per_prompt[i];
     }
     const int64_t npad = (nmax + 3) & ~(int64_t)3;
@@ -612,13 +637,19 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
         wsp[i].fused = handoff_p + handoff * i;
         wsp[i].vote = votes_p + (size_t)i * Hq * (size_t)npad;
         wsp[i].stat_part = reinterpret_cast<float2*>(sp);
-        wsp[i].lse = reinterpret_cast<float*>(sp + up(stream_stat_bytes(G[i])));
+        wsp[i].lse = reinterpret_cast<float*>(sp + per_prompt[i] - up(sizeof(float) * (size_t)Hq * W));
         sp += per_prompt[i];
         G[i].vpitch = npad;
     }
-    int rest[kMaxBatch], nrest = count;
-    for (int i = 0; i < count; ++i) rest[i] = i;
-    std::sort(rest, rest + count, [&](int a, int b) { return L[a] != L[b] ? L[a] > L[b] : a < b; });
+    int rest[kMaxBatch], nrest = 0, nwide = 0;
+    WidePrompt WP[kMaxBatch];
+    static_assert(kMaxBatch <= kMaxWide, "the prompts of a batch that take the two-pass kernels share their launches");
+    for (int i = 0; i < count; ++i) {
+        if (wide[i]) WP[nwide++] = WidePrompt{q_win[i], k[i], wsp[i].vote, wsp[i].stat_part, &G[i]};
+        else rest[nrest++] = i;
+    }
+    if (nwide > 0 && launch_score_wide(dtype, D, nwide, WP, st) != hipSuccess) return SNAPKV_ERR_HIP;
+    std::sort(rest, rest + nrest, [&](int a, int b) { return L[a] != L[b] ? L[a] > L[b] : a < b; });
     while (nrest > 0) {
         ScoreGeom Gr[kMaxBatch];
         FusedGeom Fr[kMaxBatch];

@@ -2,6 +2,8 @@
 // translation units).
 #include "snapkv_internal.h"
 
+#include <algorithm>
+
 namespace snapkv {
 
 ScoreGeom make_geom(int64_t L, int Hq, int Hkv, int D, int W) {
@@ -40,7 +42,7 @@ size_t workspace_layout(const ScoreGeom& G, Workspace* ws, void* base) {
     // one vote row per query head, or per 32-row block of a window of 64, 96, ... rows
     const size_t vote = align_up(sizeof(float) * (size_t)G.Hkv * G.g * G.BH * (size_t)(G.n > 0 ? G.n : 1));
     const size_t score = align_up(sizeof(float) * (size_t)Hsel * (size_t)(G.n > 0 ? G.n : 1));
-    const size_t stat = stream_stat_bytes(G);
+    const size_t stat = std::max(stream_stat_bytes(G), wide_part_bytes(G));   // one scoring path per call
     const size_t lse = align_up(sizeof(float) * (size_t)G.Hkv * G.g * G.W);
     const size_t logit = long_logit_bytes(G);
     const size_t off = counters + fused;

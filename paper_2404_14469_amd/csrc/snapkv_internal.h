@@ -157,6 +157,20 @@ hipError_t launch_score_fused(int dtype, int D, const void* q, const void* k, co
 // hipErrorCooperativeLaunchTooLarge when this form of the kernel cannot keep the plan's grid resident.
 hipError_t launch_score_fused_layers(int dtype, int D, const ScoreLayers& SL, const ScoreGeom& G, const FusedGeom& F,
                                      const FusedSync& S, float* vote, hipStream_t st, bool probe_only = false);
+// The two-pass kernels for KV heads met by 64 or more window rows (snapkv_wide.hip): two-byte element types,
+// windows of at most 128 rows.  One vote row per query head, whatever the window.  Up to kMaxWide prompts or
+// layers of one model share the two launches (equal heads, window, row stride); paged K: one only.
+constexpr int kMaxWide = 32;
+struct WidePrompt {
+    const void* q;
+    const void* k;
+    float* vote;             // [Hkv * g][G->vpitch]
+    float2* part;            // wide_part_bytes(*G)
+    const ScoreGeom* G;
+};
+bool wide_ok(int dtype, int D, const ScoreGeom& G);
+size_t wide_part_bytes(const ScoreGeom& G);
+hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st);
 unsigned read_sync_timeouts();
 bool reset_sync_timeouts();     // (test hook) both synchronise the device
 bool reset_select_timeouts();

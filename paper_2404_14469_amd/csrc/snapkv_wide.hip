@@ -1,0 +1,725 @@
+// Window scoring and voting in two streaming passes for prompts whose KV heads are met by many window
+// rows (Listing 1: the compute_attn call and the column sum; Eq. 1): grouped-query heads and wide windows.
+//
+// The single-read kernel (snapkv_fused.hip) keeps every exponential in registers until its row's normaliser
+// is known, so a wave holds 32 rows x 64 keys, a KV head with 128 window rows is cut into four parts, every part
+// streams the head's keys through the compute units again, and two thirds of the vector instructions go to the
+// row maxima, hand-offs and votes of only 64 keys.  Here nothing is kept: all 128 rows of a block meet every key
+// of a round while it is on chip, first for the row statistics (wide_stats), then, once these are merged, for
+// the votes (wide_votes).  K is read from memory once per pass whatever the number of query heads, and a logit
+// costs a multiply-add, an exponential and an addition (or a multiply-add) per pass.
+//
+//   * The window rows of a KV head form blocks of whole query heads, at most eight 16-row units each; a unit of
+//     work is one block.  A wave owns 32 of the block's rows, its Q in registers as MFMA fragments.
+//   * The keys of a unit are cut into at most 64 slices of RPS rounds of 128 keys.  The slice length depends on the
+//     prompt length alone, so a head's result does not depend on which other heads share the launch.
+//   * A round's keys pass through LDS (landing registers -> two buffers, one barrier a round), where four groups
+//     of waves x two parts of the keys read them as fragments; the next round is on its way meanwhile.
+//   * A persistent grid of two workgroups per compute unit walks the slices of all units (of all prompts or layers of
+//     the call) in order, a contiguous run of whole slices each; a launch whose slices all find a place at once
+//     has a workgroup per slice.
+//
+// What bounds it: matrix and vector instructions of a SIMD hardly overlap on this part (16x16x32 MFMAs and
+// multiply-adds measured together take 0.9 of the sum of both), so a pass costs their sum: 16 + 15 cycles per 64
+// logits and about 10 of overhead, 320 us for the 1.03e9 logits of 32 grouped-query layers of 31337 keys, against
+// 340 us that 2.05 GB of keys take at 6.1 TB/s; together 415 us (wide_stats) and 488 us (wide_votes) where the
+// single-read kernel took 1218 us.  Tried on the way: all 128 rows in one wave with Q in LDS (two waves per SIMD,
+// 425 + 512 us, and 240 registers); the rows' references from row maxima (a longer prologue: 24 against 19 us per
+// pass at 28471 keys, 8 heads).  At 131072 keys, W = 64 (two blocks per head): 95 + 106 us against 277 us.
+//
+// The row reference.  Exponentials are taken relative to the row's logit with the prompt's first key instead of a
+// running maximum: 2^(s - ref) loses no precision whatever ref is, and terms that underflow are far below the row's
+// largest.  Where a logit exceeds ref by so much (2^128) that the sum leaves the fp32 range, wide_votes finds
+// the true maxima from all keys of the unit (rows_from_keys).
+//
+// MFMA layout: that of snapkv_fused.hip (16x16x32, lane l: row / column l % 16, contraction slice l / 16;
+// accumulator register r is row (l / 16) * 4 + r, column l % 16; the 16-byte pieces 4p + l / 16 of a row).
+#include "snapkv_internal.h"
+
+#include <algorithm>
+
+namespace snapkv {
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 wbf16x8;
+typedef __attribute__((ext_vector_type(8))) _Float16 wf16x8;
+typedef __attribute__((ext_vector_type(4))) float wf32x4;
+
+struct w_bf16 {};
+struct w_f16 {};
+
+constexpr int kWaves = 8;                    // waves per workgroup, two workgroups per compute unit
+constexpr int kThreads = kWaves * 64;
+constexpr int kRound = kWaves * 16;          // keys of a round: every wave brings one 16-key tile to LDS
+constexpr int kSlices = 64;                  // slices per unit at most
+constexpr int kWaveRows = 2;                 // 16-row units of a wave
+constexpr int RUW = 8;                       // 16-row units of a block
+// Window rows of a KV head (in whole 16-row units) times keys from which the two passes beat the single-read kernel.
+// Microseconds per call, 32/8 heads of 128 in bf16, this path / the single-read kernel, one layer and four in one call:
+//   W = 32 (128 rows):  8192 keys 51 / 45, 71 / 73;  16384: 57 / 55, 93 / 105;  20000: 60 / 70, 110 / 167;
+//                      40001: 75 / 108, 194 / 323;  131072: 141 / 182, 483 / 632
+//   W = 64 (256 rows):  8192: 57 / 53, 91 / 104;  10007: 65 / 73, 100 / 169;  28471: 85 / 110, 189 / 320;
+//                      131072: 206 / 314, 785 / 1167
+// With 64 rows (W = 16 there, or W = 64 and a head each) the single-read kernel is faster at every length but the
+// few that leave it compute units idle, so those do not come here.
+constexpr int64_t kMinRowKeys = 9 << 18;
+constexpr int64_t kMaxRounds = 1 << 26;      // rounds of one prompt at most (kMaxWide of them are counted in 32 bits)
+
+template <int D> struct KFrag {
+    static constexpr int NP = D / 32;        // 16-byte pieces per lane and row (2-byte elements)
+    uint4 v[NP];
+};
+
+__device__ __forceinline__ wf32x4 mma16(w_bf16, uint4 a, uint4 b, wf32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(wbf16x8, a), __builtin_bit_cast(wbf16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ wf32x4 mma16(w_f16, uint4 a, uint4 b, wf32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(wf16x8, a), __builtin_bit_cast(wf16x8, b), c, 0, 0, 0);
+}
+template <typename T, int D>
+__device__ __forceinline__ wf32x4 logits16(const KFrag<D>& q, const KFrag<D>& k) {
+    wf32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = 0; p < KFrag<D>::NP; ++p) acc = mma16(T{}, q.v[p], k.v[p], acc);
+    return acc;
+}
+
+template <int CTRL> __device__ __forceinline__ float wdpp(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lanes16_max(float x) {
+    x = fmaxf(x, wdpp<0xB1>(x));
+    x = fmaxf(x, wdpp<0x4E>(x));
+    x = fmaxf(x, wdpp<0x141>(x));
+    return fmaxf(x, wdpp<0x140>(x));
+}
+__device__ __forceinline__ float lanes16_sum(float x) {
+    x += wdpp<0xB1>(x);
+    x += wdpp<0x4E>(x);
+    x += wdpp<0x141>(x);
+    return x + wdpp<0x140>(x);
+}
+
+// Orders LDS traffic only: the K rounds in flight are not waited for.
+__device__ __forceinline__ void lds_meet() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// One prompt (or layer) of a launch.
+struct WideEntry {
+    const char* q;
+    const char* k;
+    float* vote;
+    float2* part;        // [units][NS][RUW * 16] per slice and row: (reference, sum of 2^(s - reference))
+    int64_t k_hs;        // bytes between the K rows of consecutive KV heads
+    int64_t vpitch;      // floats between vote rows
+    unsigned round_begin; // rounds of the entries before this one
+    int L, n, RPS, NS, units;
+};
+template <int N> struct WideArgs {   // N: 1 or kMaxWide (a single prompt's launch has little to fetch before its first load)
+    int count, direct, g, W, UH, hb, nblk;   // hb query heads per block, nblk blocks per KV head, UH row units per query head
+    float c2;
+    int64_t k_rs;
+    const int32_t* table;            // paged K (one entry only): see ScoreGeom
+    int page;
+    int64_t pages, row0;
+    unsigned rounds;                 // of all entries
+    WideEntry e[N];
+};
+
+// Where a workgroup stands in the launch's sequence of rounds (all wave-uniform).
+struct Cursor {
+    int e, u, sl, rd;                // entry, unit, slice of the unit, round of the slice
+    int L, n, RPS, NS, units;
+    const char* kb;                  // K rows of the unit's head
+};
+
+template <int N> __device__ __forceinline__ void enter(const WideArgs<N>& A, Cursor& c) {
+    const WideEntry& E = A.e[c.e];
+    c.L = E.L;
+    c.n = E.n;
+    c.RPS = E.RPS;
+    c.NS = E.NS;
+    c.units = E.units;
+    c.kb = E.k + (int64_t)(c.u / A.nblk) * E.k_hs;
+}
+
+// First round at or after `r` at which a slice begins.
+template <int N> __device__ __forceinline__ unsigned slice_start(const WideArgs<N>& A, unsigned r) {
+    if (r >= A.rounds) return A.rounds;
+    int e = 0;
+    if constexpr (N > 1)
+        for (int i = 1; i < A.count; ++i)
+            if (r >= A.e[i].round_begin) e = i;
+    const unsigned in = r - A.e[e].round_begin, rps = (unsigned)A.e[e].RPS;
+    return A.e[e].round_begin + (in + rps - 1) / rps * rps;
+}
+// The workgroup's stretch of rounds: equal shares, moved to the next slice's start.
+template <int N> __device__ __forceinline__ unsigned share(const WideArgs<N>& A, unsigned wg) {
+    return slice_start(A, (unsigned)((uint64_t)A.rounds * wg / gridDim.x));
+}
+
+template <int N> __device__ __forceinline__ Cursor cursor_at(const WideArgs<N>& A, unsigned r) {
+    Cursor c;
+    c.e = 0;
+    if constexpr (N > 1)
+        for (int i = 1; i < A.count; ++i)
+            if (r >= A.e[i].round_begin) c.e = i;
+    const WideEntry& E = A.e[c.e];
+    const unsigned in = (r - E.round_begin) / (unsigned)E.RPS;   // r is the start of a slice
+    c.u = (int)(in / (unsigned)E.NS);
+    c.sl = (int)(in % (unsigned)E.NS);
+    c.rd = 0;
+    enter(A, c);
+    return c;
+}
+
+// Where the workgroup starts and how many rounds are its own.  A launch whose slices all find a place at once has a
+// workgroup per slice (grid: slices of a unit x units).
+template <int N> __device__ __forceinline__ Cursor begin_share(const WideArgs<N>& A, int& rounds) {
+    if (N == 1 && A.direct) {
+        Cursor c;
+        c.e = 0;
+        c.u = (int)blockIdx.y;
+        c.sl = (int)blockIdx.x;
+        c.rd = 0;
+        enter(A, c);
+        rounds = c.RPS;
+        return c;
+    }
+    const unsigned r0 = share(A, blockIdx.x), r1 = share(A, blockIdx.x + 1);
+    rounds = (int)(r1 - r0);
+    return cursor_at(A, r0 < A.rounds ? r0 : 0u);
+}
+
+// The next round; stays on the launch's last one.  Returns whether the unit changed.
+template <int N> __device__ __forceinline__ bool advance(const WideArgs<N>& A, Cursor& c) {
+    if (++c.rd < c.RPS) return false;
+    if (c.sl + 1 < c.NS) {
+        ++c.sl;
+        c.rd = 0;
+        return false;
+    }
+    if (c.u + 1 < c.units) {
+        ++c.u;
+    } else if (N > 1 && c.e + 1 < A.count) {
+        ++c.e;
+        c.u = 0;
+    } else {
+        --c.rd;
+        return false;
+    }
+    c.sl = c.rd = 0;
+    enter(A, c);
+    return true;
+}
+
+// The workgroup's waves, lanes and K stream; shared by both passes.
+template <typename T, int D, bool PAGED, int N> struct WideWave {
+    static constexpr int NP = KFrag<D>::NP;
+    static constexpr int R = RUW * 16;
+    static constexpr int GROUPS = RUW / kWaveRows;      // groups of 32 window rows
+    static constexpr int PARTS = kWaves / GROUPS;       // parts of a round's keys; a wave meets one part with one group
+    static constexpr int TILES = kWaves / PARTS;        // 16-key tiles of a part
+    static_assert(TILES == 4, "the exchange of the votes is written for four tiles");
+    const WideArgs<N>& A;
+    const int tid, lane, n16, kg, w, rg, kp;
+    // paged K: the page id the next request uses, asked for one round ahead of it
+    int32_t page_id = 0;
+    int in_page = 0;
+
+    __device__ __forceinline__ WideWave(const WideArgs<N>& a)
+        : A(a), tid(threadIdx.x), lane(threadIdx.x & 63), n16(threadIdx.x & 15), kg((threadIdx.x & 63) >> 4),
+          w(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)), rg(w % GROUPS), kp(w / GROUPS) {}
+
+    __device__ __forceinline__ int64_t round_key(const Cursor& c) const { return ((int64_t)c.sl * c.RPS + c.rd) * kRound; }
+    __device__ __forceinline__ int64_t row_of(const Cursor& c, int64_t j) const {   // keys past the end: the last row
+        j = j < c.L ? j : c.L - 1;
+        if constexpr (PAGED) j = physical_row(A.table, A.page, A.pages, j + A.row0);
+        return j;
+    }
+    __device__ __forceinline__ void load_row(KFrag<D>& f, const Cursor& c, int64_t row) const {
+        const char* p = c.kb + row * A.k_rs + kg * 16;
+#pragma unroll
+        for (int x = 0; x < NP; ++x) f.v[x] = *reinterpret_cast<const uint4*>(p + 64 * x);
+    }
+    __device__ __forceinline__ void ask_page(const Cursor& c) {
+        if constexpr (PAGED) {
+            int64_t j = round_key(c) + w * 16 + n16;
+            j = (j < c.L ? j : c.L - 1) + A.row0;
+            page_id = A.table[j / A.page];
+            in_page = (int)(j % A.page);
+        }
+    }
+    // This wave's tile of the cursor's round, and the cursor moved on.  Unconditional (see row_of).
+    __device__ __forceinline__ KFrag<D> request(Cursor& c) {
+        KFrag<D> f;
+        const Cursor at = c;
+        advance(A, c);
+        int64_t row;
+        if constexpr (PAGED) {
+            int64_t pg = page_id;
+            pg = pg < 0 ? 0 : (pg >= A.pages ? A.pages - 1 : pg);
+            row = pg * A.page + in_page;
+            ask_page(c);
+        } else {
+            row = row_of(at, round_key(at) + w * 16 + n16);
+        }
+        load_row(f, at, row);
+        __builtin_amdgcn_sched_barrier(0);
+        return f;
+    }
+    // The wave's Q rows (MFMA fragments).  Padding rows repeat a valid one and are ignored later.
+    __device__ __forceinline__ void load_q(KFrag<D> (&q)[kWaveRows], const Cursor& c) const {
+        const WideEntry& E = A.e[c.e];
+        const int kv = c.u / A.nblk, blk = c.u % A.nblk;
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i) {
+            const int ru = rg * kWaveRows + i;
+            int head = blk * A.hb + ru / A.UH, row = (ru % A.UH) * 16 + n16;
+            head = head < A.g ? head : A.g - 1;
+            row = row < A.W ? row : A.W - 1;
+            const char* p = E.q + (((int64_t)kv * A.g + head) * A.W + row) * (D * 2) + kg * 16;
+#pragma unroll
+            for (int x = 0; x < NP; ++x) q[i].v[x] = *reinterpret_cast<const uint4*>(p + 64 * x);
+        }
+    }
+    // Prompt-phase causal mask of the 16 keys from j0 on against row unit i of the wave: row x does not see keys
+    // after n + x (which for a real row covers the keys past the end; what padding rows hold is ignored).
+    __device__ __forceinline__ void mask(wf32x4& a, int64_t j0, int i, const Cursor& c) const {
+        const int d = (int)(j0 - c.n) + n16 - kg * 4 - ((rg * kWaveRows + i) % A.UH) * 16;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (d > r) a[r] = -INFINITY;
+    }
+    __device__ __forceinline__ void keep(uint4* buf, const KFrag<D>& f) const {   // the wave's tile into the round's buffer
+#pragma unroll
+        for (int x = 0; x < NP; ++x) buf[(w * NP + x) * 64 + lane] = f.v[x];
+    }
+    __device__ __forceinline__ void tile(KFrag<D>& f, const uint4* buf, int t) const {   // tile t of the wave's part
+#pragma unroll
+        for (int x = 0; x < NP; ++x) f.v[x] = buf[((kp * TILES + t) * NP + x) * 64 + lane];
+    }
+};
+
+template <typename T, int D, bool PAGED, int N>
+__global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
+    using Wv = WideWave<T, D, PAGED, N>;
+    constexpr int R = Wv::R, TILES = Wv::TILES, PARTS = Wv::PARTS;
+    __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];                      // K of two rounds as MFMA fragments
+    __shared__ __attribute__((aligned(16))) float sm_ref[2][R];          // the rows' references
+    __shared__ __attribute__((aligned(16))) float sm_sum[2][PARTS][R];   // per part: the slice's sums relative to them
+    Wv W(A);
+    int rounds;
+    Cursor cc = begin_share(A, rounds), pc = cc;
+    if (rounds <= 0) return;
+    KFrag<D> q[kWaveRows], S;
+    float z[kWaveRows][4], ref[kWaveRows][4];
+
+    auto reference = [&](float m) __attribute__((always_inline)) { return m == -INFINITY ? 0.f : m; };
+    // A unit begins: the wave's Q rows, and the rows' references, their logits with the prompt's first key (which every
+    // row sees): all lanes bring that key, so that a row's sixteen lanes hold the same number.
+    auto ask_unit = [&](KFrag<D>& f) __attribute__((always_inline)) {
+        W.load_q(q, cc);
+        W.load_row(f, cc, W.row_of(cc, 0));
+    };
+    auto begin_unit = [&](const KFrag<D>& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i) {
+            const wf32x4 a = logits16<T, D>(q[i], f);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                ref[i][r] = reference(a[r] * A.c2);
+                z[i][r] = 0.f;
+            }
+        }
+    };
+    int par = 0;                         // which half of sm_ref and sm_sum the current slice uses
+    float2* pending = nullptr;           // where the pairs of the slice before go, once all waves have left theirs
+    auto store_slice = [&](int half) __attribute__((always_inline)) {
+        if (W.tid < R) {                 // fixed order over the parts
+            float m = sm_ref[half][W.tid], s = 0.f;
+#pragma unroll
+            for (int v = 0; v < PARTS; ++v) s += sm_sum[half][v][W.tid];
+            if (s > 0x1p60f) {           // keep the reference within reach of the row's largest logit
+                m += 64.f;
+                s *= 0x1p-64f;
+            }
+            pending[W.tid] = make_float2(m, s);
+        }
+        pending = nullptr;
+    };
+
+    KFrag<D> first;
+    W.ask_page(pc);
+    ask_unit(first);
+    S = W.request(pc);
+    begin_unit(first);
+    int left = rounds;
+    // A round: its keys go from the landing registers to LDS, the next round is requested, and every wave meets its
+    // part of the keys with its rows.
+    for (int half = 0;; half ^= 1) {
+        const uint4* const buf = kbuf[half];
+        W.keep(kbuf[half], S);
+        S = W.request(pc);
+        lds_meet();
+        if (pending) store_slice(par ^ 1);
+        const int64_t j0 = W.round_key(cc) + W.kp * (TILES * 16);
+        const bool special = j0 + TILES * 16 > cc.n;   // window columns or keys past the end among the wave's
+        float y[kWaveRows][4];           // the round's sums
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            KFrag<D> f;
+            W.tile(f, buf, t);
+#pragma unroll
+            for (int i = 0; i < kWaveRows; ++i) {
+                wf32x4 a = logits16<T, D>(q[i], f);
+                if (special) W.mask(a, j0 + t * 16, i, cc);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float x = __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -ref[i][r]));
+                    y[i][r] = t == 0 ? x : y[i][r] + x;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);   // (one tile at a time: more do not fit the registers)
+        }
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[i][r] += y[i][r];
+        --left;
+        if (cc.rd + 1 == cc.RPS) {       // the slice's last round
+#pragma unroll
+            for (int i = 0; i < kWaveRows; ++i) {
+                float y[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) y[r] = lanes16_sum(z[i][r]);
+                if (W.n16 == 0) {
+                    const int at = (W.rg * kWaveRows + i) * 16 + W.kg * 4;
+                    *reinterpret_cast<float4*>(&sm_sum[par][W.kp][at]) = make_float4(y[0], y[1], y[2], y[3]);
+                    if (W.kp == 0) *reinterpret_cast<float4*>(&sm_ref[par][at]) = make_float4(ref[i][0], ref[i][1], ref[i][2], ref[i][3]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kWaveRows; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[i][r] = 0.f;
+            pending = A.e[cc.e].part + ((int64_t)cc.u * cc.NS + cc.sl) * R;
+            par ^= 1;
+        }
+        if (left <= 0) break;
+        if (advance(A, cc)) {
+            ask_unit(first);
+            begin_unit(first);
+        }
+    }
+    lds_meet();
+    store_slice(par ^ 1);                // (a workgroup's share ends with a slice)
+}
+
+template <typename T, int D, bool PAGED, int N>
+__global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
+    using Wv = WideWave<T, D, PAGED, N>;
+    constexpr int R = Wv::R, TILES = Wv::TILES, SUB = kThreads / R;   // SUB threads share a row in the merge of its slices
+    __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];
+    __shared__ float sm_v[2][RUW][kRound];                            // sums over the rows of a row unit, per key
+    __shared__ float2 sm[SUB][R];
+    __shared__ __attribute__((aligned(16))) float2 smf[R];
+    __shared__ int sm_over;                                           // a row's sum left the fp32 range
+    Wv W(A);
+    int rounds;
+    Cursor cc = begin_share(A, rounds), pc = cc;
+    if (rounds <= 0) return;
+    KFrag<D> q[kWaveRows], S;
+    W.ask_page(pc);
+    S = W.request(pc);
+
+    float mref[kWaveRows][4], wgt[kWaveRows][4];   // the rows' reference and 1 / sum (padding rows: +inf and 0)
+    // (reference, sum) pairs merged in a balanced tree (fixed order, few roundings)
+    auto fold = [](const auto& y, float& m, float& s) __attribute__((always_inline)) {
+        constexpr int n = sizeof(y) / sizeof(float2);
+        float t[n];
+        m = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < n; ++i) m = fmaxf(m, y[i].y != 0.f ? y[i].x : -INFINITY);
+#pragma unroll
+        for (int i = 0; i < n; ++i) t[i] = y[i].y != 0.f ? y[i].y * __builtin_amdgcn_exp2f(y[i].x - m) : 0.f;
+#pragma unroll
+        for (int d = 1; d < n; d <<= 1)
+#pragma unroll
+            for (int i = 0; i + d < n; i += 2 * d) t[i] += t[i + d];
+        s = t[0];
+    };
+    // A row some of whose logits lie too far above its reference: the unit's rows with their true maxima, from all of
+    // its keys, leaving smf as the merge below does.  Every workgroup of the unit does the same.
+    auto rows_from_keys = [&]() __attribute__((always_inline)) {
+        Cursor c = cc;
+        float m[kWaveRows][4], s[kWaveRows][4];
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m[i][r] = -INFINITY, s[i][r] = 0.f;
+        for (int pass = 0; pass < 2; ++pass) {   // the wave's keys: first the maxima, then the sums
+#pragma clang loop unroll(disable)
+            for (int x = 0; x < c.NS * c.RPS * TILES; ++x) {
+                const int64_t j0 = (int64_t)(x / TILES) * kRound + (W.kp * TILES + x % TILES) * 16;
+                KFrag<D> f;
+                W.load_row(f, c, W.row_of(c, j0 + W.n16));
+#pragma unroll
+                for (int i = 0; i < kWaveRows; ++i) {
+                    wf32x4 a = logits16<T, D>(q[i], f);
+                    W.mask(a, j0, i, c);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (pass == 1) s[i][r] += __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -m[i][r]));
+                        else m[i][r] = fmaxf(m[i][r], a[r]);
+                    }
+                }
+            }
+            if (pass == 0)
+#pragma unroll
+                for (int i = 0; i < kWaveRows; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        m[i][r] = lanes16_max(m[i][r]) * A.c2;
+                        if (m[i][r] == -INFINITY) m[i][r] = 0.f;
+                    }
+        }
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float sum = lanes16_sum(s[i][r]);
+                if (W.n16 == 0) sm[W.kp][(W.rg * kWaveRows + i) * 16 + W.kg * 4 + r] = make_float2(m[i][r], sum);
+            }
+        lds_meet();
+        if (W.tid < R && smf[W.tid].x != INFINITY) {   // (padding rows stay as they are)
+            float2 y[Wv::PARTS];
+            float mm, ss;
+#pragma unroll
+            for (int i = 0; i < Wv::PARTS; ++i) y[i] = sm[i][W.tid];
+            fold(y, mm, ss);
+            smf[W.tid] = make_float2(mm, 1.0f / ss);
+        }
+        lds_meet();
+    };
+    auto begin_unit = [&]() __attribute__((always_inline)) {            // the unit's slices merged in a fixed order, and the wave's Q rows
+        const int row = W.tid % R, sub = W.tid / R;
+        const float2* src = A.e[cc.e].part + (int64_t)cc.u * cc.NS * R + row;
+        float m = -INFINITY, s = 0.f;
+#pragma clang loop unroll(disable)
+        for (int s0 = sub; s0 < cc.NS; s0 += 8 * SUB) {   // eight slices' pairs in flight at a time
+            float2 x[9];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int sl = s0 + i * SUB;
+                x[i] = sl < cc.NS ? src[(int64_t)sl * R] : make_float2(-INFINITY, 0.f);
+            }
+            x[8] = make_float2(m, s);
+            fold(x, m, s);
+        }
+        sm[sub][row] = make_float2(m, s);
+        if (W.tid == 0) sm_over = 0;
+        W.load_q(q, cc);
+        lds_meet();
+        if (W.tid < R) {
+            float2 y[SUB];
+#pragma unroll
+            for (int i = 0; i < SUB; ++i) y[i] = sm[i][W.tid];
+            fold(y, m, s);
+            const int ru = W.tid >> 4, blk = cc.u % A.nblk;
+            const bool real = ru / A.UH < A.hb && blk * A.hb + ru / A.UH < A.g && (ru % A.UH) * 16 + (W.tid & 15) < A.W && s > 0.f;
+            smf[W.tid] = real ? make_float2(m, 1.0f / s) : make_float2(INFINITY, 0.f);
+            if (real && s == INFINITY) sm_over = 1;
+        }
+        lds_meet();
+        if (sm_over) rows_from_keys();
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i) {
+            const float4* f4 = reinterpret_cast<const float4*>(&smf[(W.rg * kWaveRows + i) * 16 + W.kg * 4]);
+            const float4 a = f4[0], b = f4[1];
+            mref[i][0] = a.x, wgt[i][0] = a.y, mref[i][1] = a.z, wgt[i][1] = a.w;
+            mref[i][2] = b.x, wgt[i][2] = b.y, mref[i][3] = b.z, wgt[i][3] = b.w;
+        }
+    };
+    begin_unit();
+
+    // The votes of the round before: the row units of every query head added up and stored.
+    float* pending = nullptr;            // its first key in the first query head's vote row
+    int64_t pend_pitch = 0;
+    int pend_keys = 0, pend_heads = 0;
+    auto store_votes = [&](int half) __attribute__((always_inline)) {
+        const int key = W.tid % kRound;
+        if (key < pend_keys)
+            for (int h = W.tid / kRound; h < pend_heads; h += kThreads / kRound) {
+                float s = sm_v[half][h * A.UH][key];
+                for (int u = 1; u < A.UH; ++u) s += sm_v[half][h * A.UH + u][key];
+                // (device scope: see the vote stores of the single-read kernel)
+                __hip_atomic_store(pending + (int64_t)h * pend_pitch + key, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+    };
+    int left = rounds;
+    for (int half = 0;; half ^= 1) {
+        W.keep(kbuf[half], S);
+        S = W.request(pc);
+        lds_meet();
+        if (pending) store_votes(half ^ 1);
+        float v[kWaveRows][TILES];
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            KFrag<D> f;
+            W.tile(f, kbuf[half], t);
+#pragma unroll
+            for (int i = 0; i < kWaveRows; ++i) {
+                const wf32x4 a = logits16<T, D>(q[i], f);
+                float s = 0.f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s = fmaf(__builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -mref[i][r])), wgt[i][r], s);
+                v[i][t] = s;
+            }
+            if (t & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        // sums over the four lanes of a column: pairs of tiles share the exchanges, so that a lane ends with one tile's
+        auto halves = [](float a, float b) __attribute__((always_inline)) {   // lanes 0-31: a of lane l and l + 32, lanes 32-63: b
+            const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+            return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+        };
+        auto quarters = [](float a, float b) __attribute__((always_inline)) {   // even rows of 16 lanes: a of both rows of the half, odd ones: b
+            const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+            return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+        };
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i) {
+            float* dst = &sm_v[half][W.rg * kWaveRows + i][W.kp * (TILES * 16)];
+            dst[((W.kg >> 1) + 2 * (W.kg & 1)) * 16 + W.n16] = quarters(halves(v[i][0], v[i][1]), halves(v[i][2], v[i][3]));
+        }
+        const WideEntry& E = A.e[cc.e];
+        const int kv = cc.u / A.nblk, h0 = (cc.u % A.nblk) * A.hb;
+        const int64_t k0 = W.round_key(cc);
+        pending = E.vote + ((int64_t)kv * A.g + h0) * E.vpitch + k0;
+        pend_pitch = E.vpitch;
+        pend_keys = (int)(cc.n - k0 < kRound ? cc.n - k0 : kRound);
+        pend_heads = A.g - h0 < A.hb ? A.g - h0 : A.hb;
+        --left;
+        if (left <= 0) break;
+        if (advance(A, cc)) begin_unit();
+    }
+    lds_meet();
+    store_votes((rounds & 1) ^ 1);
+}
+
+struct Blocks {
+    int UH, hb, nblk;
+};
+bool row_blocks(const ScoreGeom& G, Blocks* b) {
+    b->UH = (G.W + 15) / 16;
+    if (b->UH > RUW || G.g * b->UH < RUW) return false;   // (at least 128 window rows per KV head)
+    const int most = std::min(G.g, RUW / b->UH);
+    b->nblk = (G.g + most - 1) / most;
+    b->hb = (G.g + b->nblk - 1) / b->nblk;   // blocks of about equal size
+    return true;
+}
+
+int rounds_per_slice(int64_t L) { return (int)((L + (int64_t)kRound * kSlices - 1) / ((int64_t)kRound * kSlices)); }
+int slices_of(int64_t L) {
+    const int64_t keys = (int64_t)rounds_per_slice(L) * kRound;
+    return (int)((L + keys - 1) / keys);
+}
+
+int wide_cus() {
+    static int cached[64] = {0};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    if (cached[dev] == 0) {
+        int n = 0;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+        cached[dev] = n;
+    }
+    return cached[dev];
+}
+
+template <typename T, int D, bool PAGED, int N>
+hipError_t launch_both(const WideArgs<kMaxWide>& all, dim3 grid, hipStream_t st) {
+    WideArgs<N> A;
+    A.count = all.count, A.direct = all.direct, A.g = all.g, A.W = all.W, A.UH = all.UH, A.hb = all.hb, A.nblk = all.nblk;
+    A.c2 = all.c2, A.k_rs = all.k_rs, A.table = all.table, A.page = all.page, A.pages = all.pages, A.row0 = all.row0;
+    A.rounds = all.rounds;
+    for (int i = 0; i < N; ++i) A.e[i] = all.e[i];
+    hipLaunchKernelGGL((wide_stats<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
+    stage_done(st, kStagePass1);
+    hipLaunchKernelGGL((wide_votes<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
+    stage_done(st, kStagePass2);
+    return hipGetLastError();
+}
+template <typename T, int D> hipError_t by_entries(const WideArgs<kMaxWide>& A, dim3 grid, hipStream_t st) {
+    if (A.count > 1) return launch_both<T, D, false, kMaxWide>(A, grid, st);
+    return A.table ? launch_both<T, D, true, 1>(A, grid, st) : launch_both<T, D, false, 1>(A, grid, st);
+}
+
+}  // namespace
+
+bool wide_ok(int dtype, int D, const ScoreGeom& G) {
+    Blocks b;
+    if ((dtype != 0 && dtype != 2) || (D != 64 && D != 128) || G.n <= 0 || !row_blocks(G, &b)) return false;
+    if ((int64_t)G.g * b.UH * 16 * G.L < kMinRowKeys) return false;
+    return (int64_t)G.Hkv * b.nblk * slices_of(G.L) * rounds_per_slice(G.L) <= kMaxRounds;
+}
+
+size_t wide_part_bytes(const ScoreGeom& G) {
+    Blocks b;
+    if (G.n <= 0 || !row_blocks(G, &b)) return 0;
+    return (sizeof(float2) * (size_t)G.Hkv * b.nblk * slices_of(G.L) * RUW * 16 + 255) & ~(size_t)255;
+}
+
+hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st) {
+    if (count < 1 || count > kMaxWide) return hipErrorInvalidValue;
+    Blocks b;
+    if ((dtype != 0 && dtype != 2) || (D != 64 && D != 128) || !row_blocks(*P[0].G, &b)) return hipErrorInvalidValue;
+    const ScoreGeom& G0 = *P[0].G;
+    if (G0.k_table && count != 1) return hipErrorInvalidValue;
+    WideArgs<kMaxWide> A;
+    A.count = count;
+    A.g = G0.g;
+    A.W = G0.W;
+    A.UH = b.UH;
+    A.hb = b.hb;
+    A.nblk = b.nblk;
+    A.c2 = G0.c2;
+    A.k_rs = G0.k_rs;
+    A.table = G0.k_table;
+    A.page = G0.k_page;
+    A.pages = G0.k_pages;
+    A.row0 = G0.k_row0;
+    A.rounds = 0;
+    int64_t slices = 0;
+    for (int i = 0; i < count; ++i) {
+        const ScoreGeom& G = *P[i].G;
+        if (G.g != G0.g || G.W != G0.W || G.k_rs != G0.k_rs || G.n <= 0 || G.L >= (int64_t)1 << 31) return hipErrorInvalidValue;
+        WideEntry& E = A.e[i];
+        E.q = static_cast<const char*>(P[i].q);
+        E.k = static_cast<const char*>(P[i].k);
+        E.vote = P[i].vote;
+        E.part = P[i].part;
+        E.k_hs = G.k_hs;
+        E.vpitch = G.vpitch;
+        E.round_begin = A.rounds;
+        E.L = (int)G.L;
+        E.n = (int)G.n;
+        E.RPS = rounds_per_slice(G.L);
+        E.NS = slices_of(G.L);
+        E.units = G.Hkv * b.nblk;
+        if ((int64_t)E.units * E.NS * E.RPS > kMaxRounds) return hipErrorInvalidValue;
+        A.rounds += (unsigned)E.units * E.NS * E.RPS;
+        slices += (int64_t)E.units * E.NS;
+    }
+    for (int i = count; i < kMaxWide; ++i) A.e[i] = A.e[0];
+    const int64_t places = 2 * wide_cus();   // two workgroups per compute unit
+    A.direct = count == 1 && slices <= places;
+    const dim3 grid = A.direct ? dim3((unsigned)A.e[0].NS, (unsigned)A.e[0].units) : dim3((unsigned)std::min(slices, places));
+    if (dtype == 0) return D == 128 ? by_entries<w_bf16, 128>(A, grid, st) : by_entries<w_bf16, 64>(A, grid, st);
+    return D == 128 ? by_entries<w_f16, 128>(A, grid, st) : by_entries<w_f16, 64>(A, grid, st);
+}
+
+}  // namespace snapkv

@@ -1,0 +1,115 @@
+"""Prompts whose KV heads are met by 128 window rows or more, long enough for the two-pass scoring kernels
+(csrc/snapkv_wide.hip): edges of rounds (128 keys), of slices (multiples of 128 keys, at most 64 of them) and of the
+row blocks (128 rows, whole query heads), every storage type and layout, and rows whose sums leave the fp32 range."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2404_14469_amd import workloads
+from paper_2404_14469_amd.workloads import Workload
+from parity import check_against_oracle, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+MIN_ROW_KEYS = 9 << 18   # csrc/snapkv_wide.hip: window rows times keys from which these kernels are used
+
+
+def work(L, g, W, Hkv=2, D=128, dtype="bf16", C=300, p=7, pool_kind=0):
+    assert g * (-(-W // 16)) >= 8 and g * 16 * (-(-W // 16)) * L >= MIN_ROW_KEYS, "not a shape of the two-pass kernels"
+    return Workload("wide", L=L, Hq=g * Hkv, Hkv=Hkv, D=D, W=W, pool_kind=pool_kind, p=p, C=C, dtype=dtype, clusters=(5, 5),
+                    radius=6, layers=2, seed=5200)
+
+
+CASES = {
+    "w32_first": work(18432, 4, 32),                       # the shortest of this width; whole rounds
+    "w32_one_more": work(18433, 4, 32),                    # one key in the last round
+    "w32_round_edge": work(18432 + 127, 4, 32, pool_kind=1, p=5),
+    "w64_two_blocks": work(9216 + 31, 4, 64, p=13),        # 256 rows: two blocks per KV head
+    "w128_one_head": work(18500, 1, 128, Hkv=3),           # a block is one query head
+    "w16_eight_heads": work(18437, 8, 16, p=5),
+    "w48_padded": work(16400, 3, 48),                      # nine row units: blocks of six, padded to eight
+    "w31_padded_rows": work(18450, 4, 31),
+    "g5_uneven_blocks": work(14800, 5, 32),                # five heads of two units: blocks of three and two heads
+    "d64_f16": work(18439, 4, 32, D=64, dtype="f16"),
+    "f16": work(18441, 4, 32, dtype="f16"),
+    "many_slices": work(40001, 4, 32, Hkv=1, C=1024),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_against_oracle(snapkv, name):
+    w = CASES[name]
+    case = workloads.generate(w, device="cuda")
+    res = run_gpu(snapkv, case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C)
+    check_against_oracle(case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C, *res)
+
+
+def outputs(w, n, dtype):
+    return ([torch.zeros((w.Hkv, w.C, w.D), dtype=dtype, device="cuda") for _ in range(n)],
+            [torch.zeros((w.Hkv, w.C, w.D), dtype=dtype, device="cuda") for _ in range(n)],
+            [torch.full((w.Hkv, w.C), -1, dtype=torch.int32, device="cuda") for _ in range(n)])
+
+
+def test_layouts_layers_and_batches_equal_single_calls(snapkv):
+    """Token-major, paged, separately allocated and stacked layers, a batch with prompts on both sides of the rule:
+    every one bit for bit what a single contiguous call gives (a head's result depends on its own prompt only)."""
+    w = CASES["w32_one_more"]
+    cases = [workloads.generate(w, layer=l, device="cuda") for l in range(2)]
+    want = [run_gpu(snapkv, c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C) for c in cases]
+    q, k, v = (cases[0][n] for n in ("q_win", "k", "v"))
+
+    def same(ok, ov, oi, ref, what):
+        assert np.array_equal(oi.cpu().numpy(), ref[3]), what
+        assert torch.equal(ok, ref[1]) and torch.equal(ov, ref[2]), what
+
+    ok, ov, oi = (t[0] for t in outputs(w, 1, k.dtype))
+    kt, vt = (t.transpose(0, 1).contiguous().transpose(0, 1) for t in (k, v))
+    snapkv.snapkv_compress_strided(q, kt, vt, w.pool_kind, w.p, w.C, ok, ov, oi)
+    same(ok, ov, oi, want[0], "token-major")
+
+    page, pages = 16, -(-w.L // 16)
+    table = torch.randperm(pages, device="cuda").to(torch.int32)
+    paged = []
+    for t in (k, v):
+        pad = torch.zeros((w.Hkv, pages * page, w.D), dtype=t.dtype, device="cuda")
+        pad[:, :w.L] = t
+        cache = torch.empty((pages, page, w.Hkv, w.D), dtype=t.dtype, device="cuda")
+        cache[table.long()] = pad.view(w.Hkv, pages, page, w.D).permute(1, 2, 0, 3)
+        paged.append(cache)
+    oi.fill_(-1)
+    snapkv.snapkv_compress_paged(q, paged[0], paged[1], table, w.L, w.pool_kind, w.p, w.C, ok, ov, oi)
+    same(ok, ov, oi, want[0], "paged")
+
+    for stack in (False, True):
+        lists = [[c[n] for c in cases] for n in ("q_win", "k", "v")]
+        oks, ovs, ois = outputs(w, 2, k.dtype)
+        if stack:
+            lists = [list(torch.stack(x).contiguous()) for x in lists]
+            oks, ovs, ois = (list(torch.stack(x).contiguous()) for x in (oks, ovs, ois))
+        snapkv.snapkv_compress_layers(*lists, w.pool_kind, w.p, w.C, oks, ovs, ois)
+        for l in range(2):
+            same(oks[l], ovs[l], ois[l], want[l], f"layers, stacked={stack}")
+
+    short = workloads.generate(w.with_(L=5000), device="cuda")
+    batch = [cases[0], short, cases[1]]
+    refs = [want[0], run_gpu(snapkv, short["q_win"], short["k"], short["v"], w.pool_kind, w.p, w.C), want[1]]
+    oks, ovs, ois = outputs(w, 3, k.dtype)
+    snapkv.snapkv_compress_varlen([c["q_win"] for c in batch], [c["k"] for c in batch], [c["v"] for c in batch],
+                                  w.pool_kind, w.p, w.C, oks, ovs, ois)
+    for i in range(3):
+        same(oks[i], ovs[i], ois[i], refs[i], f"batch, prompt {i}")
+
+
+def test_logits_far_above_the_first_key(snapkv):
+    """The rows' reference is their logit with key 0; here a stretch of keys lies about 130 nats above it (2^187), so
+    the sums relative to it overflow and the rows are taken from the keys again."""
+    w = work(18461, 4, 32, Hkv=1, C=300)
+    case = workloads.generate(w, device="cuda")
+    q, k, v = case["q_win"].clone(), case["k"].clone(), case["v"]
+    u = torch.zeros(w.D, device="cuda")
+    u[3] = 1.0
+    q += (12.0 * u).to(q.dtype)
+    k[:, 0] = 0
+    k[:, 7000:12000] += (122.0 * u).to(k.dtype)          # 12 * 122 / sqrt(128) = 129 nats
+    res = run_gpu(snapkv, q, k, v, w.pool_kind, w.p, w.C)
+    check_against_oracle(q, k, v, w.pool_kind, w.p, w.C, *res)
