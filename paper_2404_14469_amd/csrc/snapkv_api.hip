@@ -40,15 +40,49 @@ struct DeviceScratch {
 };
 DeviceScratch g_scratch[kMaxDevices];
 std::mutex g_mu;
-DeviceScratch g_decode_scratch[kMaxDevices];   // partial results of decode attention and the hit-rate probe's logits:
-                                               // kept apart so that they leave the compression scratch's ready state alone
+// The entries that use the library's own scratch keep a host-side record of the state their last kernel
+// leaves it in, and may allocate; neither survives being recorded into a graph and replayed later, so
+// they refuse a stream that is capturing (snapkv_compress_ws and snapkv_compress_static are the forms to capture).
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
 
-// The auxiliary buffer of the current device, grown when needed (need > 0).
-int aux_scratch(size_t need, void** out) {
+// Kept apart from the compression scratch so that they leave its ready state alone: the partial results of decode
+// attention (one size for all calls, never moved, so that a captured call keeps its buffer) and the hit-rate
+// probe's logits.
+DeviceScratch g_decode_scratch[kMaxDevices];
+DeviceScratch g_probe_scratch[kMaxDevices];
+
+// The decoding step's buffer of the current device; null on a capturing stream that comes before the first call that
+// allocates it.
+int decode_scratch(hipStream_t st, void** out) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SNAPKV_ERR_HIP;
     std::lock_guard<std::mutex> lock(g_mu);
     DeviceScratch& s = g_decode_scratch[dev];
+    if (!s.ptr && !capturing(st)) {
+        if (hipMalloc(&s.ptr, kDecodeScratchBytes) != hipSuccess) {
+            s.ptr = nullptr;
+            (void)hipGetLastError();
+            return SNAPKV_ERR_HIP;
+        }
+        s.bytes = kDecodeScratchBytes;
+    }
+    *out = s.ptr;
+    return SNAPKV_OK;
+}
+
+// The probe's buffer of the current device, grown when needed (need > 0).
+int probe_scratch(size_t need, void** out) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SNAPKV_ERR_HIP;
+    std::lock_guard<std::mutex> lock(g_mu);
+    DeviceScratch& s = g_probe_scratch[dev];
     if (s.bytes < need) {
         if (s.ptr && hipFree(s.ptr) != hipSuccess) return SNAPKV_ERR_HIP;   // waits for work still using it
         s.ptr = nullptr;
@@ -99,18 +133,6 @@ int check_score_args(const void* q_win, const void* k, int64_t L, int Hq, int Hk
     if (Hkv > 65535) return SNAPKV_ERR_UNSUPPORTED;
     if (!aligned16(q_win) || !aligned16(k)) return SNAPKV_ERR_MISALIGNED;
     return SNAPKV_OK;
-}
-
-// The entries that use the library's own scratch keep a host-side record of the state their last kernel
-// leaves it in, and may allocate; neither survives being recorded into a graph and replayed later, so
-// they refuse a stream that is capturing (snapkv_compress_ws and snapkv_compress_static are the forms to capture).
-bool capturing(hipStream_t st) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return cs != hipStreamCaptureStatusNone;
 }
 
 // Hands out the device's buffer.  Whoever takes it may leave it in any state, so the record of a
@@ -1128,12 +1150,12 @@ int snapkv_decode_attention(int dtype, const void* q, const void* k_cache, const
     if ((reinterpret_cast<uintptr_t>(out) & 3u) != 0 || (reinterpret_cast<uintptr_t>(out_lse) & 3u) != 0 ||
         (reinterpret_cast<uintptr_t>(lens) & 3u) != 0)
         return SNAPKV_ERR_MISALIGNED;
-    const int nsplit = decode_splits(B, Hkv, S);
-    const size_t need = decode_scratch_bytes(B, Hq, D, nsplit);
+    int nsplit = decode_splits(B, Hkv, S);
     void* base = nullptr;
-    if (need > 0) {
-        const int rc = aux_scratch(need, &base);
+    if (nsplit > 1) {
+        const int rc = decode_scratch(static_cast<hipStream_t>(stream), &base);
         if (rc != SNAPKV_OK) return rc;
+        if (!base || decode_scratch_bytes(B, Hq, D, nsplit) > kDecodeScratchBytes) nsplit = 1;   // (captured before any eager call)
     }
     return launch_decode(dtype, D, q, k_cache, v_cache, lens, B, Hq, Hkv, S, cap, nsplit, base, out, out_lse,
                          static_cast<hipStream_t>(stream)) == hipSuccess
@@ -1155,7 +1177,7 @@ int snapkv_hit_rate(int dtype, const void* q_cur, const void* k, int64_t Lk, int
     if ((reinterpret_cast<uintptr_t>(idx) & 3u) != 0 || (reinterpret_cast<uintptr_t>(out_counts) & 3u) != 0)
         return SNAPKV_ERR_MISALIGNED;
     void* base = nullptr;
-    const int rc = aux_scratch(hit_rate_scratch_bytes(Hq, Lk), &base);
+    const int rc = probe_scratch(hit_rate_scratch_bytes(Hq, Lk), &base);
     if (rc != SNAPKV_OK) return rc;
     return launch_hit_rate(dtype, D, q_cur, k, Lk, n, Hq, Hkv, idx, Hidx, kcount, idx_stride, theta, base, out_counts,
                            static_cast<hipStream_t>(stream)) == hipSuccess
@@ -1179,12 +1201,13 @@ void snapkv_release(void) {
         if (hipSetDevice(d) == hipSuccess) (void)hipHostFree(g_scratch[d].sticky);
         g_scratch[d].sticky = nullptr;
     }
-    for (int d = 0; d < kMaxDevices; ++d) {
-        if (!g_decode_scratch[d].ptr) continue;
-        if (hipSetDevice(d) == hipSuccess) (void)hipFree(g_decode_scratch[d].ptr);
-        g_decode_scratch[d].ptr = nullptr;
-        g_decode_scratch[d].bytes = 0;
-    }
+    for (DeviceScratch* all : {g_decode_scratch, g_probe_scratch})
+        for (int d = 0; d < kMaxDevices; ++d) {
+            if (!all[d].ptr) continue;
+            if (hipSetDevice(d) == hipSuccess) (void)hipFree(all[d].ptr);
+            all[d].ptr = nullptr;
+            all[d].bytes = 0;
+        }
     if (have_cur) (void)hipSetDevice(cur);
 }
 

@@ -283,23 +283,47 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_attn(const DecodeArgs A
     }
 }
 
-// Merges the partials of the splits of one query head: one workgroup of D threads per head.
+// Merges the partials of the splits of one query head: one wave per head, lane l holding head-dim elements
+// 2l, 2l + 1 (D = 128) or l (D = 64).  Latency-bound: all (max, sum) pairs are fetched at once, a split per lane
+// (decode_splits gives at most 64), and the partial outputs eight splits at a time.
 template <int D>
-__global__ __launch_bounds__(D) void decode_merge(const float* part_acc, const float2* part_ml, int nsplit,
-                                                  float* out, float* lse) {
+__global__ __launch_bounds__(64) void decode_merge(const float* part_acc, const float2* part_ml, int nsplit,
+                                                   float* out, float* lse) {
+    constexpr int E = D / 64;
     const int64_t hq = blockIdx.x;
-    const int d = threadIdx.x;
-    float M = -INFINITY;
-    for (int s = 0; s < nsplit; ++s) M = fmaxf(M, part_ml[hq * nsplit + s].x);
-    float Lq = 0.f, o = 0.f;
-    for (int s = 0; s < nsplit; ++s) {
-        const float2 ml = part_ml[hq * nsplit + s];
-        const float f = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - M);
-        Lq += ml.y * f;
-        o += part_acc[(hq * nsplit + s) * D + d] * f;
+    const int lane = threadIdx.x;
+    const float* pa = part_acc + hq * nsplit * D + lane * E;
+    const float2 ml = lane < nsplit ? part_ml[hq * nsplit + lane] : make_float2(-INFINITY, 0.f);
+    float M = ml.x;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) M = fmaxf(M, __shfl_xor(M, d));
+    const float f = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - M);
+    float Lq = ml.y * f;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) Lq += __shfl_xor(Lq, d);
+    float o[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = 0.f;
+    for (int s0 = 0; s0 < nsplit; s0 += 8) {
+        float x[8][E];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) x[i][e] = 0.f;
+            if (s0 + i < nsplit)
+#pragma unroll
+                for (int e = 0; e < E; ++e) x[i][e] = pa[(int64_t)(s0 + i) * D + e];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float fs = __shfl(f, (s0 + i) & 63);   // lanes beyond the last split hold zero
+#pragma unroll
+            for (int e = 0; e < E; ++e) o[e] += x[i][e] * fs;
+        }
     }
-    out[hq * D + d] = Lq > 0.f ? o / Lq : 0.f;
-    if (lse && d == 0) lse[hq] = Lq > 0.f ? (M + __builtin_amdgcn_logf(Lq)) * 0.6931471805599453f : -INFINITY;
+#pragma unroll
+    for (int e = 0; e < E; ++e) out[hq * D + lane * E + e] = Lq > 0.f ? o[e] / Lq : 0.f;
+    if (lse && lane == 0) lse[hq] = Lq > 0.f ? (M + __builtin_amdgcn_logf(Lq)) * 0.6931471805599453f : -INFINITY;
 }
 
 int cu_count() {
@@ -316,14 +340,28 @@ int cu_count() {
 
 }  // namespace
 
-// Splits of a (sequence, KV head) pair's keys.  Measured: long-running workgroups, about one per
-// compute unit, stream best, so the keys are split only when the pairs alone leave units idle,
-// and never below 128 keys per wave.
+// Splits of a (sequence, KV head) pair's keys, down to 32 keys per wave: the number that costs least when workgroups
+// run in rounds of one per compute unit.  In keys of time (a key of one pair at a compute unit's share of HBM): the
+// stream cannot go below everybody's keys divided evenly, nor a round below 0.8 of its workgroup's keys (a unit alone
+// draws a quarter more than its share); a round costs about 100 besides, the merge of the splits 150.  Microseconds
+// per call with splits of at least 512 keys, as near as possible to one workgroup per unit, and with this rule (bf16, 32
+// query heads): one sequence of 2113 keys and 8 KV heads 15.3 / 11.8 (32 instead of 136 workgroups were in flight), of
+// 16384 keys 26.1 / 18.8; three sequences of 32 heads and 2560 keys 38.1 / 25.0 (288 workgroups: 32 units had two),
+// five of 16384 keys 295 / 226; eight of 2560 keys, one workgroup each either way, 55.1 / 55.0.
 int decode_splits(int B, int Hkv, int64_t S) {
-    const int64_t pairs = (int64_t)B * Hkv;
-    const int64_t want = (cu_count() + pairs / 2) / pairs;
-    const int64_t most = std::max<int64_t>(1, S / (128 * kDecWaves));
-    return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(want, most), 64));
+    const int64_t pairs = (int64_t)B * Hkv, cus = cu_count(), steps = (S + 31) / 32;
+    const int64_t most = std::min<int64_t>(std::min<int64_t>(64, kDecodeMaxGroups / pairs), (steps + kDecWaves - 1) / kDecWaves);
+    int best = 1;
+    double least = 0.0;
+    for (int64_t n = 1; n <= most; ++n) {
+        const double rounds = (double)((n * pairs + cus - 1) / cus), keys = 32.0 * (double)((steps + n - 1) / n);
+        const double cost = std::max((double)(pairs * S) / (double)cus, 0.8 * rounds * keys) + 100.0 * rounds + (n > 1 ? 150.0 : 0.0);
+        if (n == 1 || cost < least) {
+            best = (int)n;
+            least = cost;
+        }
+    }
+    return best;
 }
 
 size_t decode_scratch_bytes(int B, int Hq, int D, int nsplit) {
@@ -365,7 +403,7 @@ hipError_t launch_decode(int dtype, int D, const void* q, const void* k, const v
     else return hipErrorInvalidValue;
     if (nsplit > 1) {
         const unsigned heads = (unsigned)((int64_t)B * Hq);
-        if (D == 128) hipLaunchKernelGGL((decode_merge<128>), dim3(heads), dim3(128), 0, st, A.part_acc, A.part_ml, nsplit, out, lse);
+        if (D == 128) hipLaunchKernelGGL((decode_merge<128>), dim3(heads), dim3(64), 0, st, A.part_acc, A.part_ml, nsplit, out, lse);
         else hipLaunchKernelGGL((decode_merge<64>), dim3(heads), dim3(64), 0, st, A.part_acc, A.part_ml, nsplit, out, lse);
     }
     return hipGetLastError();

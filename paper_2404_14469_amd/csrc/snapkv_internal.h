@@ -222,6 +222,9 @@ hipError_t launch_hit_rate(int dtype, int D, const void* q, const void* k, int64
                            void* scratch, int32_t* counts, hipStream_t st);
 
 // One decoding step of attention over a cache of [B, Hkv, cap, D] rows (snapkv_decode.hip).
+// A split launch has at most kDecodeMaxGroups workgroups, which bounds the scratch any call can need.
+constexpr int64_t kDecodeMaxGroups = 1024;
+constexpr size_t kDecodeScratchBytes = (size_t)kDecodeMaxGroups * 16 * (128 * sizeof(float) + sizeof(float2)) + 512;
 int decode_splits(int B, int Hkv, int64_t S);
 size_t decode_scratch_bytes(int B, int Hq, int D, int nsplit);
 hipError_t launch_decode(int dtype, int D, const void* q, const void* k, const void* v, const int32_t* lens,

@@ -57,6 +57,11 @@ CASES = [
     DecodeWorkload("many_pairs_no_split", B=40, Hq=32, Hkv=32, D=128, S=200, cap=200, seed=9),
     DecodeWorkload("lens_mixed", B=6, Hq=8, Hkv=4, D=64, S=900, cap=901, ragged=True, seed=10),
     DecodeWorkload("f16", B=2, Hq=8, Hkv=4, D=128, S=1234, cap=1300, dtype="f16", seed=11),
+    DecodeWorkload("split_small", B=1, Hq=8, Hkv=2, D=128, S=129, cap=140, seed=13),            # one step of 32 keys per wave
+    DecodeWorkload("split_odd", B=1, Hq=32, Hkv=8, D=128, S=2113, cap=2560, seed=14),           # 17 splits
+    DecodeWorkload("split_most", B=1, Hq=2, Hkv=1, D=64, S=16400, cap=16400, seed=15),          # 64 splits
+    DecodeWorkload("split_ragged_short", B=3, Hq=16, Hkv=8, D=128, S=3000, cap=3000, ragged=True, seed=16),
+    DecodeWorkload("split_rounds", B=3, Hq=32, Hkv=32, D=128, S=2100, cap=2100, seed=17),       # more workgroups than units
     DecodeWorkload("f16_d64_split", B=1, Hq=4, Hkv=4, D=64, S=4100, cap=4100, dtype="f16", seed=12),
 ]
 
