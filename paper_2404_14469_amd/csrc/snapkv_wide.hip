@@ -648,9 +648,8 @@ hipError_t launch_both(const WideArgs<kMaxWide>& all, dim3 grid, hipStream_t st)
     A.rounds = all.rounds;
     for (int i = 0; i < N; ++i) A.e[i] = all.e[i];
     hipLaunchKernelGGL((wide_stats<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
-    stage_done(st, kStagePass1);
     hipLaunchKernelGGL((wide_votes<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
-    stage_done(st, kStagePass2);
+    stage_done(st, kStageFused);   // (both launches: the stage that scores all keys of a prompt)
     return hipGetLastError();
 }
 template <typename T, int D> hipError_t by_entries(const WideArgs<kMaxWide>& A, dim3 grid, hipStream_t st) {
@@ -660,16 +659,26 @@ template <typename T, int D> hipError_t by_entries(const WideArgs<kMaxWide>& A, 
 
 }  // namespace
 
+// Whether these kernels take the prompt: enough window rows and keys (kMinRowKeys), and statistics that fit what a workspace
+// holds anyway (a region of the streaming passes, or the pooled scores that come later), a head at a time so that
+// the answer does not depend on how many heads a call has.
+static bool wide_shape(const ScoreGeom& G, Blocks* b) {
+    if (G.n <= 0 || !row_blocks(G, b) || (int64_t)G.g * b->UH * 16 * G.L < kMinRowKeys) return false;
+    ScoreGeom one = G;
+    one.Hkv = 1;
+    const size_t part = sizeof(float2) * (size_t)b->nblk * slices_of(G.L) * RUW * 16;
+    return part <= std::max(stream_stat_bytes(one), sizeof(float) * (size_t)G.g * (size_t)G.n);
+}
+
 bool wide_ok(int dtype, int D, const ScoreGeom& G) {
     Blocks b;
-    if ((dtype != 0 && dtype != 2) || (D != 64 && D != 128) || G.n <= 0 || !row_blocks(G, &b)) return false;
-    if ((int64_t)G.g * b.UH * 16 * G.L < kMinRowKeys) return false;
+    if ((dtype != 0 && dtype != 2) || (D != 64 && D != 128) || !wide_shape(G, &b)) return false;
     return (int64_t)G.Hkv * b.nblk * slices_of(G.L) * rounds_per_slice(G.L) <= kMaxRounds;
 }
 
 size_t wide_part_bytes(const ScoreGeom& G) {
     Blocks b;
-    if (G.n <= 0 || !row_blocks(G, &b)) return 0;
+    if (!wide_shape(G, &b)) return 0;
     return (sizeof(float2) * (size_t)G.Hkv * b.nblk * slices_of(G.L) * RUW * 16 + 255) & ~(size_t)255;
 }
 
