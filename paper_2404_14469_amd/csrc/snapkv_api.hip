@@ -241,7 +241,7 @@ bool layers_table_ok(int dtype, int D, const ScoreGeom& G, int kv_heads_per_laye
 }
 
 int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGeom& G,
-               const Workspace& ws, int pool_kind, int p, float* score, unsigned* minmax,
+               const Workspace& ws, int pool_kind, int p, float* score, int64_t score_pitch, unsigned* minmax,
                bool prepare_select, ScoreGeom* Gv, hipStream_t st, bool already_prepared = false,
                CleanJob* clean = nullptr, const float* lse = nullptr, bool allow_blocks = false,
                bool allow_long = false, const ScoreLayers* layers = nullptr) {
@@ -261,7 +261,7 @@ int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGe
         Gp.VB = 1;
         if (Gv) *Gv = Gp;
         if (!score) return SNAPKV_OK;
-        if (launch_pool(Gp, ws.vote, pool_kind, p, score, minmax, st) != hipSuccess) return SNAPKV_ERR_HIP;
+        if (launch_pool(Gp, ws.vote, pool_kind, p, score, score_pitch, minmax, st) != hipSuccess) return SNAPKV_ERR_HIP;
         stage_done(st, kStagePool);
         return SNAPKV_OK;
     }
@@ -331,7 +331,7 @@ int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGe
             P[x].q = layers ? layers->q[x] : q_win;
             P[x].k = layers ? layers->k[x] : k;
             P[x].vote = ws.vote + (int64_t)x * Ge.Hkv * G.g * G.vpitch;
-            P[x].part = ws.stat_part + (int64_t)x * (int64_t)(wide_part_bytes(Ge) / sizeof(float2));
+            P[x].part = ws.wide_part + (int64_t)x * (int64_t)(wide_part_bytes(Ge) / sizeof(float2));
             P[x].G = &Ge;
         }
         if (launch_score_wide(dtype, D, count, P, st) != hipSuccess) return SNAPKV_ERR_HIP;
@@ -350,7 +350,7 @@ int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGe
     }
     if (Gv) *Gv = Gp;
     if (!score) return SNAPKV_OK;
-    if (launch_pool(Gp, ws.vote, pool_kind, p, score, minmax, st) != hipSuccess) return SNAPKV_ERR_HIP;
+    if (launch_pool(Gp, ws.vote, pool_kind, p, score, score_pitch, minmax, st) != hipSuccess) return SNAPKV_ERR_HIP;
     stage_done(st, kStagePool);
     return SNAPKV_OK;
 }
@@ -422,6 +422,7 @@ int64_t compress_impl(int dtype, const void* q_win, const void* k, const void* v
     G.k_table = pm.table;
     G.k_page = pm.page;
     G.k_pages = pm.pages;
+    G.vpitch = row_pitch(G);
     const size_t need = workspace_layout(G, nullptr, nullptr);
     const size_t need_up = (need + 255) & ~(size_t)255;
     void* base = workspace;
@@ -505,7 +506,7 @@ int64_t compress_impl(int dtype, const void* q_win, const void* k, const void* v
             }
         }
         ScoreGeom Gv = G;
-        rc = run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, nullptr, nullptr, true, &Gv, st, prepared,
+        rc = run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, nullptr, 0, nullptr, true, &Gv, st, prepared,
                         mine ? &clean : nullptr, lse, blocks_ok, true, score_layers);
         if (rc != SNAPKV_OK) return rc;
         if (per_query_head) Gv = Gsel;
@@ -517,19 +518,19 @@ int64_t compress_impl(int dtype, const void* q_win, const void* k, const void* v
     } else {
         if (per_query_head) {   // votes first, then pooled per query head
             ScoreGeom Gv = G;
-            rc = run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, nullptr, nullptr, true, &Gv, st, false, nullptr, lse,
+            rc = run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, nullptr, 0, nullptr, true, &Gv, st, false, nullptr, lse,
                             false, true);
             if (rc != SNAPKV_OK) return rc;
             if (Gv.VB != 1 || Gv.NV != G.g) return SNAPKV_ERR_UNSUPPORTED;
-            if (launch_pool(Gsel, ws.vote, pool_kind, p, ws.score, ws.sel.minmax, st) != hipSuccess)
+            if (launch_pool(Gsel, ws.vote, pool_kind, p, ws.score, G.vpitch, ws.sel.minmax, st) != hipSuccess)
                 return SNAPKV_ERR_HIP;
             stage_done(st, kStagePool);
         } else {
-            rc = run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, ws.score, ws.sel.minmax,
+            rc = run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, ws.score, G.vpitch, ws.sel.minmax,
                             true, nullptr, st, false, nullptr, lse, blocks_ok, true, score_layers);
             if (rc != SNAPKV_OK) return rc;
         }
-        se = launch_select_chunked(ws.score, Hout, G.n, C - W, C, W, idx_dst, ws.sel, pool_tiles(G.n), st);
+        se = launch_select_chunked(ws.score, G.vpitch, Hout, G.n, C - W, C, W, idx_dst, ws.sel, pool_tiles(G.n), st);
     }
     if (se != hipSuccess) return SNAPKV_ERR_HIP;
     stage_done(st, kStageSelect);
@@ -558,13 +559,14 @@ int scores_impl(int dtype, const void* q_win, const void* k, int64_t L, int Hq, 
     ScoreGeom G = make_geom(L, Hq, Hkv, D, W);
     G.k_rs = (int64_t)D * elem_bytes(dtype);
     G.k_hs = G.k_rs * L;
+    G.vpitch = row_pitch(G);
     void* base = nullptr;
     if (capturing(static_cast<hipStream_t>(stream))) return SNAPKV_ERR_UNSUPPORTED;
     rc = internal_scratch(workspace_layout(G, nullptr, nullptr), &base);
     if (rc != SNAPKV_OK) return rc;
     Workspace ws;
     workspace_layout(G, &ws, base);
-    return run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, out_scores, nullptr, false, nullptr,
+    return run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, out_scores, G.n, nullptr, false, nullptr,
                       static_cast<hipStream_t>(stream), false, nullptr, lse, !lse, true);
 }
 
@@ -659,6 +661,7 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
         wsp[i].fused = handoff_p + handoff * i;
         wsp[i].vote = votes_p + (size_t)i * Hq * (size_t)npad;
         wsp[i].stat_part = reinterpret_cast<float2*>(sp);
+        wsp[i].wide_part = wsp[i].stat_part;
         wsp[i].lse = reinterpret_cast<float*>(sp + per_prompt[i] - up(sizeof(float) * (size_t)Hq * W));
         sp += per_prompt[i];
         G[i].vpitch = npad;
@@ -667,7 +670,7 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
     WidePrompt WP[kMaxBatch];
     static_assert(kMaxBatch <= kMaxWide, "the prompts of a batch that take the two-pass kernels share their launches");
     for (int i = 0; i < count; ++i) {
-        if (wide[i]) WP[nwide++] = WidePrompt{q_win[i], k[i], wsp[i].vote, wsp[i].stat_part, &G[i]};
+        if (wide[i]) WP[nwide++] = WidePrompt{q_win[i], k[i], wsp[i].vote, wsp[i].wide_part, &G[i]};
         else rest[nrest++] = i;
     }
     if (nwide > 0 && launch_score_wide(dtype, D, nwide, WP, st) != hipSuccess) return SNAPKV_ERR_HIP;
@@ -681,7 +684,7 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
         if (taken == 0) {   // the longest of the rest goes alone
             const int i = rest[0];
             ScoreGeom Gv = G[i];
-            rc = run_scores(dtype, q_win[i], k[i], D, G[i], wsp[i], pool_kind, p, nullptr, nullptr, false, &Gv, st, true);
+            rc = run_scores(dtype, q_win[i], k[i], D, G[i], wsp[i], pool_kind, p, nullptr, 0, nullptr, false, &Gv, st, true);
             if (rc != SNAPKV_OK) return rc;
             if (Gv.VB != 1 || Gv.NV != g) return SNAPKV_ERR_UNSUPPORTED;   // not reached: lse_plan held above
             for (int r = 1; r < nrest; ++r) rest[r - 1] = rest[r];
@@ -1133,7 +1136,7 @@ int snapkv_select_topk(const float* scores, int H, int64_t n, int64_t kcount, in
     SelectScratch S;
     select_layout(H, n, &S, base);
     if (launch_select_init(S, H, st) != hipSuccess) return SNAPKV_ERR_HIP;
-    if (launch_select_chunked(scores, H, n, kcount, kcount, 0, out_idx, S, 0, st) != hipSuccess)
+    if (launch_select_chunked(scores, n, H, n, kcount, kcount, 0, out_idx, S, 0, st) != hipSuccess)
         return SNAPKV_ERR_HIP;
     return SNAPKV_OK;
 }

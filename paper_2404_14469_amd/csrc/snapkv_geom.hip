@@ -2,8 +2,6 @@
 // translation units).
 #include "snapkv_internal.h"
 
-#include <algorithm>
-
 namespace snapkv {
 
 ScoreGeom make_geom(int64_t L, int Hq, int Hkv, int D, int W) {
@@ -27,6 +25,9 @@ ScoreGeom make_geom(int64_t L, int Hq, int Hkv, int D, int W) {
     return G;
 }
 
+// (a window of more than 2048 rows has so many vote rows that padding them would outgrow the rest of the workspace)
+int64_t row_pitch(const ScoreGeom& G) { return G.BH <= 64 ? (G.n + 3) & ~(int64_t)3 : G.n; }
+
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The two regions whose contents carry over between calls come first, at offsets that depend on
@@ -40,9 +41,13 @@ size_t workspace_layout(const ScoreGeom& G, Workspace* ws, void* base) {
     const size_t counters = select_counter_bytes(Hsel);
     const size_t fused = fused_sync_bytes(G);
     // one vote row per query head, or per 32-row block of a window of 64, 96, ... rows
-    const size_t vote = align_up(sizeof(float) * (size_t)G.Hkv * G.g * G.BH * (size_t)(G.n > 0 ? G.n : 1));
-    const size_t score = align_up(sizeof(float) * (size_t)Hsel * (size_t)(G.n > 0 ? G.n : 1));
-    const size_t stat = std::max(stream_stat_bytes(G), wide_part_bytes(G));   // one scoring path per call
+    const size_t row = (size_t)(G.n > 0 ? row_pitch(G) : 1);
+    const size_t vote = align_up(sizeof(float) * (size_t)G.Hkv * G.g * G.BH * row);
+    const size_t score = align_up(sizeof(float) * (size_t)Hsel * row);
+    // the statistics of the two-pass kernels are done with before anything is pooled: they take the place of the
+    // pooled scores where they need more than the streaming passes' region
+    const size_t wide = wide_part_bytes(G), stream = stream_stat_bytes(G);
+    const size_t stat = wide > stream && wide > score ? wide : stream;
     const size_t lse = align_up(sizeof(float) * (size_t)G.Hkv * G.g * G.W);
     const size_t logit = long_logit_bytes(G);
     const size_t off = counters + fused;
@@ -52,6 +57,7 @@ size_t workspace_layout(const ScoreGeom& G, Workspace* ws, void* base) {
         ws->vote = reinterpret_cast<float*>(b + off);
         ws->score = reinterpret_cast<float*>(b + off + vote);
         ws->stat_part = reinterpret_cast<float2*>(b + off + vote + score);
+        ws->wide_part = wide <= stat ? ws->stat_part : reinterpret_cast<float2*>(ws->score);
         ws->lse = reinterpret_cast<float*>(b + off + vote + score + stat);
         ws->long_logit = logit ? reinterpret_cast<float*>(b + off + vote + score + stat + lse) : nullptr;
         ws->long_logit_bytes = logit;

@@ -93,8 +93,7 @@ struct SelectScratch {
     // in `cand` above; the first two arrays are contiguous and must be zero when the kernel starts
     // (ps_zero_words words from ps_arrive)
     unsigned* ps_arrive;   // [H][8]        arrival counters of the group-wide rendezvous points
-    unsigned* ps_hist;     // [H][3][2048]  digit histograms, one per refinement level
-    unsigned* ps_range;    // [H][512][2]   per-workgroup (smallest, largest) score bit pattern
+    unsigned* ps_hist;     // [H][6144]     digit histograms, one per refinement level
     unsigned* ps_part;     // [H][512][2]   per-workgroup (#above the threshold bin, #inside it)
     int64_t ps_zero_words;
     unsigned* ps_flag;     // null, or a word of the call's scratch that is set when a bounded wait gives up
@@ -103,9 +102,10 @@ struct SelectScratch {
 struct Workspace {
     unsigned* status_flag;   // first word of the block: set by a kernel whose bounded wait gave up, read and cleared by
                              // the call's last kernel
-    float* vote;     // [Hkv][NV][n]
-    float* score;    // [Hkv][n]
+    float* vote;     // [Hkv][NV][row_pitch]
+    float* score;    // [Hkv][row_pitch]
     char* fused;     // hand-off buffers of the single-read path (see fused_sync_layout)
+    float2* wide_part;   // statistics of the two-pass kernels (see launch_score_wide)
     float2* stat_part;   // [units][Gg][R] per-slice (row max, row sum-exp) of the streaming statistics pass
     float* lse;          // [Hq][W] the window rows' log-sum-exp computed from them
     float* long_logit;   // null, or [units][keys][16] masked window logits of the keys a long prompt's single-read
@@ -115,6 +115,9 @@ struct Workspace {
 
 ScoreGeom make_geom(int64_t L, int Hq, int Hkv, int D, int W);
 size_t workspace_layout(const ScoreGeom& G, Workspace* ws, void* base);
+// Floats between the rows of votes and of pooled scores in a workspace: whole 16-byte pieces, so that the pooling
+// kernels read them as such whatever the prompt's length.
+int64_t row_pitch(const ScoreGeom& G);
 
 // Stage boundaries for the optional per-stage timing (snapkv_profile_start/stop): when timing is
 // active, stage_done records an event on the stream after the stage's launch; otherwise it is a
@@ -174,8 +177,9 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
 unsigned read_sync_timeouts();
 bool reset_sync_timeouts();     // (test hook) both synchronise the device
 bool reset_select_timeouts();
+// vote rows are G.vpitch floats apart, score rows score_pitch
 hipError_t launch_pool(const ScoreGeom& G, const float* vote, int pool_kind, int p, float* score,
-                       unsigned* minmax, hipStream_t st);
+                       int64_t score_pitch, unsigned* minmax, hipStream_t st);
 size_t select_counter_bytes(int H);
 size_t select_layout(int H, int64_t n, SelectScratch* S, void* base, bool own_counters = true,
                      void* counters = nullptr);
@@ -230,7 +234,8 @@ size_t decode_scratch_bytes(int B, int Hq, int D, int nsplit);
 hipError_t launch_decode(int dtype, int D, const void* q, const void* k, const void* v, const int32_t* lens,
                          int B, int Hq, int Hkv, int64_t S, int64_t cap, int nsplit, void* scratch,
                          float* out, float* lse, hipStream_t st);
-hipError_t launch_select_chunked(const float* score, int H, int64_t n, int64_t kcount,
+// score: [H] rows of n, score_pitch floats apart
+hipError_t launch_select_chunked(const float* score, int64_t score_pitch, int H, int64_t n, int64_t kcount,
                                  int64_t out_stride, int W_tail, int32_t* out_idx,
                                  const SelectScratch& S, int minmax_parts, hipStream_t st);
 int pool_tiles(int64_t n);

@@ -21,7 +21,7 @@ constexpr int kPoolPerThread = kPoolTile / 256;
 template <int P>
 __global__ __launch_bounds__(256) void pool_group(const float* __restrict__ vote,
                                                   float* __restrict__ score, const ScoreGeom G,
-                                                  const int pool_kind, const int p_arg,
+                                                  const int64_t spitch, const int pool_kind, const int p_arg,
                                                   unsigned* __restrict__ minmax) {
     __shared__ unsigned sh_lo[4], sh_hi[4];
     const int hkv = blockIdx.y;
@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void pool_group(const float* __restrict__ vote
 #pragma unroll
     for (int e = 0; e < kPoolPerThread; ++e) acc[e] = 0.f;
     for (int h = 0; h < G.g; ++h) {
-        const float* vb = vote + ((int64_t)hkv * G.NV + (int64_t)h * G.VB) * G.n;
+        const float* vb = vote + ((int64_t)hkv * G.NV + (int64_t)h * G.VB) * G.vpitch;
 #pragma unroll
         for (int e = 0; e < kPoolPerThread; ++e) {
             const int64_t j = t0 + threadIdx.x + e * 256;
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void pool_group(const float* __restrict__ vote
                     float tap = pad;
                     if (x >= 0 && x < G.n) {
                         tap = vb[x];
-                        for (int b = 1; b < G.VB; ++b) tap += vb[(int64_t)b * G.n + x];
+                        for (int b = 1; b < G.VB; ++b) tap += vb[(int64_t)b * G.vpitch + x];
                     }
                     val = d == -r ? tap : (pool_kind == 0 ? fmaxf(val, tap) : val + tap);
                 }
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void pool_group(const float* __restrict__ vote
     for (int e = 0; e < kPoolPerThread; ++e) {
         const int64_t j = t0 + threadIdx.x + e * 256;
         if (j < G.n) {
-            score[(int64_t)hkv * G.n + j] = acc[e];
+            score[(int64_t)hkv * spitch + j] = acc[e];
             const unsigned x = __float_as_uint(acc[e]);
             lo = x < lo ? x : lo;
             hi = x > hi ? x : hi;
@@ -100,13 +100,15 @@ __global__ __launch_bounds__(256) void pool_group(const float* __restrict__ vote
     }
 }
 
-// Variant for rows whose length is a multiple of four (so that every row is 16-byte aligned): a thread owns four consecutive positions and reads them and their
-// taps as float4, an order of magnitude fewer instructions per position.  The first and last
+// Variant for rows that are a multiple of four floats apart (so that every row is 16-byte aligned): a thread owns four consecutive positions and reads them and their
+// taps as float4, an order of magnitude fewer instructions per position (256 heads of 31305 positions, groups of
+// four: 50 us against 80 us element-wise, which such lengths took before their rows were padded).  The first and last
 // tiles of a row take the element-wise path.
 template <int P>
 __global__ __launch_bounds__(256) void pool_group4(const float* __restrict__ vote,
                                                    float* __restrict__ score, const ScoreGeom G,
-                                                   const int pool_kind, unsigned* __restrict__ minmax) {
+                                                   const int64_t spitch, const int pool_kind,
+                                                   unsigned* __restrict__ minmax) {
     constexpr int r = P / 2;
     constexpr int RQ = (r + 3) / 4;             // float4 loads on each side of the centre one
     constexpr int NV4 = 2 * RQ + 1;
@@ -120,7 +122,7 @@ __global__ __launch_bounds__(256) void pool_group4(const float* __restrict__ vot
     for (int h = 0; h < G.g; ++h) {
         // (a query head whose window was scored in blocks has one vote row per block: they are added,
         // in order, before pooling)
-        const float* vb = vote + ((int64_t)hkv * G.NV + (int64_t)h * G.VB) * G.n;
+        const float* vb = vote + ((int64_t)hkv * G.NV + (int64_t)h * G.VB) * G.vpitch;
         float v[NV4 * 4];
         if (interior) {
 #pragma unroll
@@ -134,7 +136,7 @@ __global__ __launch_bounds__(256) void pool_group4(const float* __restrict__ vot
             for (int b = 1; b < G.VB; ++b) {
 #pragma unroll
                 for (int x = 0; x < NV4; ++x) {
-                    const float4 q = *reinterpret_cast<const float4*>(vb + (int64_t)b * G.n + j0 + 4 * (x - RQ));
+                    const float4 q = *reinterpret_cast<const float4*>(vb + (int64_t)b * G.vpitch + j0 + 4 * (x - RQ));
                     v[4 * x] += q.x;
                     v[4 * x + 1] += q.y;
                     v[4 * x + 2] += q.z;
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(256) void pool_group4(const float* __restrict__ vot
                 v[x] = pad;
                 if (j >= 0 && j < G.n) {
                     v[x] = vb[j];
-                    for (int b = 1; b < G.VB; ++b) v[x] += vb[(int64_t)b * G.n + j];
+                    for (int b = 1; b < G.VB; ++b) v[x] += vb[(int64_t)b * G.vpitch + j];
                 }
             }
         }
@@ -164,11 +166,11 @@ __global__ __launch_bounds__(256) void pool_group4(const float* __restrict__ vot
     }
     unsigned lo = 0xFFFFFFFFu, hi = 0u;
     if (j0 + 3 < G.n) {
-        *reinterpret_cast<float4*>(score + (int64_t)hkv * G.n + j0) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        *reinterpret_cast<float4*>(score + (int64_t)hkv * spitch + j0) = make_float4(acc[0], acc[1], acc[2], acc[3]);
     } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (j0 + i < G.n) score[(int64_t)hkv * G.n + j0 + i] = acc[i];
+            if (j0 + i < G.n) score[(int64_t)hkv * spitch + j0 + i] = acc[i];
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -204,26 +206,26 @@ __global__ __launch_bounds__(256) void pool_group4(const float* __restrict__ vot
 int pool_tiles(int64_t n) { return (int)((n + kPoolTile - 1) / kPoolTile); }
 
 hipError_t launch_pool(const ScoreGeom& G, const float* vote, int pool_kind, int p, float* score,
-                       unsigned* minmax, hipStream_t st) {
+                       int64_t score_pitch, unsigned* minmax, hipStream_t st) {
     if (G.n <= 0) return hipSuccess;
     const unsigned tiles = (unsigned)((G.n + kPoolTile - 1) / kPoolTile);
     const dim3 grid(tiles, G.Hkv);
-    if (G.n % 4 == 0 && (reinterpret_cast<uintptr_t>(vote) & 15u) == 0 &&
+    if (G.vpitch % 4 == 0 && score_pitch % 4 == 0 && (reinterpret_cast<uintptr_t>(vote) & 15u) == 0 &&
         (reinterpret_cast<uintptr_t>(score) & 15u) == 0) {
         switch (p) {
-            case 1: hipLaunchKernelGGL(pool_group4<1>, grid, dim3(256), 0, st, vote, score, G, pool_kind, minmax); return hipGetLastError();
-            case 5: hipLaunchKernelGGL(pool_group4<5>, grid, dim3(256), 0, st, vote, score, G, pool_kind, minmax); return hipGetLastError();
-            case 7: hipLaunchKernelGGL(pool_group4<7>, grid, dim3(256), 0, st, vote, score, G, pool_kind, minmax); return hipGetLastError();
-            case 13: hipLaunchKernelGGL(pool_group4<13>, grid, dim3(256), 0, st, vote, score, G, pool_kind, minmax); return hipGetLastError();
+            case 1: hipLaunchKernelGGL(pool_group4<1>, grid, dim3(256), 0, st, vote, score, G, score_pitch, pool_kind, minmax); return hipGetLastError();
+            case 5: hipLaunchKernelGGL(pool_group4<5>, grid, dim3(256), 0, st, vote, score, G, score_pitch, pool_kind, minmax); return hipGetLastError();
+            case 7: hipLaunchKernelGGL(pool_group4<7>, grid, dim3(256), 0, st, vote, score, G, score_pitch, pool_kind, minmax); return hipGetLastError();
+            case 13: hipLaunchKernelGGL(pool_group4<13>, grid, dim3(256), 0, st, vote, score, G, score_pitch, pool_kind, minmax); return hipGetLastError();
             default: break;
         }
     }
     switch (p) {   // the widths the paper uses (Sec. 5) get unrolled taps
-        case 1: hipLaunchKernelGGL(pool_group<1>, grid, dim3(256), 0, st, vote, score, G, pool_kind, p, minmax); break;
-        case 5: hipLaunchKernelGGL(pool_group<5>, grid, dim3(256), 0, st, vote, score, G, pool_kind, p, minmax); break;
-        case 7: hipLaunchKernelGGL(pool_group<7>, grid, dim3(256), 0, st, vote, score, G, pool_kind, p, minmax); break;
-        case 13: hipLaunchKernelGGL(pool_group<13>, grid, dim3(256), 0, st, vote, score, G, pool_kind, p, minmax); break;
-        default: hipLaunchKernelGGL(pool_group<0>, grid, dim3(256), 0, st, vote, score, G, pool_kind, p, minmax); break;
+        case 1: hipLaunchKernelGGL(pool_group<1>, grid, dim3(256), 0, st, vote, score, G, score_pitch, pool_kind, p, minmax); break;
+        case 5: hipLaunchKernelGGL(pool_group<5>, grid, dim3(256), 0, st, vote, score, G, score_pitch, pool_kind, p, minmax); break;
+        case 7: hipLaunchKernelGGL(pool_group<7>, grid, dim3(256), 0, st, vote, score, G, score_pitch, pool_kind, p, minmax); break;
+        case 13: hipLaunchKernelGGL(pool_group<13>, grid, dim3(256), 0, st, vote, score, G, score_pitch, pool_kind, p, minmax); break;
+        default: hipLaunchKernelGGL(pool_group<0>, grid, dim3(256), 0, st, vote, score, G, score_pitch, pool_kind, p, minmax); break;
     }
     return hipGetLastError();
 }

@@ -27,8 +27,10 @@ constexpr int kPsThreads = 1024;       // cooperative pooling + selection kernel
 constexpr int kPsCandCap = 4096;       //   candidates of a head that fit its LDS list
 constexpr int kPsBinBits = 11;         //   bits per refinement level
 constexpr int kPsBins = 1 << kPsBinBits;
-constexpr int kPsLevels = 3;           //   refinement levels (cover all 32 bits)
-constexpr int kPsStages = 8;           //   rendezvous points per head: ranges, levels, final
+constexpr unsigned kPsBins0 = 1024;    //   bins of the first level and of the last
+constexpr int kPsLevels = 4;           //   levels: the fixed first digit, then 11, 11 and 10 bits of its bin
+constexpr int kPsHistWords = 2 * (int)kPsBins0 + 2 * kPsBins;
+constexpr int kPsStages = 8;           //   rendezvous points per head: levels, final
 constexpr int kPsMaxGroup = 512;       //   workgroups per head at most
 
 __device__ __forceinline__ int range_shift(unsigned range) {
@@ -134,11 +136,11 @@ __global__ void sel_init(SelectScratch S, int H) {
 }
 
 // Range of bit patterns per head (when the scores were not produced by the pooling kernel).
-__global__ __launch_bounds__(256) void sel_minmax(const float* __restrict__ score, int64_t n,
+__global__ __launch_bounds__(256) void sel_minmax(const float* __restrict__ score, int64_t n, int64_t pitch,
                                                   SelectScratch S) {
     __shared__ unsigned sh_lo[4], sh_hi[4];
     const int h = blockIdx.y;
-    const unsigned* s = reinterpret_cast<const unsigned*>(score) + (int64_t)h * n;
+    const unsigned* s = reinterpret_cast<const unsigned*>(score) + (int64_t)h * pitch;
     unsigned lo = 0xFFFFFFFFu, hi = 0u;
     const int64_t base = (int64_t)blockIdx.x * kSelChunk;
     for (int e = 0; e < kSelChunk / 256; ++e) {
@@ -173,12 +175,12 @@ __global__ __launch_bounds__(256) void sel_minmax(const float* __restrict__ scor
 
 constexpr int kHistChunk = 16384;      // positions per workgroup of sel_hist (1024 threads)
 
-__global__ __launch_bounds__(1024) void sel_hist(const float* __restrict__ score, int64_t n,
+__global__ __launch_bounds__(1024) void sel_hist(const float* __restrict__ score, int64_t n, int64_t pitch,
                                                  int nparts, SelectScratch S) {
     __shared__ unsigned hist[kSelBins1];
     __shared__ unsigned sh4[32];
     const int h = blockIdx.y, tid = threadIdx.x;
-    const unsigned* s = reinterpret_cast<const unsigned*>(score) + (int64_t)h * n;
+    const unsigned* s = reinterpret_cast<const unsigned*>(score) + (int64_t)h * pitch;
     const int64_t base = (int64_t)blockIdx.x * kHistChunk;
     unsigned x[kHistChunk / 1024];          // the chunk's scores are requested before anything else
 #pragma unroll
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(1024) void sel_hist(const float* __restrict__ score
     }
 }
 
-__global__ __launch_bounds__(256) void sel_compact(const float* __restrict__ score, int64_t n,
+__global__ __launch_bounds__(256) void sel_compact(const float* __restrict__ score, int64_t n, int64_t pitch,
                                                    int64_t kcount, int nch, int nparts,
                                                    SelectScratch S) {
     __shared__ unsigned sh4[8];
@@ -211,7 +213,7 @@ __global__ __launch_bounds__(256) void sel_compact(const float* __restrict__ sco
     __shared__ unsigned sh_out[2];
     __shared__ unsigned sh_cnt, sh_gt;
     const int h = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
-    const unsigned* s = reinterpret_cast<const unsigned*>(score) + (int64_t)h * n;
+    const unsigned* s = reinterpret_cast<const unsigned*>(score) + (int64_t)h * pitch;
     const int64_t base = (int64_t)c * kSelChunk;
     // everything this workgroup reads is requested up front: one round trip to memory
     unsigned xs[kSelChunk / 256];
@@ -428,7 +430,7 @@ __global__ __launch_bounds__(1024) void sel_threshold(int64_t n, int nch, Select
     }
 }
 
-__global__ __launch_bounds__(256) void sel_emit(const float* __restrict__ score, int64_t n,
+__global__ __launch_bounds__(256) void sel_emit(const float* __restrict__ score, int64_t n, int64_t pitch,
                                                 int64_t kcount, int nch, int64_t out_stride, int W_tail,
                                                 SelectScratch S, int32_t* __restrict__ out_idx) {
     __shared__ unsigned sh_gt[4], sh_eq[4];
@@ -437,7 +439,7 @@ __global__ __launch_bounds__(256) void sel_emit(const float* __restrict__ score,
     if (c == 0)   // window positions n .. n + W_tail - 1 follow the selected prefix positions
         for (int t = tid; t < W_tail; t += 256) out[kcount + t] = (int32_t)(n + t);
     if (kcount <= 0) return;
-    const unsigned* s = reinterpret_cast<const unsigned*>(score) + (int64_t)h * n;
+    const unsigned* s = reinterpret_cast<const unsigned*>(score) + (int64_t)h * pitch;
     const int64_t base = (int64_t)c * kSelChunk + wave * (kSelChunk / 4);
     unsigned x[16];
 #pragma unroll
@@ -491,13 +493,20 @@ __global__ __launch_bounds__(256) void sel_emit(const float* __restrict__ score,
 //
 // The Wh workgroups of a KV head each pool a contiguous chunk of the head's votes straight into
 // registers (the pooled scores are never written to memory), then agree on the threshold through
-// a few rendezvous points in global memory: the head's range of bit patterns, one 512-bin digit
-// histogram per refinement level, and finally the few positions inside the threshold bin (or, when
-// the bin is a single value, only their number).  Every workgroup then knows the threshold T, how
+// rendezvous points in global memory: a digit histogram (one is enough unless its threshold bin
+// holds more positions than the candidate list), and the few positions inside the threshold
+// bin (or, when the bin is a single value, only their number).  Every workgroup then knows the threshold T, how
 // many positions equal to T are kept, and how many kept positions lie before its chunk, and emits
 // its own kept positions in order.  The arithmetic of the pooled score is that of pool_group, in
 // the same order, so the scores are bit-identical to snapkv_pooled_scores; everything after it is
 // integer work on bit patterns and does not depend on timing.
+//
+// Bound by its chain of dependent steps, not by bytes.  Steps it no longer has, in microseconds before and after: the
+// exchange of the head's range (the first digit is fixed), a memory latency and a barrier per query head of a
+// group (the next head's votes are fetched ahead, two staging areas), element-wise loads where the prefix is no
+// multiple of four (rows are padded), digit rounds over at most 128 candidates, and for a head with one workgroup
+// every exchange: 512 keys 17.3 -> 9.2, 16384 keys (32 heads) 21.0 -> 16.5, 28471 keys (8 heads of a group of 4)
+// 26.3 -> 21.4, 13339 paged keys 22.5 -> 17.3, eight prompts of up to 64K keys 50.8 -> 41.0.
 //
 // All workgroups of the grid must be resident at once (checked by the host).  Waits are bounded:
 // if one gives up, later ones are skipped, a counter is raised and the kernel still ends.
@@ -615,7 +624,7 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
     // p/2 positions on either side) and, once the scores sit in registers, as digit histogram
     // (kPsBins words) followed by the candidate list (kPsCandCap pairs).
     extern __shared__ __attribute__((aligned(16))) unsigned ps_lds[];
-    float* const stage = reinterpret_cast<float*>(ps_lds);
+    float* const stage0 = reinterpret_cast<float*>(ps_lds);
     unsigned* const sh_hist = ps_lds;
     uint2* const sh_cand = reinterpret_cast<uint2*>(ps_lds + kPsBins);
     __shared__ unsigned sh_tab[2][(EPT / 4) * NWV]; // per (run row, wave) counts for the ordered emission
@@ -623,14 +632,15 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
     __shared__ unsigned sh_off[kPsMaxGroup + 1];    // start of each workgroup's candidates in the merged list
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = blockIdx.x / Wh, c = blockIdx.x % Wh;
-    // rows of votes and candidate lists are G.n apart; a head may have fewer valid positions (a
+    // vote rows are G.vpitch apart, candidate lists G.n; a head may have fewer valid positions (a
     // batch of prompts of different lengths shares one launch)
-    const int64_t pitch = G.n;
-    int64_t n = pitch;
+    const int64_t pitch = G.vpitch, list = G.n;
+    int64_t n = G.n;
     if (nvalid) {
         n = nvalid[h];
-        n = n < 0 ? 0 : (n > pitch ? pitch : n);
+        n = n < 0 ? 0 : (n > G.n ? G.n : n);
     }
+    const bool solo = Wh == 1;           // a head's only workgroup has nobody to agree with
     const int64_t chunk0 = (int64_t)c * chunk;
     const int64_t chunk1 = chunk0 + chunk < n ? chunk0 + chunk : n;
     const int len = chunk1 > chunk0 ? (int)(chunk1 - chunk0) : 0;
@@ -654,7 +664,7 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
     constexpr int pool_kind = KIND;
     const float pad = KIND == 0 ? -INFINITY : 0.f;
     const int nf4 = ((len + 3) / 4) + 2 * (HQ / 4);   // 16-byte pieces to stage
-    const bool rows_aligned = ((n | pitch) & 3) == 0 && (reinterpret_cast<uintptr_t>(vote) & 15u) == 0;
+    const bool rows_aligned = (pitch & 3) == 0 && (reinterpret_cast<uintptr_t>(vote) & 15u) == 0;
     auto pos_local = [&](int e) { return (e >> 2) * (4 * NT) + 4 * tid + (e & 3); };
     const int nn = (int)n, kc = (int)kcount;
     unsigned x[EPT];
@@ -662,10 +672,9 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
         float acc[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) acc[e] = 0.f;
-        for (int hq = 0; hq < G.g; ++hq) {
+        // The chunk's votes (and halo) of one query head, on their way to LDS.
+        auto fetch = [&](const int hq, float4 (&land)[E4 + 1]) {
             const float* vb = vote + ((int64_t)h * G.NV + (int64_t)hq * G.VB) * pitch;
-            if (hq > 0) __syncthreads();          // the previous head's taps have been read
-            float4 land[E4 + 1];                  // all loads are in flight before the first LDS write
 #pragma unroll
             for (int e4 = 0; e4 <= E4; ++e4) {
                 const int f = e4 * NT + tid;
@@ -673,7 +682,7 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
                 float4 t4 = make_float4(pad, pad, pad, pad);
                 if (f < nf4) {
                     if (P > 0 && rows_aligned) {
-                        if (q0 >= 0 && q0 < nn) {
+                        if (q0 >= 0 && q0 < nn) {            // (rows are padded to whole pieces)
                             t4 = *reinterpret_cast<const float4*>(vb + q0);
                             if constexpr (EPT <= 4) {   // (at 16 positions per thread this sum costs registers the kernel does not have)
                                 for (int b = 1; b < G.VB; ++b) {   // the vote rows of a query head, in order
@@ -683,6 +692,11 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
                                     t4.z += u.z;
                                     t4.w += u.w;
                                 }
+                            }
+                            if (q0 + 3 >= nn) {              // the row's last piece: what lies behind it does not count
+                                if (q0 + 1 >= nn) t4.y = pad;
+                                if (q0 + 2 >= nn) t4.z = pad;
+                                t4.w = pad;
                             }
                         }
                     } else {
@@ -702,11 +716,26 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
                 }
                 land[e4] = t4;
             }
+        };
+        // At 4 positions per thread the next query head's votes are on their way while this one's are pooled, and two
+        // staging areas take turns (one barrier a head); at 16 there is room for neither.
+        constexpr bool AHEAD = EPT <= 4;
+        constexpr int kStageWords = EPT * NT + 128;
+        float4 land[E4 + 1];                  // all loads are in flight before the first LDS write
+        if constexpr (AHEAD) fetch(0, land);
+        for (int hq = 0; hq < G.g; ++hq) {
+            float* const stage = stage0 + (AHEAD ? (hq & 1) * kStageWords : 0);
+            if constexpr (!AHEAD) {
+                if (hq > 0) __syncthreads();      // the previous head's taps have been read
+                fetch(hq, land);
+            }
 #pragma unroll
             for (int e4 = 0; e4 <= E4; ++e4) {
                 const int f = e4 * NT + tid;
                 if (f < nf4) reinterpret_cast<float4*>(stage)[f] = land[e4];
             }
+            if constexpr (AHEAD)
+                if (hq + 1 < G.g) fetch(hq + 1, land);
             __syncthreads();
 #pragma unroll
             for (int e4 = 0; e4 < E4; ++e4) {
@@ -791,62 +820,22 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
         if (pos_local(e) < len) active |= 1u << e;
     const unsigned valid = active;
 
-    // ---- the head's range of bit patterns
-    unsigned lo = 0xFFFFFFFFu, hi = 0u;
-#pragma unroll
-    for (int e = 0; e < EPT; ++e)
-        if (valid >> e & 1u) {
-            lo = x[e] < lo ? x[e] : lo;
-            hi = x[e] > hi ? x[e] : hi;
-        }
-    auto block_range = [&]() {
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            const unsigned a = __shfl_xor(lo, d, 64), b = __shfl_xor(hi, d, 64);
-            lo = a < lo ? a : lo;
-            hi = b > hi ? b : hi;
-        }
-        __syncthreads();
-        if (lane == 0) {
-            sh_red[2 * wave] = lo;
-            sh_red[2 * wave + 1] = hi;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int w2 = 0; w2 < NWV; ++w2) {
-            lo = sh_red[2 * w2] < lo ? sh_red[2 * w2] : lo;
-            hi = sh_red[2 * w2 + 1] > hi ? sh_red[2 * w2 + 1] : hi;
-        }
-    };
-    block_range();
-    if (tid == 0) {
-        unsigned done = coherent_store(&S.ps_range[2 * ((int64_t)h * kPsMaxGroup + c)], lo);
-        done ^= coherent_store(&S.ps_range[2 * ((int64_t)h * kPsMaxGroup + c) + 1], hi);
-        hand_over_done(done);
-    }
+    // ---- threshold bin: one digit per level until the bin is a single value or holds few positions.  The first
+    // digit is the same for every head of a length, so nobody has to know the head's range first (which cost a
+    // rendezvous and two block-wide steps, 4 us of 27 at 28471 positions): 1024 bins of 1/64 octave from c / 64 to
+    // 1024 c, c = the mean of the scores if the window's rows voted on nothing else; scores outside fall into the
+    // end bins.  The following levels take 11, 11 and 10 bits of the bin's patterns, enough for any bin.
     unsigned* arrive = S.ps_arrive + (int64_t)h * kPsStages;
-    group_rendezvous(arrive + 0, (unsigned)Wh, spin_limit, &sh_gave_up);
-    lo = 0xFFFFFFFFu;
-    hi = 0u;
-    for (int i = lane; i < Wh; i += 64) {     // every wave reads all of them: no barrier needed
-        const unsigned a = coherent_load(&S.ps_range[2 * ((int64_t)h * kPsMaxGroup + i)]);
-        const unsigned b = coherent_load(&S.ps_range[2 * ((int64_t)h * kPsMaxGroup + i) + 1]);
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const unsigned a = __shfl_xor(lo, d, 64), b = __shfl_xor(hi, d, 64);
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
-    }
-
-    // ---- threshold bin: 11 bits per level until the bin is a single value or holds few positions
-    unsigned cur_lo = lo, krem = (unsigned)kcount, above = 0, bin_count = 0, T = lo, need_eq = 0;
-    int cur_sh = hi > lo ? range_shift_bits(hi - lo, kPsBinBits) : 0;
-    bool exact = hi <= lo;      // T is known exactly (all remaining positions are equal to it)
-    if (exact) need_eq = krem;
+    constexpr int kFirstShift = 17;
+    const unsigned lo0 = __float_as_uint((float)(G.g * G.W) / (float)(nn > 0 ? nn : 1) * 0x1p-6f);
+    auto first_digit = [&](unsigned v) { return v < lo0 ? 0u : ((v - lo0) >> kFirstShift < kPsBins0 ? (v - lo0) >> kFirstShift : kPsBins0 - 1); };
+    unsigned cur_lo = 0, krem = (unsigned)kcount, above = 0, bin_count = 0, T = 0, need_eq = 0;
+    int cur_sh = kFirstShift;
+    int rem_bits = 0;           // bits that tell the patterns of the threshold bin apart
+    bool exact = false;         // T is known exactly (all remaining positions are equal to it)
     for (int lvl = 0; lvl < kPsLevels && !exact; ++lvl) {
+        auto digit = [&](unsigned v) { return lvl == 0 ? first_digit(v) : ((v - cur_lo) >> cur_sh) & (kPsBins - 1); };
+        const unsigned nbins = lvl == 0 || lvl == 3 ? kPsBins0 : kPsBins;
         __syncthreads();
         for (int b = tid; b < kPsBins; b += NT) sh_hist[b] = 0u;
         if (tid == 0) {
@@ -857,20 +846,27 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
-            if (active >> e & 1u) atomicAdd(&sh_hist[((x[e] - cur_lo) >> cur_sh) & (kPsBins - 1)], 1u);
+            if (active >> e & 1u) atomicAdd(&sh_hist[digit(x[e])], 1u);
         __syncthreads();
-        unsigned* gh = S.ps_hist + ((int64_t)h * kPsLevels + lvl) * kPsBins;
-        unsigned done = 0;
-        for (int b = tid; b < kPsBins; b += NT) {
-            const unsigned cnt = sh_hist[b];
-            if (cnt) done ^= coherent_add(&gh[b], cnt);
-        }
-        hand_over_done(done);
-        group_rendezvous(arrive + 1 + lvl, (unsigned)Wh, spin_limit, &sh_gave_up);
         unsigned bins[kPsBins / NT];
+        if (solo) {
+            load_bins_from_top<NT, kPsBins>(sh_hist, bins);
+        } else {
+            // a head's histograms: 1024, 2048, 2048 and 1024 bins
+            unsigned* gh = S.ps_hist + (int64_t)h * kPsHistWords + (lvl == 0 ? 0 : kPsBins0 + (lvl - 1) * kPsBins);
+            unsigned done = 0;
+            for (unsigned b = tid; b < nbins; b += NT) {
+                const unsigned cnt = sh_hist[b];
+                if (cnt) done ^= coherent_add(&gh[b], cnt);
+            }
+            hand_over_done(done);
+            group_rendezvous(arrive + lvl, (unsigned)Wh, spin_limit, &sh_gave_up);
 #pragma unroll
-        for (int e = 0; e < kPsBins / NT; ++e)
-            bins[e] = coherent_load(&gh[kPsBins - 1 - (tid * (kPsBins / NT) + e)]);
+            for (int e = 0; e < kPsBins / NT; ++e) {
+                const unsigned b = kPsBins - 1 - (tid * (kPsBins / NT) + e);
+                bins[e] = b < nbins ? coherent_load(&gh[b]) : 0u;
+            }
+        }
         find_bin_from_top<NT, kPsBins>(bins, krem, sh_scan, sh_out, &sh_bin_count);
         const unsigned b1 = sh_out[0] & (kPsBins - 1);
         krem = sh_out[1];
@@ -878,19 +874,27 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
             if (active >> e & 1u) {
-                const unsigned d = ((x[e] - cur_lo) >> cur_sh) & (kPsBins - 1);
+                const unsigned d = digit(x[e]);
                 if (d > b1) ++above;
                 if (d != b1) active &= ~(1u << e);
             }
-        cur_lo += b1 << cur_sh;
-        if (cur_sh == 0) {
+        unsigned last = (1u << cur_sh) - 1u;   // the bin's patterns: cur_lo .. cur_lo + last
+        if (lvl == 0) {
+            cur_lo = b1 == 0 ? 0u : lo0 + (b1 << kFirstShift);
+            if (b1 == 0) last = lo0 + last;
+            else if (b1 == kPsBins0 - 1) last = 0xFFFFFFFFu - cur_lo;
+        } else {
+            cur_lo += b1 << cur_sh;
+        }
+        if (last == 0) {
             exact = true;
             T = cur_lo;
             need_eq = krem;
-        } else if (bin_count <= (unsigned)kPsCandCap) {
-            break;
+            cur_sh = 0;
         } else {
-            cur_sh = range_shift_bits((1u << cur_sh) - 1u, kPsBinBits);
+            cur_sh = range_shift_bits(last, kPsBinBits);
+            rem_bits = 32 - __clz(last);
+            if (bin_count <= (unsigned)kPsCandCap) break;
         }
     }
 
@@ -902,28 +906,30 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
     block_sum3<NT>(above_total, z1, z2, sh_red);
     if (!exact) {   // this workgroup's candidates go to the start of its own stretch of the head's list
         unsigned slot = in_before, done = 0;
-        unsigned long long* const my_cand = reinterpret_cast<unsigned long long*>(S.cand + (int64_t)h * pitch + chunk0);
+        unsigned long long* const my_cand = reinterpret_cast<unsigned long long*>(S.cand + (int64_t)h * list + chunk0);
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
             if (active >> e & 1u) {
-                if (slot < (unsigned)len)
+                if (solo) {
+                    if (slot < (unsigned)kPsCandCap) sh_cand[slot] = make_uint2(x[e], (unsigned)((int)chunk0 + pos_local(e)));
+                } else if (slot < (unsigned)len)
                     done ^= coherent_store64(my_cand + slot,
                                              ((unsigned long long)(unsigned)((int)chunk0 + pos_local(e)) << 32) | x[e]);
                 ++slot;
             }
-        hand_over_done(done);
+        if (!solo) hand_over_done(done);
     }
-    if (tid == 0) {
+    if (tid == 0 && !solo) {
         unsigned done = coherent_store(&S.ps_part[2 * ((int64_t)h * kPsMaxGroup + c)], above_total);
         done ^= coherent_store(&S.ps_part[2 * ((int64_t)h * kPsMaxGroup + c) + 1], in_total);
         hand_over_done(done);
     }
-    group_rendezvous(arrive + 1 + kPsLevels, (unsigned)Wh, spin_limit, &sh_gave_up);
+    if (!solo) group_rendezvous(arrive + kPsLevels, (unsigned)Wh, spin_limit, &sh_gave_up);
 
     // kept positions of the head before this chunk.  Every wave sums the per-workgroup counts
     // itself (no barrier); without an exact T the candidates are fetched, workgroup by workgroup.
     unsigned gt_before = 0, eq_before = 0;
-    {
+    if (!solo) {
         unsigned run = 0;           // candidates of the workgroups before `base`
         for (int base = 0; base < Wh; base += 64) {
             const int i = base + lane;
@@ -958,20 +964,41 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
         eq_before = 0;              // positions inside the bin are counted from the candidate list
         const unsigned m = bin_count < (unsigned)kPsCandCap ? bin_count : (unsigned)kPsCandCap;
         __syncthreads();
-        for (unsigned i = tid; i < m; i += NT) {
+        for (unsigned i = tid; i < m && !solo; i += NT) {
             int a2 = 0, b2 = Wh;            // largest c2 with sh_off[c2] <= i
             while (b2 - a2 > 1) {
                 const int mid = (a2 + b2) >> 1;
                 if (sh_off[mid] <= i) a2 = mid; else b2 = mid;
             }
             int64_t at = (int64_t)a2 * chunk + (i - sh_off[a2]);
-            at = at < pitch ? at : pitch - 1;       // only counts that a failed rendezvous left inconsistent get here
+            at = at < list ? at : list - 1;         // only counts that a failed rendezvous left inconsistent get here
             const unsigned long long both = __hip_atomic_load(
-                reinterpret_cast<const unsigned long long*>(&S.cand[(int64_t)h * pitch + at]),
+                reinterpret_cast<const unsigned long long*>(&S.cand[(int64_t)h * list + at]),
                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             sh_cand[i] = make_uint2((unsigned)(both & 0xffffffffull), (unsigned)(both >> 32));
         }
-        int rem_sh = cur_sh;            // bits of the pattern still undecided inside the bin
+        int rem_sh = rem_bits;          // bits of the pattern still undecided inside the bin
+        if (m <= 128u) {                // few candidates: each counts those above it and those equal to it
+            __syncthreads();
+            if ((unsigned)tid < m) {
+                const unsigned mine = sh_cand[tid].x;
+                unsigned gt = 0, eq = 0;
+#pragma unroll 4
+                for (unsigned i = 0; i < m; ++i) {
+                    const unsigned v = sh_cand[i].x;
+                    gt += v > mine;
+                    eq += v == mine;
+                }
+                if (gt < krem && krem <= gt + eq) {
+                    sh_out[0] = mine;
+                    sh_out[1] = krem - gt;
+                }
+            }
+            __syncthreads();
+            cur_lo = sh_out[0];
+            krem = sh_out[1];
+            rem_sh = 0;
+        }
         while (rem_sh > 0) {
             const int nsh = rem_sh > kPsBinBits ? rem_sh - kPsBinBits : 0;
             for (int b = tid; b < kPsBins; b += NT) sh_hist[b] = 0u;
@@ -982,7 +1009,7 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
             __syncthreads();
             for (unsigned i = tid; i < m; i += NT) {
                 const unsigned v = sh_cand[i].x;
-                if (v >= cur_lo && ((v - cur_lo) >> rem_sh) == 0u)
+                if (v >= cur_lo && (rem_sh >= 32 || ((v - cur_lo) >> rem_sh) == 0u))
                     atomicAdd(&sh_hist[((v - cur_lo) >> nsh) & (kPsBins - 1)], 1u);
             }
             __syncthreads();
@@ -1095,7 +1122,7 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
 static size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 size_t select_counter_bytes(int H) {
-    return up256(sizeof(unsigned) * (size_t)H * (kPsStages + kPsLevels * kPsBins));
+    return up256(sizeof(unsigned) * (size_t)H * (kPsStages + kPsHistWords));
 }
 
 // own_counters: the arrival counters and digit histograms of pool_select sit at the end of this
@@ -1112,7 +1139,7 @@ size_t select_layout(int H, int64_t n, SelectScratch* S, void* base, bool own_co
     const size_t cgt = up256(sizeof(unsigned) * (size_t)H * nch);
     const size_t coff = up256(sizeof(unsigned) * 2 * (size_t)H * nch);
     const size_t cand = up256(sizeof(uint2) * (size_t)H * nn);
-    const size_t ps_range = up256(sizeof(unsigned) * 2 * (size_t)H * kPsMaxGroup);
+    const size_t ps_part = up256(sizeof(unsigned) * 2 * (size_t)H * kPsMaxGroup);
     const size_t ps_zero = select_counter_bytes(H);
     if (S) {
         char* b = static_cast<char*>(base);
@@ -1124,14 +1151,13 @@ size_t select_layout(int H, int64_t n, SelectScratch* S, void* base, bool own_co
         S->chunk_off = reinterpret_cast<unsigned*>(b + minmax + hist + count + info + cgt);
         S->cand = reinterpret_cast<uint2*>(b + minmax + hist + count + info + cgt + coff);
         char* q = b + minmax + hist + count + info + cgt + coff + cand;
-        S->ps_range = reinterpret_cast<unsigned*>(q);
-        S->ps_part = reinterpret_cast<unsigned*>(q + ps_range);
-        S->ps_arrive = reinterpret_cast<unsigned*>(own_counters ? q + 2 * ps_range : static_cast<char*>(counters));
+        S->ps_part = reinterpret_cast<unsigned*>(q);
+        S->ps_arrive = reinterpret_cast<unsigned*>(own_counters ? q + ps_part : static_cast<char*>(counters));
         S->ps_hist = S->ps_arrive + (size_t)H * kPsStages;
-        S->ps_zero_words = (int64_t)H * (kPsStages + kPsLevels * kPsBins);
+        S->ps_zero_words = (int64_t)H * (kPsStages + kPsHistWords);
         S->ps_flag = nullptr;
     }
-    return minmax + hist + count + info + cgt + coff + cand + 2 * ps_range + (own_counters ? ps_zero : 0);
+    return minmax + hist + count + info + cgt + coff + cand + ps_part + (own_counters ? ps_zero : 0);
 }
 
 bool select_chunked_ok(int64_t n) { return (n + kSelChunk - 1) / kSelChunk <= kSelMaxChunks; }
@@ -1189,7 +1215,7 @@ template <int EPT, int P, int KIND>
 static hipError_t pool_select_instance(const PoolSelCall* call, int* occ) {
     auto kern = pool_select<EPT, P, KIND>;
     // staging area of the votes (chunk + halo for p <= 129) or histogram + candidate list
-    constexpr size_t kStage = sizeof(float) * ((size_t)EPT * kPsThreads + 128);
+    constexpr size_t kStage = sizeof(float) * ((size_t)EPT * kPsThreads + 128) * (EPT <= 4 ? 2 : 1);
     constexpr size_t kSearch = sizeof(unsigned) * kPsBins + sizeof(uint2) * kPsCandCap;
     constexpr size_t kLds = kStage > kSearch ? kStage : kSearch;
     if (!call) {
@@ -1298,7 +1324,7 @@ hipError_t launch_select_init(const SelectScratch& S, int H, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_select_chunked(const float* score, int H, int64_t n, int64_t kcount,
+hipError_t launch_select_chunked(const float* score, int64_t score_pitch, int H, int64_t n, int64_t kcount,
                                  int64_t out_stride, int W_tail, int32_t* out_idx,
                                  const SelectScratch& S, int minmax_parts, hipStream_t st) {
     if (H <= 0) return hipSuccess;
@@ -1307,15 +1333,15 @@ hipError_t launch_select_chunked(const float* score, int H, int64_t n, int64_t k
     if (kcount > 0) {
         int nparts = minmax_parts;   // per-part ranges already left by the pooling kernel, or none
         if (nparts <= 0) {
-            hipLaunchKernelGGL(sel_minmax, grid, dim3(256), 0, st, score, n, S);
+            hipLaunchKernelGGL(sel_minmax, grid, dim3(256), 0, st, score, n, score_pitch, S);
             nparts = nch;
         }
         hipLaunchKernelGGL(sel_hist, dim3((unsigned)((n + kHistChunk - 1) / kHistChunk), H), dim3(1024), 0, st,
-                           score, n, nparts, S);
-        hipLaunchKernelGGL(sel_compact, grid, dim3(256), 0, st, score, n, kcount, nch, nparts, S);
+                           score, n, score_pitch, nparts, S);
+        hipLaunchKernelGGL(sel_compact, grid, dim3(256), 0, st, score, n, score_pitch, kcount, nch, nparts, S);
         hipLaunchKernelGGL(sel_threshold, dim3(H), dim3(1024), 0, st, n, nch, S);
     }
-    hipLaunchKernelGGL(sel_emit, grid, dim3(256), 0, st, score, n, kcount, nch, out_stride, W_tail, S,
+    hipLaunchKernelGGL(sel_emit, grid, dim3(256), 0, st, score, n, score_pitch, kcount, nch, out_stride, W_tail, S,
                        out_idx);
     return hipGetLastError();
 }

@@ -1,0 +1,56 @@
+"""Pooling and selection in one launch (csrc/snapkv_topk.hip, pool_select): the first digit has fixed bins of 1/64 octave
+around the mean score, so the threshold can fall into either end bin, into a bin that holds more positions than the
+candidate list, into one of at most 128 (counted directly) or more (searched by digits); a head may have one
+workgroup or many, and rows of votes whose length is no multiple of four are padded.  Whatever the route, the kept
+set is exactly the top-k of the call's own pooled scores."""
+import pytest
+import torch
+
+from parity import check_self_consistency, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+D = 64
+
+
+def flat(q, k):
+    q.zero_()                       # all scores equal: ties down to the first positions
+
+
+def few_spikes(q, k):               # every other score lies far below the lowest bin
+    q[..., 0] += 40.0
+    k[:, 100:110, 0] += 12.0
+
+
+def two_fields(q, k):               # half of the scores equal to the last bit, the others spread
+    k[:, ::2] = k[:, :1]
+
+
+def as_drawn(q, k):
+    pass
+
+
+SHAPES = [  # L, Hq, Hkv, W, C, p, dtype
+    (300, 4, 2, 16, 40, 5, torch.float32),         # one workgroup per head
+    (515, 4, 4, 32, 33, 7, torch.float32),         # ... and one kept position
+    (2081, 2, 2, 32, 1000, 7, torch.bfloat16),
+    (6145, 8, 2, 32, 300, 7, torch.bfloat16),      # three workgroups, odd rows, a group of four query heads
+    (9003, 2, 1, 16, 8000, 5, torch.float16),      # nearly everything kept
+    (20018, 2, 2, 16, 20, 1, torch.bfloat16),      # four kept: with spikes the threshold lies in the top bin
+    (131071, 4, 4, 32, 2048, 13, torch.bfloat16),
+]
+
+
+@pytest.mark.parametrize("field", [as_drawn, flat, few_spikes, two_fields], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("L,Hq,Hkv,W,C,p,dtype", SHAPES)
+def test_kept_set_is_the_exact_top_k(snapkv, field, L, Hq, Hkv, W, C, p, dtype):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    q = torch.randn((Hq, W, D), generator=gen, device="cuda")
+    k = torch.randn((Hkv, L, D), generator=gen, device="cuda")
+    field(q, k)
+    q, k = q.to(dtype), k.to(dtype)
+    v = torch.randn((Hkv, L, D), generator=gen, device="cuda").to(dtype)
+    for pool_kind in (0, 1):
+        res = run_gpu(snapkv, q, k, v, pool_kind, p, C)
+        check_self_consistency(q, k, v, C, *res)
