@@ -515,6 +515,13 @@ int64_t compress_impl(int dtype, const void* q_win, const void* k, const void* v
             clean.zeros = ws.sel.ps_arrive;
             clean.nzeros = ws.sel.ps_zero_words;
         }
+    } else if (g_allow_pool_select && pool_pick_ok(Gsel, p, C - W)) {   // more heads, or longer ones: the votes read once
+        ScoreGeom Gv = G;   // (these kernels find no counters to start from: only the hand-off words are made ready)
+        rc = run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, nullptr, 0, nullptr, false, &Gv, st, false, nullptr, lse,
+                        blocks_ok, true, score_layers);
+        if (rc != SNAPKV_OK) return rc;
+        if (per_query_head) Gv = Gsel;
+        se = launch_pool_pick(Gv, ws.vote, pool_kind, p, C - W, C, W, idx_dst, ws.sel, st);
     } else {
         if (per_query_head) {   // votes first, then pooled per query head
             ScoreGeom Gv = G;

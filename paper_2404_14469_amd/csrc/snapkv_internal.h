@@ -218,6 +218,10 @@ hipError_t launch_pool_select(const ScoreGeom& G, const float* vote, int pool_ki
                               int64_t out_stride, int W_tail, int32_t* out_idx, const SelectScratch& S,
                               hipStream_t st, const int32_t* nvalid = nullptr);
 unsigned read_select_timeouts();
+// Pooling and selection of many or long heads with the votes read once (three launches, nothing waits).
+bool pool_pick_ok(const ScoreGeom& G, int p, int64_t kcount);
+hipError_t launch_pool_pick(const ScoreGeom& G, const float* vote, int pool_kind, int p, int64_t kcount, int64_t out_stride,
+                            int W_tail, int32_t* out_idx, const SelectScratch& S, hipStream_t st);
 
 // Hit rate of the voting (snapkv_hitrate.hip).
 size_t hit_rate_scratch_bytes(int Hq, int64_t Lk);

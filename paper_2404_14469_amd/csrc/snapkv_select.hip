@@ -1,6 +1,7 @@
 // Pooling + group sum (Sec. 4.3; Listing 1, the pool1d call) as a kernel of its own, and the gather of the
 // kept rows (Listing 1, the two gathers and concatenations).  The top-k selection is in snapkv_topk.hip.
 #include "snapkv_internal.h"
+#include "snapkv_pool.h"
 #include <type_traits>
 
 namespace snapkv {
@@ -109,61 +110,13 @@ __global__ __launch_bounds__(256) void pool_group4(const float* __restrict__ vot
                                                    float* __restrict__ score, const ScoreGeom G,
                                                    const int64_t spitch, const int pool_kind,
                                                    unsigned* __restrict__ minmax) {
-    constexpr int r = P / 2;
-    constexpr int RQ = (r + 3) / 4;             // float4 loads on each side of the centre one
-    constexpr int NV4 = 2 * RQ + 1;
+    constexpr int RQ = (P / 2 + 3) / 4;
     __shared__ unsigned sh_lo[4], sh_hi[4];
     const int hkv = blockIdx.y;
     const int64_t t0 = (int64_t)blockIdx.x * kPoolTile;
     const int64_t j0 = t0 + 4 * threadIdx.x;
-    const bool interior = t0 >= 4 * RQ && t0 + kPoolTile + 4 * RQ <= G.n;
-    const float pad = pool_kind == 0 ? -INFINITY : 0.f;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int h = 0; h < G.g; ++h) {
-        // (a query head whose window was scored in blocks has one vote row per block: they are added,
-        // in order, before pooling)
-        const float* vb = vote + ((int64_t)hkv * G.NV + (int64_t)h * G.VB) * G.vpitch;
-        float v[NV4 * 4];
-        if (interior) {
-#pragma unroll
-            for (int x = 0; x < NV4; ++x) {
-                const float4 q = *reinterpret_cast<const float4*>(vb + j0 + 4 * (x - RQ));
-                v[4 * x] = q.x;
-                v[4 * x + 1] = q.y;
-                v[4 * x + 2] = q.z;
-                v[4 * x + 3] = q.w;
-            }
-            for (int b = 1; b < G.VB; ++b) {
-#pragma unroll
-                for (int x = 0; x < NV4; ++x) {
-                    const float4 q = *reinterpret_cast<const float4*>(vb + (int64_t)b * G.vpitch + j0 + 4 * (x - RQ));
-                    v[4 * x] += q.x;
-                    v[4 * x + 1] += q.y;
-                    v[4 * x + 2] += q.z;
-                    v[4 * x + 3] += q.w;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int x = 0; x < NV4 * 4; ++x) {
-                const int64_t j = j0 + x - 4 * RQ;
-                v[x] = pad;
-                if (j >= 0 && j < G.n) {
-                    v[x] = vb[j];
-                    for (int b = 1; b < G.VB; ++b) v[x] += vb[(int64_t)b * G.vpitch + j];
-                }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float val = v[4 * RQ + i - r];
-#pragma unroll
-            for (int d = 1; d < P; ++d)
-                val = pool_kind == 0 ? fmaxf(val, v[4 * RQ + i - r + d]) : val + v[4 * RQ + i - r + d];
-            if (pool_kind != 0) val = val / (float)P;
-            acc[i] += val;
-        }
-    }
+    float acc[4];
+    pooled_run<P>(vote, G, hkv, j0, t0 >= 4 * RQ && t0 + kPoolTile + 4 * RQ <= G.n, pool_kind, acc);
     unsigned lo = 0xFFFFFFFFu, hi = 0u;
     if (j0 + 3 < G.n) {
         *reinterpret_cast<float4*>(score + (int64_t)hkv * spitch + j0) = make_float4(acc[0], acc[1], acc[2], acc[3]);

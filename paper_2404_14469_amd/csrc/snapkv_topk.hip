@@ -16,6 +16,7 @@
 //                 round), then turns per-chunk counts into per-chunk output offsets
 //   sel_emit      chunks again: ordered emission by wavefront ballot / prefix counts
 #include "snapkv_internal.h"
+#include "snapkv_pool.h"
 
 namespace snapkv {
 
@@ -487,6 +488,353 @@ __global__ __launch_bounds__(256) void sel_emit(const float* __restrict__ score,
     }
 }
 
+
+// ------------------------------------------------------------------------------------------------
+// Pooling, group sum and top-k of many heads, or of heads too long for the one-launch kernel below, without storing
+// the scores.  The kernels above read 4 bytes per position and pass from memory, three times after the pooling kernel
+// has written them; here the votes are read once:
+//
+//   pick_bracket   one workgroup per head: scores of 2048 sampled positions (512 runs of four, evenly spread) give a
+//                  pattern Tlo that with near certainty no more than a small multiple of kcount positions reach, and at
+//                  least kcount do (the sample's rank is kcount's plus five standard deviations of its count,
+//                  the four positions of a run taken as one)
+//   pool_collect   chunks of 4096 positions: pooled scores, the positions with pattern >= Tlo kept in order in the
+//                  chunk's part of the candidate list
+//   pick_finish    one workgroup per head: the exact threshold among the candidates by digits of 1/64 octave, 11 and 6
+//                  bits, then the ordered emission; a head whose sample misled (fewer than kcount candidates) is
+//                  collected again by its own workgroup with Tlo = 0, so the result never depends on the sample
+//
+// Microseconds after the scoring, before (pool_group4, sel_hist, sel_compact, sel_threshold, sel_emit and the counters
+// they start from) and now: 1024 heads of 131040 positions 693 / 297 (pool_collect reads its 537 MB in 176, 3.0 TB/s),
+// 32 heads of 379984 positions 83 / 57, 256 heads in groups of four of 31305 positions 103 / 98.
+// ------------------------------------------------------------------------------------------------
+constexpr int kPickSamples = 2048;
+constexpr int kPickShift = 17;         // digits of 1/64 octave
+
+// Lower edge of the first-digit bins (see pool_select): 1/64 of the mean if the window's rows voted on nothing else.
+__device__ __forceinline__ unsigned bins_from(const ScoreGeom& G, int64_t n) {
+    return __float_as_uint((float)(G.g * G.W) / (float)(n > 0 ? n : 1) * 0x1p-6f);
+}
+
+template <int P>
+__global__ __launch_bounds__(512) void pick_bracket(const float* __restrict__ vote, const ScoreGeom G, const int pool_kind,
+                                                    const unsigned rank, SelectScratch S) {
+    constexpr int RQ = (P / 2 + 3) / 4;
+    __shared__ unsigned hist[kSelBins];
+    __shared__ unsigned sh_scan[16], sh_out[2];
+    const int h = blockIdx.x, tid = threadIdx.x;
+    if (rank >= (unsigned)kPickSamples || G.n < 4 * kPickSamples) {   // (uniform) nearly everything is kept, or little to gain
+        if (tid == 0) S.info[4 * h] = 0u;
+        return;
+    }
+    for (int b = tid; b < kSelBins; b += 512) hist[b] = 0u;
+    if (tid == 0) sh_out[0] = 0u;
+    __syncthreads();
+    const int64_t j0 = ((G.n - 4) * tid / 511) & ~(int64_t)3;         // runs inside the row
+    float acc[4];
+    pooled_run<P>(vote, G, h, j0, j0 >= 4 * RQ && j0 + 4 + 4 * RQ <= G.n, pool_kind, acc);
+    const unsigned lo0 = bins_from(G, G.n);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned x = __float_as_uint(acc[i]);
+        const unsigned d = x < lo0 ? 0u : (x - lo0) >> kPickShift;
+        atomicAdd(&hist[d < kSelBins ? d : kSelBins - 1], 1u);
+    }
+    __syncthreads();
+    unsigned bins[kSelBins / 512];
+    load_bins_from_top<512, kSelBins>(hist, bins);
+    find_bin_from_top<512, kSelBins>(bins, rank, sh_scan, sh_out);
+    if (tid == 0) S.info[4 * h] = sh_out[0] == 0u ? 0u : lo0 + (sh_out[0] << kPickShift);
+}
+
+// The chunk's votes pass through LDS once per query head (the next head's are on their way meanwhile); a thread owns
+// four runs of four positions, 1024 apart.
+template <int P>
+__global__ __launch_bounds__(256) void pool_collect(const float* __restrict__ vote, const ScoreGeom G, const int pool_kind,
+                                                    const int nch, SelectScratch S) {
+    static_assert(kSelChunk == 16 * 256, "a chunk is four runs of four positions per thread");
+    constexpr int NT = 256, NW = NT / 64, RQ = (P / 2 + 3) / 4, NV4 = 2 * RQ + 1;
+    constexpr int PIECES = kSelChunk / 4 + 2 * RQ;
+    __shared__ float4 stage[PIECES];
+    __shared__ unsigned sh[4 * NW];
+    const int h = blockIdx.y, c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int base = c * kSelChunk, n = (int)G.n;     // (at most 2^24 positions)
+    const float pad = pool_kind == 0 ? -INFINITY : 0.f;
+    const unsigned tlo = S.info[4 * h];
+    auto piece = [&](const float* row, int f) {       // piece f of the staged stretch, which begins RQ pieces early
+        const int q0 = base + 4 * (f - RQ);
+        float4 t = make_float4(pad, pad, pad, pad);
+        if (q0 >= 0 && q0 < n) {
+            t = *reinterpret_cast<const float4*>(row + q0);
+            for (int b = 1; b < G.VB; ++b) {          // the vote rows of a query head, in order
+                const float4 u = *reinterpret_cast<const float4*>(row + (int64_t)b * G.vpitch + q0);
+                t.x += u.x;
+                t.y += u.y;
+                t.z += u.z;
+                t.w += u.w;
+            }
+            if (q0 + 3 >= n) {
+                if (q0 + 1 >= n) t.y = pad;
+                if (q0 + 2 >= n) t.z = pad;
+                t.w = pad;
+            }
+        }
+        return t;
+    };
+    float4 land[5];
+    auto fetch = [&](int hq) {
+        const float* row = vote + ((int64_t)h * G.NV + (int64_t)hq * G.VB) * G.vpitch;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) land[e] = piece(row, e * NT + tid);
+        if (tid < 2 * RQ) land[4] = piece(row, 4 * NT + tid);
+    };
+    float acc[4][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[e][k] = 0.f;
+    fetch(0);
+    for (int hq = 0; hq < G.g; ++hq) {
+        if (hq > 0) __syncthreads();                  // the previous head's taps have been read
+#pragma unroll
+        for (int e = 0; e < 4; ++e) stage[e * NT + tid] = land[e];
+        if (tid < 2 * RQ) stage[4 * NT + tid] = land[4];
+        if (hq + 1 < G.g) fetch(hq + 1);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float v[4 * NV4];
+#pragma unroll
+            for (int x = 0; x < NV4; ++x) {
+                const float4 q = stage[e * NT + tid + x];
+                v[4 * x] = q.x;
+                v[4 * x + 1] = q.y;
+                v[4 * x + 2] = q.z;
+                v[4 * x + 3] = q.w;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {             // (arithmetic and order of pooled_run)
+                float val = v[4 * RQ + k - P / 2];
+#pragma unroll
+                for (int d = 1; d < P; ++d)
+                    val = pool_kind == 0 ? fmaxf(val, v[4 * RQ + k - P / 2 + d]) : val + v[4 * RQ + k - P / 2 + d];
+                if (pool_kind != 0) val = val / (float)P;
+                acc[e][k] += val;
+            }
+        }
+    }
+    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    unsigned before[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int j0 = base + e * (4 * NT) + 4 * tid;
+        unsigned cnt = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) cnt += j0 + k < n && __float_as_uint(acc[e][k]) >= tlo;
+        unsigned ex = 0, tot = 0;        // counts are at most 4: the wave's exclusive scan is three ballots
+#pragma unroll
+        for (int bit = 0; bit < 3; ++bit) {
+            const unsigned long long m = __ballot(cnt >> bit & 1u);
+            ex += (unsigned)__popcll(m & lt_mask) << bit;
+            tot += (unsigned)__popcll(m) << bit;
+        }
+        before[e] = ex;
+        if (lane == 0) sh[e * NW + wave] = tot;
+    }
+    __syncthreads();
+    unsigned total = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            if (w == wave) before[e] += total;
+            total += sh[e * NW + w];
+        }
+    uint2* const dst = S.cand + (int64_t)h * G.n + base;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int j0 = base + e * (4 * NT) + 4 * tid;
+        unsigned at = before[e];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const unsigned x = __float_as_uint(acc[e][k]);
+            if (j0 + k < n && x >= tlo) dst[at++] = make_uint2(x, (unsigned)(j0 + k));
+        }
+    }
+    if (tid == 0) S.cand_count[(int64_t)h * nch + c] = total;
+}
+
+// (64 registers, so that two heads share a compute unit: only the path of a sample that misled spills)
+template <int P>
+__global__ __launch_bounds__(1024, 8) void pick_finish(const float* __restrict__ vote, const ScoreGeom G, const int pool_kind,
+                                                    const int64_t kcount, const int nch, const int64_t out_stride,
+                                                    const int W_tail, SelectScratch S, int32_t* __restrict__ out_idx) {
+    __shared__ unsigned hist[kSelBins];
+    __shared__ unsigned sh_scan[16], sh_out[2];
+    __shared__ unsigned cnt[kSelMaxChunks], cgt[kSelMaxChunks], ceq[kSelMaxChunks];
+    constexpr int CPT = kSelMaxChunks / 1024;
+    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int32_t* out = out_idx + (int64_t)h * out_stride;
+    for (int t = tid; t < W_tail; t += 1024) out[kcount + t] = (int32_t)(G.n + t);   // window positions follow the prefix's
+    uint2* const list = S.cand + (int64_t)h * G.n;
+    unsigned mine = 0, total = 0;
+#pragma unroll
+    for (int e = 0; e < CPT; ++e) {
+        const int c = tid * CPT + e;
+        const unsigned v = c < nch ? S.cand_count[(int64_t)h * nch + c] : 0u;
+        cnt[c] = v;
+        mine += v;
+    }
+    block_exclusive_scan<1024>(mine, sh_scan, &total);
+    unsigned tlo = S.info[4 * h];
+    if (total < (unsigned)kcount) {      // the sample misled: every position of the head is a candidate
+        constexpr int RQ = (P / 2 + 3) / 4;
+        tlo = 0u;
+        for (int64_t j0 = 4 * tid; j0 < G.n; j0 += 4 * 1024) {
+            float acc[4];
+            pooled_run<P>(vote, G, h, j0, j0 >= 4 * RQ && j0 + 4 + 4 * RQ <= G.n, pool_kind, acc);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (j0 + k < G.n) list[j0 + k] = make_uint2(__float_as_uint(acc[k]), (unsigned)(j0 + k));
+        }
+        for (int c = tid; c < nch; c += 1024) {
+            const int64_t left = G.n - (int64_t)c * kSelChunk;
+            cnt[c] = (unsigned)(left < kSelChunk ? left : kSelChunk);
+        }
+        __threadfence_block();
+    }
+    __syncthreads();
+    // ---- the threshold, a digit per pass over the candidates (a wave per chunk)
+    auto each = [&](auto f) {
+        for (int c = wave; c < nch; c += 16) {
+            const unsigned m = cnt[c];
+            const uint2* p = list + (int64_t)c * kSelChunk;
+            for (unsigned i = lane; i < m; i += 4 * 64) {   // four loads in flight
+                unsigned x[4];
+#pragma unroll
+                for (unsigned u = 0; u < 4; ++u) x[u] = p[i + 64 * u < m ? i + 64 * u : i].x;
+#pragma unroll
+                for (unsigned u = 0; u < 4; ++u)
+                    if (i + 64 * u < m) f(x[u]);
+            }
+        }
+    };
+    unsigned cur_lo = tlo, last = 0xFFFFFFFFu - tlo, krem = (unsigned)kcount;   // the threshold lies in cur_lo .. cur_lo + last
+    int sh = kPickShift;
+    while (last > 0) {
+        for (int b = tid; b < kSelBins; b += 1024) hist[b] = 0u;
+        if (tid == 0) {
+            sh_out[0] = 0u;
+            sh_out[1] = 1u;
+        }
+        __syncthreads();
+        each([&](unsigned x) {
+            const unsigned d = x - cur_lo;
+            if (x >= cur_lo && d <= last) atomicAdd(&hist[d >> sh < kSelBins ? d >> sh : kSelBins - 1], 1u);
+        });
+        __syncthreads();
+        unsigned bins[kSelBins / 1024];
+        load_bins_from_top<1024, kSelBins>(hist, bins);
+        find_bin_from_top<1024, kSelBins>(bins, krem, sh_scan, sh_out);
+        const unsigned b1 = sh_out[0];
+        krem = sh_out[1];
+        const bool open = b1 == kSelBins - 1;   // the last bin holds everything above its lower edge too
+        const unsigned from = b1 << sh;
+        last = open ? last - from : (last - from < (1u << sh) - 1u ? last - from : (1u << sh) - 1u);
+        cur_lo += from;
+        sh = range_shift_bits(last, 11);
+        __syncthreads();
+    }
+    const unsigned T = cur_lo, need_eq = krem;
+    // ---- ordered emission: candidates above and equal to T per chunk, their prefix sums, the kept positions
+    for (int c = wave; c < nch; c += 16) {
+        const unsigned m = cnt[c];
+        const uint2* p = list + (int64_t)c * kSelChunk;
+        unsigned a = 0, q = 0;
+        for (unsigned i = lane; i < m; i += 64) {
+            const unsigned x = p[i].x;
+            a += x > T;
+            q += x == T;
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            a += __shfl_xor(a, d, 64);
+            q += __shfl_xor(q, d, 64);
+        }
+        if (lane == 0) {
+            cgt[c] = a;
+            ceq[c] = q;
+        }
+    }
+    __syncthreads();
+    unsigned g[CPT], q[CPT], gsum = 0, qsum = 0;
+#pragma unroll
+    for (int e = 0; e < CPT; ++e) {
+        const int c = tid * CPT + e;
+        g[e] = c < nch ? cgt[c] : 0u;
+        q[e] = c < nch ? ceq[c] : 0u;
+        gsum += g[e];
+        qsum += q[e];
+    }
+    unsigned gb = block_exclusive_scan<1024>(gsum, sh_scan, nullptr);
+    unsigned qb = block_exclusive_scan<1024>(qsum, sh_scan, nullptr);
+#pragma unroll
+    for (int e = 0; e < CPT; ++e) {
+        const int c = tid * CPT + e;
+        if (c < nch) {
+            cgt[c] = gb;
+            ceq[c] = qb;
+        }
+        gb += g[e];
+        qb += q[e];
+    }
+    __syncthreads();
+    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    for (int c = wave; c < nch; c += 16) {
+        const unsigned m = cnt[c];
+        const uint2* p = list + (int64_t)c * kSelChunk;
+        unsigned gt_b = cgt[c], eq_b = ceq[c];
+        for (unsigned i0 = 0; i0 < m; i0 += 64) {
+            const bool on = i0 + lane < m;
+            const uint2 v = on ? p[i0 + lane] : make_uint2(0u, 0u);
+            const bool gt = on && v.x > T, eq = on && v.x == T;
+            const unsigned long long mg = __ballot(gt), mq = __ballot(eq);
+            const unsigned gt_before = gt_b + (unsigned)__popcll(mg & lt_mask), eq_before = eq_b + (unsigned)__popcll(mq & lt_mask);
+            if (gt || (eq && eq_before < need_eq))
+                out[gt_before + (eq_before < need_eq ? eq_before : need_eq)] = (int32_t)v.y;
+            gt_b += (unsigned)__popcll(mg);
+            eq_b += (unsigned)__popcll(mq);
+        }
+    }
+}
+
+template <int P>
+static hipError_t pool_pick(const ScoreGeom& G, const float* vote, int pool_kind, int64_t kcount, int64_t out_stride, int W_tail,
+                            int32_t* out_idx, const SelectScratch& S, hipStream_t st) {
+    const int nch = (int)((G.n + kSelChunk - 1) / kSelChunk);
+    const double want = (double)kPickSamples * (double)kcount / (double)G.n;
+    const unsigned rank = (unsigned)(want + 5.0 * __builtin_sqrt(4.0 * want) + 8.0);
+    hipLaunchKernelGGL(pick_bracket<P>, dim3(G.Hkv), dim3(512), 0, st, vote, G, pool_kind, rank, S);
+    hipLaunchKernelGGL(pool_collect<P>, dim3(nch, G.Hkv), dim3(256), 0, st, vote, G, pool_kind, nch, S);
+    hipLaunchKernelGGL(pick_finish<P>, dim3(G.Hkv), dim3(1024), 0, st, vote, G, pool_kind, kcount, nch, out_stride, W_tail, S, out_idx);
+    return hipGetLastError();
+}
+
+bool pool_pick_ok(const ScoreGeom& G, int p, int64_t kcount) {
+    return (p == 1 || p == 5 || p == 7 || p == 13) && G.n >= 1 && kcount >= 1 && kcount <= G.n && (G.vpitch & 3) == 0 &&
+           select_chunked_ok(G.n) && G.Hkv <= 65535;
+}
+
+hipError_t launch_pool_pick(const ScoreGeom& G, const float* vote, int pool_kind, int p, int64_t kcount, int64_t out_stride,
+                            int W_tail, int32_t* out_idx, const SelectScratch& S, hipStream_t st) {
+    if (!pool_pick_ok(G, p, kcount) || (reinterpret_cast<uintptr_t>(vote) & 15u) != 0) return hipErrorInvalidValue;
+    switch (p) {
+        case 1: return pool_pick<1>(G, vote, pool_kind, kcount, out_stride, W_tail, out_idx, S, st);
+        case 5: return pool_pick<5>(G, vote, pool_kind, kcount, out_stride, W_tail, out_idx, S, st);
+        case 7: return pool_pick<7>(G, vote, pool_kind, kcount, out_stride, W_tail, out_idx, S, st);
+        default: return pool_pick<13>(G, vote, pool_kind, kcount, out_stride, W_tail, out_idx, S, st);
+    }
+}
 
 // ------------------------------------------------------------------------------------------------
 // Pooling (Sec. 4.3), group sum and top-k selection (Eq. 2) in ONE cooperative launch.

@@ -54,3 +54,31 @@ def test_kept_set_is_the_exact_top_k(snapkv, field, L, Hq, Hkv, W, C, p, dtype):
     for pool_kind in (0, 1):
         res = run_gpu(snapkv, q, k, v, pool_kind, p, C)
         check_self_consistency(q, k, v, C, *res)
+
+
+@pytest.mark.parametrize("field", [as_drawn, flat, few_spikes, two_fields], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("layers,L,Hq,Hkv,W,C,p,dtype", [
+    (40, 9001, 16, 8, 32, 700, 7, torch.bfloat16),   # more heads than the one-launch kernel keeps resident: votes read once
+    (66, 4100, 4, 4, 16, 600, 5, torch.float16),     # too short to sample: every position a candidate
+    (36, 8209, 8, 8, 32, 8000, 13, torch.bfloat16),  # nearly everything kept
+    (20, 20483, 16, 16, 16, 17, 1, torch.bfloat16),  # one position kept per head
+])
+def test_many_heads_keep_what_single_calls_keep(snapkv, field, layers, L, Hq, Hkv, W, C, p, dtype):
+    """Stacked layers, whose selection samples a lower bound of the threshold and finishes among the positions
+    above it (a sample that misleads costs time only): bit for bit the single calls' kept sets."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    q = torch.randn((layers * Hq, W, D), generator=gen, device="cuda")
+    k = torch.randn((layers * Hkv, L, D), generator=gen, device="cuda")
+    field(q, k)
+    q, k = q.to(dtype), k.to(dtype)
+    ok = torch.empty((layers * Hkv, C, D), dtype=dtype, device="cuda")
+    ov = torch.empty_like(ok)
+    oi = torch.full((layers * Hkv, C), -1, dtype=torch.int32, device="cuda")
+    lists = [list(t.split(t.shape[0] // layers)) for t in (q, k, k, ok, ov, oi)]
+    for pool_kind in (0, 1):
+        snapkv.snapkv_compress_layers(*lists[:3], pool_kind, p, C, *lists[3:])
+        for l in (0, 1, layers - 1):
+            res = run_gpu(snapkv, lists[0][l], lists[1][l], lists[2][l], pool_kind, p, C)
+            assert (lists[5][l].cpu().numpy() == res[3]).all(), (l, pool_kind)
+            assert torch.equal(lists[3][l], res[1]) and torch.equal(lists[4][l], res[2]), (l, pool_kind)
