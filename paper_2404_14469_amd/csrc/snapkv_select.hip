@@ -205,6 +205,8 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4_nt;
 
 struct NoLayers {};
 
+// (Rows are 8, 16 or 32 pieces: a piece's row and place come from a shift, not from 64-bit divisions, of which a thread
+// made four: 58.9 -> 58.1 us per call at 16384 keys and 32 heads.)
 // Each thread moves 16 bytes of a K row and the matching 16 bytes of the V row; consecutive
 // threads cover consecutive pieces of a row, so a 256-byte row is one coalesced 16-lane access.
 // Every row is read once and written once: the non-temporal policy keeps both out of the way of
@@ -214,12 +216,12 @@ struct NoLayers {};
 template <typename LY>
 __device__ __forceinline__ void gather_body(const uint4* __restrict__ k, const uint4* __restrict__ v,
                                             const int32_t* __restrict__ idx, const int64_t L, const int64_t rows,
-                                            const int64_t out_stride, const int pieces, uint4* __restrict__ out_k,
+                                            const int64_t out_stride, const int shift, uint4* __restrict__ out_k,
                                             uint4* __restrict__ out_v, const RowLayout& kl, const RowLayout& vl,
                                             const int head_div, const PageMap& pm, const CleanJob& clean, const LY& ly) {
     constexpr bool LAYERS = std::is_same<LY, GatherLayers>::value;
     const int h = blockIdx.y;
-    const int64_t total = rows * pieces;
+    const int64_t pieces = (int64_t)1 << shift, total = rows << shift;   // 16-byte pieces per row: a power of two (8, 16 or 32)
     const uint4 *kb, *vb;
     uint4 *okb, *ovb;
     int32_t* ob = nullptr;
@@ -251,8 +253,8 @@ __device__ __forceinline__ void gather_body(const uint4* __restrict__ k, const u
         for (int u = 0; u < U; ++u) {
             const int64_t e = e0 + u * stride;
             on[u] = e < total;
-            r[u] = on[u] ? e / pieces : 0;
-            c[u] = on[u] ? (int)(e - r[u] * pieces) : 0;
+            r[u] = on[u] ? e >> shift : 0;
+            c[u] = on[u] ? (int)(e & (pieces - 1)) : 0;
             raw[u] = ib[r[u]];
             int64_t pos = raw[u];
             pos = pos < 0 ? 0 : (pos < L ? pos : L - 1);   // whatever idx holds, the read stays inside the prompt
@@ -292,20 +294,20 @@ __global__ __launch_bounds__(256) void gather_rows(const uint4* __restrict__ k,
                                                    const int32_t* __restrict__ idx,
                                                    const int64_t L /* rows per head of k and v */,
                                                    const int64_t rows, const int64_t out_stride,
-                                                   const int pieces /* 16-byte pieces per row */,
+                                                   const int shift /* log2 of the 16-byte pieces per row */,
                                                    uint4* __restrict__ out_k,
                                                    uint4* __restrict__ out_v, const RowLayout kl,
                                                    const RowLayout vl /* strides in 16-byte pieces */,
                                                    const int head_div /* output heads per source head */,
                                                    const PageMap pm, const CleanJob clean) {
-    gather_body(k, v, idx, L, rows, out_stride, pieces, out_k, out_v, kl, vl, head_div, pm, clean, NoLayers{});
+    gather_body(k, v, idx, L, rows, out_stride, shift, out_k, out_v, kl, vl, head_div, pm, clean, NoLayers{});
 }
 
 __global__ __launch_bounds__(256) void gather_rows_layers(const GatherLayers ly, const int32_t* __restrict__ idx,
                                                           const int64_t L, const int64_t rows, const int64_t out_stride,
-                                                          const int pieces, const RowLayout kl, const RowLayout vl,
+                                                          const int shift, const RowLayout kl, const RowLayout vl,
                                                           const CleanJob clean) {
-    gather_body(nullptr, nullptr, idx, L, rows, out_stride, pieces, nullptr, nullptr, kl, vl, 1, PageMap{}, clean, ly);
+    gather_body(nullptr, nullptr, idx, L, rows, out_stride, shift, nullptr, nullptr, kl, vl, 1, PageMap{}, clean, ly);
 }
 
 // Per-head valid prefix lengths of a batch: head h of the batch belongs to prompt h / Hkv.
@@ -323,7 +325,8 @@ hipError_t launch_batch_lengths(const BatchDesc& B, int32_t* nvalid, hipStream_t
 // gather_rows for a batch: head h of the grid is KV head h % Hkv of prompt h / Hkv; the kept
 // positions come from one [heads, C] array and are also copied to the prompt's own out_idx.
 __global__ __launch_bounds__(256) void gather_rows_batch(const BatchDesc B, const int32_t* __restrict__ idx,
-                                                         const int64_t C, const int pieces, const CleanJob clean) {
+                                                         const int64_t C, const int shift, const CleanJob clean) {
+    const int64_t pieces = (int64_t)1 << shift;
     const int h = blockIdx.y, pr = h / B.Hkv, head = h % B.Hkv;
     const int64_t L = B.L[pr];
     const uint4* kb = static_cast<const uint4*>(B.k[pr]) + (int64_t)head * L * pieces;
@@ -332,17 +335,29 @@ __global__ __launch_bounds__(256) void gather_rows_batch(const BatchDesc B, cons
     uint4* ovb = static_cast<uint4*>(B.out_v[pr]) + (int64_t)head * C * pieces;
     const int32_t* ib = idx + (int64_t)h * C;
     int32_t* ob = B.out_idx[pr] + (int64_t)head * C;
-    const int64_t total = C * pieces;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        const int64_t r = e / pieces;
-        const int c = (int)(e - r * pieces);
-        int64_t src = ib[r];
-        src = src < 0 ? 0 : (src < L ? src : L - 1);   // a failed selection cannot send a read outside the prompt
-        const u32x4_nt a = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt*>(&kb[src * pieces + c]));
-        const u32x4_nt b = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt*>(&vb[src * pieces + c]));
-        __builtin_nontemporal_store(a, reinterpret_cast<u32x4_nt*>(&okb[r * pieces + c]));
-        __builtin_nontemporal_store(b, reinterpret_cast<u32x4_nt*>(&ovb[r * pieces + c]));
-        if (c == 0) ob[r] = ib[r];
+    const int64_t total = C << shift, stride = (int64_t)gridDim.x * 256;
+    constexpr int U = 4;   // four pieces per thread in flight, as in gather_body
+    for (int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x; e0 < total; e0 += U * stride) {
+        int32_t raw[U];
+        u32x4_nt a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) raw[u] = e0 + u * stride < total ? ib[(e0 + u * stride) >> shift] : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int64_t src = raw[u];
+            src = src < 0 ? 0 : (src < L ? src : L - 1);   // a failed selection cannot send a read outside the prompt
+            const int64_t at = src * pieces + ((e0 + u * stride) & (pieces - 1));
+            a[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt*>(&kb[at]));
+            b[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt*>(&vb[at]));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = e0 + u * stride;
+            if (e >= total) continue;
+            __builtin_nontemporal_store(a[u], reinterpret_cast<u32x4_nt*>(&okb[e]));
+            __builtin_nontemporal_store(b[u], reinterpret_cast<u32x4_nt*>(&ovb[e]));
+            if ((e & (pieces - 1)) == 0) ob[e >> shift] = raw[u];
+        }
     }
     const int64_t gid = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
     const int64_t gsz = (int64_t)gridDim.y * gridDim.x * 256;
@@ -355,9 +370,10 @@ hipError_t launch_gather_batch(const BatchDesc& B, const int32_t* idx, int64_t C
     if (B.count <= 0 || C <= 0) return hipSuccess;
     const int pieces = row_bytes / 16;
     const int64_t total = C * pieces;
-    unsigned bx = (unsigned)((total + 255) / 256);
+    unsigned bx = (unsigned)((total + 1023) / 1024);   // four pieces per thread
     if (bx > 1024) bx = 1024;
-    hipLaunchKernelGGL(gather_rows_batch, dim3(bx, B.count * B.Hkv), dim3(256), 0, st, B, idx, C, pieces, clean);
+    hipLaunchKernelGGL(gather_rows_batch, dim3(bx, B.count * B.Hkv), dim3(256), 0, st, B, idx, C,
+                       __builtin_ctz((unsigned)pieces), clean);
     return hipGetLastError();
 }
 
@@ -372,7 +388,7 @@ hipError_t launch_gather_layers(const GatherLayers& GL, const int32_t* idx, int6
     if (bx > 4096) bx = 4096;
     const RowLayout rl{L * pieces, pieces};   // contiguous [heads, L, D] in 16-byte pieces
     hipLaunchKernelGGL(gather_rows_layers, dim3(bx, GL.count * GL.heads), dim3(256), 0, st, GL, idx, L, rows, out_stride,
-                       pieces, rl, rl, clean);
+                       __builtin_ctz((unsigned)pieces), rl, rl, clean);
     return hipGetLastError();
 }
 
@@ -388,7 +404,7 @@ hipError_t launch_gather(const void* k, const void* v, const int32_t* idx, int H
     if (bx > 4096) bx = 4096;
     const RowLayout kp{kl.head_stride / 16, kl.row_stride / 16}, vp{vl.head_stride / 16, vl.row_stride / 16};
     hipLaunchKernelGGL(gather_rows, dim3(bx, H), dim3(256), 0, st, static_cast<const uint4*>(k),
-                       static_cast<const uint4*>(v), idx, L, rows, out_stride, pieces,
+                       static_cast<const uint4*>(v), idx, L, rows, out_stride, __builtin_ctz((unsigned)pieces),
                        static_cast<uint4*>(out_k), static_cast<uint4*>(out_v), kp, vp, head_div, pm, clean);
     return hipGetLastError();
 }
