@@ -244,7 +244,8 @@ int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGe
                const Workspace& ws, int pool_kind, int p, float* score, int64_t score_pitch, unsigned* minmax,
                bool prepare_select, ScoreGeom* Gv, hipStream_t st, bool already_prepared = false,
                CleanJob* clean = nullptr, const float* lse = nullptr, bool allow_blocks = false,
-               bool allow_long = false, const ScoreLayers* layers = nullptr) {
+               bool allow_long = false, const ScoreLayers* layers = nullptr, bool one_launch_select = false) {
+    // one_launch_select: pool_select follows, which needs its counters and the status word cleared and nothing else
     FusedGeom F;
     ScoreGeom Gp = G;
     if (layers && (lse || allow_blocks)) return SNAPKV_ERR_UNSUPPORTED;
@@ -274,7 +275,8 @@ int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGe
     if (split_read) fused_sync_layout(LP.Gf, F, &S, ws.fused);   // F is the front part's plan
     const bool handoff = fused || split_read;
     if (handoff) S.gave_up_flag = ws.status_flag;
-    if (!already_prepared) {
+    const bool scoring_clears = path == kPathWide && one_launch_select && !already_prepared;
+    if (!already_prepared && !scoring_clears) {
         if (launch_prepare(handoff ? S.part : nullptr, handoff ? fused_sync_pairs(F) : 0,
                            prepare_select ? &ws.sel : nullptr, G.Hkv * G.g, st, ws.status_flag) != hipSuccess)   // scratch is laid out per query head
             return SNAPKV_ERR_HIP;
@@ -334,7 +336,9 @@ int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGe
             P[x].part = ws.wide_part + (int64_t)x * (int64_t)(wide_part_bytes(Ge) / sizeof(float2));
             P[x].G = &Ge;
         }
-        if (launch_score_wide(dtype, D, count, P, st) != hipSuccess) return SNAPKV_ERR_HIP;
+        WideClear clear;
+        if (scoring_clears) clear = WideClear{ws.sel.ps_arrive, ws.sel.ps_zero_words, ws.status_flag};
+        if (launch_score_wide(dtype, D, count, P, st, clear) != hipSuccess) return SNAPKV_ERR_HIP;
         Gp.NV = G.g;
         Gp.VB = 1;
     } else if (path == kPathStream) {
@@ -507,7 +511,7 @@ int64_t compress_impl(int dtype, const void* q_win, const void* k, const void* v
         }
         ScoreGeom Gv = G;
         rc = run_scores(dtype, q_win, k, D, G, ws, pool_kind, p, nullptr, 0, nullptr, true, &Gv, st, prepared,
-                        mine ? &clean : nullptr, lse, blocks_ok, true, score_layers);
+                        mine ? &clean : nullptr, lse, blocks_ok, true, score_layers, true);
         if (rc != SNAPKV_OK) return rc;
         if (per_query_head) Gv = Gsel;
         se = launch_pool_select(Gv, ws.vote, pool_kind, p, C - W, C, W, idx_dst, ws.sel, st);

@@ -126,6 +126,9 @@ template <int N> struct WideArgs {   // N: 1 or kMaxWide (a single prompt's laun
     int page;
     int64_t pages, row0;
     unsigned rounds;                 // of all entries
+    unsigned* zeros;                 // words the selection expects to be zero (see WideClear); null: none
+    int64_t nzeros;
+    unsigned* flag;
     WideEntry e[N];
 };
 
@@ -312,6 +315,11 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     __shared__ __attribute__((aligned(16))) float sm_ref[2][R];          // the rows' references
     __shared__ __attribute__((aligned(16))) float sm_sum[2][PARTS][R];   // per part: the slice's sums relative to them
     Wv W(A);
+    {
+        const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, all = (int64_t)gridDim.x * gridDim.y * kThreads;
+        for (int64_t i = wg * kThreads + W.tid; i < A.nzeros; i += all) A.zeros[i] = 0u;
+        if (A.flag && wg == 0 && W.tid == 0) *A.flag = 0u;
+    }
     int rounds;
     Cursor cc = begin_share(A, rounds), pc = cc;
     if (rounds <= 0) return;
@@ -645,7 +653,7 @@ hipError_t launch_both(const WideArgs<kMaxWide>& all, dim3 grid, hipStream_t st)
     WideArgs<N> A;
     A.count = all.count, A.direct = all.direct, A.g = all.g, A.W = all.W, A.UH = all.UH, A.hb = all.hb, A.nblk = all.nblk;
     A.c2 = all.c2, A.k_rs = all.k_rs, A.table = all.table, A.page = all.page, A.pages = all.pages, A.row0 = all.row0;
-    A.rounds = all.rounds;
+    A.rounds = all.rounds, A.zeros = all.zeros, A.nzeros = all.nzeros, A.flag = all.flag;
     for (int i = 0; i < N; ++i) A.e[i] = all.e[i];
     hipLaunchKernelGGL((wide_stats<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
     hipLaunchKernelGGL((wide_votes<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
@@ -682,7 +690,7 @@ size_t wide_part_bytes(const ScoreGeom& G) {
     return (sizeof(float2) * (size_t)G.Hkv * b.nblk * slices_of(G.L) * RUW * 16 + 255) & ~(size_t)255;
 }
 
-hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st) {
+hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st, const WideClear& clear) {
     if (count < 1 || count > kMaxWide) return hipErrorInvalidValue;
     Blocks b;
     if ((dtype != 0 && dtype != 2) || (D != 64 && D != 128) || !row_blocks(*P[0].G, &b)) return hipErrorInvalidValue;
@@ -702,6 +710,9 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
     A.pages = G0.k_pages;
     A.row0 = G0.k_row0;
     A.rounds = 0;
+    A.zeros = clear.zeros;
+    A.nzeros = clear.zeros ? clear.nzeros : 0;
+    A.flag = clear.flag;
     int64_t slices = 0;
     for (int i = 0; i < count; ++i) {
         const ScoreGeom& G = *P[i].G;
