@@ -27,10 +27,17 @@
 // 425 + 512 us, and 240 registers); the rows' references from row maxima (a longer prologue: 24 against 19 us per
 // pass at 28471 keys, 8 heads).  At 131072 keys, W = 64 (two blocks per head): 95 + 106 us against 277 us.
 //
-// The row reference.  Exponentials are taken relative to the row's logit with the prompt's first key instead of a
-// running maximum: 2^(s - ref) loses no precision whatever ref is, and terms that underflow are far below the row's
-// largest.  Where a logit exceeds ref by so much (2^128) that the sum leaves the fp32 range, wide_votes finds
-// the true maxima from all keys of the unit (rows_from_keys).
+// The row reference.  Exponentials are taken relative to a reference of the row that is known before its keys are: its
+// largest logit among the prompt's first four keys.  The argument s - ref is rounded to fp32, so the terms that matter
+// must not lie far from the reference: a round in which a row's logits exceed it by about 2^kRaiseAt raises the row's
+// reference to its largest logit less kRaiseBelow for the rest of the slice and takes its exponentials again, and
+// wide_votes uses the largest of the slices' references.  Normally distributed logits get there at 4.5 standard
+// deviations where one is 4.6 (base two), and not at all where it is 2.6.  No sum can overflow.  The margin below
+// the largest logit keeps the many small terms of a peaked row nearer to the reference.  Relative error of the votes
+// against float64 (2-norm, 1e-8; 18461 keys, 32/8 heads, 32 rows), single-read kernel / a reference that stays at the
+// first key's logit / as it is: logits N(0, 1.8 nats) 12.2 / 12.6 / 12.3; with 40 keys 6, 20 and 40 nats above those
+// 12.1 / 11.9 / 10.6, 15.8 / 17.5 / 15.2 and 28.1 / 34.5 / 28.0.  Checking and raising cost 0.8 of 64 us per call at
+// 28471 keys, 0.5 of 67 at 32749 and nothing measurable at 131072.
 //
 // MFMA layout: that of snapkv_fused.hip (16x16x32, lane l: row / column l % 16, contraction slice l / 16;
 // accumulator register r is row (l / 16) * 4 + r, column l % 16; the 16-byte pieces 4p + l / 16 of a row).
@@ -54,6 +61,9 @@ constexpr int kRound = kWaves * 16;          // keys of a round: every wave brin
 constexpr int kSlices = 64;                  // slices per unit at most
 constexpr int kWaveRows = 2;                 // 16-row units of a wave
 constexpr int RUW = 8;                       // 16-row units of a block
+constexpr float kRaiseAt = 0x1p16f;          // exponential (of a lane's sum) from which a row's reference is raised,
+constexpr float kRaiseMin = 8.f;             //   by rows whose largest logit lies this far above it (base two),
+constexpr float kRaiseBelow = 7.f;           //   to that logit less this
 // Window rows of a KV head (in whole 16-row units) times keys from which the two passes beat the single-read kernel.
 // Microseconds per call, 32/8 heads of 128 in bf16, this path / the single-read kernel, one layer and four in one call:
 //   W = 32 (128 rows):  8192 keys 51 / 45, 71 / 73;  16384: 57 / 55, 93 / 105;  20000: 60 / 70, 110 / 167;
@@ -120,6 +130,7 @@ struct WideEntry {
 };
 template <int N> struct WideArgs {   // N: 1 or kMaxWide (a single prompt's launch has little to fetch before its first load)
     int count, direct, g, W, UH, hb, nblk;   // hb query heads per block, nblk blocks per KV head, UH row units per query head
+    int inv_uh;                      // 256 / UH rounded up: a row unit's query head is ru * inv_uh >> 8
     float c2;
     int64_t k_rs;
     const int32_t* table;            // paged K (one entry only): see ScoreGeom
@@ -134,7 +145,7 @@ template <int N> struct WideArgs {   // N: 1 or kMaxWide (a single prompt's laun
 
 // Where a workgroup stands in the launch's sequence of rounds (all wave-uniform).
 struct Cursor {
-    int e, u, sl, rd;                // entry, unit, slice of the unit, round of the slice
+    int e, kv, blk, sl, rd;          // entry, KV head and block of the unit, slice of the unit, round of the slice
     int L, n, RPS, NS, units;
     const char* kb;                  // K rows of the unit's head
 };
@@ -146,7 +157,7 @@ template <int N> __device__ __forceinline__ void enter(const WideArgs<N>& A, Cur
     c.RPS = E.RPS;
     c.NS = E.NS;
     c.units = E.units;
-    c.kb = E.k + (int64_t)(c.u / A.nblk) * E.k_hs;
+    c.kb = E.k + (int64_t)c.kv * E.k_hs;
 }
 
 // First round at or after `r` at which a slice begins.
@@ -172,20 +183,23 @@ template <int N> __device__ __forceinline__ Cursor cursor_at(const WideArgs<N>& 
             if (r >= A.e[i].round_begin) c.e = i;
     const WideEntry& E = A.e[c.e];
     const unsigned in = (r - E.round_begin) / (unsigned)E.RPS;   // r is the start of a slice
-    c.u = (int)(in / (unsigned)E.NS);
+    const int u = (int)(in / (unsigned)E.NS);
     c.sl = (int)(in % (unsigned)E.NS);
+    c.kv = u / A.nblk;
+    c.blk = u % A.nblk;
     c.rd = 0;
     enter(A, c);
     return c;
 }
 
 // Where the workgroup starts and how many rounds are its own.  A launch whose slices all find a place at once has a
-// workgroup per slice (grid: slices of a unit x units).
+// workgroup per slice (grid: slices of a unit x blocks of a KV head x KV heads; no divisions before the first load).
 template <int N> __device__ __forceinline__ Cursor begin_share(const WideArgs<N>& A, int& rounds) {
     if (N == 1 && A.direct) {
         Cursor c;
         c.e = 0;
-        c.u = (int)blockIdx.y;
+        c.kv = (int)blockIdx.z;
+        c.blk = (int)blockIdx.y;
         c.sl = (int)blockIdx.x;
         c.rd = 0;
         enter(A, c);
@@ -205,11 +219,14 @@ template <int N> __device__ __forceinline__ bool advance(const WideArgs<N>& A, C
         c.rd = 0;
         return false;
     }
-    if (c.u + 1 < c.units) {
-        ++c.u;
+    if (c.blk + 1 < A.nblk) {
+        ++c.blk;
+    } else if ((c.kv + 1) * A.nblk < c.units) {
+        ++c.kv;
+        c.blk = 0;
     } else if (N > 1 && c.e + 1 < A.count) {
         ++c.e;
-        c.u = 0;
+        c.kv = c.blk = 0;
     } else {
         --c.rd;
         return false;
@@ -277,22 +294,24 @@ template <typename T, int D, bool PAGED, int N> struct WideWave {
     // The wave's Q rows (MFMA fragments).  Padding rows repeat a valid one and are ignored later.
     __device__ __forceinline__ void load_q(KFrag<D> (&q)[kWaveRows], const Cursor& c) const {
         const WideEntry& E = A.e[c.e];
-        const int kv = c.u / A.nblk, blk = c.u % A.nblk;
+        int at = n16;
+        asm volatile("" : "+v"(at));     // (rows addressed afresh for every unit: kept over the rounds they cost registers)
 #pragma unroll
         for (int i = 0; i < kWaveRows; ++i) {
             const int ru = rg * kWaveRows + i;
-            int head = blk * A.hb + ru / A.UH, row = (ru % A.UH) * 16 + n16;
+            const int rh = ru * A.inv_uh >> 8;
+            int head = c.blk * A.hb + rh, row = (ru - rh * A.UH) * 16 + at;
             head = head < A.g ? head : A.g - 1;
             row = row < A.W ? row : A.W - 1;
-            const char* p = E.q + (((int64_t)kv * A.g + head) * A.W + row) * (D * 2) + kg * 16;
+            const char* p = E.q + (((int64_t)c.kv * A.g + head) * A.W + row) * (D * 2) + kg * 16;
 #pragma unroll
             for (int x = 0; x < NP; ++x) q[i].v[x] = *reinterpret_cast<const uint4*>(p + 64 * x);
         }
     }
     // Prompt-phase causal mask of the 16 keys from j0 on against row unit i of the wave: row x does not see keys
     // after n + x (which for a real row covers the keys past the end; what padding rows hold is ignored).
-    __device__ __forceinline__ void mask(wf32x4& a, int64_t j0, int i, const Cursor& c) const {
-        const int d = (int)(j0 - c.n) + n16 - kg * 4 - ((rg * kWaveRows + i) % A.UH) * 16;
+    __device__ __forceinline__ void mask(wf32x4& a, int j0, int i, const Cursor& c) const {
+        const int ru = rg * kWaveRows + i, d = j0 - c.n + n16 - kg * 4 - (ru - (ru * A.inv_uh >> 8) * A.UH) * 16;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (d > r) a[r] = -INFINITY;
@@ -312,11 +331,11 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     using Wv = WideWave<T, D, PAGED, N>;
     constexpr int R = Wv::R, TILES = Wv::TILES, PARTS = Wv::PARTS;
     __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];                      // K of two rounds as MFMA fragments
-    __shared__ __attribute__((aligned(16))) float sm_ref[2][R];          // the rows' references
-    __shared__ __attribute__((aligned(16))) float sm_sum[2][PARTS][R];   // per part: the slice's sums relative to them
+    enum { kBase, kRef, kSum = kRef + 2, kStatArrays = kSum + 2 };        // per part and row: the references at a slice's
+    __shared__ __attribute__((aligned(16))) float sm_st[kStatArrays][PARTS][R];   // start, two slices' references and their sums
     Wv W(A);
     {
-        const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, all = (int64_t)gridDim.x * gridDim.y * kThreads;
+        const int64_t wg = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, all = (int64_t)gridDim.x * gridDim.y * gridDim.z * kThreads;
         for (int64_t i = wg * kThreads + W.tid; i < A.nzeros; i += all) A.zeros[i] = 0u;
         if (A.flag && wg == 0 && W.tid == 0) *A.flag = 0u;
     }
@@ -326,12 +345,13 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     KFrag<D> q[kWaveRows], S;
     float z[kWaveRows][4], ref[kWaveRows][4];
 
-    auto reference = [&](float m) __attribute__((always_inline)) { return m == -INFINITY ? 0.f : m; };
-    // A unit begins: the wave's Q rows, and the rows' references, their logits with the prompt's first key (which every
-    // row sees): all lanes bring that key, so that a row's sixteen lanes hold the same number.
+    // A unit begins: the wave's Q rows, and the rows' references from the prompt's first four keys (or fewer: those that
+    // every row sees; each quad of lanes brings all four).  They depend on the unit alone, and every slice starts from
+    // them, so a slice's result does not depend on which slices its workgroup had before.
+    float* const my = &sm_st[kBase][W.kp][W.rg * kWaveRows * 16 + W.kg * 4];   // from the lane's first row on
     auto ask_unit = [&](KFrag<D>& f) __attribute__((always_inline)) {
         W.load_q(q, cc);
-        W.load_row(f, cc, W.row_of(cc, 0));
+        W.load_row(f, cc, W.row_of(cc, (W.n16 & 3) < cc.n ? (W.n16 & 3) : cc.n));
     };
     auto begin_unit = [&](const KFrag<D>& f) __attribute__((always_inline)) {
 #pragma unroll
@@ -339,22 +359,25 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
             const wf32x4 a = logits16<T, D>(q[i], f);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                ref[i][r] = reference(a[r] * A.c2);
+                float m = fmaxf(a[r], wdpp<0xB1>(a[r]));
+                m = fmaxf(m, wdpp<0x4E>(m)) * A.c2;
+                ref[i][r] = m == -INFINITY ? 0.f : m;
                 z[i][r] = 0.f;
             }
+            // (each lane reads back what it wrote itself)
+            *reinterpret_cast<float4*>(my + i * 16) = make_float4(ref[i][0], ref[i][1], ref[i][2], ref[i][3]);
         }
     };
+    bool raised = false;                 // (wave-uniform) a reference was raised since the slice's start
     int par = 0;                         // which half of sm_ref and sm_sum the current slice uses
     float2* pending = nullptr;           // where the pairs of the slice before go, once all waves have left theirs
     auto store_slice = [&](int half) __attribute__((always_inline)) {
         if (W.tid < R) {                 // fixed order over the parts
-            float m = sm_ref[half][W.tid], s = 0.f;
+            float m = -INFINITY, s = 0.f;
 #pragma unroll
-            for (int v = 0; v < PARTS; ++v) s += sm_sum[half][v][W.tid];
-            if (s > 0x1p60f) {           // keep the reference within reach of the row's largest logit
-                m += 64.f;
-                s *= 0x1p-64f;
-            }
+            for (int v = 0; v < PARTS; ++v) m = fmaxf(m, sm_st[kRef + half][v][W.tid]);
+#pragma unroll
+            for (int v = 0; v < PARTS; ++v) s += sm_st[kSum + half][v][W.tid] * __builtin_amdgcn_exp2f(sm_st[kRef + half][v][W.tid] - m);
             pending[W.tid] = make_float2(m, s);
         }
         pending = nullptr;
@@ -374,7 +397,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
         S = W.request(pc);
         lds_meet();
         if (pending) store_slice(par ^ 1);
-        const int64_t j0 = W.round_key(cc) + W.kp * (TILES * 16);
+        const int j0 = (int)W.round_key(cc) + W.kp * (TILES * 16);   // (prompts have less than 2^31 keys)
         const bool special = j0 + TILES * 16 > cc.n;   // window columns or keys past the end among the wave's
         float y[kWaveRows][4];           // the round's sums
 #pragma unroll
@@ -393,6 +416,48 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
             }
             __builtin_amdgcn_sched_barrier(0);   // (one tile at a time: more do not fit the registers)
         }
+        float top = y[0][0];
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) top = fmaxf(top, y[i][r]);
+        if (__any(top > kRaiseAt)) {     // some row's logits lie far above its reference: first their maxima, then the sums again
+            raised = true;
+            auto each = [&](auto f2) __attribute__((always_inline)) {
+#pragma clang loop unroll(disable)
+                for (int t = 0; t < TILES; ++t) {
+                    KFrag<D> f;
+                    W.tile(f, buf, t);
+#pragma unroll
+                    for (int i = 0; i < kWaveRows; ++i) {
+                        wf32x4 a = logits16<T, D>(q[i], f);
+                        W.mask(a, j0 + t * 16, i, cc);
+                        f2(a, i);
+                    }
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < kWaveRows; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) y[i][r] = -INFINITY;
+            each([&](const wf32x4& a, int i) __attribute__((always_inline)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) y[i][r] = fmaxf(y[i][r], a[r]);
+            });
+#pragma unroll
+            for (int i = 0; i < kWaveRows; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float m = lanes16_max(y[i][r]) * A.c2, to = m > ref[i][r] + kRaiseMin ? m - kRaiseBelow : ref[i][r];
+                    z[i][r] *= __builtin_amdgcn_exp2f(ref[i][r] - to);
+                    ref[i][r] = to;
+                    y[i][r] = 0.f;
+                }
+            each([&](const wf32x4& a, int i) __attribute__((always_inline)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) y[i][r] += __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -ref[i][r]));
+            });
+        }
 #pragma unroll
         for (int i = 0; i < kWaveRows; ++i)
 #pragma unroll
@@ -405,16 +470,20 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) y[r] = lanes16_sum(z[i][r]);
                 if (W.n16 == 0) {
-                    const int at = (W.rg * kWaveRows + i) * 16 + W.kg * 4;
-                    *reinterpret_cast<float4*>(&sm_sum[par][W.kp][at]) = make_float4(y[0], y[1], y[2], y[3]);
-                    if (W.kp == 0) *reinterpret_cast<float4*>(&sm_ref[par][at]) = make_float4(ref[i][0], ref[i][1], ref[i][2], ref[i][3]);
+                    *reinterpret_cast<float4*>(my + (kSum + par) * (PARTS * R) + i * 16) = make_float4(y[0], y[1], y[2], y[3]);
+                    *reinterpret_cast<float4*>(my + (kRef + par) * (PARTS * R) + i * 16) = make_float4(ref[i][0], ref[i][1], ref[i][2], ref[i][3]);
+                }
+                if (raised) {
+                    const float4 b = *reinterpret_cast<const float4*>(my + i * 16);
+                    ref[i][0] = b.x, ref[i][1] = b.y, ref[i][2] = b.z, ref[i][3] = b.w;
                 }
             }
+            raised = false;
 #pragma unroll
             for (int i = 0; i < kWaveRows; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) z[i][r] = 0.f;
-            pending = A.e[cc.e].part + ((int64_t)cc.u * cc.NS + cc.sl) * R;
+            pending = A.e[cc.e].part + (((int64_t)cc.kv * A.nblk + cc.blk) * cc.NS + cc.sl) * R;
             par ^= 1;
         }
         if (left <= 0) break;
@@ -435,7 +504,6 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
     __shared__ float sm_v[2][RUW][kRound];                            // sums over the rows of a row unit, per key
     __shared__ float2 sm[SUB][R];
     __shared__ __attribute__((aligned(16))) float2 smf[R];
-    __shared__ int sm_over;                                           // a row's sum left the fp32 range
     Wv W(A);
     int rounds;
     Cursor cc = begin_share(A, rounds), pc = cc;
@@ -460,62 +528,9 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
             for (int i = 0; i + d < n; i += 2 * d) t[i] += t[i + d];
         s = t[0];
     };
-    // A row some of whose logits lie too far above its reference: the unit's rows with their true maxima, from all of
-    // its keys, leaving smf as the merge below does.  Every workgroup of the unit does the same.
-    auto rows_from_keys = [&]() __attribute__((always_inline)) {
-        Cursor c = cc;
-        float m[kWaveRows][4], s[kWaveRows][4];
-#pragma unroll
-        for (int i = 0; i < kWaveRows; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) m[i][r] = -INFINITY, s[i][r] = 0.f;
-        for (int pass = 0; pass < 2; ++pass) {   // the wave's keys: first the maxima, then the sums
-#pragma clang loop unroll(disable)
-            for (int x = 0; x < c.NS * c.RPS * TILES; ++x) {
-                const int64_t j0 = (int64_t)(x / TILES) * kRound + (W.kp * TILES + x % TILES) * 16;
-                KFrag<D> f;
-                W.load_row(f, c, W.row_of(c, j0 + W.n16));
-#pragma unroll
-                for (int i = 0; i < kWaveRows; ++i) {
-                    wf32x4 a = logits16<T, D>(q[i], f);
-                    W.mask(a, j0, i, c);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        if (pass == 1) s[i][r] += __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -m[i][r]));
-                        else m[i][r] = fmaxf(m[i][r], a[r]);
-                    }
-                }
-            }
-            if (pass == 0)
-#pragma unroll
-                for (int i = 0; i < kWaveRows; ++i)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        m[i][r] = lanes16_max(m[i][r]) * A.c2;
-                        if (m[i][r] == -INFINITY) m[i][r] = 0.f;
-                    }
-        }
-#pragma unroll
-        for (int i = 0; i < kWaveRows; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float sum = lanes16_sum(s[i][r]);
-                if (W.n16 == 0) sm[W.kp][(W.rg * kWaveRows + i) * 16 + W.kg * 4 + r] = make_float2(m[i][r], sum);
-            }
-        lds_meet();
-        if (W.tid < R && smf[W.tid].x != INFINITY) {   // (padding rows stay as they are)
-            float2 y[Wv::PARTS];
-            float mm, ss;
-#pragma unroll
-            for (int i = 0; i < Wv::PARTS; ++i) y[i] = sm[i][W.tid];
-            fold(y, mm, ss);
-            smf[W.tid] = make_float2(mm, 1.0f / ss);
-        }
-        lds_meet();
-    };
     auto begin_unit = [&]() __attribute__((always_inline)) {            // the unit's slices merged in a fixed order, and the wave's Q rows
         const int row = W.tid % R, sub = W.tid / R;
-        const float2* src = A.e[cc.e].part + (int64_t)cc.u * cc.NS * R + row;
+        const float2* src = A.e[cc.e].part + ((int64_t)cc.kv * A.nblk + cc.blk) * cc.NS * R + row;
         float m = -INFINITY, s = 0.f;
 #pragma clang loop unroll(disable)
         for (int s0 = sub; s0 < cc.NS; s0 += 8 * SUB) {   // eight slices' pairs in flight at a time
@@ -529,7 +544,6 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
             fold(x, m, s);
         }
         sm[sub][row] = make_float2(m, s);
-        if (W.tid == 0) sm_over = 0;
         W.load_q(q, cc);
         lds_meet();
         if (W.tid < R) {
@@ -537,13 +551,11 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
 #pragma unroll
             for (int i = 0; i < SUB; ++i) y[i] = sm[i][W.tid];
             fold(y, m, s);
-            const int ru = W.tid >> 4, blk = cc.u % A.nblk;
-            const bool real = ru / A.UH < A.hb && blk * A.hb + ru / A.UH < A.g && (ru % A.UH) * 16 + (W.tid & 15) < A.W && s > 0.f;
+            const int ru = W.tid >> 4, rh = ru * A.inv_uh >> 8;
+            const bool real = rh < A.hb && cc.blk * A.hb + rh < A.g && (ru - rh * A.UH) * 16 + (W.tid & 15) < A.W && s > 0.f;
             smf[W.tid] = real ? make_float2(m, 1.0f / s) : make_float2(INFINITY, 0.f);
-            if (real && s == INFINITY) sm_over = 1;
         }
         lds_meet();
-        if (sm_over) rows_from_keys();
 #pragma unroll
         for (int i = 0; i < kWaveRows; ++i) {
             const float4* f4 = reinterpret_cast<const float4*>(&smf[(W.rg * kWaveRows + i) * 16 + W.kg * 4]);
@@ -604,9 +616,9 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
             dst[((W.kg >> 1) + 2 * (W.kg & 1)) * 16 + W.n16] = quarters(halves(v[i][0], v[i][1]), halves(v[i][2], v[i][3]));
         }
         const WideEntry& E = A.e[cc.e];
-        const int kv = cc.u / A.nblk, h0 = (cc.u % A.nblk) * A.hb;
+        const int h0 = cc.blk * A.hb;
         const int64_t k0 = W.round_key(cc);
-        pending = E.vote + ((int64_t)kv * A.g + h0) * E.vpitch + k0;
+        pending = E.vote + ((int64_t)cc.kv * A.g + h0) * E.vpitch + k0;
         pend_pitch = E.vpitch;
         pend_keys = (int)(cc.n - k0 < kRound ? cc.n - k0 : kRound);
         pend_heads = A.g - h0 < A.hb ? A.g - h0 : A.hb;
@@ -651,7 +663,7 @@ int wide_cus() {
 template <typename T, int D, bool PAGED, int N>
 hipError_t launch_both(const WideArgs<kMaxWide>& all, dim3 grid, hipStream_t st) {
     WideArgs<N> A;
-    A.count = all.count, A.direct = all.direct, A.g = all.g, A.W = all.W, A.UH = all.UH, A.hb = all.hb, A.nblk = all.nblk;
+    A.count = all.count, A.direct = all.direct, A.g = all.g, A.W = all.W, A.UH = all.UH, A.hb = all.hb, A.nblk = all.nblk, A.inv_uh = all.inv_uh;
     A.c2 = all.c2, A.k_rs = all.k_rs, A.table = all.table, A.page = all.page, A.pages = all.pages, A.row0 = all.row0;
     A.rounds = all.rounds, A.zeros = all.zeros, A.nzeros = all.nzeros, A.flag = all.flag;
     for (int i = 0; i < N; ++i) A.e[i] = all.e[i];
@@ -703,6 +715,7 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
     A.UH = b.UH;
     A.hb = b.hb;
     A.nblk = b.nblk;
+    A.inv_uh = (256 + b.UH - 1) / b.UH;
     A.c2 = G0.c2;
     A.k_rs = G0.k_rs;
     A.table = G0.k_table;
@@ -737,7 +750,7 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
     for (int i = count; i < kMaxWide; ++i) A.e[i] = A.e[0];
     const int64_t places = 2 * wide_cus();   // two workgroups per compute unit
     A.direct = count == 1 && slices <= places;
-    const dim3 grid = A.direct ? dim3((unsigned)A.e[0].NS, (unsigned)A.e[0].units) : dim3((unsigned)std::min(slices, places));
+    const dim3 grid = A.direct ? dim3((unsigned)A.e[0].NS, (unsigned)b.nblk, (unsigned)G0.Hkv) : dim3((unsigned)std::min(slices, places));
     if (dtype == 0) return D == 128 ? by_entries<w_bf16, 128>(A, grid, st) : by_entries<w_bf16, 64>(A, grid, st);
     return D == 128 ? by_entries<w_f16, 128>(A, grid, st) : by_entries<w_f16, 64>(A, grid, st);
 }

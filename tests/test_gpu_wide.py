@@ -113,3 +113,29 @@ def test_logits_far_above_the_first_key(snapkv):
     k[:, 7000:12000] += (122.0 * u).to(k.dtype)          # 12 * 122 / sqrt(128) = 129 nats
     res = run_gpu(snapkv, q, k, v, w.pool_kind, w.p, w.C)
     check_against_oracle(q, k, v, w.pool_kind, w.p, w.C, *res)
+
+
+@pytest.mark.parametrize("nats", [0.0, 10.0, 40.0, 80.0, 120.0])
+def test_score_error_does_not_grow_with_the_logits_range(snapkv, nats):
+    """A stretch of keys that the whole window looks for, `nats` above the prompt's first keys.  All rows of the window
+    are the same and every logit is exact in fp32 (two non-zero elements of few bits), so what remains is the
+    rounding of the exponentials' arguments, which no average over rows hides.  Bound: half an ulp of an argument
+    below 16 (2^-21, as a factor 2^-21 ln 2 = 3.3e-7) and one ulp of exp2 (1.2e-7)."""
+    Hq, L, W, D = 4, 18461, 32, 128
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(17)
+    q = torch.zeros((Hq, W, D), device="cuda")
+    q[..., 3], q[..., 7] = 16.0, 1.0 / 8
+    k = torch.zeros((1, L, D), device="cuda")
+    k[0, :, 7] = torch.randint(-256, 257, (L,), generator=gen, device="cuda")              # logits within +-32 / sqrt(128)
+    k[0, 7000:12000, 3] = round(nats * D ** 0.5 / 16 * 4) / 4
+    q, k = q.bfloat16(), k.bfloat16()
+    sc = torch.empty((1, L - W), device="cuda")
+    snapkv.snapkv_pooled_scores(q, k, 0, 1, sc)
+    logits = (q[0].double() @ k[0].double().t()) / D ** 0.5                                # [W, L]
+    seen = torch.arange(L, device="cuda") <= torch.arange(L - W, L, device="cuda").unsqueeze(1)
+    p = torch.softmax(logits.masked_fill(~seen, float("-inf")), dim=1)
+    want = Hq * p[:, :L - W].sum(0)
+    err = float((sc[0].double() - want).norm() / want.norm())
+    print(f"score error at {nats} nats: {err:.2e}")
+    assert err < 4.5e-7, err
