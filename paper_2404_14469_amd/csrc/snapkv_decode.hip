@@ -340,7 +340,11 @@ int cu_count() {
 
 }  // namespace
 
-// Splits of a (sequence, KV head) pair's keys, down to 32 keys per wave: the number that costs least when workgroups
+// Splits of a (sequence, KV head) pair's keys.  A step whose pairs alone occupy two thirds of the compute units, or of
+// fewer than 1024 keys, is not split: it needs no buffer, so steps like it on several streams do not meet in the one
+// that split steps share (288 pairs of 2560 keys would take 75 instead of 95 us split, one sequence of 900 keys and
+// 8 KV heads 12 instead of 17; one of 300 takes 9 instead of 12 as it is).
+// Otherwise, down to 32 keys per wave, the number that costs least when workgroups
 // run in rounds of one per compute unit.  In keys of time (a key of one pair at a compute unit's share of HBM): the
 // stream cannot go below everybody's keys divided evenly, nor a round below 0.8 of its workgroup's keys (a unit alone
 // draws a quarter more than its share); a round costs about 100 besides, the merge of the splits 150.  Microseconds
@@ -350,6 +354,7 @@ int cu_count() {
 // five of 16384 keys 295 / 226; eight of 2560 keys, one workgroup each either way, 55.1 / 55.0.
 int decode_splits(int B, int Hkv, int64_t S) {
     const int64_t pairs = (int64_t)B * Hkv, cus = cu_count(), steps = (S + 31) / 32;
+    if ((cus + pairs / 2) / pairs < 2 || S < 1024) return 1;
     const int64_t most = std::min<int64_t>(std::min<int64_t>(64, kDecodeMaxGroups / pairs), (steps + kDecWaves - 1) / kDecWaves);
     int best = 1;
     double least = 0.0;

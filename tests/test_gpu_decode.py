@@ -57,7 +57,8 @@ CASES = [
     DecodeWorkload("many_pairs_no_split", B=40, Hq=32, Hkv=32, D=128, S=200, cap=200, seed=9),
     DecodeWorkload("lens_mixed", B=6, Hq=8, Hkv=4, D=64, S=900, cap=901, ragged=True, seed=10),
     DecodeWorkload("f16", B=2, Hq=8, Hkv=4, D=128, S=1234, cap=1300, dtype="f16", seed=11),
-    DecodeWorkload("split_small", B=1, Hq=8, Hkv=2, D=128, S=129, cap=140, seed=13),            # one step of 32 keys per wave
+    DecodeWorkload("split_small", B=1, Hq=8, Hkv=2, D=128, S=129, cap=140, seed=13),            # too short to split
+    DecodeWorkload("split_first", B=1, Hq=8, Hkv=2, D=128, S=1024, cap=1100, seed=18),          # one step of 32 keys per wave
     DecodeWorkload("split_odd", B=1, Hq=32, Hkv=8, D=128, S=2113, cap=2560, seed=14),           # 17 splits
     DecodeWorkload("split_most", B=1, Hq=2, Hkv=1, D=64, S=16400, cap=16400, seed=15),          # 64 splits
     DecodeWorkload("split_ragged_short", B=3, Hq=16, Hkv=8, D=128, S=3000, cap=3000, ragged=True, seed=16),
@@ -131,6 +132,29 @@ def test_compressed_cache_feeds_the_decoding_step(snapkv):
     torch.cuda.synchronize()
     check_against_oracle(case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C, sc.cpu().numpy(), out_k, out_v,
                          out_idx.cpu().numpy(), kept)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S", [(9, 32, 32, 2560), (22, 8, 8, 1500), (1, 32, 8, 1023), (3, 8, 8, 900)])
+def test_unsplit_steps_on_two_streams_are_independent(snapkv, B, Hq, Hkv, S):
+    """Steps of more pairs than two thirds of the compute units, or of fewer than 1024 keys, are not split, so they share
+    no buffer: enqueued on two streams without any order between them, both give what they give alone."""
+    cases = [workloads.generate_decode(DecodeWorkload("streams", B=B, Hq=Hq, Hkv=Hkv, D=64, S=S, cap=S, seed=s), device="cuda")
+             for s in (41, 42)]
+    def step(c, o, s):
+        snapkv.snapkv_decode_attention(c["q"], c["k_cache"], c["v_cache"], S, o[0], o[1], stream=s)
+    new = lambda: (torch.zeros((B, Hq, 64), device="cuda"), torch.zeros((B, Hq), device="cuda"))
+    want, got = [new() for _ in cases], [[new() for _ in range(10)] for _ in cases]
+    for c, o in zip(cases, want):
+        step(c, o, None)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in cases]
+    for i in range(10):
+        for c, outs, s in zip(cases, got, streams):
+            step(c, outs[i], s)
+    torch.cuda.synchronize()
+    for w, outs in zip(want, got):
+        for o in outs:
+            assert torch.equal(o[0], w[0]) and torch.equal(o[1], w[1])
 
 
 def test_bad_arguments_are_refused(snapkv):
