@@ -59,8 +59,8 @@ def test_kept_set_is_the_exact_top_k(snapkv, field, L, Hq, Hkv, W, C, p, dtype):
 @pytest.mark.parametrize("field", [as_drawn, flat, few_spikes, two_fields], ids=lambda f: f.__name__)
 @pytest.mark.parametrize("layers,L,Hq,Hkv,W,C,p,dtype", [
     (40, 9001, 16, 8, 32, 700, 7, torch.bfloat16),   # more heads than the one-launch kernel keeps resident: votes read once
-    (66, 4100, 4, 4, 16, 600, 5, torch.float16),     # too short to sample: every position a candidate
-    (36, 8209, 8, 8, 32, 8000, 13, torch.bfloat16),  # nearly everything kept
+    (66, 4100, 4, 4, 16, 600, 5, torch.float16),     # too short to sample: the separate kernels
+    (36, 8209, 8, 8, 32, 8000, 13, torch.bfloat16),  # nearly everything kept: the separate kernels
     (20, 20483, 16, 16, 16, 17, 1, torch.bfloat16),  # one position kept per head
 ])
 def test_many_heads_keep_what_single_calls_keep(snapkv, field, layers, L, Hq, Hkv, W, C, p, dtype):
@@ -82,3 +82,33 @@ def test_many_heads_keep_what_single_calls_keep(snapkv, field, layers, L, Hq, Hk
             res = run_gpu(snapkv, lists[0][l], lists[1][l], lists[2][l], pool_kind, p, C)
             assert (lists[5][l].cpu().numpy() == res[3]).all(), (l, pool_kind)
             assert torch.equal(lists[3][l], res[1]) and torch.equal(lists[4][l], res[2]), (l, pool_kind)
+
+
+@pytest.mark.parametrize("heads,L,kcount,once", [
+    (1024, 2048, 200, False),     # too short to sample
+    (1024, 8191, 200, False),
+    (1024, 8208, 500, True),
+    (1024, 8208, 6000, False),    # the candidates of a head cost more than the scores of all
+    (600, 20016, 1000, True),
+    (600, 20016, 10000, False),
+])
+def test_votes_are_read_once_only_where_that_is_faster(snapkv, heads, L, kcount, once):
+    """The rule of pool_pick_ok: short prompts and large kept shares go through the kernels that store the scores (the
+    stage pool_group), which are twice as fast there.  Either way the kept positions are a single call's."""
+    Hkv, W, D = 8, 16, 64
+    layers, C = heads // Hkv, kcount + W
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    q = torch.randn((layers * Hkv, W, D), generator=gen, device="cuda").bfloat16()
+    k = torch.randn((layers * Hkv, L, D), generator=gen, device="cuda").bfloat16()
+    ok = torch.empty((layers * Hkv, C, D), dtype=torch.bfloat16, device="cuda")
+    ov = torch.empty_like(ok)
+    oi = torch.full((layers * Hkv, C), -1, dtype=torch.int32, device="cuda")
+    lists = [list(t.split(Hkv)) for t in (q, k, k, ok, ov, oi)]
+    snapkv.snapkv_profile_start(1)
+    snapkv.snapkv_compress_layers(*lists[:3], 0, 5, C, *lists[3:])
+    stages, calls = snapkv.snapkv_profile_stop()
+    assert calls == 1 and (stages["pool_group"] == 0.0) == once, stages
+    for l in (0, layers - 1):
+        res = run_gpu(snapkv, lists[0][l], lists[1][l], lists[2][l], 0, 5, C)
+        assert (lists[5][l].cpu().numpy() == res[3]).all(), l
