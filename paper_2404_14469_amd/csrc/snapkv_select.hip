@@ -205,15 +205,14 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4_nt;
 
 struct NoLayers {};
 
-// (Rows are 8, 16 or 32 pieces: a piece's row and place come from a shift, not from 64-bit divisions, of which a thread
-// made four: 58.9 -> 58.1 us per call at 16384 keys and 32 heads.)
+// (Rows are 8, 16 or 32 pieces: a piece's row and place come from a shift, not from 64-bit divisions.)
 // Each thread moves 16 bytes of a K row and the matching 16 bytes of the V row; consecutive
 // threads cover consecutive pieces of a row, so a 256-byte row is one coalesced 16-lane access.
 // Every row is read once and written once: the non-temporal policy keeps both out of the way of
 // the next call's K stream.  LY = GatherLayers: head h is head h % ly.heads of the separately allocated
 // layer h / ly.heads (k, v, out_k and out_v are then unused) and the positions are copied to that layer's
 // out_idx as well.
-template <typename LY>
+template <int U, typename LY>
 __device__ __forceinline__ void gather_body(const uint4* __restrict__ k, const uint4* __restrict__ v,
                                             const int32_t* __restrict__ idx, const int64_t L, const int64_t rows,
                                             const int64_t out_stride, const int shift, uint4* __restrict__ out_k,
@@ -239,10 +238,8 @@ __device__ __forceinline__ void gather_body(const uint4* __restrict__ k, const u
         ovb = out_v + (int64_t)h * out_stride * pieces;
     }
     const int32_t* ib = idx + (int64_t)h * out_stride;
-    // Four pieces per thread and pass, a grid stride apart: the positions are fetched first, then all
-    // eight loads are in flight together, then the stores; a thread's two dependent memory latencies
-    // (position, then row) are so paid once per four pieces.
-    constexpr int U = 4;
+    // U pieces per thread and pass, a grid stride apart: the positions are fetched first, then all 2 U loads are in flight
+    // together, then the stores.
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x; e0 < total; e0 += U * stride) {
         int64_t r[U], src[U];
@@ -289,6 +286,7 @@ __device__ __forceinline__ void gather_body(const uint4* __restrict__ k, const u
     }
 }
 
+template <int U>
 __global__ __launch_bounds__(256) void gather_rows(const uint4* __restrict__ k,
                                                    const uint4* __restrict__ v,
                                                    const int32_t* __restrict__ idx,
@@ -300,14 +298,14 @@ __global__ __launch_bounds__(256) void gather_rows(const uint4* __restrict__ k,
                                                    const RowLayout vl /* strides in 16-byte pieces */,
                                                    const int head_div /* output heads per source head */,
                                                    const PageMap pm, const CleanJob clean) {
-    gather_body(k, v, idx, L, rows, out_stride, shift, out_k, out_v, kl, vl, head_div, pm, clean, NoLayers{});
+    gather_body<U>(k, v, idx, L, rows, out_stride, shift, out_k, out_v, kl, vl, head_div, pm, clean, NoLayers{});
 }
 
 __global__ __launch_bounds__(256) void gather_rows_layers(const GatherLayers ly, const int32_t* __restrict__ idx,
                                                           const int64_t L, const int64_t rows, const int64_t out_stride,
                                                           const int shift, const RowLayout kl, const RowLayout vl,
                                                           const CleanJob clean) {
-    gather_body(nullptr, nullptr, idx, L, rows, out_stride, shift, nullptr, nullptr, kl, vl, 1, PageMap{}, clean, ly);
+    gather_body<4>(nullptr, nullptr, idx, L, rows, out_stride, shift, nullptr, nullptr, kl, vl, 1, PageMap{}, clean, ly);
 }
 
 // Per-head valid prefix lengths of a batch: head h of the batch belongs to prompt h / Hkv.
@@ -324,6 +322,7 @@ hipError_t launch_batch_lengths(const BatchDesc& B, int32_t* nvalid, hipStream_t
 
 // gather_rows for a batch: head h of the grid is KV head h % Hkv of prompt h / Hkv; the kept
 // positions come from one [heads, C] array and are also copied to the prompt's own out_idx.
+template <int U>
 __global__ __launch_bounds__(256) void gather_rows_batch(const BatchDesc B, const int32_t* __restrict__ idx,
                                                          const int64_t C, const int shift, const CleanJob clean) {
     const int64_t pieces = (int64_t)1 << shift;
@@ -336,8 +335,7 @@ __global__ __launch_bounds__(256) void gather_rows_batch(const BatchDesc B, cons
     const int32_t* ib = idx + (int64_t)h * C;
     int32_t* ob = B.out_idx[pr] + (int64_t)head * C;
     const int64_t total = C << shift, stride = (int64_t)gridDim.x * 256;
-    constexpr int U = 4;   // four pieces per thread in flight, as in gather_body
-    for (int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x; e0 < total; e0 += U * stride) {
+    for (int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x; e0 < total; e0 += U * stride) {   // as in gather_body
         int32_t raw[U];
         u32x4_nt a[U], b[U];
 #pragma unroll
@@ -365,15 +363,28 @@ __global__ __launch_bounds__(256) void gather_rows_batch(const BatchDesc B, cons
     for (int64_t j = gid; j < clean.nzeros; j += gsz) clean.zeros[j] = 0u;
 }
 
+// Pieces per thread of the gathers.  With few rows in all (16-byte pieces of all heads, in workgroups of 256) four in flight
+// hide the two dependent latencies (position, then row) best; with more they crowd the memory, and one is better; a
+// paged cache's four page look-ups cost more than they hide.  Separately allocated layers do better with four throughout.
+// Microseconds of the gather with four (their places from divisions / from shifts) and with one: 32 heads of which
+// 12000 rows are kept 55 / 63 / 46; 32 layers of 8 heads, 3686 rows 136 / 150 / 117, 1024 rows 51 / 51 / 45; eight prompts of
+// 8 heads, 4000 rows - / 44 / 33; four of 1024 rows (2048 workgroups) - / 10.0 / 11.5; whole calls, 8 of 32 heads, 16384
+// keys, 2048 rows (1024 workgroups) 46.2 / 41.6 / 41.9, 3000 rows 47.8 / 44.0 / 43.8, 12000 rows 59.3 / 56.0 / 54.8; 13339
+// paged keys, 1024 rows - / 43.9 / 42.1; 32 separate layers of 32 heads, 1900 rows 309 / 311 / 321.
+static bool few_pieces(int64_t total, int64_t heads) { return (total + 255) / 256 * heads <= 2048; }
+
 hipError_t launch_gather_batch(const BatchDesc& B, const int32_t* idx, int64_t C, int row_bytes,
                                const CleanJob& clean, hipStream_t st) {
     if (B.count <= 0 || C <= 0) return hipSuccess;
     const int pieces = row_bytes / 16;
     const int64_t total = C * pieces;
-    unsigned bx = (unsigned)((total + 1023) / 1024);   // four pieces per thread
+    const bool few = few_pieces(total, (int64_t)B.count * B.Hkv);
+    unsigned bx = (unsigned)(few ? (total + 1023) / 1024 : (total + 255) / 256);
     if (bx > 1024) bx = 1024;
-    hipLaunchKernelGGL(gather_rows_batch, dim3(bx, B.count * B.Hkv), dim3(256), 0, st, B, idx, C,
-                       __builtin_ctz((unsigned)pieces), clean);
+    const dim3 grid(bx, B.count * B.Hkv);
+    const int shift = __builtin_ctz((unsigned)pieces);
+    if (few) hipLaunchKernelGGL(gather_rows_batch<4>, grid, dim3(256), 0, st, B, idx, C, shift, clean);
+    else hipLaunchKernelGGL(gather_rows_batch<1>, grid, dim3(256), 0, st, B, idx, C, shift, clean);
     return hipGetLastError();
 }
 
@@ -400,10 +411,11 @@ hipError_t launch_gather(const void* k, const void* v, const int32_t* idx, int H
     if (H <= 0 || rows <= 0) return hipSuccess;
     const int pieces = row_bytes / 16;
     const int64_t total = rows * pieces;
-    unsigned bx = (unsigned)((total + 1023) / 1024);   // four pieces per thread
+    const bool four = !pm.table && few_pieces(total, H);
+    unsigned bx = (unsigned)(four ? (total + 1023) / 1024 : (total + 255) / 256);
     if (bx > 4096) bx = 4096;
     const RowLayout kp{kl.head_stride / 16, kl.row_stride / 16}, vp{vl.head_stride / 16, vl.row_stride / 16};
-    hipLaunchKernelGGL(gather_rows, dim3(bx, H), dim3(256), 0, st, static_cast<const uint4*>(k),
+    hipLaunchKernelGGL(four ? gather_rows<4> : gather_rows<1>, dim3(bx, H), dim3(256), 0, st, static_cast<const uint4*>(k),
                        static_cast<const uint4*>(v), idx, L, rows, out_stride, __builtin_ctz((unsigned)pieces),
                        static_cast<uint4*>(out_k), static_cast<uint4*>(out_v), kp, vp, head_div, pm, clean);
     return hipGetLastError();

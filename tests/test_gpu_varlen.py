@@ -49,6 +49,9 @@ MIXES = {
     "d64_f16": dict(lengths=[2222, 5555, 3333], D=64, dtype="f16", C=200),
     "wide_window_runs_one_by_one": dict(lengths=[1500, 2100], W=160, C=320, p=5),
     "single_prompt": dict(lengths=[4321]),
+    # the gathers move four pieces per thread up to 2048 workgroups of single pieces and one beyond: batch / single calls
+    "many_rows": dict(lengths=[6001, 5003, 5500], Hq=8, Hkv=8, C=1501),              # 2256 / 752
+    "many_rows_alone": dict(lengths=[6001], Hq=8, Hkv=8, C=5003),                    # - / 2504
 }
 
 
