@@ -285,27 +285,25 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_attn(const DecodeArgs A
 
 // Merges the partials of the splits of one query head: one wave per head, lane l holding head-dim elements
 // 2l, 2l + 1 (D = 128) or l (D = 64).  Latency-bound: all (max, sum) pairs are fetched at once, a split per lane
-// (decode_splits gives at most 64), and the partial outputs eight splits at a time, the first eight of them before anything
-// is waited for.  The reductions over the splits take as many cross-lane steps as their number asks for, not six: with
-// six, steps of two splits took 0.2 to 0.4 us more than with the merge that this one replaced (13 sequences of
-// 1024 keys and 8 KV heads 13.9 / 14.1 / 13.8 us, 16 sequences 17.6 / 17.9 / 17.6: before, with six and now).
+// (decode_splits gives at most 64), and the partial outputs sixteen splits at a time, the first of them before anything is
+// waited for.  The reductions over the splits take as many cross-lane steps as their number asks for.  Microseconds per
+// step with the merge that went through the splits one by one / eight at a time after six-step reductions / this one:
+// two splits (16 sequences of 1024 keys, 8 KV heads) 17.8 / 17.8 / 17.4, 32 splits (one of 10611 keys) 20.1 / 13.9 / 13.3.
 template <int D>
 __global__ __launch_bounds__(64) void decode_merge(const float* part_acc, const float2* part_ml, int nsplit,
                                                    float* out, float* lse) {
-    constexpr int E = D / 64;
+    constexpr int E = D / 64, kBatch = 16;
     const int64_t hq = blockIdx.x;
     const int lane = threadIdx.x;
     const float* pa = part_acc + hq * nsplit * D + lane * E;
     const float2 ml = lane < nsplit ? part_ml[hq * nsplit + lane] : make_float2(-INFINITY, 0.f);
-    float x[8][E];
-    auto fetch = [&](int s0) __attribute__((always_inline)) {
+    float x[kBatch][E];
+    auto fetch = [&](int s0) __attribute__((always_inline)) {   // (past the last split: the last one, whose weight there is zero)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < kBatch; ++i) {
+            const int sp = s0 + i < nsplit ? s0 + i : nsplit - 1;
 #pragma unroll
-            for (int e = 0; e < E; ++e) x[i][e] = 0.f;
-            if (s0 + i < nsplit)
-#pragma unroll
-                for (int e = 0; e < E; ++e) x[i][e] = pa[(int64_t)(s0 + i) * D + e];
+            for (int e = 0; e < E; ++e) x[i][e] = pa[(int64_t)sp * D + e];
         }
     };
     fetch(0);
@@ -314,19 +312,23 @@ __global__ __launch_bounds__(64) void decode_merge(const float* part_acc, const 
     };
     const int top = nsplit <= 1 ? 0 : 32 >> __builtin_clz((unsigned)(nsplit - 1) << 26);   // lanes beyond the splits add nothing
     float M = ml.x;
-    for (int d = top; d >= 1; d >>= 1) M = fmaxf(M, __shfl_xor(M, d));
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+        if (d <= top) M = fmaxf(M, __shfl_xor(M, d));
     M = first_lane(M);
     const float f = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - M);
     float Lq = ml.y * f;
-    for (int d = top; d >= 1; d >>= 1) Lq += __shfl_xor(Lq, d);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+        if (d <= top) Lq += __shfl_xor(Lq, d);
     Lq = first_lane(Lq);
     float o[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] = 0.f;
-    for (int s0 = 0; s0 < nsplit; s0 += 8) {
+    for (int s0 = 0; s0 < nsplit; s0 += kBatch) {
         if (s0 > 0) fetch(s0);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < kBatch; ++i) {
             const float fs = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), s0 + i));   // (at most 64 splits)
 #pragma unroll
             for (int e = 0; e < E; ++e) o[e] += x[i][e] * fs;
