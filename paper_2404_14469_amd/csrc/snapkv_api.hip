@@ -375,6 +375,7 @@ struct CompressOptions {
     // the outputs are then taken from these tables, library's own scratch only)
     const ScoreLayers* score_layers = nullptr;
     const GatherLayers* gather_layers = nullptr;
+    int own_kv = 0;                     // KV heads of one layer where Hq and Hkv count those of several (0: Hkv)
 };
 
 int64_t compress_impl(int dtype, const void* q_win, const void* k, const void* v, int64_t L, int Hq,
@@ -421,6 +422,7 @@ int64_t compress_impl(int dtype, const void* q_win, const void* k, const void* v
     }
 
     ScoreGeom G = make_geom(L, Hq, Hkv, D, W);
+    if (opt.own_kv > 0) G.own_kv = opt.own_kv;
     G.k_hs = kl.head_stride;
     G.k_rs = kl.row_stride;
     G.k_table = pm.table;
@@ -1080,6 +1082,7 @@ int snapkv_compress_layers(int dtype, int n_layers, const void* const* q_win, co
             while (i + t < n_layers && t < most_sep && (i + t + 1 >= n_layers || !follows(i + t))) ++t;
             if (t > 1) {
                 ScoreGeom Gt = make_geom(L, Hq * t, Hkv * t, D, W);
+                Gt.own_kv = Hkv;
                 Gt.k_rs = (int64_t)D * e;
                 Gt.k_hs = Gt.k_rs * L;
                 if (layers_table_ok(dtype, D, Gt, Hkv)) {
@@ -1098,6 +1101,7 @@ int snapkv_compress_layers(int dtype, int n_layers, const void* const* q_win, co
                     CompressOptions opt;
                     opt.score_layers = &SL;
                     opt.gather_layers = &GL;
+                    opt.own_kv = Hkv;
                     const int64_t got = compress_impl(dtype, q_win[i], k[i], v[i], L, Hq * t, Hkv * t, D, W, pool_kind, p, C,
                                                       out_k[i], out_v[i], out_idx[i], stream, opt);
                     if (got < 0) return (int)got;
@@ -1106,8 +1110,10 @@ int snapkv_compress_layers(int dtype, int n_layers, const void* const* q_win, co
                 }
             }
         }
+        CompressOptions stacked;
+        stacked.own_kv = Hkv;
         const int64_t got = compress_impl(dtype, q_win[i], k[i], v[i], L, Hq * r, Hkv * r, D, W, pool_kind, p, C, out_k[i],
-                                          out_v[i], out_idx[i], stream);
+                                          out_v[i], out_idx[i], stream, stacked);
         if (got < 0) return (int)got;
         i += r;
     }

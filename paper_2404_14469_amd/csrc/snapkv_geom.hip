@@ -11,6 +11,7 @@ ScoreGeom make_geom(int64_t L, int Hq, int Hkv, int D, int W) {
     G.W = W;
     G.g = Hq / Hkv;
     G.Hkv = Hkv;
+    G.own_kv = Hkv;
     G.BH = (W + 31) / 32;
     G.VB = 1;          // the scoring launch says how many vote rows it left per query head
     G.NV = G.g;

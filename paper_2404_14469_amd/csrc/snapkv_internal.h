@@ -17,6 +17,7 @@ struct ScoreGeom {
     int W;           // observation window
     int g;           // query heads per KV head
     int Hkv;         // KV heads
+    int own_kv;      // KV heads of the prompt or layer itself, of which the call may have several one behind the other
     int BH;          // 32-row blocks per query head, ceil(W / 32)
     int NV;          // vote rows per KV head
     int VB;          // vote rows per query head

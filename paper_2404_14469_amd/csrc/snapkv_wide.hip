@@ -11,8 +11,9 @@
 //
 //   * The window rows of a KV head form blocks of whole query heads, at most eight 16-row units each; a unit of
 //     work is one block.  A wave owns 32 of the block's rows, its Q in registers as MFMA fragments.
-//   * The keys of a unit are cut into at most 64 slices of RPS rounds of 128 keys.  The slice length depends on the
-//     prompt length alone, so a head's result does not depend on which other heads share the launch.
+//   * The keys of a unit are cut into at most 64 slices of RPS rounds of 128 keys, or into up to 256 if the prompt has
+//     fewer than four units.  The slice length depends on the prompt's length and its own heads alone, so a head's
+//     result does not depend on which other layers or prompts share the launch.
 //   * A round's keys pass through LDS (landing registers -> two buffers, one barrier a round), where four groups
 //     of waves x two parts of the keys read them as fragments; the next round is on its way meanwhile.
 //   * A persistent grid of two workgroups per compute unit walks the slices of all units (of all prompts or layers of
@@ -58,7 +59,8 @@ struct w_f16 {};
 constexpr int kWaves = 8;                    // waves per workgroup, two workgroups per compute unit
 constexpr int kThreads = kWaves * 64;
 constexpr int kRound = kWaves * 16;          // keys of a round: every wave brings one 16-key tile to LDS
-constexpr int kSlices = 64;                  // slices per unit at most
+constexpr int kSlices = 64;                  // slices per unit at most,
+constexpr int kPlaces = 256;                 //   or as many as give a prompt of few units this many in all
 constexpr int kWaveRows = 2;                 // 16-row units of a wave
 constexpr int RUW = 8;                       // 16-row units of a block
 constexpr float kRaiseAt = 0x1p16f;          // exponential (of a lane's sum) from which a row's reference is raised,
@@ -70,6 +72,10 @@ constexpr float kRaiseBelow = 7.f;           //   to that logit less this
 //                      40001: 75 / 108, 194 / 323;  131072: 141 / 182, 483 / 632
 //   W = 64 (256 rows):  8192: 57 / 53, 91 / 104;  10007: 65 / 73, 100 / 169;  28471: 85 / 110, 189 / 320;
 //                      131072: 206 / 314, 785 / 1167
+// Few KV heads (W = 32, single-read kernel / 64 slices per unit / kPlaces in all):
+//   1 head: 18439 keys 40 / 41 / 39;  46087: 45 / 50 / 43;  131072: 55 / 80 / 53;  700001: 313 / 292 / 116
+//   2 heads: 27655: 46 / 46 / 42;  131072: 77 / 85 / 66;  32 layers of 1 head, 31337: 196 / 144 / 151
+// (with 512 in all: 1 head, 46087: 55, 131072: 67; 2 heads, 27655: 52)
 // With 64 rows (W = 16 there, or W = 64 and a head each) the single-read kernel is faster at every length but the
 // few that leave it compute units idle, so those do not come here.
 constexpr int64_t kMinRowKeys = 9 << 18;
@@ -642,10 +648,15 @@ bool row_blocks(const ScoreGeom& G, Blocks* b) {
     return true;
 }
 
-int rounds_per_slice(int64_t L) { return (int)((L + (int64_t)kRound * kSlices - 1) / ((int64_t)kRound * kSlices)); }
-int slices_of(int64_t L) {
-    const int64_t keys = (int64_t)rounds_per_slice(L) * kRound;
-    return (int)((L + keys - 1) / keys);
+// Rounds per slice and slices per unit.  They depend on the prompt and its own heads only, not on what else the call holds.
+int rounds_per_slice(const ScoreGeom& G, const Blocks& b) {
+    auto rounds = [&](int64_t most) { return (G.L + kRound * most - 1) / (kRound * most); };
+    const int64_t usual = rounds(kSlices), few_units = rounds(std::max<int64_t>(kSlices, kPlaces / ((int64_t)G.own_kv * b.nblk)));
+    return (int)std::max(few_units, std::min<int64_t>(usual, 2));   // (a slice's end costs half a round)
+}
+int slices_of(const ScoreGeom& G, const Blocks& b) {
+    const int64_t keys = (int64_t)rounds_per_slice(G, b) * kRound;
+    return (int)((G.L + keys - 1) / keys);
 }
 
 int wide_cus() {
@@ -686,20 +697,20 @@ static bool wide_shape(const ScoreGeom& G, Blocks* b) {
     if (G.n <= 0 || !row_blocks(G, b) || (int64_t)G.g * b->UH * 16 * G.L < kMinRowKeys) return false;
     ScoreGeom one = G;
     one.Hkv = 1;
-    const size_t part = sizeof(float2) * (size_t)b->nblk * slices_of(G.L) * RUW * 16;
+    const size_t part = sizeof(float2) * (size_t)b->nblk * slices_of(G, *b) * RUW * 16;
     return part <= std::max(stream_stat_bytes(one), sizeof(float) * (size_t)G.g * (size_t)G.n);
 }
 
 bool wide_ok(int dtype, int D, const ScoreGeom& G) {
     Blocks b;
     if ((dtype != 0 && dtype != 2) || (D != 64 && D != 128) || !wide_shape(G, &b)) return false;
-    return (int64_t)G.Hkv * b.nblk * slices_of(G.L) * rounds_per_slice(G.L) <= kMaxRounds;
+    return (int64_t)G.Hkv * b.nblk * slices_of(G, b) * rounds_per_slice(G, b) <= kMaxRounds;
 }
 
 size_t wide_part_bytes(const ScoreGeom& G) {
     Blocks b;
     if (!wide_shape(G, &b)) return 0;
-    return (sizeof(float2) * (size_t)G.Hkv * b.nblk * slices_of(G.L) * RUW * 16 + 255) & ~(size_t)255;
+    return (sizeof(float2) * (size_t)G.Hkv * b.nblk * slices_of(G, b) * RUW * 16 + 255) & ~(size_t)255;
 }
 
 hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st, const WideClear& clear) {
@@ -740,8 +751,8 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
         E.round_begin = A.rounds;
         E.L = (int)G.L;
         E.n = (int)G.n;
-        E.RPS = rounds_per_slice(G.L);
-        E.NS = slices_of(G.L);
+        E.RPS = rounds_per_slice(G, b);
+        E.NS = slices_of(G, b);
         E.units = G.Hkv * b.nblk;
         if ((int64_t)E.units * E.NS * E.RPS > kMaxRounds) return hipErrorInvalidValue;
         A.rounds += (unsigned)E.units * E.NS * E.RPS;

@@ -33,6 +33,11 @@ CASES = {
     "d64_f16": work(18439, 4, 32, D=64, dtype="f16"),
     "f16": work(18441, 4, 32, dtype="f16"),
     "many_slices": work(40001, 4, 32, Hkv=1, C=1024),
+    # prompts of few heads are cut into up to 256 slices per head instead of 64, of two rounds at least
+    "one_head_256_slices": work(65536, 4, 32, Hkv=1),
+    "one_head_171_slices": work(65537, 4, 32, Hkv=1),              # the last one holds one key
+    "two_heads_128_slices": work(2 * 16384 - 5, 4, 32),
+    "three_heads_85_slices": work(85 * 256, 4, 32, Hkv=3),
 }
 
 
@@ -98,6 +103,28 @@ def test_layouts_layers_and_batches_equal_single_calls(snapkv):
                                   w.pool_kind, w.p, w.C, oks, ovs, ois)
     for i in range(3):
         same(oks[i], ovs[i], ois[i], refs[i], f"batch, prompt {i}")
+
+
+@pytest.mark.parametrize("Hkv,L", [(1, 18433), (2, 30011)])
+def test_few_heads_in_layers_and_batches_equal_single_calls(snapkv, Hkv, L):
+    """The cut of a prompt into slices follows its own heads, not those of the call: layers, stacked or separate, and the
+    prompts of a batch keep, bit for bit, what single calls keep."""
+    w = work(L, 4, 32, Hkv=Hkv)
+    cases = [workloads.generate(w, layer=l, device="cuda") for l in range(2)] + [workloads.generate(w.with_(L=L + 70), device="cuda")]
+    want = [run_gpu(snapkv, c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C) for c in cases]
+    lists = [[c[n] for c in cases[:2]] for n in ("q_win", "k", "v")]
+    for stack in (False, True):
+        oks, ovs, ois = outputs(w, 2, cases[0]["k"].dtype)
+        if stack:
+            lists = [list(torch.stack(x).contiguous()) for x in lists]
+            oks, ovs, ois = (list(torch.stack(x).contiguous()) for x in (oks, ovs, ois))
+        snapkv.snapkv_compress_layers(*lists, w.pool_kind, w.p, w.C, oks, ovs, ois)
+        for l in range(2):
+            assert np.array_equal(ois[l].cpu().numpy(), want[l][3]) and torch.equal(oks[l], want[l][1]), (l, stack)
+    oks, ovs, ois = outputs(w, 3, cases[0]["k"].dtype)
+    snapkv.snapkv_compress_varlen(*([c[n] for c in cases] for n in ("q_win", "k", "v")), w.pool_kind, w.p, w.C, oks, ovs, ois)
+    for i in range(3):
+        assert np.array_equal(ois[i].cpu().numpy(), want[i][3]) and torch.equal(oks[i], want[i][1]), i
 
 
 def test_logits_far_above_the_first_key(snapkv):
