@@ -123,7 +123,7 @@ int64_t row_pitch(const ScoreGeom& G);
 // Stage boundaries for the optional per-stage timing (snapkv_profile_start/stop): when timing is
 // active, stage_done records an event on the stream after the stage's launch; otherwise it is a
 // no-op.  kStageBegin marks the start of a call.
-enum Stage { kStageBegin = 0, kStagePrepare, kStagePass1, kStageReduce, kStageFused, kStagePass2,
+enum Stage { kStageBegin = 0, kStagePrepare, kStagePass1, kStageReduce, kStageWide, kStageFused, kStagePass2,
              kStagePool, kStageSelect, kStageGather, kNumStageMarks };
 void stage_done(hipStream_t st, int stage);
 

@@ -680,7 +680,7 @@ hipError_t launch_both(const WideArgs<kMaxWide>& all, dim3 grid, hipStream_t st)
     for (int i = 0; i < N; ++i) A.e[i] = all.e[i];
     hipLaunchKernelGGL((wide_stats<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
     hipLaunchKernelGGL((wide_votes<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
-    stage_done(st, kStageFused);   // (both launches: the stage that scores all keys of a prompt)
+    stage_done(st, kStageWide);    // (both launches)
     return hipGetLastError();
 }
 template <typename T, int D> hipError_t by_entries(const WideArgs<kMaxWide>& A, dim3 grid, hipStream_t st) {

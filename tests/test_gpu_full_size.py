@@ -107,17 +107,29 @@ def test_window_64_pool_13_at_full_size(snapkv):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("L,heads", [(65536, [3]), (131072, [6]), (100003, [0])])
-def test_grouped_query_prompts_whose_parts_follow_one_another(snapkv, L, heads):
-    """Grouped-query prompts so long that the parts of a KV head (one query head each) no longer fit
-    the chip side by side: they follow one another on the same workgroups, and the single-read kernel
-    still takes the prompt (two groups of two parts at 65536 tokens, one group at 131072)."""
-    w = workloads.MISTRAL_7B_GQA_32K.with_(name=f"gqa_{L}", L=L, C=4096)
+def _scoring_stages(snapkv, w, heads):
     snapkv.snapkv_profile_start(4)
     _run(snapkv, w, 1, heads)
     ms, calls = snapkv.snapkv_profile_stop()
-    assert ms.get("score_fused", 0.0) > 0.0 and ms.get("score_stream", 0.0) == 0.0, ms
     torch.cuda.empty_cache()
+    assert calls > 0
+    return {n for n, t in ms.items() if n.startswith("score") and t > 0.0}
+
+
+@pytest.mark.parametrize("L,W,dtype,heads", [(65536, 32, "f32", [3]), (131072, 16, "bf16", [6]), (100003, 16, "bf16", [0])])
+def test_grouped_query_prompts_whose_parts_follow_one_another(snapkv, L, W, dtype, heads):
+    """Grouped-query prompts so long that the parts of a KV head (32 window rows each) no longer fit the chip side by
+    side: they follow one another on the same workgroups, and the single-read kernel still takes the prompt (two groups
+    of two parts at 65536 tokens and W = 32, one part at a time in the others)."""
+    w = workloads.MISTRAL_7B_GQA_32K.with_(name=f"gqa_{L}", L=L, W=W, dtype=dtype, C=4096)
+    assert _scoring_stages(snapkv, w, heads) == {"score_fused"}
+
+
+@pytest.mark.parametrize("L,heads", [(65536, [3]), (131072, [6]), (100003, [0])])
+def test_long_grouped_query_prompts_take_the_two_passes(snapkv, L, heads):
+    """128 window rows per KV head in a two-byte type, at any length from 18432 keys on."""
+    w = workloads.MISTRAL_7B_GQA_32K.with_(name=f"gqa_{L}", L=L, C=4096)
+    assert _scoring_stages(snapkv, w, heads) == {"score_wide"}
 
 
 def test_varlen_batch(snapkv):
