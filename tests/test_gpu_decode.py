@@ -157,6 +157,35 @@ def test_unsplit_steps_on_two_streams_are_independent(snapkv, B, Hq, Hkv, S):
             assert torch.equal(o[0], w[0]) and torch.equal(o[1], w[1])
 
 
+def test_step_captured_before_any_eager_call(snapkv):
+    """A capturing stream cannot allocate the partials' buffer: a step captured before the first eager one that is split
+    is recorded unsplit, and one captured afterwards as the eager step is; both replay right."""
+    w = DecodeWorkload("captured", B=1, Hq=8, Hkv=2, D=128, S=4100, cap=4100, seed=51)
+    cases = [workloads.generate_decode(DecodeWorkload(**{**w.__dict__, "seed": 51 + i}), device="cuda") for i in range(2)]
+    q, k, v = (torch.empty_like(cases[0][n]) for n in ("q", "k_cache", "v_cache"))
+    out, lse = torch.empty((w.B, w.Hq, w.D), device="cuda"), torch.empty((w.B, w.Hq), device="cuda")
+    torch.cuda.synchronize()
+    snapkv.snapkv_release()                              # as in a process that has not decoded yet
+    graphs = []
+    for i in range(2):
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            snapkv.snapkv_decode_attention(q, k, v, w.S, out, lse)
+        if i == 0:
+            eager, eager_lse = run(snapkv, w, cases[0])
+    for rep in range(4):
+        c = cases[rep % 2]
+        for t, n in ((q, "q"), (k, "k_cache"), (v, "v_cache")):
+            t.copy_(c[n])
+        for i, graph in enumerate(graphs):
+            out.fill_(float("nan")), lse.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            check(w, c, out.cpu().numpy(), lse.cpu().numpy())
+            if i == 1 and rep % 2 == 0:
+                assert np.array_equal(out.cpu().numpy(), eager) and np.array_equal(lse.cpu().numpy(), eager_lse)
+
+
 def test_bad_arguments_are_refused(snapkv):
     w = DecodeWorkload("bad", B=1, Hq=4, Hkv=4, D=64, S=10, cap=16, seed=23)
     case = workloads.generate_decode(w, device="cuda")

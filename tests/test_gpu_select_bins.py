@@ -3,6 +3,7 @@ around the mean score, so the threshold can fall into either end bin, into a bin
 candidate list, into one of at most 128 (counted directly) or more (searched by digits); a head may have one
 workgroup or many, and rows of votes whose length is no multiple of four are padded.  Whatever the route, the kept
 set is exactly the top-k of the call's own pooled scores."""
+import numpy as np
 import pytest
 import torch
 
@@ -112,3 +113,41 @@ def test_votes_are_read_once_only_where_that_is_faster(snapkv, heads, L, kcount,
     for l in (0, layers - 1):
         res = run_gpu(snapkv, lists[0][l], lists[1][l], lists[2][l], 0, 5, C)
         assert (lists[5][l].cpu().numpy() == res[3]).all(), l
+
+
+@pytest.mark.parametrize("pool_kind,p", [(0, 1), (0, 5), (1, 5)])
+def test_heads_whose_sample_misleads_are_collected_again(snapkv, pool_kind, p):
+    """Only the 2048 sampled positions (runs of four, evenly spread) score high, and more positions than those are kept: the
+    sample's lower bound lets too few candidates through and pick_finish has to take all of the head's positions."""
+    layers, Hkv, L, W, D, kc = 20, 8, 40032, 16, 64, 3000
+    n, C = L - W, kc + W
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    u = torch.zeros(D, device="cuda")
+    u[7] = 1.0
+    q = torch.randn((layers * Hkv, W, D), generator=gen, device="cuda") * 0.5 + 8 * u
+    k = torch.randn((layers * Hkv, L, D), generator=gen, device="cuda")
+    sampled = ((n - 4) * torch.arange(512) // 511 & ~3).unsqueeze(1) + torch.arange(4)
+    k[:, sampled.flatten().cuda()] += 8 * u
+    q, k = q.bfloat16(), k.bfloat16()
+    v = torch.randn((layers * Hkv, L, D), generator=gen, device="cuda").bfloat16()
+    ok = torch.empty((layers * Hkv, C, D), dtype=torch.bfloat16, device="cuda")
+    ov = torch.empty_like(ok)
+    oi = torch.full((layers * Hkv, C), -1, dtype=torch.int32, device="cuda")
+    lists = [list(t.split(Hkv)) for t in (q, k, v, ok, ov, oi)]
+    snapkv.snapkv_profile_start(1)
+    snapkv.snapkv_compress_layers(*lists[:3], pool_kind, p, C, *lists[3:])
+    stages, calls = snapkv.snapkv_profile_stop()
+    assert calls == 1 and stages["pool_group"] == 0.0 and stages["select_topk"] > 0.0, stages
+    for l in (0, 7, layers - 1):
+        res = run_gpu(snapkv, lists[0][l], lists[1][l], lists[2][l], pool_kind, p, C)
+        assert (lists[5][l].cpu().numpy() == res[3]).all(), l
+        assert torch.equal(lists[3][l], res[1]) and torch.equal(lists[4][l], res[2]), l
+        # the sample's bound as pick_bracket takes it: digits of 2^17 patterns from 1/64 of the mean on
+        want = 2048 * kc / n
+        rank = int(want + 5 * (4 * want) ** 0.5 + 8)
+        lo0 = int(np.float32(np.float32(W / n) * np.float32(1 / 64)).view(np.uint32))
+        bits = res[0].view(np.uint32).astype(np.int64)
+        digits = np.clip((bits - lo0) >> 17, 0, 2047)
+        tlo = lo0 + (np.sort(digits[:, sampled.flatten().numpy()], axis=1)[:, -rank] << 17)
+        assert ((bits >= tlo[:, None]).sum(axis=1) < kc).all()

@@ -166,3 +166,71 @@ def test_score_error_does_not_grow_with_the_logits_range(snapkv, nats):
     err = float((sc[0].double() - want).norm() / want.norm())
     print(f"score error at {nats} nats: {err:.2e}")
     assert err < 4.5e-7, err
+
+
+def test_one_cache_per_query_head(snapkv):
+    """The per-query-head form takes its votes from the two passes too, one row per query head."""
+    w = work(18440, 4, 32, Hkv=2)
+    case = workloads.generate(w, device="cuda")
+    q, k, v = case["q_win"], case["k"], case["v"]
+    ok = torch.zeros((w.Hq, w.C, w.D), dtype=k.dtype, device="cuda")
+    ov = torch.zeros_like(ok)
+    oi = torch.full((w.Hq, w.C), -1, dtype=torch.int32, device="cuda")
+    kept = snapkv.snapkv_compress_per_query_head(q, k, v, w.pool_kind, w.p, w.C, ok, ov, oi)
+    kr, vr = (t.repeat_interleave(w.Hq // w.Hkv, dim=0).contiguous() for t in (k, v))
+    sc = torch.empty((w.Hq, w.n), device="cuda")
+    snapkv.snapkv_pooled_scores(q, kr, w.pool_kind, w.p, sc)          # (scores of another kernel: the band decides)
+    torch.cuda.synchronize()
+    check_against_oracle(q, kr, vr, w.pool_kind, w.p, w.C, sc.cpu().numpy(), ok, ov, oi.cpu().numpy(), kept,
+                         own_topk_exact=False)
+
+
+def test_callers_scratch_static_scratch_and_replay_equal_own_scratch(snapkv):
+    """On a caller's workspace, on the static scratch and replayed from a graph the first pass clears what the selection
+    expects to be zero: with scratch full of ones beforehand, and whatever the call before left in it, every call is
+    bit for bit the own-scratch call."""
+    w = work(18433, 4, 32)
+    cases = [workloads.generate(w, layer=l, device="cuda") for l in range(3)]
+    want = [run_gpu(snapkv, c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C) for c in cases]
+    q, k, v = (cases[0][n].clone() for n in ("q_win", "k", "v"))
+    ok, ov, oi = (t[0] for t in outputs(w, 1, k.dtype))
+    ws = torch.full((snapkv.snapkv_workspace_bytes(w.L, w.Hq, w.Hkv, w.D, w.W),), 255, dtype=torch.uint8, device="cuda")
+    status = torch.full((1,), -77, dtype=torch.int32, device="cuda")
+    args = (w.pool_kind, w.p, w.C, ok, ov, oi)
+
+    def load(l):
+        for t, n in ((q, "q_win"), (k, "k"), (v, "v")):
+            t.copy_(cases[l][n])
+        ok.zero_(), ov.zero_(), oi.fill_(-1), status.fill_(-77)
+
+    def same(l, what):
+        torch.cuda.synchronize()
+        assert np.array_equal(oi.cpu().numpy(), want[l][3]), (what, l)
+        assert torch.equal(ok, want[l][1]) and torch.equal(ov, want[l][2]), (what, l)
+
+    for l in (0, 1, 2):
+        load(l)
+        snapkv.snapkv_compress(q, k, v, *args, workspace=ws)
+        same(l, "workspace")
+        load(l)
+        snapkv.snapkv_compress_ws_status(q, k, v, *args, ws, status)
+        same(l, "status")
+        assert int(status.item()) == w.C
+        load(l)
+        snapkv.snapkv_compress_static(q, k, v, *args)
+        same(l, "static")
+    graphs = {}
+    for what, call in (("workspace", lambda: snapkv.snapkv_compress_ws_status(q, k, v, *args, ws, status)),
+                       ("static", lambda: snapkv.snapkv_compress_static(q, k, v, *args))):
+        graphs[what] = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graphs[what]):
+            call()
+    for rep in range(6):
+        for what, graph in graphs.items():
+            load(rep % 3)
+            if rep == 3:
+                ws.fill_(255)
+            graph.replay()
+            same(rep % 3, f"{what}, replay {rep}")
+            assert what == "static" or int(status.item()) == w.C
+    assert snapkv.snapkv_sync_timeouts() == 0
