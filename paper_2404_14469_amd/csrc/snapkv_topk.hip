@@ -525,6 +525,10 @@ __global__ __launch_bounds__(512) void pick_bracket(const float* __restrict__ vo
     __shared__ unsigned hist[kSelBins];
     __shared__ unsigned sh_scan[16], sh_out[2];
     const int h = blockIdx.x, tid = threadIdx.x;
+    if (G.n < 4 * kPickSamples) {        // (uniform) too short to sample: every position is a candidate
+        if (tid == 0) S.info[4 * h] = 0u;
+        return;
+    }
     for (int b = tid; b < kSelBins; b += 512) hist[b] = 0u;
     if (tid == 0) sh_out[0] = 0u;
     __syncthreads();
@@ -822,17 +826,21 @@ static hipError_t pool_pick(const ScoreGeom& G, const float* vote, int pool_kind
 // what is spent is a workgroup per head that passes over its candidates (a little more than kcount) several times, 512
 // heads at a time, a wave per chunk of 4096 positions.  In nanoseconds, fitted to 800 measured shapes of 4 to 2048 heads
 // and 8200 to 16000000 positions so that this path is not taken where it is slower; in doubt (a quarter and more of the
-// positions kept) the separate kernels are.  Prompts too short to be sampled, whose positions are all candidates, do not come
-// here.  Microseconds of pooling and selection, this path / the separate kernels (max pooling, p = 5), at kcount = 1008,
-// n / 8 and n / 2:
-//   1024 heads of 8200: 75 / 99, 76 / 99, 140 / 101;  31336: 104 / 196, 135 / 199, 277 / 205;  131072: 238 / 660,
-//   387 / 676, 983 / 700;   512 heads of 20000: 53 / 91, 60 / 92, 112 / 95;   32 heads of 380000: 57 / 87, 120 / 99,
-//   363 / 146;   8 heads of 1000000: 77 / 69, 234 / 103;   1024 heads in groups of four, 31336: 223 / 268, 252 / 271,
-//   365 / 279;   without a sample, 1024 heads of 2000: 87 / 66;  4096: 141 / 76;  7984: 221 / 104
+// positions kept) the separate kernels are.  Of prompts too short to be sampled, whose positions are all candidates, only
+// the shortest come here.  Microseconds of pooling and selection, this path / the separate kernels (max pooling, p = 5),
+// at kcount = 1008, n / 8 and n / 2:
+//   1024 heads of 8200: 75 / 99, 76 / 99, 140 / 101;  31336: 104 / 196, 135 / 199, 277 / 205;
+//   131072: 238 / 660, 387 / 676, 983 / 700;
+//   512 heads of 20000: 53 / 91, 60 / 92, 112 / 95;  32 heads of 380000: 57 / 87, 120 / 99, 363 / 146;
+//   8 heads of 1000000: 77 / 69, 234 / 103;  1024 heads in groups of four, 31336: 223 / 268, 252 / 271, 365 / 279;
+// without a sample:
+//   512 heads of 200: 29 / 38;  1000: 37 / 40;  2000: 50 / 43;
+//   1024 heads of 200: 46 / 57;  600: 54 / 58;  1000: 61 / 60;  2000: 87 / 67;  4096: 141 / 76;  7984: 221 / 104
 bool pool_pick_ok(const ScoreGeom& G, int p, int64_t kcount) {
-    if (!((p == 1 || p == 5 || p == 7 || p == 13) && G.n >= 4 * kPickSamples && kcount >= 1 && kcount <= G.n && (G.vpitch & 3) == 0 &&
+    if (!((p == 1 || p == 5 || p == 7 || p == 13) && G.n >= 1 && kcount >= 1 && kcount <= G.n && (G.vpitch & 3) == 0 &&
           select_chunked_ok(G.n) && G.Hkv <= 65535))
         return false;
+    if (G.n < 4 * kPickSamples) return G.n <= (G.Hkv <= 512 ? 1024 : 600);
     const double heads = G.Hkv, chunks = (double)((G.n + kSelChunk - 1) / kSelChunk);
     const double saved = (G.g == 1 ? 4.4e-3 / (1.0 + heads / 12000.0) : 3.1e-3 / (1.0 + heads / 3600.0)) * heads * (double)G.n;
     const double spent = (double)kcount * (1.9 + 6.7e-3 * heads) * std::max(1.0, 9.0 / chunks) + 180.0 * chunks;

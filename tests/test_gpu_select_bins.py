@@ -86,7 +86,11 @@ def test_many_heads_keep_what_single_calls_keep(snapkv, field, layers, L, Hq, Hk
 
 
 @pytest.mark.parametrize("heads,L,kcount,once", [
-    (1024, 2048, 200, False),     # too short to sample
+    (1024, 616, 100, True),       # too short to sample, but few positions in all
+    (512, 1040, 900, True),
+    (1024, 617, 100, False),
+    (512, 1041, 100, False),
+    (1024, 2048, 200, False),
     (1024, 8191, 200, False),
     (1024, 8208, 500, True),
     (1024, 8208, 6000, False),    # the candidates of a head cost more than the scores of all
