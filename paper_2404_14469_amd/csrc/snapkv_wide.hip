@@ -261,9 +261,16 @@ template <typename T, int D, bool PAGED, int N> struct WideWave {
           w(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)), rg(w % GROUPS), kp(w / GROUPS) {}
 
     __device__ __forceinline__ int64_t round_key(const Cursor& c) const { return ((int64_t)c.sl * c.RPS + c.rd) * kRound; }
+    __device__ __forceinline__ int64_t paged_row(int64_t pg, int in) const {   // ids outside the table: see physical_row
+        pg = pg < 0 ? 0 : (pg >= A.pages ? A.pages - 1 : pg);
+        return pg * A.page + in;
+    }
     __device__ __forceinline__ int64_t row_of(const Cursor& c, int64_t j) const {   // keys past the end: the last row
         j = j < c.L ? j : c.L - 1;
-        if constexpr (PAGED) j = physical_row(A.table, A.page, A.pages, j + A.row0);
+        if constexpr (PAGED) {
+            const unsigned l = (unsigned)(j + A.row0);
+            return paged_row(A.table[l / (unsigned)A.page], (int)(l % (unsigned)A.page));
+        }
         return j;
     }
     __device__ __forceinline__ void load_row(KFrag<D>& f, const Cursor& c, int64_t row) const {
@@ -273,10 +280,10 @@ template <typename T, int D, bool PAGED, int N> struct WideWave {
     }
     __device__ __forceinline__ void ask_page(const Cursor& c) {
         if constexpr (PAGED) {
-            int64_t j = round_key(c) + w * 16 + n16;
-            j = (j < c.L ? j : c.L - 1) + A.row0;
-            page_id = A.table[j / A.page];
-            in_page = (int)(j % A.page);
+            unsigned j = (unsigned)round_key(c) + w * 16 + n16;      // (logical rows are below 2^31)
+            j = (j < (unsigned)c.L ? j : (unsigned)c.L - 1) + (unsigned)A.row0;
+            page_id = A.table[j / (unsigned)A.page];
+            in_page = (int)(j % (unsigned)A.page);
         }
     }
     // This wave's tile of the cursor's round, and the cursor moved on.  Unconditional (see row_of).
@@ -286,9 +293,7 @@ template <typename T, int D, bool PAGED, int N> struct WideWave {
         advance(A, c);
         int64_t row;
         if constexpr (PAGED) {
-            int64_t pg = page_id;
-            pg = pg < 0 ? 0 : (pg >= A.pages ? A.pages - 1 : pg);
-            row = pg * A.page + in_page;
+            row = paged_row(page_id, in_page);
             ask_page(c);
         } else {
             row = row_of(at, round_key(at) + w * 16 + n16);
@@ -740,7 +745,7 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
     int64_t slices = 0;
     for (int i = 0; i < count; ++i) {
         const ScoreGeom& G = *P[i].G;
-        if (G.g != G0.g || G.W != G0.W || G.k_rs != G0.k_rs || G.n <= 0 || G.L >= (int64_t)1 << 31) return hipErrorInvalidValue;
+        if (G.g != G0.g || G.W != G0.W || G.k_rs != G0.k_rs || G.n <= 0 || G.L + G.k_row0 >= (int64_t)1 << 31) return hipErrorInvalidValue;
         WideEntry& E = A.e[i];
         E.q = static_cast<const char*>(P[i].q);
         E.k = static_cast<const char*>(P[i].k);

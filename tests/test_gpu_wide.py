@@ -105,6 +105,28 @@ def test_layouts_layers_and_batches_equal_single_calls(snapkv):
         same(oks[i], ovs[i], ois[i], refs[i], f"batch, prompt {i}")
 
 
+@pytest.mark.parametrize("page", [1, 7, 300])
+def test_page_sizes_equal_the_contiguous_call(snapkv, page):
+    """Pages of one row, of an odd number of rows and longer than a round; an id past the last page is taken for it."""
+    w = work(18450, 4, 32)
+    case = workloads.generate(w, device="cuda")
+    pages = -(-w.L // page)
+    table = torch.randperm(pages, generator=torch.Generator().manual_seed(page)).to(torch.int32).cuda()
+    pos = torch.arange(w.L, device="cuda")
+    paged = []
+    for t in (case["k"], case["v"]):
+        cache = torch.zeros((pages, page, w.Hkv, w.D), dtype=t.dtype, device="cuda")
+        cache[table.long()[pos // page], pos % page] = t.permute(1, 0, 2)
+        paged.append(cache)
+    ids = table.clone()
+    ids[table == pages - 1] = pages + 5                   # clamped to the last page, which is the one it names
+    want = run_gpu(snapkv, case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C)
+    ok, ov, oi = (t[0] for t in outputs(w, 1, case["k"].dtype))
+    snapkv.snapkv_compress_paged(case["q_win"], paged[0], paged[1], ids, w.L, w.pool_kind, w.p, w.C, ok, ov, oi)
+    assert np.array_equal(oi.cpu().numpy(), want[3])
+    assert torch.equal(ok, want[1]) and torch.equal(ov, want[2])
+
+
 @pytest.mark.parametrize("Hkv,L", [(1, 18433), (2, 30011)])
 def test_few_heads_in_layers_and_batches_equal_single_calls(snapkv, Hkv, L):
     """The cut of a prompt into slices follows its own heads, not those of the call: layers, stacked or separate, and the
