@@ -244,8 +244,8 @@ int snapkv_compress_varlen(int dtype, int n_prompts, const void* const* q_win, c
  * tensors, for q_win, k, v, out_k, out_v and out_idx alike) are taken as they lie; layers that are separate
  * allocations are reached through a table of their addresses, up to 32 of them per run of launches (two-byte
  * element types; every prompt length; windows that a single call would not score in 32-row blocks, i.e. of
- * at most 32 rows, or of 33-128 rows that are not a whole number of such blocks).  What fits neither is done
- * one layer after the other inside the call.
+ * at most 32 rows, of 33-128 rows that are not a whole number of such blocks, or of a prompt that takes the two
+ * passes over all window rows).  What fits neither is done one layer after the other inside the call.
  *
  *   n_layers >= 0
  *   q_win, k, v, out_k, out_v, out_idx   HOST arrays of n_layers DEVICE pointers, each as the argument of the
@@ -316,8 +316,8 @@ int64_t snapkv_capacity_for_rate(int64_t L, int W, double rate);
  *           against row h / g), Hq rows for snapkv_compress_per_query_head.
  *   out_counts [Hq, 2] device int32: per query head (important, hits); overwritten.
  *
- * The logits of the call live in the per-device auxiliary buffer the decoding step also uses (hipMalloc
- * on first use and on growth; concurrent calls on one device would race).
+ * The logits of the call live in a per-device buffer of its own (hipMalloc on first use and on growth;
+ * concurrent calls on one device would race).
  */
 int snapkv_hit_rate(int dtype, const void* q_cur, const void* k, int64_t Lk, int64_t n, int Hq, int Hkv, int D,
                     const int32_t* idx, int Hidx, int64_t kcount, int64_t idx_stride, float theta,
@@ -341,9 +341,13 @@ int snapkv_hit_rate(int dtype, const void* q_cur, const void* k, int64_t Lk, int
  *   Hq % Hkv == 0, Hq / Hkv <= 16, D in {64, 128}
  *   out     [B, Hq, D] device float32;  out_lse [B, Hq] device float32 or NULL
  *
- * Partial results of split key ranges live in a per-device buffer of their own that the library
- * allocates on first use and grows when needed (hipMalloc); concurrent calls on different streams
- * of one device would share it and race.  Returns SNAPKV_OK or a negative SNAPKV_ERR_* code.
+ * Steps of at least 1024 rows (S) whose B * Hkv pairs leave a third of the compute units idle are split:
+ * the partial results of their key ranges live in a per-device buffer that the library allocates when
+ * the first such step is called (hipMalloc, 8.5 MB whatever the shape, never moved).  Such steps on different
+ * streams of one device share it and race; other steps use no scratch and are independent.  A step may be
+ * captured into a graph: one captured before that first call is recorded unsplit and stays so for the
+ * graph's life, a split one replays into the buffer, which snapkv_release frees (do not replay it afterwards).
+ * Returns SNAPKV_OK or a negative SNAPKV_ERR_* code.
  */
 int snapkv_decode_attention(int dtype, const void* q, const void* k_cache, const void* v_cache,
                             const int32_t* lens, int B, int Hq, int Hkv, int D, int64_t S, int64_t cap,
@@ -374,14 +378,17 @@ int snapkv_num_stages(void);
 const char* snapkv_stage_name(int stage);
 
 /*
- * Kernel scheme, a bit set (default 0).  Bit 0 clear: prompts whose window logits fit the chip's
- * register files are scored by the single-read kernel (K is streamed once); of a longer prompt that
- * kernel takes the keys that fit and two streaming passes the rest (those keys are streamed twice; the
- * streaming passes hand nothing between workgroups); bit 0 set: always two streaming passes over
- * all keys.  Bit 2 set (test hook): plans of the single-read kernel count 16 workgroups as resident, so
- * that prompts of a few thousand tokens already take the path of the long ones.  Bit 1 clear:
- * pooling and top-k selection run as one cooperative launch where a head's scores fit the
- * resident workgroups, otherwise as separate kernels; bit 1 set: always the separate kernels.
+ * Kernel scheme, a bit set (default 0).  Bit 0 clear: prompts whose KV heads are met by 128 or more window
+ * rows, in a two-byte type and long enough, are scored by two passes over K that meet all those rows at once;
+ * other prompts whose window logits fit the chip's register files by the single-read kernel (K is
+ * streamed once); of a longer prompt that kernel takes the keys that fit and two streaming passes the rest
+ * (those keys are streamed twice; the streaming passes hand nothing between workgroups).  Bit 0 set: always
+ * two streaming passes over all keys.  Bit 2 set (test hook): plans of the single-read kernel count 16
+ * workgroups as resident, so that prompts of a few thousand tokens already take the path of the long ones,
+ * and no prompt takes the two passes over all window rows.  Bit 1 clear: pooling and top-k selection run as
+ * one cooperative launch where the scores of all heads fit the resident workgroups, otherwise as three
+ * kernels that read the votes once where that is the faster form, otherwise as kernels that store the
+ * scores; bit 1 set: always the last.
  * All schemes give the scores of Eq. 1 to within rounding, and the selection of Eq. 2 exactly
  * for the scores they computed; the setting is process-wide and meant for tests and measurements.
  */
@@ -404,7 +411,8 @@ int64_t snapkv_sync_timeouts(void);
  */
 int snapkv_debug_set_wait_limit(long long polls);
 
-/* Frees the library's per-device scratch buffers (synchronises each device that has one). */
+/* Frees the library's per-device scratch buffers (synchronises each device that has one).  A captured decoding step that was
+ * split replays into one of them: destroy such graphs first. */
 void snapkv_release(void);
 
 #ifdef __cplusplus

@@ -6,7 +6,7 @@
 // Work split.  A workgroup of four waves owns a range of keys of one (sequence, KV head) and all
 // g query heads that read it; a wave walks its keys 32 at a time (two 16-key tiles X and Y).
 // With few (sequence, head) pairs the keys of a pair are split over several workgroups, which
-// leave (max, sum, unnormalised output) partials that a second small kernel merges.
+// leave (max, sum, unnormalised output) partials that a second small kernel merges (see decode_splits).
 //
 // MFMA layout (16x16x32, 64 lanes): lane l supplies row/column l%16 and contraction slice l/16
 // (eight elements); accumulator register r of lane l is row 4*(l/16) + r, column l%16.
@@ -103,7 +103,7 @@ struct DecodeArgs {
     float2* part_ml;      // [B, Hq, nsplit]
 };
 
-constexpr int kDecWaves = 4;   // four or eight waves measure the same; four keeps short caches unsplit
+constexpr int kDecWaves = 4;   // (eight measure the same)
 
 template <typename T, int D>
 __global__ __launch_bounds__(kDecWaves * 64) void decode_attn(const DecodeArgs A) {

@@ -20,13 +20,13 @@
 //     the call) in order, a contiguous run of whole slices each; a launch whose slices all find a place at once
 //     has a workgroup per slice.
 //
-// What bounds it: matrix and vector instructions of a SIMD hardly overlap on this part (16x16x32 MFMAs and
-// multiply-adds measured together take 0.9 of the sum of both), so a pass costs their sum: 16 + 15 cycles per 64
-// logits and about 10 of overhead, 320 us for the 1.03e9 logits of 32 grouped-query layers of 31337 keys, against
-// 340 us that 2.05 GB of keys take at 6.1 TB/s; together 415 us (wide_stats) and 488 us (wide_votes) where the
-// single-read kernel took 1218 us.  Tried on the way: all 128 rows in one wave with Q in LDS (two waves per SIMD,
-// 425 + 512 us, and 240 registers); the rows' references from row maxima (a longer prologue: 24 against 19 us per
-// pass at 28471 keys, 8 heads).  At 131072 keys, W = 64 (two blocks per head): 95 + 106 us against 277 us.
+// What bounds it: matrix and vector instructions of a SIMD hardly overlap here, so a pass costs about their sum.  Counters
+// (profiles/sq_counters_gqa_two_pass.txt; 32 layers of 32/8 heads of 32768 keys, 1.07e9 logits): of the 781 thousand
+// cycles of wide_stats a SIMD's matrix unit is busy for 263 (16 a 64 logits) and its vector instructions take 436; of the
+// 992 of wide_votes 262 and 443.  That is 411 and 480 us, where 2.15 GB of keys take 350 us at 6.1 TB/s, and the
+// single-read kernel took 1218 us (31337 keys; the two passes 430 and 492 us there).  Tried on the way: all 128 rows in one
+// wave with Q in LDS (two waves per SIMD, 425 + 512 us, and 240 registers).  At 131072 keys, W = 64 (two blocks per
+// head): 97 + 103 us against 277 us.
 //
 // The row reference.  Exponentials are taken relative to a reference of the row that is known before its keys are: its
 // largest logit among the prompt's first four keys.  The argument s - ref is rounded to fp32, so the terms that matter
