@@ -142,7 +142,8 @@ template <int N> struct WideArgs {   // N: 1 or kMaxWide (a single prompt's laun
     const int32_t* table;            // paged K (one entry only): see ScoreGeom
     int page;
     int64_t pages, row0;
-    unsigned rounds;                 // of all entries
+    unsigned rounds;                 // of all entries: each workgroup's share is share rounds, one more for the first `more`
+    unsigned share, more;
     unsigned* zeros;                 // words the selection expects to be zero (see WideClear); null: none
     int64_t nzeros;
     unsigned* flag;
@@ -176,9 +177,9 @@ template <int N> __device__ __forceinline__ unsigned slice_start(const WideArgs<
     const unsigned in = r - A.e[e].round_begin, rps = (unsigned)A.e[e].RPS;
     return A.e[e].round_begin + (in + rps - 1) / rps * rps;
 }
-// The workgroup's stretch of rounds: equal shares, moved to the next slice's start.
+// Where the workgroup's stretch of rounds begins: equal shares, moved to the next slice's start.
 template <int N> __device__ __forceinline__ unsigned share(const WideArgs<N>& A, unsigned wg) {
-    return slice_start(A, (unsigned)((uint64_t)A.rounds * wg / gridDim.x));
+    return slice_start(A, A.share * wg + (wg < A.more ? wg : A.more));
 }
 
 template <int N> __device__ __forceinline__ Cursor cursor_at(const WideArgs<N>& A, unsigned r) {
@@ -681,7 +682,7 @@ hipError_t launch_both(const WideArgs<kMaxWide>& all, dim3 grid, hipStream_t st)
     WideArgs<N> A;
     A.count = all.count, A.direct = all.direct, A.g = all.g, A.W = all.W, A.UH = all.UH, A.hb = all.hb, A.nblk = all.nblk, A.inv_uh = all.inv_uh;
     A.c2 = all.c2, A.k_rs = all.k_rs, A.table = all.table, A.page = all.page, A.pages = all.pages, A.row0 = all.row0;
-    A.rounds = all.rounds, A.zeros = all.zeros, A.nzeros = all.nzeros, A.flag = all.flag;
+    A.rounds = all.rounds, A.share = all.share, A.more = all.more, A.zeros = all.zeros, A.nzeros = all.nzeros, A.flag = all.flag;
     for (int i = 0; i < N; ++i) A.e[i] = all.e[i];
     hipLaunchKernelGGL((wide_stats<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
     hipLaunchKernelGGL((wide_votes<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
@@ -767,6 +768,8 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
     const int64_t places = 2 * wide_cus();   // two workgroups per compute unit
     A.direct = count == 1 && slices <= places;
     const dim3 grid = A.direct ? dim3((unsigned)A.e[0].NS, (unsigned)b.nblk, (unsigned)G0.Hkv) : dim3((unsigned)std::min(slices, places));
+    A.share = A.rounds / grid.x;         // (of a launch with a grid of one dimension)
+    A.more = A.rounds % grid.x;
     if (dtype == 0) return D == 128 ? by_entries<w_bf16, 128>(A, grid, st) : by_entries<w_bf16, 64>(A, grid, st);
     return D == 128 ? by_entries<w_f16, 128>(A, grid, st) : by_entries<w_f16, 64>(A, grid, st);
 }
