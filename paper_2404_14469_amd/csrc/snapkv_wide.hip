@@ -433,7 +433,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
         for (int i = 0; i < kWaveRows; ++i)
 #pragma unroll
             for (int r = 0; r < 4; ++r) top = fmaxf(top, y[i][r]);
-        if (__builtin_expect(__any(top > kRaiseAt), 0)) {   // some row's logits lie far above its reference: first their maxima, then the sums again
+        if (__any(top > kRaiseAt)) {     // some row's logits lie far above its reference: first their maxima, then the sums again
             raised = true;
             auto each = [&](auto f2) __attribute__((always_inline)) {
 #pragma clang loop unroll(disable)
