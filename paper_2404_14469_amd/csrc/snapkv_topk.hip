@@ -35,6 +35,8 @@ constexpr int kPsLevels = 4;           //   levels: the fixed first digit, then 
 constexpr int kPsHistWords = 2 * (int)kPsBins0 + 2 * kPsBins;
 constexpr int kPsStages = 8;           //   rendezvous points per head: levels, final
 constexpr int kPsMaxGroup = 512;       //   workgroups per head at most
+constexpr int kPsSlots = 64;           //   words of a workgroup in the exchange of candidates (half of them where its
+constexpr int kPsSlotWords = (kPsHistWords - (int)kPsBins0) / 2;   //   head's share of the scratch holds no more)
 
 __device__ __forceinline__ int range_shift(unsigned range) {
     // smallest shift with (range >> shift) < kSelBins1
@@ -48,18 +50,24 @@ __device__ __forceinline__ int range_shift_bits(unsigned range, int digit_bits) 
     return bits > digit_bits ? bits - digit_bits : 0;
 }
 
+// Inclusive prefix sum over a wave (all lanes active): six additions on permuted operands, no LDS.
+__device__ __forceinline__ unsigned wave_inclusive_scan(unsigned v) {
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8: within 16 lanes
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast 15: rows 0 and 2 into 1 and 3
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast 31: the lower half into the upper
+    return v;
+}
+
 // Exclusive prefix sum over the block (NT threads, NT a multiple of 64, at most 1024); returns
-// the sum of the values of lower thread ids, *total gets the block total.  sh needs 16 words.
+// the sum of the values of lower thread ids, *total gets the block total.  sh needs 16 words, which no
+// wave may still read from an earlier call.
 template <int NT>
-__device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned* sh, unsigned* total) {
+__device__ __forceinline__ unsigned block_exclusive_scan_once(unsigned v, unsigned* sh, unsigned* total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned up = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += up;
-    }
-    __syncthreads();                      // sh may still be read from an earlier call
+    const unsigned incl = wave_inclusive_scan(v);
     if (lane == 63) sh[wave] = incl;
     __syncthreads();
     unsigned base = 0, tot = 0;
@@ -71,6 +79,11 @@ __device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned* s
     }
     if (total) *total = tot;
     return base + incl - v;
+}
+template <int NT>
+__device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned* sh, unsigned* total) {
+    __syncthreads();                      // sh may still be read from an earlier call
+    return block_exclusive_scan_once<NT>(v, sh, total);
 }
 
 // Walking the bins of hist[0..NBINS) from the top, find the bin where the running count first
@@ -862,21 +875,28 @@ hipError_t launch_pool_pick(const ScoreGeom& G, const float* vote, int pool_kind
 // Pooling (Sec. 4.3), group sum and top-k selection (Eq. 2) in ONE cooperative launch.
 //
 // The Wh workgroups of a KV head each pool a contiguous chunk of the head's votes straight into
-// registers (the pooled scores are never written to memory), then agree on the threshold through
-// rendezvous points in global memory: a digit histogram (one is enough unless its threshold bin
-// holds more positions than the candidate list), and the few positions inside the threshold
-// bin (or, when the bin is a single value, only their number).  Every workgroup then knows the threshold T, how
+// registers (the pooled scores are never written to memory), then agree on the threshold through two
+// exchanges in global memory that need no arrival counters:
+//   * a digit histogram with fixed bins.  Every workgroup adds its own and reads the sum until the bins hold as many
+//     positions as the head has: then everybody's additions are in it.
+//   * the few positions inside the threshold bin, and how many lie above it, per workgroup: 32 or 64 words each that
+//     are zero until they are written and never zero afterwards, polled by the workgroups that need them.
+// Where the threshold bin holds more positions than a workgroup's words or the candidate list (thousands of nearly
+// equal scores), or a head has more than 80 workgroups, the general way is taken: further digits, and counter, then
+// data, at rendezvous points.  Every workgroup then knows the threshold T, how
 // many positions equal to T are kept, and how many kept positions lie before its chunk, and emits
 // its own kept positions in order.  The arithmetic of the pooled score is that of pool_group, in
 // the same order, so the scores are bit-identical to snapkv_pooled_scores; everything after it is
 // integer work on bit patterns and does not depend on timing.
 //
-// Bound by its chain of dependent steps, not by bytes.  Steps it no longer has, in microseconds before and after: the
-// exchange of the head's range (the first digit is fixed), a memory latency and a barrier per query head of a
+// Bound by its chain of dependent steps, not by bytes: with the two exchanges at rendezvous points (hand over and wait,
+// barrier, count in, poll the counter, read the data: 2.4 and 6 us of 21 at 28471 positions) and prefix sums through
+// LDS permutes a call of 512 keys, fp32, 4 heads took 28.7 us, now 26.0; 16384 keys, 32 heads 58.1, now 52.8; 28471 keys,
+// 32/8 heads 64.6, now 57.5; 13339 paged keys 42.0, now 37.2; 131072 keys, W = 64 213.1, now 206.5.  Steps it
+// lost before: the exchange of the head's range (the first digit is fixed), a memory latency and a barrier per query head of a
 // group (the next head's votes are fetched ahead, two staging areas), element-wise loads where the prefix is no
 // multiple of four (rows are padded), digit rounds over at most 128 candidates, and for a head with one workgroup
-// every exchange: 512 keys 17.3 -> 9.2, 16384 keys (32 heads) 21.0 -> 16.5, 28471 keys (8 heads of a group of 4)
-// 26.3 -> 21.4, 13339 paged keys 22.5 -> 17.3, eight prompts of up to 64K keys 50.8 -> 41.0.
+// every exchange.
 //
 // All workgroups of the grid must be resident at once (checked by the host).  Waits are bounded:
 // if one gives up, later ones are skipped, a counter is raised and the kernel still ends.
@@ -955,31 +975,11 @@ __device__ __forceinline__ void group_rendezvous(unsigned* ctr, unsigned expect,
     __syncthreads();
 }
 
-// Sums of up to three values over the block, one barrier pair for all of them; every thread gets
-// the totals.  sh needs 3 * NT / 64 words and may be reused right after the call returns.
-template <int NT>
-__device__ __forceinline__ void block_sum3(unsigned& a, unsigned& b, unsigned& c, unsigned* sh) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        a += __shfl_xor(a, d, 64);
-        b += __shfl_xor(b, d, 64);
-        c += __shfl_xor(c, d, 64);
-    }
-    __syncthreads();
-    if (lane == 0) {
-        sh[wave] = a;
-        sh[NT / 64 + wave] = b;
-        sh[2 * (NT / 64) + wave] = c;
-    }
-    __syncthreads();
-    a = b = c = 0u;
-#pragma unroll
-    for (int w2 = 0; w2 < NT / 64; ++w2) {
-        a += sh[w2];
-        b += sh[NT / 64 + w2];
-        c += sh[2 * (NT / 64) + w2];
-    }
+// Sum over eight neighbouring lanes, in all of them.
+__device__ __forceinline__ unsigned octet_sum(unsigned v) {
+    v += (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);    // quad_perm 1,0,3,2
+    v += (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);    // quad_perm 2,3,0,1
+    return v + (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true);   // row_half_mirror
 }
 
 template <int EPT, int P, int KIND>   // KIND: 0 max pooling, 1 average pooling
@@ -998,7 +998,11 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
     unsigned* const sh_hist = ps_lds;
     uint2* const sh_cand = reinterpret_cast<uint2*>(ps_lds + kPsBins);
     __shared__ unsigned sh_tab[2][(EPT / 4) * NWV]; // per (run row, wave) counts for the ordered emission
-    __shared__ unsigned sh_scan[16], sh_out[2], sh_red[3 * NWV], sh_gave_up, sh_bin_count;
+    __shared__ unsigned sh_first[kPsBins0];         // first digit's histogram
+    __shared__ unsigned long long sh_slot[kPsSlots];   // the workgroup's own words of the exchange (see below)
+    __shared__ unsigned sh_scan[2][16], sh_out[2], sh_gave_up, sh_bin_count;
+    enum { kAbove, kInside, kBefore, kListed, kSpilt, kGreater, kEqual, kTallies };
+    __shared__ unsigned sh_n[kTallies];             // counts of the exchange and the emission, all zero at first
     __shared__ unsigned sh_off[kPsMaxGroup + 1];    // start of each workgroup's candidates in the merged list
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h = blockIdx.x / Wh, c = blockIdx.x % Wh;
@@ -1018,7 +1022,15 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
     if (c == 0)   // window positions follow the selected prefix positions
         for (int t = tid; t < W_tail; t += NT) out[kcount + t] = (int32_t)(n + t);
     if (kcount <= 0) return;
-    if (tid == 0) sh_gave_up = 0u;
+    // (the barriers of the pooling below come before any use of these)
+    sh_first[tid] = 0u;
+    if (tid < kTallies) sh_n[tid] = 0u;
+    if (tid == 0) {
+        sh_gave_up = 0u;
+        sh_out[0] = 0u;
+        sh_out[1] = 1u;
+        sh_bin_count = 0u;
+    }
 
     // ---- pooled, group-summed scores of this thread's positions, in the arithmetic and order of
     // pool_group.  A thread owns EPT / 4 runs of four consecutive positions: element e = 4 * e4 + k
@@ -1200,12 +1212,62 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
     const unsigned lo0 = __float_as_uint((float)(G.g * G.W) / (float)(nn > 0 ? nn : 1) * 0x1p-6f);
     auto first_digit = [&](unsigned v) { return v < lo0 ? 0u : ((v - lo0) >> kFirstShift < kPsBins0 ? (v - lo0) >> kFirstShift : kPsBins0 - 1); };
     unsigned cur_lo = 0, krem = (unsigned)kcount, above = 0, bin_count = 0, T = 0, need_eq = 0;
-    int cur_sh = kFirstShift;
+    int cur_sh = 0;
     int rem_bits = 0;           // bits that tell the patterns of the threshold bin apart
     bool exact = false;         // T is known exactly (all remaining positions are equal to it)
-    for (int lvl = 0; lvl < kPsLevels && !exact; ++lvl) {
-        auto digit = [&](unsigned v) { return lvl == 0 ? first_digit(v) : ((v - cur_lo) >> cur_sh) & (kPsBins - 1); };
-        const unsigned nbins = lvl == 0 || lvl == 3 ? kPsBins0 : kPsBins;
+    unsigned polls = spin_limit;   // that a wait may make
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+        if (active >> e & 1u) atomicAdd(&sh_first[first_digit(x[e])], 1u);
+    __syncthreads();
+    {
+        static_assert(kPsBins0 == NT, "a thread has one bin of the first digit");
+        unsigned cnt = sh_first[kPsBins0 - 1 - tid], before, total;   // bins from the top
+        if (solo) {
+            before = block_exclusive_scan_once<NT>(cnt, sh_scan[0], nullptr);
+        } else {
+            // Added to the head's histogram, which is complete when its bins sum up to the head's positions: every
+            // position is in one bin and a bin only grows, so nobody is told that the others have arrived.
+            unsigned* const bin = S.ps_hist + (int64_t)h * kPsHistWords + (kPsBins0 - 1 - tid);
+            if (cnt) (void)__hip_atomic_fetch_add(bin, cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (unsigned spins = 0;;) {
+                cnt = coherent_load(bin);
+                before = block_exclusive_scan_once<NT>(cnt, sh_scan[spins & 1], &total);
+                if (total == (unsigned)nn) break;
+                if (++spins > polls) {
+                    if (tid == 0) sh_gave_up = 1u;
+                    break;
+                }
+            }
+        }
+        if (before < krem && krem <= before + cnt) {
+            sh_out[0] = (unsigned)(kPsBins0 - 1 - tid);
+            sh_out[1] = krem - before;
+            sh_bin_count = cnt;
+        }
+        __syncthreads();
+        const unsigned b1 = sh_out[0] & (kPsBins0 - 1);
+        krem = sh_out[1];
+        bin_count = sh_bin_count;
+        if (sh_gave_up) polls = 0;
+#pragma unroll
+        for (int e = 0; e < EPT; ++e)
+            if (active >> e & 1u) {
+                const unsigned d = first_digit(x[e]);
+                if (d > b1) ++above;
+                if (d != b1) active &= ~(1u << e);
+            }
+        unsigned last = (1u << kFirstShift) - 1u;   // the bin's patterns: cur_lo .. cur_lo + last
+        cur_lo = b1 == 0 ? 0u : lo0 + (b1 << kFirstShift);
+        if (b1 == 0) last = lo0 + last;
+        else if (b1 == kPsBins0 - 1) last = 0xFFFFFFFFu - cur_lo;
+        cur_sh = range_shift_bits(last, kPsBinBits);
+        rem_bits = 32 - __clz(last);
+    }
+    const bool first_is_enough = bin_count <= (unsigned)kPsCandCap;
+    for (int lvl = 1; lvl < kPsLevels && !exact && !first_is_enough; ++lvl) {
+        auto digit = [&](unsigned v) { return ((v - cur_lo) >> cur_sh) & (kPsBins - 1); };
+        const unsigned nbins = lvl == 3 ? kPsBins0 : kPsBins;
         __syncthreads();
         for (int b = tid; b < kPsBins; b += NT) sh_hist[b] = 0u;
         if (tid == 0) {
@@ -1223,21 +1285,21 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
             load_bins_from_top<NT, kPsBins>(sh_hist, bins);
         } else {
             // a head's histograms: 1024, 2048, 2048 and 1024 bins
-            unsigned* gh = S.ps_hist + (int64_t)h * kPsHistWords + (lvl == 0 ? 0 : kPsBins0 + (lvl - 1) * kPsBins);
+            unsigned* gh = S.ps_hist + (int64_t)h * kPsHistWords + kPsBins0 + (lvl - 1) * kPsBins;
             unsigned done = 0;
             for (unsigned b = tid; b < nbins; b += NT) {
                 const unsigned cnt = sh_hist[b];
                 if (cnt) done ^= coherent_add(&gh[b], cnt);
             }
             hand_over_done(done);
-            group_rendezvous(arrive + lvl, (unsigned)Wh, spin_limit, &sh_gave_up);
+            group_rendezvous(arrive + lvl, (unsigned)Wh, polls, &sh_gave_up);
 #pragma unroll
             for (int e = 0; e < kPsBins / NT; ++e) {
                 const unsigned b = kPsBins - 1 - (tid * (kPsBins / NT) + e);
                 bins[e] = b < nbins ? coherent_load(&gh[b]) : 0u;
             }
         }
-        find_bin_from_top<NT, kPsBins>(bins, krem, sh_scan, sh_out, &sh_bin_count);
+        find_bin_from_top<NT, kPsBins>(bins, krem, sh_scan[0], sh_out, &sh_bin_count);
         const unsigned b1 = sh_out[0] & (kPsBins - 1);
         krem = sh_out[1];
         bin_count = sh_bin_count;
@@ -1248,14 +1310,8 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
                 if (d > b1) ++above;
                 if (d != b1) active &= ~(1u << e);
             }
-        unsigned last = (1u << cur_sh) - 1u;   // the bin's patterns: cur_lo .. cur_lo + last
-        if (lvl == 0) {
-            cur_lo = b1 == 0 ? 0u : lo0 + (b1 << kFirstShift);
-            if (b1 == 0) last = lo0 + last;
-            else if (b1 == kPsBins0 - 1) last = 0xFFFFFFFFu - cur_lo;
-        } else {
-            cur_lo += b1 << cur_sh;
-        }
+        const unsigned last = (1u << cur_sh) - 1u;   // the bin's patterns: cur_lo .. cur_lo + last
+        cur_lo += b1 << cur_sh;
         if (last == 0) {
             exact = true;
             T = cur_lo;
@@ -1268,39 +1324,99 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
         }
     }
 
-    // ---- final exchange: counts per workgroup, and the candidates unless T is already exact
-    const unsigned mine_in = (unsigned)__popc(active);
-    unsigned in_total = 0;
-    const unsigned in_before = block_exclusive_scan<NT>(mine_in, sh_scan, &in_total);
-    unsigned above_total = above, z1 = 0, z2 = 0;
-    block_sum3<NT>(above_total, z1, z2, sh_red);
-    if (!exact) {   // this workgroup's candidates go to the start of its own stretch of the head's list
-        unsigned slot = in_before, done = 0;
-        unsigned long long* const my_cand = reinterpret_cast<unsigned long long*>(S.cand + (int64_t)h * list + chunk0);
+    // ---- final exchange: the positions above the threshold bin before this chunk, and the candidates unless T is
+    // already exact
+    unsigned gt_before = 0, eq_before = 0;
+    const unsigned m = bin_count < (unsigned)kPsCandCap ? bin_count : (unsigned)kPsCandCap;
+    bool listed = false;                // the head's candidates are in sh_cand (in any order)
+    if (solo) {
+        listed = true;
+        if (!exact) {
+#pragma unroll
+            for (int e = 0; e < EPT; ++e)
+                if (active >> e & 1u) {
+                    const unsigned at = atomicAdd(&sh_n[kListed], 1u);
+                    if (at < (unsigned)kPsCandCap) sh_cand[at] = make_uint2(x[e], (unsigned)((int)chunk0 + pos_local(e)));
+                }
+            __syncthreads();
+        }
+    }
+    // A few words per workgroup that validate themselves (none is zero, zero is what the scratch holds before): its
+    // counts, then its candidates, then "none".  They lie where the later levels' histograms, which this head
+    // does not use, would; a workgroup with more candidates than words says so and the head goes the general way.
+    const int slots = Wh * kPsSlots <= kPsSlotWords ? kPsSlots : (Wh * (kPsSlots / 2) <= kPsSlotWords ? kPsSlots / 2 : 0);
+    if (!solo && first_is_enough && slots > 0) {
+        unsigned long long* const words = reinterpret_cast<unsigned long long*>(S.ps_hist + (int64_t)h * kPsHistWords + kPsBins0);
+        auto word = [](unsigned hi, unsigned lo) { return (unsigned long long)hi << 32 | lo; };
+        constexpr unsigned kNone = 0xFFFFFFFFu;
+        unsigned wave_above = 0;
+#pragma unroll
+        for (int bit = 0; bit < (EPT <= 4 ? 3 : 5); ++bit) wave_above += (unsigned)__popcll(__ballot(above >> bit & 1u)) << bit;
+        if (lane == 0 && wave_above) atomicAdd(&sh_n[kAbove], wave_above);
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
             if (active >> e & 1u) {
-                if (solo) {
-                    if (slot < (unsigned)kPsCandCap) sh_cand[slot] = make_uint2(x[e], (unsigned)((int)chunk0 + pos_local(e)));
-                } else if (slot < (unsigned)len)
-                    done ^= coherent_store64(my_cand + slot,
-                                             ((unsigned long long)(unsigned)((int)chunk0 + pos_local(e)) << 32) | x[e]);
-                ++slot;
+                const unsigned at = atomicAdd(&sh_n[kInside], 1u) + 1;
+                if (at < (unsigned)slots) sh_slot[at] = word((unsigned)((int)chunk0 + pos_local(e)) + 1u, x[e]);
             }
-        if (!solo) hand_over_done(done);
+        __syncthreads();
+        if (tid < slots) {
+            const unsigned inside = sh_n[kInside];
+            const unsigned long long mine = tid == 0 ? word(inside + 1u, sh_n[kAbove]) : ((unsigned)tid <= inside ? sh_slot[tid] : word(kNone, 0u));
+            __hip_atomic_store(words + c * slots + tid, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        for (int base = 0; base < Wh * slots; base += NT) {
+            const int i = base + tid;
+            const bool due = i < Wh * slots;
+            unsigned long long got = 0;
+            for (unsigned spins = 0;;) {
+                if (due && got == 0) got = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!__any(due && got == 0) || ++spins > polls) break;
+            }
+            const unsigned hi = (unsigned)(got >> 32), lo = (unsigned)got;
+            if (due && got == 0) {
+                sh_gave_up = 1u;
+            } else if (due && (i & (slots - 1)) == 0) {
+                if (i < c * slots && lo) atomicAdd(&sh_n[kBefore], lo);
+                if (hi > (unsigned)slots) sh_n[kSpilt] = 1u;
+            } else if (due && hi != kNone) {
+                const unsigned at = atomicAdd(&sh_n[kListed], 1u);
+                if (at < (unsigned)kPsCandCap) sh_cand[at] = make_uint2(lo, hi - 1u);
+            }
+        }
+        __syncthreads();
+        listed = sh_n[kSpilt] == 0u;
+        if (listed) gt_before = sh_n[kBefore];
+        if (sh_gave_up) polls = 0;
     }
-    if (tid == 0 && !solo) {
-        unsigned done = coherent_store(&S.ps_part[2 * ((int64_t)h * kPsMaxGroup + c)], above_total);
-        done ^= coherent_store(&S.ps_part[2 * ((int64_t)h * kPsMaxGroup + c) + 1], in_total);
-        hand_over_done(done);
-    }
-    if (!solo) group_rendezvous(arrive + kPsLevels, (unsigned)Wh, spin_limit, &sh_gave_up);
+    if (!listed) {
+        const unsigned mine_in = (unsigned)__popc(active);
+        unsigned in_total = 0, above_total = 0;
+        const unsigned in_before = block_exclusive_scan<NT>(mine_in, sh_scan[0], &in_total);
+        block_exclusive_scan<NT>(above, sh_scan[1], &above_total);
+        if (!exact) {   // this workgroup's candidates go to the start of its own stretch of the head's list
+            unsigned slot = in_before, done = 0;
+            unsigned long long* const my_cand = reinterpret_cast<unsigned long long*>(S.cand + (int64_t)h * list + chunk0);
+#pragma unroll
+            for (int e = 0; e < EPT; ++e)
+                if (active >> e & 1u) {
+                    if (slot < (unsigned)len)
+                        done ^= coherent_store64(my_cand + slot,
+                                                 ((unsigned long long)(unsigned)((int)chunk0 + pos_local(e)) << 32) | x[e]);
+                    ++slot;
+                }
+            hand_over_done(done);
+        }
+        if (tid == 0) {
+            unsigned done = coherent_store(&S.ps_part[2 * ((int64_t)h * kPsMaxGroup + c)], above_total);
+            done ^= coherent_store(&S.ps_part[2 * ((int64_t)h * kPsMaxGroup + c) + 1], in_total);
+            hand_over_done(done);
+        }
+        group_rendezvous(arrive + kPsLevels, (unsigned)Wh, polls, &sh_gave_up);
 
-    // kept positions of the head before this chunk.  Every wave sums the per-workgroup counts
-    // itself (no barrier); without an exact T the candidates are fetched, workgroup by workgroup.
-    unsigned gt_before = 0, eq_before = 0;
-    if (!solo) {
-        unsigned run = 0;           // candidates of the workgroups before `base`
+        // Every wave sums the per-workgroup counts itself (no barrier); without an exact T the candidates are
+        // fetched, workgroup by workgroup.
+        unsigned run = 0;               // candidates of the workgroups before `base`
         for (int base = 0; base < Wh; base += 64) {
             const int i = base + lane;
             unsigned ab = 0, cnt = 0;
@@ -1313,56 +1429,52 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
                 eq_before += cnt;
             }
             if (!exact && wave == 0) {   // where each workgroup's candidates start in the merged list
-                unsigned inc = cnt;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const unsigned up = __shfl_up(inc, d, 64);
-                    if (lane >= d) inc += up;
-                }
+                const unsigned inc = wave_inclusive_scan(cnt);
                 if (i < Wh) sh_off[i] = run + inc - cnt;
                 run += __shfl(inc, 63, 64);
             }
         }
         if (!exact && wave == 0 && lane == 0) sh_off[Wh] = run;
-    }
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        gt_before += __shfl_xor(gt_before, d, 64);
-        eq_before += __shfl_xor(eq_before, d, 64);
+        for (int d = 32; d >= 1; d >>= 1) {
+            gt_before += __shfl_xor(gt_before, d, 64);
+            eq_before += __shfl_xor(eq_before, d, 64);
+        }
+        if (!exact) {
+            __syncthreads();
+            for (unsigned i = tid; i < m; i += NT) {
+                int a2 = 0, b2 = Wh;            // largest c2 with sh_off[c2] <= i
+                while (b2 - a2 > 1) {
+                    const int mid = (a2 + b2) >> 1;
+                    if (sh_off[mid] <= i) a2 = mid; else b2 = mid;
+                }
+                int64_t at = (int64_t)a2 * chunk + (i - sh_off[a2]);
+                at = at < list ? at : list - 1;         // only counts that a failed rendezvous left inconsistent get here
+                const unsigned long long both = __hip_atomic_load(
+                    reinterpret_cast<const unsigned long long*>(&S.cand[(int64_t)h * list + at]),
+                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sh_cand[i] = make_uint2((unsigned)(both & 0xffffffffull), (unsigned)(both >> 32));
+            }
+            __syncthreads();
+        }
     }
     if (!exact) {
         eq_before = 0;              // positions inside the bin are counted from the candidate list
-        const unsigned m = bin_count < (unsigned)kPsCandCap ? bin_count : (unsigned)kPsCandCap;
-        __syncthreads();
-        for (unsigned i = tid; i < m && !solo; i += NT) {
-            int a2 = 0, b2 = Wh;            // largest c2 with sh_off[c2] <= i
-            while (b2 - a2 > 1) {
-                const int mid = (a2 + b2) >> 1;
-                if (sh_off[mid] <= i) a2 = mid; else b2 = mid;
-            }
-            int64_t at = (int64_t)a2 * chunk + (i - sh_off[a2]);
-            at = at < list ? at : list - 1;         // only counts that a failed rendezvous left inconsistent get here
-            const unsigned long long both = __hip_atomic_load(
-                reinterpret_cast<const unsigned long long*>(&S.cand[(int64_t)h * list + at]),
-                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sh_cand[i] = make_uint2((unsigned)(both & 0xffffffffull), (unsigned)(both >> 32));
-        }
         int rem_sh = rem_bits;          // bits of the pattern still undecided inside the bin
-        if (m <= 128u) {                // few candidates: each counts those above it and those equal to it
-            __syncthreads();
-            if ((unsigned)tid < m) {
-                const unsigned mine = sh_cand[tid].x;
-                unsigned gt = 0, eq = 0;
-#pragma unroll 4
-                for (unsigned i = 0; i < m; ++i) {
-                    const unsigned v = sh_cand[i].x;
-                    gt += v > mine;
-                    eq += v == mine;
-                }
-                if (gt < krem && krem <= gt + eq) {
-                    sh_out[0] = mine;
-                    sh_out[1] = krem - gt;
-                }
+        if (m <= 128u) {                // few candidates: each is compared with all of them, by eight threads
+            const unsigned i = (unsigned)tid >> 3;
+            const unsigned mine = i < m ? sh_cand[i].x : 0u;
+            unsigned gt = 0, eq = 0;
+            for (unsigned j = tid & 7; j < m; j += 8) {
+                const unsigned v = sh_cand[j].x;
+                gt += v > mine;
+                eq += v == mine;
+            }
+            gt = octet_sum(gt);
+            eq = octet_sum(eq);
+            if (i < m && gt < krem && krem <= gt + eq) {
+                sh_out[0] = mine;
+                sh_out[1] = krem - gt;
             }
             __syncthreads();
             cur_lo = sh_out[0];
@@ -1385,26 +1497,21 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
             __syncthreads();
             unsigned bins[kPsBins / NT];
             load_bins_from_top<NT, kPsBins>(sh_hist, bins);
-            find_bin_from_top<NT, kPsBins>(bins, krem, sh_scan, sh_out);
+            find_bin_from_top<NT, kPsBins>(bins, krem, sh_scan[0], sh_out);
             cur_lo += (sh_out[0] & (kPsBins - 1)) << nsh;
             krem = sh_out[1];
             rem_sh = nsh;
             __syncthreads();
         }
-        __syncthreads();
         T = cur_lo;
         need_eq = krem;
-        unsigned g2 = 0, q2 = 0, z = 0;   // candidates before this chunk: greater than / equal to T
-        for (unsigned i = tid; i < m; i += NT) {
+        for (unsigned i = tid; i < m; i += NT) {   // candidates before this chunk: greater than / equal to T
             const uint2 cd = sh_cand[i];
             if ((int64_t)cd.y < chunk0) {
-                g2 += cd.x > T;
-                q2 += cd.x == T;
+                if (cd.x > T) atomicAdd(&sh_n[kGreater], 1u);
+                if (cd.x == T) atomicAdd(&sh_n[kEqual], 1u);
             }
         }
-        block_sum3<NT>(g2, q2, z, sh_red);
-        gt_before += g2;
-        eq_before = q2;
     }
 
     // ---- ordered emission: position order is (run e4, wave, lane, k).  Every wave leaves the
@@ -1439,6 +1546,8 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
         }
     }
     __syncthreads();
+    gt_before += sh_n[kGreater];
+    eq_before += sh_n[kEqual];
     unsigned base_gt = 0, base_eq = 0;          // lane e4 < E4: kept positions before (row e4, this wave)
     {
         unsigned row_gt = 0, row_eq = 0, mine_gt = 0, mine_eq = 0;

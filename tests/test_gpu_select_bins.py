@@ -1,6 +1,7 @@
 """Pooling and selection in one launch (csrc/snapkv_topk.hip, pool_select): the first digit has fixed bins of 1/64 octave
 around the mean score, so the threshold can fall into either end bin, into a bin that holds more positions than the
-candidate list, into one of at most 128 (counted directly) or more (searched by digits); a head may have one
+candidate list, into one of at most 128 (counted directly) or more (searched by digits), or of more than a workgroup has words
+in the exchange; a head may have one
 workgroup or many, and rows of votes whose length is no multiple of four are padded.  Whatever the route, the kept
 set is exactly the top-k of the call's own pooled scores."""
 import numpy as np
@@ -55,6 +56,28 @@ def test_kept_set_is_the_exact_top_k(snapkv, field, L, Hq, Hkv, W, C, p, dtype):
     for pool_kind in (0, 1):
         res = run_gpu(snapkv, q, k, v, pool_kind, p, C)
         check_self_consistency(q, k, v, C, *res)
+
+
+def narrow(q, k):                   # a stretch of scores within one bin, far above the others
+    k[:, 1000:1400] = k[:, 1000:1001] + 1e-3 * k[:, 1000:1400]
+    k[:, 1000:1400, 0] += 12.0
+    q[..., 0] += 8.0
+
+
+@pytest.mark.parametrize("field", [as_drawn, narrow], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("L", [9001, 83985, 84008, 131072, 165904, 165921])
+def test_exchange_of_candidates(snapkv, field, L):
+    """One head's workgroups exchange 64 words each (up to 40 workgroups of 2048 positions), 32 (up to 80) or go the general
+    way; so does a head one of whose workgroups has more candidates than words."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    q = torch.randn((1, 16, D), generator=gen, device="cuda")
+    k = torch.randn((1, L, D), generator=gen, device="cuda")
+    field(q, k)
+    q, k = q.bfloat16(), k.bfloat16()
+    for C in (216, 1016):
+        res = run_gpu(snapkv, q, k, k, 0, 1, C)
+        check_self_consistency(q, k, k, C, *res)
 
 
 @pytest.mark.parametrize("field", [as_drawn, flat, few_spikes, two_fields], ids=lambda f: f.__name__)
