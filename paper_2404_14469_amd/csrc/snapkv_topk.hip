@@ -894,7 +894,7 @@ hipError_t launch_pool_pick(const ScoreGeom& G, const float* vote, int pool_kind
 // LDS permutes a call of 512 keys, fp32, 4 heads took 28.7 us, now 26.0; 16384 keys, 32 heads 58.1, now 52.8; 28471 keys,
 // 32/8 heads 64.6, now 57.5; 13339 paged keys 42.0, now 37.2; 131072 keys, W = 64 213.1, now 206.5.  Steps it
 // lost before: the exchange of the head's range (the first digit is fixed), a memory latency and a barrier per query head of a
-// group (the next head's votes are fetched ahead, two staging areas), element-wise loads where the prefix is no
+// group (four heads staged at a time), element-wise loads where the prefix is no
 // multiple of four (rows are padded), digit rounds over at most 128 candidates, and for a head with one workgroup
 // every exchange.
 //
@@ -982,7 +982,9 @@ __device__ __forceinline__ unsigned octet_sum(unsigned v) {
     return v + (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true);   // row_half_mirror
 }
 
-template <int EPT, int P, int KIND>   // KIND: 0 max pooling, 1 average pooling
+// KIND: 0 max pooling, 1 average pooling.  DEEP: query heads staged at a time, 4 (4 positions per thread, one vote row per
+// query head, unrolled taps: 28471 keys, 32/8 heads 56.0 instead of 57.5 us a call, 13339 paged keys 35.6 / 37.1) or 1.
+template <int EPT, int P, int KIND, int DEEP>
 __global__ __launch_bounds__(kPsThreads) void pool_select(
     const float* __restrict__ vote, const ScoreGeom G, const int p_arg,
     const int64_t kcount, const int64_t out_stride, const int W_tail, int32_t* __restrict__ out_idx,
@@ -1054,6 +1056,11 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
         float acc[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) acc[e] = 0.f;
+        auto cut = [&](float4& t, const int q0) {   // a row's last piece: what lies behind its end does not count
+            if (q0 + 1 >= nn) t.y = pad;
+            if (q0 + 2 >= nn) t.z = pad;
+            t.w = pad;
+        };
         // The chunk's votes (and halo) of one query head, on their way to LDS.
         auto fetch = [&](const int hq, float4 (&land)[E4 + 1]) {
             const float* vb = vote + ((int64_t)h * G.NV + (int64_t)hq * G.VB) * pitch;
@@ -1075,11 +1082,7 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
                                     t4.w += u.w;
                                 }
                             }
-                            if (q0 + 3 >= nn) {              // the row's last piece: what lies behind it does not count
-                                if (q0 + 1 >= nn) t4.y = pad;
-                                if (q0 + 2 >= nn) t4.z = pad;
-                                t4.w = pad;
-                            }
+                            if (q0 + 3 >= nn) cut(t4, q0);
                         }
                     } else {
                         float t[4];
@@ -1099,26 +1102,8 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
                 land[e4] = t4;
             }
         };
-        // At 4 positions per thread the next query head's votes are on their way while this one's are pooled, and two
-        // staging areas take turns (one barrier a head); at 16 there is room for neither.
-        constexpr bool AHEAD = EPT <= 4;
         constexpr int kStageWords = EPT * NT + 128;
-        float4 land[E4 + 1];                  // all loads are in flight before the first LDS write
-        if constexpr (AHEAD) fetch(0, land);
-        for (int hq = 0; hq < G.g; ++hq) {
-            float* const stage = stage0 + (AHEAD ? (hq & 1) * kStageWords : 0);
-            if constexpr (!AHEAD) {
-                if (hq > 0) __syncthreads();      // the previous head's taps have been read
-                fetch(hq, land);
-            }
-#pragma unroll
-            for (int e4 = 0; e4 <= E4; ++e4) {
-                const int f = e4 * NT + tid;
-                if (f < nf4) reinterpret_cast<float4*>(stage)[f] = land[e4];
-            }
-            if constexpr (AHEAD)
-                if (hq + 1 < G.g) fetch(hq + 1, land);
-            __syncthreads();
+        auto pool_stage = [&](const float* const stage) __attribute__((always_inline)) {   // a query head's staged votes
 #pragma unroll
             for (int e4 = 0; e4 < E4; ++e4) {
                 const int i0 = e4 * (4 * NT) + 4 * tid;      // first of the four positions; its taps
@@ -1191,6 +1176,70 @@ __global__ __launch_bounds__(kPsThreads) void pool_select(
                         acc[4 * e4 + k] += val;
                     }
                 }
+            }
+        };
+        if constexpr (DEEP > 1) {
+            // The votes of DEEP query heads are asked for at once and staged side by side: a memory latency and a barrier
+            // for all of them.
+            for (int h0 = 0; h0 < G.g; h0 += DEEP) {
+                if (h0 > 0) __syncthreads();      // the taps of the heads before have been read
+                if (rows_aligned) {
+                    const float* const vb = vote + ((int64_t)h * G.NV + h0) * pitch;   // (one vote row per query head)
+#pragma unroll
+                    for (int e4 = 0; e4 <= E4; ++e4) {
+                        const int f = e4 * NT + tid, q0 = (int)chunk0 - HQ + 4 * f;
+                        if (f >= nf4) continue;
+                        float4 land[DEEP];           // all loads are in flight before the first LDS write
+#pragma unroll
+                        for (int d = 0; d < DEEP; ++d) land[d] = make_float4(pad, pad, pad, pad);
+                        if (q0 >= 0 && q0 < nn) {
+#pragma unroll
+                            for (int d = 0; d < DEEP; ++d)
+                                if (h0 + d < G.g) land[d] = *reinterpret_cast<const float4*>(vb + (int64_t)d * pitch + q0);
+                            if (q0 + 3 >= nn) {
+#pragma unroll
+                                for (int d = 0; d < DEEP; ++d) cut(land[d], q0);
+                            }
+                        }
+#pragma unroll
+                        for (int d = 0; d < DEEP; ++d)
+                            if (h0 + d < G.g) reinterpret_cast<float4*>(stage0 + d * kStageWords)[f] = land[d];
+                    }
+                } else {
+                    for (int d = 0; d < DEEP && h0 + d < G.g; ++d) {
+                        float4 land[E4 + 1];
+                        fetch(h0 + d, land);
+#pragma unroll
+                        for (int e4 = 0; e4 <= E4; ++e4) {
+                            const int f = e4 * NT + tid;
+                            if (f < nf4) reinterpret_cast<float4*>(stage0 + d * kStageWords)[f] = land[e4];
+                        }
+                    }
+                }
+                __syncthreads();
+                for (int d = 0; d < DEEP && h0 + d < G.g; ++d) pool_stage(stage0 + d * kStageWords);
+            }
+        } else {
+            // At 4 positions per thread the next query head's votes are on their way while this one's are pooled, and two
+            // staging areas take turns (one barrier a head); at 16 there is room for neither.
+            constexpr bool AHEAD = EPT <= 4;
+            float4 land[E4 + 1];                  // all loads are in flight before the first LDS write
+            if constexpr (AHEAD) fetch(0, land);
+            for (int hq = 0; hq < G.g; ++hq) {
+                float* const stage = stage0 + (AHEAD ? (hq & 1) * kStageWords : 0);
+                if constexpr (!AHEAD) {
+                    if (hq > 0) __syncthreads();      // the previous head's taps have been read
+                    fetch(hq, land);
+                }
+#pragma unroll
+                for (int e4 = 0; e4 <= E4; ++e4) {
+                    const int f = e4 * NT + tid;
+                    if (f < nf4) reinterpret_cast<float4*>(stage)[f] = land[e4];
+                }
+                if constexpr (AHEAD)
+                    if (hq + 1 < G.g) fetch(hq + 1, land);
+                __syncthreads();
+                pool_stage(stage);
             }
         }
 #pragma unroll
@@ -1690,11 +1739,13 @@ constexpr unsigned kPsSpinLimit = 1u << 14;    // polls before a rendezvous give
 
 // With call == nullptr: returns in *occ how many workgroups of this instantiation one compute unit
 // keeps resident.  Otherwise launches.
-template <int EPT, int P, int KIND>
-static hipError_t pool_select_instance(const PoolSelCall* call, int* occ) {
-    auto kern = pool_select<EPT, P, KIND>;
+template <int EPT, int P, int KIND, int DEEP = 1>
+static hipError_t pool_select_instance(bool deep, const PoolSelCall* call, int* occ) {
+    if constexpr (EPT <= 4 && P > 0 && DEEP == 1)
+        if (deep) return pool_select_instance<EPT, P, KIND, 4>(deep, call, occ);
+    auto kern = pool_select<EPT, P, KIND, DEEP>;
     // staging area of the votes (chunk + halo for p <= 129) or histogram + candidate list
-    constexpr size_t kStage = sizeof(float) * ((size_t)EPT * kPsThreads + 128) * (EPT <= 4 ? 2 : 1);
+    constexpr size_t kStage = sizeof(float) * ((size_t)EPT * kPsThreads + 128) * (EPT <= 4 ? (DEEP > 1 ? DEEP : 2) : 1);
     constexpr size_t kSearch = sizeof(unsigned) * kPsBins + sizeof(uint2) * kPsCandCap;
     constexpr size_t kLds = kStage > kSearch ? kStage : kSearch;
     if (!call) {
@@ -1722,21 +1773,23 @@ static hipError_t pool_select_instance(const PoolSelCall* call, int* occ) {
 }
 
 template <int EPT, int KIND>
-static hipError_t pool_select_by_width(int pw, const PoolSelCall* call, int* occ) {
+static hipError_t pool_select_by_width(int pw, bool deep, const PoolSelCall* call, int* occ) {
     switch (pw) {   // the widths the paper uses (Sec. 5) get unrolled taps
-        case 5: return pool_select_instance<EPT, 5, KIND>(call, occ);
-        case 7: return pool_select_instance<EPT, 7, KIND>(call, occ);
+        case 5: return pool_select_instance<EPT, 5, KIND>(deep, call, occ);
+        case 7: return pool_select_instance<EPT, 7, KIND>(deep, call, occ);
         case 13:   // 13 taps of 16 positions do not fit the registers: the loop form is faster there
-            if constexpr (EPT <= 4) return pool_select_instance<EPT, 13, KIND>(call, occ);
-            return pool_select_instance<EPT, 0, KIND>(call, occ);
-        default: return pool_select_instance<EPT, 0, KIND>(call, occ);
+            if constexpr (EPT <= 4) return pool_select_instance<EPT, 13, KIND>(deep, call, occ);
+            return pool_select_instance<EPT, 0, KIND>(deep, call, occ);
+        default: return pool_select_instance<EPT, 0, KIND>(deep, call, occ);
     }
 }
 
-static hipError_t pool_select_dispatch(int ept, int pw, int kind, const PoolSelCall* call, int* occ) {
-    if (ept == 4) return kind == 0 ? pool_select_by_width<4, 0>(pw, call, occ) : pool_select_by_width<4, 1>(pw, call, occ);
-    return kind == 0 ? pool_select_by_width<16, 0>(pw, call, occ) : pool_select_by_width<16, 1>(pw, call, occ);
+// deep: query heads share their staging (see pool_select), where there are several with a vote row each
+static hipError_t pool_select_dispatch(int ept, int pw, int kind, bool deep, const PoolSelCall* call, int* occ) {
+    if (ept == 4) return kind == 0 ? pool_select_by_width<4, 0>(pw, deep, call, occ) : pool_select_by_width<4, 1>(pw, deep, call, occ);
+    return kind == 0 ? pool_select_by_width<16, 0>(pw, deep, call, occ) : pool_select_by_width<16, 1>(pw, deep, call, occ);
 }
+static bool ps_deep(const ScoreGeom& G) { return G.g > 1 && G.VB == 1; }
 
 static int ps_cu_count() {
     static int cached[64] = {0};
@@ -1762,7 +1815,7 @@ static bool pool_select_plan(const ScoreGeom& G, int pool_kind, int p, int64_t k
     if (cus <= 0) return false;
     for (int e : {4, 16}) {   // positions per thread: the lighter variant when the chunks allow it
         int occ = 0;
-        if (pool_select_dispatch(e, ps_width(G, p, e), pool_kind, nullptr, &occ) != hipSuccess) {
+        if (pool_select_dispatch(e, ps_width(G, p, e), pool_kind, ps_deep(G), nullptr, &occ) != hipSuccess) {
             (void)hipGetLastError();
             continue;
         }
@@ -1794,7 +1847,7 @@ hipError_t launch_pool_select(const ScoreGeom& G, const float* vote, int pool_ki
     if (!pool_select_plan(G, pool_kind, p, kcount, &Wh, &chunk, &ept)) return hipErrorInvalidValue;
     const PoolSelCall call{vote, &G, pool_kind, p, kcount, out_stride, W_tail, out_idx, &S, Wh, chunk, st, nvalid};
     int occ = 0;
-    return pool_select_dispatch(ept, ps_width(G, p, ept), pool_kind, &call, &occ);
+    return pool_select_dispatch(ept, ps_width(G, p, ept), pool_kind, ps_deep(G), &call, &occ);
 }
 
 hipError_t launch_select_init(const SelectScratch& S, int H, hipStream_t st) {
