@@ -105,7 +105,10 @@ struct DecodeArgs {
 
 constexpr int kDecWaves = 4;   // (eight measure the same)
 
-template <typename T, int D>
+// ONE: no wave has more than one step (32 keys), so none asks for another's: 100 registers instead of 220, and half the
+// loads (the other form repeats its only step's).  One sequence of 2113 keys, 32/8 heads: 7.9 us a step instead of 8.9
+// with the merge, as a graph; 3000 keys 8.0 / 8.9.
+template <typename T, int D, bool ONE>
 __global__ __launch_bounds__(kDecWaves * 64) void decode_attn(const DecodeArgs A) {
     constexpr int NP = D / 32;        // 16-byte pieces per lane and row (2-byte elements)
     constexpr int NB = D / 16;        // 16-column blocks of the output
@@ -223,7 +226,12 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_attn(const DecodeArgs A
     };
     PairRegs R0, R1;
     int64_t pair = p_begin + wave;
-    if (pair < p_end) {
+    if constexpr (ONE) {
+        if (pair < p_end) {
+            request(R0, pair);
+            process(R0, pair);
+        }
+    } else if (pair < p_end) {
         request(R0, pair);
         for (;;) {
             request(R1, pair + kDecWaves < p_end ? pair + kDecWaves : pair);
@@ -360,7 +368,11 @@ int cu_count() {
 // Otherwise, down to 32 keys per wave, the number that costs least when workgroups
 // run in rounds of one per compute unit.  In keys of time (a key of one pair at a compute unit's share of HBM): the
 // stream cannot go below everybody's keys divided evenly, nor a round below 0.8 of its workgroup's keys (a unit alone
-// draws a quarter more than its share); a round costs about 100 besides, the merge of the splits 150.  Microseconds
+// draws a quarter more than its share); a round costs about 100 besides, the merge of the splits 150 and 20 for every
+// sixteen of them.  Splits of one step a wave go to the light form of the kernel, three workgroups of which share a unit; they
+// gain 20 (graphs of steps, us, the splits without that rule / with it: one sequence of 4096 keys and 8 KV heads 9.7 / 8.0,
+// of 2048 keys and 32 KV heads 11.5 / 9.5, of 8192 keys and 4 KV heads of 16 11.5 / 10.0; three of 2048 keys and 8 KV heads
+// 9.9 / 9.4; five of 1500 keys and 32 KV heads 27.1 / 24.9; a gain of 40 instead makes 6500 keys 11.2 instead of 10.5).  Microseconds
 // per call with splits of at least 512 keys, as near as possible to one workgroup per unit, and with this rule (bf16, 32
 // query heads): one sequence of 2113 keys and 8 KV heads 15.3 / 11.8 (32 instead of 136 workgroups were in flight), of
 // 16384 keys 26.1 / 18.8; three sequences of 32 heads and 2560 keys 38.1 / 25.0 (288 workgroups: 32 units had two),
@@ -372,8 +384,11 @@ int decode_splits(int B, int Hkv, int64_t S) {
     int best = 1;
     double least = 0.0;
     for (int64_t n = 1; n <= most; ++n) {
-        const double rounds = (double)((n * pairs + cus - 1) / cus), keys = 32.0 * (double)((steps + n - 1) / n);
-        const double cost = std::max((double)(pairs * S) / (double)cus, 0.8 * rounds * keys) + 100.0 * rounds + (n > 1 ? 150.0 : 0.0);
+        const int64_t most_steps = (steps + n - 1) / n;
+        const bool one = most_steps <= kDecWaves;
+        const int64_t at_once = one ? 3 * cus : cus;
+        const double rounds = (double)((n * pairs + at_once - 1) / at_once), keys = 32.0 * (double)most_steps;
+        const double cost = std::max((double)(pairs * S) / (double)cus, 0.8 * rounds * keys) + 100.0 * rounds + (n > 1 ? 150.0 + 20.0 * (double)((n + 15) / 16) : 0.0) - (one ? 20.0 : 0.0);
         if (n == 1 || cost < least) {
             best = (int)n;
             least = cost;
@@ -414,10 +429,14 @@ hipError_t launch_decode(int dtype, int D, const void* q, const void* k, const v
                                               ((heads * nsplit * D * sizeof(float) + 255) & ~(size_t)255));
     }
     const dim3 grid(nsplit, Hkv, B), block(kDecWaves * 64);
-    if (dtype == 0 && D == 128) hipLaunchKernelGGL((decode_attn<dec_bf16, 128>), grid, block, 0, st, A);
-    else if (dtype == 0 && D == 64) hipLaunchKernelGGL((decode_attn<dec_bf16, 64>), grid, block, 0, st, A);
-    else if (dtype == 2 && D == 128) hipLaunchKernelGGL((decode_attn<dec_f16, 128>), grid, block, 0, st, A);
-    else if (dtype == 2 && D == 64) hipLaunchKernelGGL((decode_attn<dec_f16, 64>), grid, block, 0, st, A);
+    // steps of a split at most (lens may say anything up to a full cache)
+    const int64_t steps = ((lens ? cap : std::min(S, cap)) + 31) / 32;
+    const bool one = (steps + nsplit - 1) / nsplit <= kDecWaves;
+    auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, A); };
+    if (dtype == 0 && D == 128) one ? launch(decode_attn<dec_bf16, 128, true>) : launch(decode_attn<dec_bf16, 128, false>);
+    else if (dtype == 0 && D == 64) one ? launch(decode_attn<dec_bf16, 64, true>) : launch(decode_attn<dec_bf16, 64, false>);
+    else if (dtype == 2 && D == 128) one ? launch(decode_attn<dec_f16, 128, true>) : launch(decode_attn<dec_f16, 128, false>);
+    else if (dtype == 2 && D == 64) one ? launch(decode_attn<dec_f16, 64, true>) : launch(decode_attn<dec_f16, 64, false>);
     else return hipErrorInvalidValue;
     if (nsplit > 1) {
         const unsigned heads = (unsigned)((int64_t)B * Hq);

@@ -63,6 +63,11 @@ CASES = [
     DecodeWorkload("split_most", B=1, Hq=2, Hkv=1, D=64, S=16400, cap=16400, seed=15),          # 64 splits
     DecodeWorkload("split_ragged_short", B=3, Hq=16, Hkv=8, D=128, S=3000, cap=3000, ragged=True, seed=16),
     DecodeWorkload("split_rounds", B=3, Hq=32, Hkv=32, D=128, S=2100, cap=2100, seed=17),       # more workgroups than units
+    DecodeWorkload("one_step_a_wave", B=1, Hq=32, Hkv=8, D=128, S=4096, cap=4096, seed=31),     # 32 splits of four steps
+    DecodeWorkload("a_fifth_step", B=1, Hq=32, Hkv=8, D=128, S=4097, cap=4200, seed=32),
+    DecodeWorkload("one_step_unsplit", B=2, Hq=4, Hkv=4, D=64, S=128, cap=200, seed=33),
+    DecodeWorkload("one_step_ragged", B=3, Hq=8, Hkv=4, D=128, S=128, cap=128, ragged=True, seed=34),
+    DecodeWorkload("one_step_three_to_a_unit", B=1, Hq=32, Hkv=32, D=128, S=2048, cap=2048, dtype="f16", seed=35),
     DecodeWorkload("f16_d64_split", B=1, Hq=4, Hkv=4, D=64, S=4100, cap=4100, dtype="f16", seed=12),
 ]
 
@@ -94,6 +99,17 @@ def test_row_order_does_not_matter(snapkv):
     b, lb = run(snapkv, w, case2)
     vmax = float(case["v_cache"].float().abs().max())
     assert np.abs(a - b).max() <= TOL * vmax and np.abs(la - lb).max() <= TOL
+
+
+def test_lens_beyond_the_step_count_of_S(snapkv):
+    """The splits are planned for S rows; lens may ask for more, up to the cache's capacity: several steps a wave then."""
+    w = DecodeWorkload("long_lens", B=2, Hq=8, Hkv=4, D=128, S=1100, cap=3000, seed=36)
+    case = workloads.generate_decode(w, device="cuda")
+    case["k_cache"][:, :, w.S:] = case["k_cache"][:, :, :1].flip(1)     # make the padding rows ordinary
+    case["v_cache"][:, :, w.S:] = case["v_cache"][:, :, :1]
+    case["lens"] = torch.tensor([3000, 2999], dtype=torch.int32, device="cuda")
+    out, lse = run(snapkv, w, case)
+    check(w, case, out, lse)
 
 
 def test_empty_sequence_and_length_clamp(snapkv):
