@@ -120,8 +120,14 @@ def _check(code: int) -> int:
     return int(code)
 
 
+# The current stream's handle without building a Stream object around it (about 1 us of a decoding step's host time).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -474,11 +480,11 @@ def snapkv_decode_attention(q: torch.Tensor, k_cache: torch.Tensor, v_cache: tor
     lib = load()
     B, Hq, D = q.shape
     Bk, Hkv, cap, Dk = k_cache.shape
-    if (Bk, Dk) != (B, D) or tuple(v_cache.shape) != tuple(k_cache.shape):
+    if Bk != B or Dk != D or v_cache.shape != k_cache.shape:
         raise ValueError("q, k_cache and v_cache disagree on their shapes")
-    if tuple(out.shape) != (B, Hq, D) or (out_lse is not None and tuple(out_lse.shape) != (B, Hq)):
+    if out.shape != q.shape or (out_lse is not None and out_lse.shape != (B, Hq)):
         raise ValueError("out must be [B, Hq, D] and out_lse [B, Hq]")
-    if lens is not None and tuple(lens.shape) != (B,):
+    if lens is not None and lens.shape != (B,):
         raise ValueError("lens must be [B]")
     code = _dtype_code(q)
     _check(lib.snapkv_decode_attention(
