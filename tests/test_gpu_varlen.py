@@ -44,6 +44,8 @@ def compare_with_single_calls(snapkv, ws, cases, oks, ovs, ois, kept, oracle_on=
 MIXES = {
     "ragged_mix": dict(lengths=[5003, 1301, 9000, 290, 2600]),                       # 290 fits the capacity: returned unchanged
     "gqa_avg_w16": dict(lengths=[4100, 12345, 800, 7001], Hq=16, Hkv=4, W=16, pool_kind=1, p=5, C=300),
+    # 122, 83 and 51 slices of 512 keys: prompts that start at blocks 122 and 205, and a chip of 256 places filled to the last
+    "filled_to_the_last": dict(lengths=[62300, 42400, 26001], Hq=8, Hkv=2, W=16, p=5, C=512),
     "equal_lengths": dict(lengths=[3000, 3000, 3000]),
     "one_long_many_short": dict(lengths=[40000, 600, 700, 650, 800, 620], C=512),    # most workgroups of the short heads are empty
     "d64_f16": dict(lengths=[2222, 5555, 3333], D=64, dtype="f16", C=200),
