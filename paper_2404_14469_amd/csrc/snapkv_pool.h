@@ -7,6 +7,42 @@
 
 namespace snapkv {
 
+// acc[i] += the pooled value of taps v[O + i .. O + i + P - 1].  Which pooling is asked once for the run: as a choice at every tap
+// both were computed, and the average's divisions with them.  Maxima do not depend on their order, so the four share the
+// taps they have in common (8 instructions of two or three operands for 24 at P = 7); sums take theirs in increasing order.
+template <int P, int O, int N>
+__device__ __forceinline__ void add_pooled(const float (&v)[N], const int pool_kind, float (&acc)[4]) {
+    static_assert(O >= 0 && O + P + 3 <= N, "taps inside the run");
+    if (pool_kind == 0) {
+        if constexpr (P >= 4) {
+            float core = v[O + 3];
+#pragma unroll
+            for (int d = 4; d < P; ++d) core = fmaxf(core, v[O + d]);
+            const float left = fmaxf(v[O + 1], v[O + 2]), right = fmaxf(v[O + P], v[O + P + 1]);
+            acc[0] += fmaxf(fmaxf(core, v[O]), left);
+            acc[1] += fmaxf(fmaxf(core, left), v[O + P]);
+            acc[2] += fmaxf(fmaxf(core, v[O + 2]), right);
+            acc[3] += fmaxf(fmaxf(core, right), v[O + P + 2]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float val = v[O + i];
+#pragma unroll
+                for (int d = 1; d < P; ++d) val = fmaxf(val, v[O + i + d]);
+                acc[i] += val;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float val = v[O + i];
+#pragma unroll
+            for (int d = 1; d < P; ++d) val = val + v[O + i + d];
+            acc[i] += val / (float)P;
+        }
+    }
+}
+
 // acc[i] = score of position j0 + i of KV head hkv (rows of votes 16-byte aligned, j0 a multiple of four; positions at
 // or past G.n get what their neighbours give and are the caller's to ignore).  interior: the run and its taps, in whole
 // 16-byte pieces, lie inside the row.  Taps are combined in increasing order and query heads in head order, as
@@ -55,15 +91,7 @@ __device__ __forceinline__ void pooled_run(const float* __restrict__ vote, const
                 }
             }
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float val = v[4 * RQ + i - r];
-#pragma unroll
-            for (int d = 1; d < P; ++d)
-                val = pool_kind == 0 ? fmaxf(val, v[4 * RQ + i - r + d]) : val + v[4 * RQ + i - r + d];
-            if (pool_kind != 0) val = val / (float)P;
-            acc[i] += val;
-        }
+        add_pooled<P, 4 * RQ - r>(v, pool_kind, acc);
     }
 }
 

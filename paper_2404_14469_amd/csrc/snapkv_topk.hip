@@ -520,8 +520,9 @@ __global__ __launch_bounds__(256) void sel_emit(const float* __restrict__ score,
 //                  collected again by its own workgroup with Tlo = 0, so the result never depends on the sample
 //
 // Microseconds after the scoring, before (pool_group4, sel_hist, sel_compact, sel_threshold, sel_emit and the counters
-// they start from) and now: 1024 heads of 131040 positions 693 / 297 (pool_collect reads its 537 MB in 176, 3.0 TB/s),
-// 32 heads of 379984 positions 83 / 57, 256 heads in groups of four of 31305 positions 103 / 98.
+// they start from) and now: 1024 heads of 131040 positions 693 / 239, 32 heads of 379984 positions 83 / 52, 256 heads in
+// groups of four of 31305 positions 103 / 82.  pool_collect is bound by its vector instructions: with the kind of pooling asked
+// at every tap and maxima that shared nothing it took 174, 21 and 44 of these, now 126 (537 MB, 4.3 TB/s), 16 and 31.
 // ------------------------------------------------------------------------------------------------
 constexpr int kPickSamples = 2048;
 constexpr int kPickShift = 17;         // digits of 1/64 octave
@@ -627,15 +628,7 @@ __global__ __launch_bounds__(256) void pool_collect(const float* __restrict__ vo
                 v[4 * x + 2] = q.z;
                 v[4 * x + 3] = q.w;
             }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {             // (arithmetic and order of pooled_run)
-                float val = v[4 * RQ + k - P / 2];
-#pragma unroll
-                for (int d = 1; d < P; ++d)
-                    val = pool_kind == 0 ? fmaxf(val, v[4 * RQ + k - P / 2 + d]) : val + v[4 * RQ + k - P / 2 + d];
-                if (pool_kind != 0) val = val / (float)P;
-                acc[e][k] += val;
-            }
+            add_pooled<P, 4 * RQ - P / 2>(v, pool_kind, acc[e]);
         }
     }
     const unsigned long long lt_mask = (1ull << lane) - 1ull;

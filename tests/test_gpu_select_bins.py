@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 import torch
 
-from parity import check_self_consistency, run_gpu
+from parity import check_against_oracle, check_self_consistency, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -178,3 +178,27 @@ def test_heads_whose_sample_misleads_are_collected_again(snapkv, pool_kind, p):
         digits = np.clip((bits - lo0) >> 17, 0, 2047)
         tlo = lo0 + (np.sort(digits[:, sampled.flatten().numpy()], axis=1)[:, -rank] << 17)
         assert ((bits >= tlo[:, None]).sum(axis=1) < kc).all()
+
+
+@pytest.mark.parametrize("pool_kind", [0, 1])
+@pytest.mark.parametrize("p", [1, 5, 7, 13])
+def test_votes_read_once_pool_as_single_calls(snapkv, p, pool_kind):
+    """Runs of four positions that share their taps, over two chunks and a ragged end (8210 positions), two query heads a KV
+    head; the single call pools the same votes in another kernel."""
+    layers, Hq, Hkv, L, W, C = 40, 16, 8, 8226, 16, 120
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(p)
+    q = torch.randn((layers * Hq, W, D), generator=gen, device="cuda").bfloat16()
+    k, v = (torch.randn((layers * Hkv, L, D), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    ok = torch.empty((layers * Hkv, C, D), dtype=torch.bfloat16, device="cuda")
+    ov = torch.empty_like(ok)
+    oi = torch.full((layers * Hkv, C), -1, dtype=torch.int32, device="cuda")
+    lists = [list(t.split(h)) for t, h in ((q, Hq), (k, Hkv), (v, Hkv), (ok, Hkv), (ov, Hkv), (oi, Hkv))]
+    snapkv.snapkv_profile_start(1)
+    snapkv.snapkv_compress_layers(*lists[:3], pool_kind, p, C, *lists[3:])
+    stages, _ = snapkv.snapkv_profile_stop()
+    assert stages["pool_group"] == 0.0 and stages["select_topk"] > 0.0, stages
+    for l in (0, 21, layers - 1):
+        res = run_gpu(snapkv, lists[0][l], lists[1][l], lists[2][l], pool_kind, p, C)
+        assert (lists[5][l].cpu().numpy() == res[3]).all(), l
+        check_against_oracle(lists[0][l], lists[1][l], lists[2][l], pool_kind, p, C, *res)
