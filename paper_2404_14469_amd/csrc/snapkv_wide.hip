@@ -20,12 +20,13 @@
 //     the call) in order, a contiguous run of whole slices each; a launch whose slices all find a place at once
 //     has a workgroup per slice.
 //
-// What bounds it: matrix and vector instructions of a SIMD hardly overlap here, so a pass costs about their sum.  Counters
-// (profiles/sq_counters_gqa_two_pass.txt; 32 layers of 32/8 heads of 32768 keys, 1.07e9 logits): of the 781 thousand
-// cycles of wide_stats a SIMD's matrix unit is busy for 263 (16 a 64 logits) and its vector instructions take 436; of the
-// 992 of wide_votes 262 and 443.  That is 411 and 480 us, where 2.15 GB of keys take 350 us at 6.1 TB/s, and the
-// single-read kernel took 1218 us (31337 keys; the two passes 430 and 492 us there).  Tried on the way: all 128 rows in one
-// wave with Q in LDS (two waves per SIMD, 425 + 512 us, and 240 registers).  At 131072 keys, W = 64 (two blocks per
+// What bounds it: the stream of keys, and arithmetic that does not hide behind it.  32 layers of 32/8 heads of 31337 keys take
+// 414 + 481 us (back to back 430 + 492; the single-read kernel 1218); the same loops without the arithmetic 384 + 471, with keys
+// that are always in the cache 334 + 351, and the keys alone 337 at 6.1 TB/s.  The votes' pass also stores 131 MB.  Counters
+// (profiles/sq_counters_gqa_two_pass.txt, 32768 keys): of the 781 thousand cycles of wide_stats a SIMD's matrix unit is busy
+// for 263 and its vector instructions take 436; of the 992 of wide_votes 262 and 443.  Tried on the way: all 128 rows in one
+// wave with Q in LDS (two waves per SIMD, 425 + 512 us, and 240 registers); keys brought to LDS without registers, a ring of four
+// rounds of 64 keys (456 + 522); a second set of landing registers (spills).  At 131072 keys, W = 64 (two blocks per
 // head): 97 + 103 us against 277 us.
 //
 // The row reference.  Exponentials are taken relative to a reference of the row that is known before its keys are: its
