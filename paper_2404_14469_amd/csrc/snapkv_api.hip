@@ -1170,7 +1170,7 @@ int snapkv_decode_attention(int dtype, const void* q, const void* k_cache, const
     if ((reinterpret_cast<uintptr_t>(out) & 3u) != 0 || (reinterpret_cast<uintptr_t>(out_lse) & 3u) != 0 ||
         (reinterpret_cast<uintptr_t>(lens) & 3u) != 0)
         return SNAPKV_ERR_MISALIGNED;
-    int nsplit = decode_splits(B, Hkv, S);
+    int nsplit = decode_splits(B, Hkv, S, decode_longest(lens, S, cap));
     void* base = nullptr;
     if (nsplit > 1) {
         const int rc = decode_scratch(static_cast<hipStream_t>(stream), &base);

@@ -359,36 +359,44 @@ int cu_count() {
     return cus;
 }
 
+// Whether no wave has more than one step when sequences of at most `longest` keys are cut into n splits: the light form of
+// the kernel.  Asked by the rule that prices splits and by the launch, with the same length.
+bool light_form(int64_t longest, int64_t n) { return ((longest + 31) / 32 + n - 1) / n <= kDecWaves; }
+
 }  // namespace
 
 // Splits of a (sequence, KV head) pair's keys.  A step whose pairs alone occupy two thirds of the compute units, or of
 // fewer than 1024 keys, is not split: it needs no buffer, so steps like it on several streams do not meet in the one
 // that split steps share (288 pairs of 2560 keys would take 75 instead of 95 us split, one sequence of 900 keys and
 // 8 KV heads 12 instead of 17; one of 300 takes 9 instead of 12 as it is).
-// Otherwise, down to 32 keys per wave, the number that costs least when workgroups
-// run in rounds of one per compute unit.  In keys of time (a key of one pair at a compute unit's share of HBM): the
-// stream cannot go below everybody's keys divided evenly, nor a round below 0.8 of its workgroup's keys (a unit alone
-// draws a quarter more than its share); a round costs about 100 besides, the merge of the splits 150 and 20 for every
-// sixteen of them.  Splits of one step a wave go to the light form of the kernel, three workgroups of which share a unit; they
-// gain 20 (graphs of steps, us, the splits without that rule / with it: one sequence of 4096 keys and 8 KV heads 9.7 / 8.0,
-// of 2048 keys and 32 KV heads 11.5 / 9.5, of 8192 keys and 4 KV heads of 16 11.5 / 10.0; three of 2048 keys and 8 KV heads
-// 9.9 / 9.4; five of 1500 keys and 32 KV heads 27.1 / 24.9; a gain of 40 instead makes 6500 keys 11.2 instead of 10.5).  Microseconds
-// per call with splits of at least 512 keys, as near as possible to one workgroup per unit, and with this rule (bf16, 32
-// query heads): one sequence of 2113 keys and 8 KV heads 15.3 / 11.8 (32 instead of 136 workgroups were in flight), of
-// 16384 keys 26.1 / 18.8; three sequences of 32 heads and 2560 keys 38.1 / 25.0 (288 workgroups: 32 units had two),
-// five of 16384 keys 295 / 226; eight of 2560 keys, one workgroup each either way, 55.1 / 55.0.
-int decode_splits(int B, int Hkv, int64_t S) {
+// Otherwise, down to 32 keys per wave, the number that costs least when workgroups run in rounds: of one per compute unit,
+// or of three where no sequence can give a wave a second step and the light form runs.  In keys of time (a key of one pair
+// at a compute unit's share of HBM): the stream cannot go below everybody's keys divided evenly, nor a round below 0.8 of its
+// workgroup's keys (a unit alone draws a quarter more than its share); a round costs about 100 besides, the merge of the
+// splits 150 and 20 for every sixteen of them; the light form gains 20.
+// The light form is priced only where it will run: with lens given a sequence may be as long as the cache.  Many splits
+// of the other form, which a longer cache once got with the prices of the light one, are slower than few (graphs of steps, us,
+// S keys and room for 512 more, lens between 0.8 S and S; few splits / many of the other form): one sequence of 2048 keys and
+// 32 KV heads 12.0 (7) / 13.8 (16), three of 2048 keys and 8 KV heads 10.9 (10) / 13.5 (16), five of 1500 and 8 KV heads
+// 11.6 (6) / 13.8 (12), three of 1024 and 32 KV heads 15.1 (2) / 18.7 (8).
+// Where it runs (caches as long as S; few splits of the other form / light splits): one sequence of 2048 keys and 32 KV heads
+// 13.1 / 11.3, of 4096 keys and 8 KV heads 10.7 / 9.4, two of 1344 keys and 32 KV heads 14.4 / 13.4, twelve of 1024 keys and 8
+// KV heads 15.2 / 14.2; three of 1344 keys and 8 KV heads 10.1 / 10.3 (264 workgroups), as far as it loses.
+// Steps called one after another, splits of at least 512 keys / splits by such costs before there was a light form (bf16, 32
+// query heads): one sequence of 2113 keys and 8 KV heads 15.3 / 11.8 us (32 instead of 136 workgroups were in flight; 9.6 with
+// the light form), of 16384 keys 26.1 / 18.8; three sequences of 32 heads and 2560 keys 38.1 / 25.0 (288 workgroups: 32
+// units had two), five of 16384 keys 295 / 226; eight of 2560 keys, one workgroup each either way, 55.1 / 55.0.
+int decode_splits(int B, int Hkv, int64_t S, int64_t longest) {
     const int64_t pairs = (int64_t)B * Hkv, cus = cu_count(), steps = (S + 31) / 32;
     if ((cus + pairs / 2) / pairs < 2 || S < 1024) return 1;
     const int64_t most = std::min<int64_t>(std::min<int64_t>(64, kDecodeMaxGroups / pairs), (steps + kDecWaves - 1) / kDecWaves);
     int best = 1;
     double least = 0.0;
     for (int64_t n = 1; n <= most; ++n) {
-        const int64_t most_steps = (steps + n - 1) / n;
-        const bool one = most_steps <= kDecWaves;
-        const int64_t at_once = one ? 3 * cus : cus;
-        const double rounds = (double)((n * pairs + at_once - 1) / at_once), keys = 32.0 * (double)most_steps;
-        const double cost = std::max((double)(pairs * S) / (double)cus, 0.8 * rounds * keys) + 100.0 * rounds + (n > 1 ? 150.0 + 20.0 * (double)((n + 15) / 16) : 0.0) - (one ? 20.0 : 0.0);
+        const bool light = light_form(longest, n);
+        const int64_t at_once = light ? 3 * cus : cus;
+        const double rounds = (double)((n * pairs + at_once - 1) / at_once), keys = 32.0 * (double)((steps + n - 1) / n);
+        const double cost = std::max((double)(pairs * S) / (double)cus, 0.8 * rounds * keys) + 100.0 * rounds + (n > 1 ? 150.0 + 20.0 * (double)((n + 15) / 16) : 0.0) - (light ? 20.0 : 0.0);
         if (n == 1 || cost < least) {
             best = (int)n;
             least = cost;
@@ -429,9 +437,7 @@ hipError_t launch_decode(int dtype, int D, const void* q, const void* k, const v
                                               ((heads * nsplit * D * sizeof(float) + 255) & ~(size_t)255));
     }
     const dim3 grid(nsplit, Hkv, B), block(kDecWaves * 64);
-    // steps of a split at most (lens may say anything up to a full cache)
-    const int64_t steps = ((lens ? cap : std::min(S, cap)) + 31) / 32;
-    const bool one = (steps + nsplit - 1) / nsplit <= kDecWaves;
+    const bool one = light_form(decode_longest(lens, S, cap), nsplit);
     auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, st, A); };
     if (dtype == 0 && D == 128) one ? launch(decode_attn<dec_bf16, 128, true>) : launch(decode_attn<dec_bf16, 128, false>);
     else if (dtype == 0 && D == 64) one ? launch(decode_attn<dec_bf16, 64, true>) : launch(decode_attn<dec_bf16, 64, false>);

@@ -242,7 +242,9 @@ hipError_t launch_hit_rate(int dtype, int D, const void* q, const void* k, int64
 // A split launch has at most kDecodeMaxGroups workgroups, which bounds the scratch any call can need.
 constexpr int64_t kDecodeMaxGroups = 1024;
 constexpr size_t kDecodeScratchBytes = (size_t)kDecodeMaxGroups * 16 * (128 * sizeof(float) + sizeof(float2)) + 512;
-int decode_splits(int B, int Hkv, int64_t S);
+// The longest sequence a step can meet (lens may say anything up to a full cache).
+inline int64_t decode_longest(const int32_t* lens, int64_t S, int64_t cap) { return lens ? cap : (S < cap ? S : cap); }
+int decode_splits(int B, int Hkv, int64_t S, int64_t longest);
 size_t decode_scratch_bytes(int B, int Hq, int D, int nsplit);
 hipError_t launch_decode(int dtype, int D, const void* q, const void* k, const void* v, const int32_t* lens,
                          int B, int Hq, int Hkv, int64_t S, int64_t cap, int nsplit, void* scratch,

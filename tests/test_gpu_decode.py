@@ -7,6 +7,8 @@ exponential), the probabilities enter the last product split into two storage-ty
 |gpu - oracle| <= 1e-4 * max|v| leaves a factor of about three over the sum of those terms; the lse
 is compared to 1e-4 absolute.
 """
+import json
+
 import numpy as np
 import pytest
 import torch
@@ -110,6 +112,40 @@ def test_lens_beyond_the_step_count_of_S(snapkv):
     case["lens"] = torch.tensor([3000, 2999], dtype=torch.int32, device="cuda")
     out, lse = run(snapkv, w, case)
     check(w, case, out, lse)
+
+
+def launched(call, tmp_path):
+    """(name, workgroups) of the kernels that a call launches."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    p.export_chrome_trace(str(tmp_path / "trace.json"))
+    events = json.loads((tmp_path / "trace.json").read_text())["traceEvents"]
+    return [(e["name"], int(np.prod(e["args"]["grid"]))) for e in events if e.get("cat") == "kernel"]
+
+
+@pytest.mark.parametrize("B,Hkv,S,cap,light", [
+    (1, 32, 2048, 2560, False), (3, 8, 2048, 2300, False), (5, 8, 1500, 1900, False), (3, 32, 1024, 1536, False),
+    (1, 32, 2048, 2049, False), (1, 32, 2040, 2048, True), (1, 8, 4000, 4096, True)])
+def test_splits_are_those_of_the_form_that_runs(snapkv, tmp_path, B, Hkv, S, cap, light):
+    """With lens given, sequences may be as long as the cache, and the light form (one step a wave) runs only where even such
+    a one has no more.  The other form has one workgroup per compute unit where the pairs leave room; the light form
+    takes as many splits as for lens = NULL."""
+    w = DecodeWorkload("form", B=B, Hq=32, Hkv=Hkv, D=128, S=S, cap=cap, ragged=True, seed=37)
+    case = workloads.generate_decode(w, device="cuda")
+    out, lse = run(snapkv, w, case)                              # (allocates the partials' buffer)
+    check(w, case, out, lse)
+    kernels = launched(lambda: run(snapkv, w, case, with_lse=False), tmp_path)
+    (name, groups), = [(n, g) for n, g in kernels if "decode_attn<" in n]
+    assert ("true>" in name) == light, name
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if light:
+        plain = launched(lambda: run(snapkv, w, dict(case, lens=None), with_lse=False), tmp_path)
+        assert (name, groups) in plain
+    else:
+        assert groups <= cus, (name, groups)
 
 
 def test_empty_sequence_and_length_clamp(snapkv):
