@@ -65,14 +65,18 @@ def narrow(q, k):                   # a stretch of scores within one bin, far ab
 
 
 @pytest.mark.parametrize("field", [as_drawn, narrow], ids=lambda f: f.__name__)
-@pytest.mark.parametrize("L", [9001, 83985, 84008, 131072, 165904, 165921])
-def test_exchange_of_candidates(snapkv, field, L):
-    """One head's workgroups exchange 64 words each (up to 40 workgroups of 2048 positions), 32 (up to 80) or go the general
-    way; so does a head one of whose workgroups has more candidates than words."""
+@pytest.mark.parametrize("L,groups,heads", [
+    (9001, 4, 1), (83983, 40, 1), (83985, 41, 1), (84008, 41, 1), (131072, 63, 1), (165903, 80, 1), (165904, 81, 1), (165921, 81, 1),
+    (83983, 40, 3), (83984, 41, 3), (165903, 80, 3), (165904, 81, 3)])
+def test_exchange_of_candidates(snapkv, field, L, groups, heads):
+    """One head's workgroups exchange 64 words each (up to 40 workgroups), 32 (up to 80) or go the general way; so does a head
+    one of whose workgroups has more candidates than words.  40 and 80 workgroups fill a head's words to the last, and
+    the next head's bins follow them."""
+    assert (L - 16) // 2048 == groups               # a workgroup for every 2048 positions
     gen = torch.Generator(device="cuda")
     gen.manual_seed(L)
-    q = torch.randn((1, 16, D), generator=gen, device="cuda")
-    k = torch.randn((1, L, D), generator=gen, device="cuda")
+    q = torch.randn((heads, 16, D), generator=gen, device="cuda")
+    k = torch.randn((heads, L, D), generator=gen, device="cuda")
     field(q, k)
     q, k = q.bfloat16(), k.bfloat16()
     for C in (216, 1016):
