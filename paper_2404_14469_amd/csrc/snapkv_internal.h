@@ -94,7 +94,8 @@ struct SelectScratch {
     // in `cand` above; the first two arrays are contiguous and must be zero when the kernel starts
     // (ps_zero_words words from ps_arrive)
     unsigned* ps_arrive;   // [H][8]        arrival counters of the group-wide rendezvous points
-    unsigned* ps_hist;     // [H][6144]     digit histograms, one per refinement level
+    unsigned* ps_hist;     // [H][6144]     digit histograms, one per refinement level; where a head needs only the first, its
+                           //               workgroups exchange candidates in the words of the others (zero: not written)
     unsigned* ps_part;     // [H][512][2]   per-workgroup (#above the threshold bin, #inside it)
     int64_t ps_zero_words;
     unsigned* ps_flag;     // null, or a word of the call's scratch that is set when a bounded wait gives up

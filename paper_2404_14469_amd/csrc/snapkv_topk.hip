@@ -521,8 +521,8 @@ __global__ __launch_bounds__(256) void sel_emit(const float* __restrict__ score,
 //
 // Microseconds after the scoring, before (pool_group4, sel_hist, sel_compact, sel_threshold, sel_emit and the counters
 // they start from) and now: 1024 heads of 131040 positions 693 / 239, 32 heads of 379984 positions 83 / 52, 256 heads in
-// groups of four of 31305 positions 103 / 82.  pool_collect is bound by its vector instructions: with the kind of pooling asked
-// at every tap and maxima that shared nothing it took 174, 21 and 44 of these, now 126 (537 MB, 4.3 TB/s), 16 and 31.
+// groups of four of 31305 positions 103 / 82.  pool_collect was bound by its vector instructions while the kind of pooling was
+// asked at every tap and maxima shared nothing: 174, 21 and 44 of these, now 126 (537 MB, 4.3 TB/s), 16 and 31.
 // ------------------------------------------------------------------------------------------------
 constexpr int kPickSamples = 2048;
 constexpr int kPickShift = 17;         // digits of 1/64 octave
@@ -830,18 +830,23 @@ static hipError_t pool_pick(const ScoreGeom& G, const float* vote, int pool_kind
 
 // Where the votes are read once instead of storing the scores.  What is saved grows with the scores of all heads;
 // what is spent is a workgroup per head that passes over its candidates (a little more than kcount) several times, 512
-// heads at a time, a wave per chunk of 4096 positions.  In nanoseconds, fitted to 800 measured shapes of 4 to 2048 heads
-// and 8200 to 16000000 positions so that this path is not taken where it is slower; in doubt (a quarter and more of the
-// positions kept) the separate kernels are.  Of prompts too short to be sampled, whose positions are all candidates, only
-// the shortest come here.  Microseconds of pooling and selection, this path / the separate kernels (max pooling, p = 5),
-// at kcount = 1008, n / 8 and n / 2:
-//   1024 heads of 8200: 75 / 99, 76 / 99, 140 / 101;  31336: 104 / 196, 135 / 199, 277 / 205;
-//   131072: 238 / 660, 387 / 676, 983 / 700;
-//   512 heads of 20000: 53 / 91, 60 / 92, 112 / 95;  32 heads of 380000: 57 / 87, 120 / 99, 363 / 146;
-//   8 heads of 1000000: 77 / 69, 234 / 103;  1024 heads in groups of four, 31336: 223 / 268, 252 / 271, 365 / 279;
-// without a sample:
-//   512 heads of 200: 29 / 38;  1000: 37 / 40;  2000: 50 / 43;
-//   1024 heads of 200: 46 / 57;  600: 54 / 58;  1000: 61 / 60;  2000: 87 / 67;  4096: 141 / 76;  7984: 221 / 104
+// heads at a time, a wave per chunk of 4096 positions.  In nanoseconds; the constants were fitted (800 shapes of 4 to 2048
+// heads and 8200 to 16000000 positions) to the kernels that pooled every position by itself, and both sides have become
+// faster since.  As they are now, of 900 random shapes between 0.4 and 4 times the line (1 to 8 query heads a KV head,
+// p from 1 to 13, both poolings) 527 come here, 24 of them slower than with the separate kernels, by 9 % on average: with
+// two fifths of the positions kept (575 heads of 42201, 16591 kept: 1.28 times) and with eight query heads (512 heads of 20823:
+// 1.19).  Of the other 373 this path would be faster for 109.  Over all of them the rule's times are 1.9 % above the
+// better choice's; a linear fit to the new times comes to 0.9 % but is wrong by up to 1.43 times.
+// Of prompts too short to be sampled, whose positions are all candidates, only the shortest come here.
+// Microseconds of pooling and selection, this path / the separate kernels (max pooling, p = 5), at kcount = 1008,
+// n / 8 and n / 2:
+//   1024 heads of 8200: 66 / 86, 66 / 84, 132 / 85;  31336: 84 / 176, 119 / 179, 265 / 186;
+//   131072: 185 / 627, 352 / 651, 938 / 673;
+//   512 heads of 20000: 45 / 83, 53 / 84, 107 / 87;  32 heads of 380000: 50 / 84, 120 / 93, 364 / 134;
+//   8 heads of 1000000: 70 / 67, 228 / 107;  1024 heads in groups of four, 31336: 193 / 239, 230 / 242, 370 / 250;
+// without a sample (n / 4):
+//   512 heads of 200: 24 / 32;  1000: 33 / 34;  2000: 47 / 36;
+//   1024 heads of 200: 37 / 44;  600: 46 / 45;  1000: 54 / 47;  2000: 82 / 53;  4096: 136 / 62;  7984: 215 / 91
 bool pool_pick_ok(const ScoreGeom& G, int p, int64_t kcount) {
     if (!((p == 1 || p == 5 || p == 7 || p == 13) && G.n >= 1 && kcount >= 1 && kcount <= G.n && (G.vpitch & 3) == 0 &&
           select_chunked_ok(G.n) && G.Hkv <= 65535))
@@ -885,7 +890,10 @@ hipError_t launch_pool_pick(const ScoreGeom& G, const float* vote, int pool_kind
 // Bound by its chain of dependent steps, not by bytes: with the two exchanges at rendezvous points (hand over and wait,
 // barrier, count in, poll the counter, read the data: 2.4 and 6 us of 21 at 28471 positions) and prefix sums through
 // LDS permutes a call of 512 keys, fp32, 4 heads took 28.7 us, now 26.0; 16384 keys, 32 heads 58.1, now 52.8; 28471 keys,
-// 32/8 heads 64.6, now 57.5; 13339 paged keys 42.0, now 37.2; 131072 keys, W = 64 213.1, now 206.5.  Steps it
+// 32/8 heads 64.6, now 57.5; 13339 paged keys 42.0, now 37.2; 131072 keys, W = 64 217.7, now 209.0 (with four heads staged at
+// a time).  All threads poll, without pauses; work on another stream does not suffer (us a call and a piece of the other
+// work, with rendezvous points / now): 28471 keys beside copies of 1 GiB 124 + 659 / 109 + 632, 16384 keys beside matrix
+// products of 4096 161 + 121.5 / 154 + 120.7, 131072 keys beside copies of 4 MiB 161 + 7.0 / 155 + 6.7.  Steps it
 // lost before: the exchange of the head's range (the first digit is fixed), a memory latency and a barrier per query head of a
 // group (four heads staged at a time), element-wise loads where the prefix is no
 // multiple of four (rows are padded), digit rounds over at most 128 candidates, and for a head with one workgroup
