@@ -162,7 +162,7 @@ hipError_t launch_score_fused(int dtype, int D, const void* q, const void* k, co
 // hipErrorCooperativeLaunchTooLarge when this form of the kernel cannot keep the plan's grid resident.
 hipError_t launch_score_fused_layers(int dtype, int D, const ScoreLayers& SL, const ScoreGeom& G, const FusedGeom& F,
                                      const FusedSync& S, float* vote, hipStream_t st, bool probe_only = false);
-// The two-pass kernels for KV heads met by 128 or more window rows (snapkv_wide.hip): two-byte element types,
+// The two-pass kernels for KV heads met by 128 or more window rows, or by 64 of a very long prompt (snapkv_wide.hip): two-byte element types,
 // windows of at most 128 rows.  One vote row per query head, whatever the window.  Up to kMaxWide prompts or
 // layers of one model share the two launches (equal heads, window, row stride); paged K: one only.
 constexpr int kMaxWide = 32;

@@ -4,13 +4,14 @@
 // The single-read kernel (snapkv_fused.hip) keeps every exponential in registers until its row's normaliser
 // is known, so a wave holds 32 rows x 64 keys, a KV head with 128 window rows is cut into four parts, every part
 // streams the head's keys through the compute units again, and two thirds of the vector instructions go to the
-// row maxima, hand-offs and votes of only 64 keys.  Here nothing is kept: all 128 rows of a block meet every key
+// row maxima, hand-offs and votes of only 64 keys.  Here nothing is kept: all rows of a block meet every key
 // of a round while it is on chip, first for the row statistics (wide_stats), then, once these are merged, for
 // the votes (wide_votes).  K is read from memory once per pass whatever the number of query heads, and a logit
 // costs a multiply-add, an exponential and an addition (or a multiply-add) per pass.
 //
-//   * The window rows of a KV head form blocks of whole query heads, at most eight 16-row units each; a unit of
-//     work is one block.  A wave owns 32 of the block's rows, its Q in registers as MFMA fragments.
+//   * The window rows of a KV head form blocks of whole query heads, at most eight 16-row units each, or four where the
+//     KV head has no more (RUW); a unit of work is one block.  A wave owns 32 of the block's rows, its Q in registers as
+//     MFMA fragments.
 //   * The keys of a unit are cut into at most 64 slices of RPS rounds of 128 keys, or into up to 256 if the prompt has
 //     fewer than four units.  The slice length depends on the prompt's length and its own heads alone, so a head's
 //     result does not depend on which other layers or prompts share the launch.
@@ -30,7 +31,7 @@
 // head): 97 + 103 us against 277 us.
 //
 // The row reference.  Exponentials are taken relative to a reference of the row that is known before its keys are: its
-// largest logit among the prompt's first four keys.  The argument s - ref is rounded to fp32, so the terms that matter
+// largest logit among the prompt's first four keys (sixteen where a block has 64 rows).  The argument s - ref is rounded to fp32, so the terms that matter
 // must not lie far from the reference: a round in which a row's logits exceed it by about 2^kRaiseAt raises the row's
 // reference to its largest logit less kRaiseBelow for the rest of the slice and takes its exponentials again, and
 // wide_votes uses the largest of the slices' references.  Normally distributed logits get there at 4.5 standard
@@ -39,7 +40,11 @@
 // against float64 (2-norm, 1e-8; 18461 keys, 32/8 heads, 32 rows), single-read kernel / a reference that stays at the
 // first key's logit / as it is: logits N(0, 1.8 nats) 12.2 / 12.6 / 12.3; with 40 keys 6, 20 and 40 nats above those
 // 12.1 / 11.9 / 10.6, 15.8 / 17.5 / 15.2 and 28.1 / 34.5 / 28.0.  Checking and raising cost 0.8 of 64 us per call at
-// 28471 keys, 0.5 of 67 at 32749 and nothing measurable at 131072.
+// 28471 keys, 0.5 of 67 at 32749 and nothing measurable at 131072.  Blocks of 64 rows, 140001 keys, logits N(0, s) with
+// clusters, mean of four draws, front and rest of the single-read kernel / first four keys / first sixteen: W = 16, four query
+// heads, s = 0.9, 1.8 and 3.6 nats 5.5 / 5.4 / 5.3, 16.4 / 18.3 / 17.4 and 42.6 / 43.0 / 43.1 (of single votes near the
+// selection's threshold 5.4 / 5.4 / 5.3, 12.4 / 12.8 / 12.2, 46.2 / 46.3 / 46.6); W = 64, one query head 23.8 / 5.2 / 5.1,
+// 27.2 / 11.2 / 10.9 and 52.9 / 30.5 / 30.3.
 //
 // MFMA layout: that of snapkv_fused.hip (16x16x32, lane l: row / column l % 16, contraction slice l / 16;
 // accumulator register r is row (l / 16) * 4 + r, column l % 16; the 16-byte pieces 4p + l / 16 of a row).
@@ -63,7 +68,6 @@ constexpr int kRound = kWaves * 16;          // keys of a round: every wave brin
 constexpr int kSlices = 64;                  // slices per unit at most,
 constexpr int kPlaces = 256;                 //   or as many as give a prompt of few units this many in all
 constexpr int kWaveRows = 2;                 // 16-row units of a wave
-constexpr int RUW = 8;                       // 16-row units of a block
 constexpr float kRaiseAt = 0x1p16f;          // exponential (of a lane's sum) from which a row's reference is raised,
 constexpr float kRaiseMin = 8.f;             //   by rows whose largest logit lies this far above it (base two),
 constexpr float kRaiseBelow = 7.f;           //   to that logit less this
@@ -77,9 +81,17 @@ constexpr float kRaiseBelow = 7.f;           //   to that logit less this
 //   1 head: 18439 keys 40 / 41 / 39;  46087: 45 / 50 / 43;  131072: 55 / 80 / 53;  700001: 313 / 292 / 116
 //   2 heads: 27655: 46 / 46 / 42;  131072: 77 / 85 / 66;  32 layers of 1 head, 31337: 196 / 144 / 151
 // (with 512 in all: 1 head, 46087: 55, 131072: 67; 2 heads, 27655: 52)
-// With 64 rows (W = 16 there, or W = 64 and a head each) the single-read kernel is faster at every length but the
-// few that leave it compute units idle, so those do not come here.
 constexpr int64_t kMinRowKeys = 9 << 18;
+// With 64 rows the single-read kernel is faster by about a fifth while it holds the prompt (131072 keys); of a longer one it
+// takes the front, the rest is read twice by the streaming kernel.  Microseconds per call, this path / front and rest:
+//   W = 16, 32/8 heads:  131073 keys 128 / 274;  140001: 150 / 283;  175001: 185 / 287;  262144: 250 / 348;  380000: 356 / 509
+//   W = 64, 32/32 heads: 131073: 463 / 758;  140001: 502 / 782;  175001: 603 / 827;  262144: 848 / 1177;  300001: 981 / 1390
+//   one KV head, W = 16 and 64: 132000: 45 / 58, 48 / 75;  1000001: 144 / 268, 149 / 328
+//   (as far as it holds them: W = 16, 65536: 80 / 67, 131072: 125 / 112;  W = 64, 32768: 125 / 103, 131072: 443 / 374)
+// A window of two row units and two query heads a KV head is streamed better there: W = 32, 32/16 heads
+//   131073: 249 / 239;  150001: 285 / 273;  160001: 298 / 290;  170001: 313 / 344;  262144: 440 / 589;  with four KV heads
+//   131073: 76 / 95,  170001: 89 / 120.
+constexpr int64_t kMinRowKeys64 = (1 << 23) + 64, kMinRowKeys64of2 = 5 << 21;
 constexpr int64_t kMaxRounds = 1 << 26;      // rounds of one prompt at most (kMaxWide of them are counted in 32 bits)
 
 template <int D> struct KFrag {
@@ -245,13 +257,13 @@ template <int N> __device__ __forceinline__ bool advance(const WideArgs<N>& A, C
 }
 
 // The workgroup's waves, lanes and K stream; shared by both passes.
-template <typename T, int D, bool PAGED, int N> struct WideWave {
+template <typename T, int D, bool PAGED, int N, int RUW> struct WideWave {   // RUW: 16-row units of a block, 8 or 4
     static constexpr int NP = KFrag<D>::NP;
     static constexpr int R = RUW * 16;
     static constexpr int GROUPS = RUW / kWaveRows;      // groups of 32 window rows
     static constexpr int PARTS = kWaves / GROUPS;       // parts of a round's keys; a wave meets one part with one group
     static constexpr int TILES = kWaves / PARTS;        // 16-key tiles of a part
-    static_assert(TILES == 4, "the exchange of the votes is written for four tiles");
+    static_assert(TILES == 4 || TILES == 2, "the exchange of the votes is written for these");
     const WideArgs<N>& A;
     const int tid, lane, n16, kg, w, rg, kp;
     // paged K: the page id the next request uses, asked for one round ahead of it
@@ -339,11 +351,12 @@ template <typename T, int D, bool PAGED, int N> struct WideWave {
     }
 };
 
-template <typename T, int D, bool PAGED, int N>
+template <typename T, int D, bool PAGED, int N, int RUW>
 __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
-    using Wv = WideWave<T, D, PAGED, N>;
+    using Wv = WideWave<T, D, PAGED, N, RUW>;
     constexpr int R = Wv::R, TILES = Wv::TILES, PARTS = Wv::PARTS;
     __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];                      // K of two rounds as MFMA fragments
+    constexpr int kFirst = RUW == 8 ? 4 : 16;
     enum { kBase, kRef, kSum = kRef + 2, kStatArrays = kSum + 2 };        // per part and row: the references at a slice's
     __shared__ __attribute__((aligned(16))) float sm_st[kStatArrays][PARTS][R];   // start, two slices' references and their sums
     Wv W(A);
@@ -358,13 +371,14 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     KFrag<D> q[kWaveRows], S;
     float z[kWaveRows][4], ref[kWaveRows][4];
 
-    // A unit begins: the wave's Q rows, and the rows' references from the prompt's first four keys (or fewer: those that
-    // every row sees; each quad of lanes brings all four).  They depend on the unit alone, and every slice starts from
+    // A unit begins: the wave's Q rows, and the rows' references from the prompt's first kFirst keys (or fewer: those that
+    // every row sees; each quad, or row, of lanes brings all of them).  They depend on the unit alone, and every slice starts from
     // them, so a slice's result does not depend on which slices its workgroup had before.
     float* const my = &sm_st[kBase][W.kp][W.rg * kWaveRows * 16 + W.kg * 4];   // from the lane's first row on
     auto ask_unit = [&](KFrag<D>& f) __attribute__((always_inline)) {
         W.load_q(q, cc);
-        W.load_row(f, cc, W.row_of(cc, (W.n16 & 3) < cc.n ? (W.n16 & 3) : cc.n));
+        const int j = W.n16 & (kFirst - 1);
+        W.load_row(f, cc, W.row_of(cc, j < cc.n ? j : cc.n));
     };
     auto begin_unit = [&](const KFrag<D>& f) __attribute__((always_inline)) {
 #pragma unroll
@@ -372,8 +386,14 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
             const wf32x4 a = logits16<T, D>(q[i], f);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                float m = fmaxf(a[r], wdpp<0xB1>(a[r]));
-                m = fmaxf(m, wdpp<0x4E>(m)) * A.c2;
+                float m = a[r];
+                if constexpr (kFirst == 16) {
+                    m = lanes16_max(m);
+                } else {
+                    m = fmaxf(m, wdpp<0xB1>(m));
+                    m = fmaxf(m, wdpp<0x4E>(m));
+                }
+                m *= A.c2;
                 ref[i][r] = m == -INFINITY ? 0.f : m;
                 z[i][r] = 0.f;
             }
@@ -509,9 +529,9 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     store_slice(par ^ 1);                // (a workgroup's share ends with a slice)
 }
 
-template <typename T, int D, bool PAGED, int N>
+template <typename T, int D, bool PAGED, int N, int RUW>
 __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
-    using Wv = WideWave<T, D, PAGED, N>;
+    using Wv = WideWave<T, D, PAGED, N, RUW>;
     constexpr int R = Wv::R, TILES = Wv::TILES, SUB = kThreads / R;   // SUB threads share a row in the merge of its slices
     __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];
     __shared__ float sm_v[2][RUW][kRound];                            // sums over the rows of a row unit, per key
@@ -623,10 +643,15 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
             const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
             return __uint_as_float(x[0]) + __uint_as_float(x[1]);
         };
+        if constexpr (TILES == 4) {
 #pragma unroll
-        for (int i = 0; i < kWaveRows; ++i) {
-            float* dst = &sm_v[half][W.rg * kWaveRows + i][W.kp * (TILES * 16)];
-            dst[((W.kg >> 1) + 2 * (W.kg & 1)) * 16 + W.n16] = quarters(halves(v[i][0], v[i][1]), halves(v[i][2], v[i][3]));
+            for (int i = 0; i < kWaveRows; ++i) {
+                float* dst = &sm_v[half][W.rg * kWaveRows + i][W.kp * (TILES * 16)];
+                dst[((W.kg >> 1) + 2 * (W.kg & 1)) * 16 + W.n16] = quarters(halves(v[i][0], v[i][1]), halves(v[i][2], v[i][3]));
+            }
+        } else {                         // the wave's two row units share them too
+            sm_v[half][W.rg * kWaveRows + (W.kg & 1)][W.kp * (TILES * 16) + (W.kg >> 1) * 16 + W.n16] =
+                quarters(halves(v[0][0], v[0][1]), halves(v[1][0], v[1][1]));
         }
         const WideEntry& E = A.e[cc.e];
         const int h0 = cc.blk * A.hb;
@@ -644,12 +669,14 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
 }
 
 struct Blocks {
-    int UH, hb, nblk;
+    int ru, UH, hb, nblk;                // 16-row units of a block (8 or 4) and of a query head, query heads of a block, blocks
 };
 bool row_blocks(const ScoreGeom& G, Blocks* b) {
     b->UH = (G.W + 15) / 16;
-    if (b->UH > RUW || G.g * b->UH < RUW) return false;   // (at least 128 window rows per KV head)
-    const int most = std::min(G.g, RUW / b->UH);
+    const int units = G.g * b->UH;
+    if (b->UH > 8 || (units < 8 && units != 4)) return false;   // (64 window rows per KV head, or at least 128)
+    b->ru = units == 4 ? 4 : 8;
+    const int most = std::min(G.g, b->ru / b->UH);
     b->nblk = (G.g + most - 1) / most;
     b->hb = (G.g + b->nblk - 1) / b->nblk;   // blocks of about equal size
     return true;
@@ -678,21 +705,24 @@ int wide_cus() {
     return cached[dev];
 }
 
-template <typename T, int D, bool PAGED, int N>
+template <typename T, int D, bool PAGED, int N, int RUW>
 hipError_t launch_both(const WideArgs<kMaxWide>& all, dim3 grid, hipStream_t st) {
     WideArgs<N> A;
     A.count = all.count, A.direct = all.direct, A.g = all.g, A.W = all.W, A.UH = all.UH, A.hb = all.hb, A.nblk = all.nblk, A.inv_uh = all.inv_uh;
     A.c2 = all.c2, A.k_rs = all.k_rs, A.table = all.table, A.page = all.page, A.pages = all.pages, A.row0 = all.row0;
     A.rounds = all.rounds, A.share = all.share, A.more = all.more, A.zeros = all.zeros, A.nzeros = all.nzeros, A.flag = all.flag;
     for (int i = 0; i < N; ++i) A.e[i] = all.e[i];
-    hipLaunchKernelGGL((wide_stats<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
-    hipLaunchKernelGGL((wide_votes<T, D, PAGED, N>), grid, dim3(kThreads), 0, st, A);
+    hipLaunchKernelGGL((wide_stats<T, D, PAGED, N, RUW>), grid, dim3(kThreads), 0, st, A);
+    hipLaunchKernelGGL((wide_votes<T, D, PAGED, N, RUW>), grid, dim3(kThreads), 0, st, A);
     stage_done(st, kStageWide);    // (both launches)
     return hipGetLastError();
 }
-template <typename T, int D> hipError_t by_entries(const WideArgs<kMaxWide>& A, dim3 grid, hipStream_t st) {
-    if (A.count > 1) return launch_both<T, D, false, kMaxWide>(A, grid, st);
-    return A.table ? launch_both<T, D, true, 1>(A, grid, st) : launch_both<T, D, false, 1>(A, grid, st);
+template <typename T, int D, int RUW> hipError_t by_entries(const WideArgs<kMaxWide>& A, dim3 grid, hipStream_t st) {
+    if (A.count > 1) return launch_both<T, D, false, kMaxWide, RUW>(A, grid, st);
+    return A.table ? launch_both<T, D, true, 1, RUW>(A, grid, st) : launch_both<T, D, false, 1, RUW>(A, grid, st);
+}
+template <typename T, int D> hipError_t by_rows(const WideArgs<kMaxWide>& A, int ru, dim3 grid, hipStream_t st) {
+    return ru == 4 ? by_entries<T, D, 4>(A, grid, st) : by_entries<T, D, 8>(A, grid, st);
 }
 
 }  // namespace
@@ -701,10 +731,10 @@ template <typename T, int D> hipError_t by_entries(const WideArgs<kMaxWide>& A, 
 // holds anyway (a region of the streaming passes, or the pooled scores that come later), a head at a time so that
 // the answer does not depend on how many heads a call has.
 static bool wide_shape(const ScoreGeom& G, Blocks* b) {
-    if (G.n <= 0 || !row_blocks(G, b) || (int64_t)G.g * b->UH * 16 * G.L < kMinRowKeys) return false;
+    if (G.n <= 0 || !row_blocks(G, b) || (int64_t)G.g * b->UH * 16 * G.L < (b->ru == 8 ? kMinRowKeys : b->UH == 2 ? kMinRowKeys64of2 : kMinRowKeys64)) return false;
     ScoreGeom one = G;
     one.Hkv = 1;
-    const size_t part = sizeof(float2) * (size_t)b->nblk * slices_of(G, *b) * RUW * 16;
+    const size_t part = sizeof(float2) * (size_t)b->nblk * slices_of(G, *b) * b->ru * 16;
     return part <= std::max(stream_stat_bytes(one), sizeof(float) * (size_t)G.g * (size_t)G.n);
 }
 
@@ -717,7 +747,7 @@ bool wide_ok(int dtype, int D, const ScoreGeom& G) {
 size_t wide_part_bytes(const ScoreGeom& G) {
     Blocks b;
     if (!wide_shape(G, &b)) return 0;
-    return (sizeof(float2) * (size_t)G.Hkv * b.nblk * slices_of(G, b) * RUW * 16 + 255) & ~(size_t)255;
+    return (sizeof(float2) * (size_t)G.Hkv * b.nblk * slices_of(G, b) * b.ru * 16 + 255) & ~(size_t)255;
 }
 
 hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st, const WideClear& clear) {
@@ -771,8 +801,8 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
     const dim3 grid = A.direct ? dim3((unsigned)A.e[0].NS, (unsigned)b.nblk, (unsigned)G0.Hkv) : dim3((unsigned)std::min(slices, places));
     A.share = A.rounds / grid.x;         // (of a launch with a grid of one dimension)
     A.more = A.rounds % grid.x;
-    if (dtype == 0) return D == 128 ? by_entries<w_bf16, 128>(A, grid, st) : by_entries<w_bf16, 64>(A, grid, st);
-    return D == 128 ? by_entries<w_f16, 128>(A, grid, st) : by_entries<w_f16, 64>(A, grid, st);
+    if (dtype == 0) return D == 128 ? by_rows<w_bf16, 128>(A, b.ru, grid, st) : by_rows<w_bf16, 64>(A, b.ru, grid, st);
+    return D == 128 ? by_rows<w_f16, 128>(A, b.ru, grid, st) : by_rows<w_f16, 64>(A, b.ru, grid, st);
 }
 
 }  // namespace snapkv

@@ -1,5 +1,5 @@
 """Prompts whose KV heads are met by 128 window rows or more, long enough for the two-pass scoring kernels
-(csrc/snapkv_wide.hip): edges of rounds (128 keys), of slices (multiples of 128 keys, at most 64 of them) and of the
+(csrc/snapkv_wide.hip), or by 64 and longer than the single-read kernel holds: edges of rounds (128 keys), of slices (multiples of 128 keys, at most 64 of them) and of the
 row blocks (128 rows, whole query heads), every storage type and layout, and rows whose sums leave the fp32 range."""
 import numpy as np
 import pytest
@@ -47,6 +47,63 @@ def test_against_oracle(snapkv, name):
     case = workloads.generate(w, device="cuda")
     res = run_gpu(snapkv, case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C)
     check_against_oracle(case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C, *res)
+
+
+# 64 window rows per KV head: blocks of four row units, prompts longer than 131072 keys
+HALF = {
+    "w16_first": dict(L=131073, g=4, W=16),                # the shortest; one key in the last round
+    "w13_padded_rows": dict(L=131072 + 129, g=4, W=13, pool_kind=1, p=5),
+    "w64_one_head": dict(L=131073 + 126, g=1, W=64, Hkv=2, p=13),
+    "w50_padded_unit": dict(L=140001, g=1, W=50),          # the fourth row unit holds two rows
+    "w32_two_heads": dict(L=163840, g=2, W=32),            # the shortest of this form
+    "d64_f16": dict(L=131075, g=4, W=16, D=64, dtype="f16", Hkv=2),
+    "five_heads": dict(L=132001, g=4, W=16, Hkv=5, C=5000),   # 64 slices per head
+}
+
+
+def half(L, g, W, Hkv=1, **kw):
+    return work(1 << 20, 8, 16, **{"C": 1500, **kw}).with_(L=L, Hq=g * Hkv, Hkv=Hkv, W=W)
+
+
+@pytest.mark.parametrize("name", sorted(HALF))
+def test_64_rows_against_oracle(snapkv, name):
+    w = half(**HALF[name])
+    case = workloads.generate(w, device="cuda")
+    res = run_gpu(snapkv, case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C)
+    check_against_oracle(case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C, *res, heads=[w.Hkv - 1])
+
+
+def test_64_rows_layers_and_batches_equal_single_calls(snapkv):
+    """Stacked and separate layers, paged rows and a batch with prompts on both sides of the rule, bit for bit."""
+    w = half(131100, 4, 16, Hkv=2)
+    cases = [workloads.generate(w, layer=l, device="cuda") for l in range(2)] + [workloads.generate(w.with_(L=9001), device="cuda")]
+    want = [run_gpu(snapkv, c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C) for c in cases]
+    lists = [[c[n] for c in cases[:2]] for n in ("q_win", "k", "v")]
+    for stack in (False, True):
+        oks, ovs, ois = outputs(w, 2, cases[0]["k"].dtype)
+        if stack:
+            lists = [list(torch.stack(x).contiguous()) for x in lists]
+            oks, ovs, ois = (list(torch.stack(x).contiguous()) for x in (oks, ovs, ois))
+        snapkv.snapkv_compress_layers(*lists, w.pool_kind, w.p, w.C, oks, ovs, ois)
+        for l in range(2):
+            assert np.array_equal(ois[l].cpu().numpy(), want[l][3]) and torch.equal(oks[l], want[l][1]), (l, stack)
+    oks, ovs, ois = outputs(w, 3, cases[0]["k"].dtype)
+    snapkv.snapkv_compress_varlen(*([c[n] for c in cases] for n in ("q_win", "k", "v")), w.pool_kind, w.p, w.C, oks, ovs, ois)
+    for i in range(3):
+        assert np.array_equal(ois[i].cpu().numpy(), want[i][3]) and torch.equal(oks[i], want[i][1]), i
+    q, k, v = (cases[0][n] for n in ("q_win", "k", "v"))
+    page, pages = 16, -(-w.L // 16)
+    table = torch.randperm(pages, generator=torch.Generator().manual_seed(3)).to(torch.int32).cuda()
+    pos = torch.arange(w.L, device="cuda")
+    paged = []
+    for t in (k, v):
+        cache = torch.zeros((pages, page, w.Hkv, w.D), dtype=t.dtype, device="cuda")
+        cache[table.long()[pos // page], pos % page] = t.permute(1, 0, 2)
+        paged.append(cache)
+    ok, ov, oi = (t[0] for t in outputs(w, 1, k.dtype))
+    snapkv.snapkv_compress_paged(q, *paged, table, w.L, w.pool_kind, w.p, w.C, ok, ov, oi)
+    assert np.array_equal(oi.cpu().numpy(), want[0][3])
+    assert torch.equal(ok, want[0][1]) and torch.equal(ov, want[0][2])
 
 
 def outputs(w, n, dtype):
