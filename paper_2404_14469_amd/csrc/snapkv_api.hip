@@ -653,7 +653,6 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
     B.Hkv = Hkv;
     for (int i = 0; i < count; ++i) {
         B.L[i] = L[i];
-        B.n[i] = G[i].n;
         B.k[i] = k[i];
         B.v[i] = v[i];
         B.out_k[i] = out_k[i];
@@ -661,9 +660,13 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
         B.out_idx[i] = out_idx[i];
     }
     stage_done(st, kStageBegin);
-    if (launch_prepare(handoff_p, (int64_t)(handoff * count / sizeof(unsigned long long)), &Sb, Htot, st) != hipSuccess)
+    BatchLengths lengths;
+    lengths.count = count;
+    lengths.Hkv = Hkv;
+    lengths.nvalid = nvalid_p;
+    for (int i = 0; i < kMaxBatch; ++i) lengths.n[i] = i < count ? (int32_t)G[i].n : 0;
+    if (launch_prepare(handoff_p, (int64_t)(handoff * count / sizeof(unsigned long long)), &Sb, Htot, st, nullptr, &lengths) != hipSuccess)
         return SNAPKV_ERR_HIP;
-    if (launch_batch_lengths(B, nvalid_p, st) != hipSuccess) return SNAPKV_ERR_HIP;
     stage_done(st, kStagePrepare);
     // scoring: the prompts, longest first, share launches of the single-read kernel as far as they fit
     // the chip together; a prompt that kernel does not take is scored by a launch sequence of its own

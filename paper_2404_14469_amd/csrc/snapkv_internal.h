@@ -195,9 +195,16 @@ size_t select_layout(int H, int64_t n, SelectScratch* S, void* base, bool own_co
                      void* counters = nullptr);
 bool select_chunked_ok(int64_t n);   // rows of up to 4096 x 4096 positions
 hipError_t launch_select_init(const SelectScratch& S, int H, hipStream_t st);
+constexpr int kMaxBatch = 32;   // prompts of a batch
 // flag (may be null): the status word of the call's scratch, cleared too (default: S->ps_flag).
+// lengths (may be null): a batch whose heads' valid prefix lengths the same launch leaves, head h being prompt h / Hkv's.
+struct BatchLengths {
+    int count, Hkv;
+    int32_t n[kMaxBatch];
+    int32_t* nvalid;         // [count * Hkv]
+};
 hipError_t launch_prepare(void* pairs, int64_t npairs, const SelectScratch* S, int H, hipStream_t st,
-                          unsigned* flag = nullptr);
+                          unsigned* flag = nullptr, const BatchLengths* lengths = nullptr);
 int64_t fused_sync_pairs(const FusedGeom& F);
 // allow_blocks: as for fused_plan, taken only where a window has more rows than the plain form tracks
 bool lse_plan(int dtype, int D, const ScoreGeom& G, FusedGeom* F, bool allow_blocks = false);
@@ -289,17 +296,15 @@ struct PageMap {
 };
 // A batch of prompts of one model (same heads, window and capacity, different lengths) whose
 // selection and gather run as one launch each.  Passed by value to the kernels.
-constexpr int kMaxBatch = 32;
 struct BatchDesc {
     int count, Hkv;
-    int64_t L[kMaxBatch], n[kMaxBatch];
+    int64_t L[kMaxBatch];
     const void* k[kMaxBatch];
     const void* v[kMaxBatch];
     void* out_k[kMaxBatch];
     void* out_v[kMaxBatch];
     int32_t* out_idx[kMaxBatch];
 };
-hipError_t launch_batch_lengths(const BatchDesc& B, int32_t* nvalid, hipStream_t st);
 hipError_t launch_gather_batch(const BatchDesc& B, const int32_t* idx, int64_t C, int row_bytes,
                                const CleanJob& clean, hipStream_t st);
 

@@ -308,18 +308,6 @@ __global__ __launch_bounds__(256) void gather_rows_layers(const GatherLayers ly,
     gather_body<4>(nullptr, nullptr, idx, L, rows, out_stride, shift, nullptr, nullptr, kl, vl, 1, PageMap{}, clean, ly);
 }
 
-// Per-head valid prefix lengths of a batch: head h of the batch belongs to prompt h / Hkv.
-__global__ __launch_bounds__(256) void batch_lengths(const BatchDesc B, int32_t* __restrict__ nvalid) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < B.count * B.Hkv) nvalid[i] = (int32_t)B.n[i / B.Hkv];
-}
-
-hipError_t launch_batch_lengths(const BatchDesc& B, int32_t* nvalid, hipStream_t st) {
-    const int items = B.count * B.Hkv;
-    hipLaunchKernelGGL(batch_lengths, dim3((items + 255) / 256), dim3(256), 0, st, B, nvalid);
-    return hipGetLastError();
-}
-
 // gather_rows for a batch: head h of the grid is KV head h % Hkv of prompt h / Hkv; the kept
 // positions come from one [heads, C] array and are also copied to the prompt's own out_idx.
 template <int U>
