@@ -691,12 +691,20 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
     }
     if (nwide > 0 && launch_score_wide(dtype, D, nwide, WP, st) != hipSuccess) return SNAPKV_ERR_HIP;
     std::sort(rest, rest + nrest, [&](int a, int b) { return L[a] != L[b] ? L[a] > L[b] : a < b; });
+    int cut[kMaxBatch], launches = 0, launch = 0;
+    {
+        ScoreGeom Gr[kMaxBatch];
+        for (int r = 0; r < nrest; ++r) Gr[r] = G[rest[r]];
+        if (g_allow_fused) launches = fused_joint_cuts(dtype, D, nrest, Gr, cut);
+    }
     while (nrest > 0) {
         ScoreGeom Gr[kMaxBatch];
         FusedGeom Fr[kMaxBatch];
         for (int r = 0; r < nrest; ++r) Gr[r] = G[rest[r]];
         int take[kMaxJointPrompts], wg_begin[kMaxJointPrompts], grid = 0;
-        const int taken = g_allow_fused ? fused_joint_plan(dtype, D, nrest, Gr, Fr, take, wg_begin, &grid) : 0;
+        const int seen = launch < launches ? cut[launch++] : nrest;
+        const int taken = g_allow_fused ? fused_joint_plan(dtype, D, seen, Gr, Fr, take, wg_begin, &grid) : 0;
+        if (taken != seen) launches = 0;   // (the cuts are of launches that take what they see)
         if (taken == 0) {   // the longest of the rest goes alone
             const int i = rest[0];
             ScoreGeom Gv = G[i];

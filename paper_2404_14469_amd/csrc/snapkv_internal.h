@@ -150,7 +150,10 @@ hipError_t launch_publish_rest(const float2* stat_part, const FusedSync& S, cons
 // (test hook) 0, or the number of workgroups the plans of the single-read kernel may count as resident
 extern int g_fused_slot_cap;
 // Several prompts of one model in one launch of the single-read kernel (snapkv_fused.hip).
+constexpr int kMaxBatch = 32;   // prompts of a batch
 constexpr int kMaxJointPrompts = 8;
+// Cuts a batch into joint launches: the number of launches and how many prompts each takes, or 0 (see its definition).
+int fused_joint_cuts(int dtype, int D, int count, const ScoreGeom* G, int* cut);
 int fused_joint_plan(int dtype, int D, int count, const ScoreGeom* G, FusedGeom* F, int* take, int* wg_begin,
                      int* grid);
 hipError_t launch_score_fused_joint(int dtype, int D, int count, const void* const* q, const void* const* k,
@@ -195,7 +198,6 @@ size_t select_layout(int H, int64_t n, SelectScratch* S, void* base, bool own_co
                      void* counters = nullptr);
 bool select_chunked_ok(int64_t n);   // rows of up to 4096 x 4096 positions
 hipError_t launch_select_init(const SelectScratch& S, int H, hipStream_t st);
-constexpr int kMaxBatch = 32;   // prompts of a batch
 // flag (may be null): the status word of the call's scratch, cleared too (default: S->ps_flag).
 // lengths (may be null): a batch whose heads' valid prefix lengths the same launch leaves, head h being prompt h / Hkv's.
 struct BatchLengths {

@@ -51,6 +51,9 @@ MIXES = {
     "d64_f16": dict(lengths=[2222, 5555, 3333], D=64, dtype="f16", C=200),
     "wide_window_runs_one_by_one": dict(lengths=[1500, 2100], W=160, C=320, p=5),
     "single_prompt": dict(lengths=[4321]),
+    # filled, one launch gives one of the eight a single group and 16 iterations; cut, seven take 8 and the last 2
+    "cut_into_seven_and_one": dict(lengths=[8500, 8490, 8507, 8501, 8499, 8508, 8493, 8510], Hq=32, Hkv=8, W=16, p=5, C=100),
+    "cut_equal_heads": dict(lengths=[17001, 9000, 16500, 16800, 2000, 16999, 17010, 16600, 900], Hq=16, Hkv=16, W=16, p=5, C=100),
     # the gathers move four pieces per thread up to 2048 workgroups of single pieces and one beyond: batch / single calls
     "many_rows": dict(lengths=[6001, 5003, 5500], Hq=8, Hkv=8, C=1501),              # 2256 / 752
     "many_rows_alone": dict(lengths=[6001], Hq=8, Hkv=8, C=5003),                    # - / 2504
