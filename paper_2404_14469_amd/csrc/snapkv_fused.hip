@@ -252,7 +252,16 @@ template <typename T, int D, int RUW, int NW> constexpr int fused_lds_bytes() {
 // LAYERS: the heads are those of several layers of one prompt that are separate allocations; the Q and K
 // rows of head h then start at SL->q / SL->k [h / heads per layer] instead of behind one another after
 // qv / kv (which are then unused).
-template <typename T, int D, int RUW, int KT, int NW, bool LAYERS = false>
+// ONE: every group has a single unit, of at most 32 slices (short prompts, one layer at a time).  Nothing is overlapped then,
+// and what the pipeline is for only costs time: a row's slices are merged by every workgroup itself, a lane per slice in the tree
+// of step L1, instead of by one half-wave that publishes them once more (the same bits: step P2 with one word multiplies by
+// exp2(0) and adds zeros); one drain step instead of two, no keys requested for a next unit, none of its code, and one generation
+// of exponentials less in registers.  Microseconds per call, general form / this one (bf16, 32/32 heads and 32/8, layers apart):
+// 512 keys, fp32, 4 heads of 64 25.7 / 24.3;  W = 32, 600 keys 23.5 / 22.1, 4096 28.1 / 26.7;  W = 16, 8000 36.6 / 32.8;
+// 32/8 heads, W = 16, 8001 29.1 / 28.1, W = 32, 4000 27.9 / 26.6;  fp32, 1000 40.8 / 34.8, 4000 47.6 / 39.5.
+// One hand-off where groups have several units is no faster (W = 16, 32/8 heads, 13339 keys 35.7 / 35.7) or slower (32 heads,
+// 16384 keys 52.6 / 55.2): the hand-off then has half the time to arrive.
+template <typename T, int D, int RUW, int KT, int NW, bool ONE, bool LAYERS = false>
 __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, const void* __restrict__ kv,
                                                  float* __restrict__ vote, const FusedSync& S,
                                                  const ScoreGeom& G, const FusedGeom& F, const int bid,
@@ -278,7 +287,7 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
     // slice, i.e. once all its waves have passed step D of the iteration two back.  Hence a
     // buffer read up to the end of iteration `it` may be rewritten from iteration it + 3 on
     // (qbuf, sm_fin: three copies), and one read by the publishing wave before it publishes
-    // from iteration it + 2 on (sm_pair: two copies).
+    // from iteration it + 2 on (sm_pair: two copies).  (ONE: nothing is written twice but sm_flag.)
     __shared__ float2 sm_pair[2][NW][R]; // per wave: (row max, row sum-exp) of the current unit
     __shared__ float sm_ref[3][NW][R];   // per wave: row maxima of the last three units (own wave only)
     __shared__ float2 sm_fin[3][R];      // (row max, 1 / row sum-exp) of the unit in step P2
@@ -302,6 +311,9 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
     const bool special = ((int64_t)(KT - 1) * TS + tile0 + 1) * 16 > G.n;
     const int hw = tid >> 5, l32 = tid & 31;
     const int real_tasks = R * F.NB;
+    constexpr int BACK = ONE ? 1 : 2;   // a unit's votes are taken this many iterations after its logits
+    constexpr int ROWS1 = R / (2 * NW);  // ONE: rows a half-wave merges
+    static_assert(!ONE || (R % (2 * NW) == 0 && !LAYERS), "ONE: whole rows per half-wave");
     bool gave_up = false;
 
     // Per-lane row addresses; they advance by one group stride per iteration.  Loads are
@@ -381,13 +393,14 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
     if (tid < 3 * NW) sm_flag[tid / NW][tid % NW] = tid < NW ? 1 : 0;   // Q of unit 0 is in place
     __syncthreads();
     // exponentials of the two previous units stay in registers (or, PARK, in LDS) until their votes are taken
-    f32x4 e1[PARK ? 1 : RUW][PARK ? 1 : KT], e2[PARK ? 1 : RUW][PARK ? 1 : KT];
+    f32x4 e1[PARK ? 1 : RUW][PARK ? 1 : KT], e2[PARK || ONE ? 1 : RUW][PARK || ONE ? 1 : KT];
 #pragma unroll
     for (int ru = 0; ru < RUW; ++ru)
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
             e[ru][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (!PARK) e1[ru][t] = e2[ru][t] = e[ru][t];
+            if constexpr (!PARK) e1[ru][t] = e[ru][t];
+            if constexpr (!PARK && !ONE) e2[ru][t] = e[ru][t];
         }
 
     // logits of tiles [T0, T1) of the unit whose Q block sits in half `par` of qbuf
@@ -422,7 +435,7 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
     // Unconditional (a group with a single unit re-reads it): the compiler derives how long a wait
     // for older loads must be from the loads that certainly follow them on every path, so no load
     // of the steady state may sit behind a branch.
-    issue_tiles(IC0{}, ICLA{}, nu > 1 ? kstep_to(1) : 0);
+    if constexpr (!ONE) issue_tiles(IC0{}, ICLA{}, nu > 1 ? kstep_to(1) : 0);
     __builtin_amdgcn_sched_barrier(0);
 
     // K requests are paced: the tile buffers are requested again at four points spread evenly
@@ -466,6 +479,11 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
         p2_at[x] = p2_ok[x] ? idx : 0;   // word 0 always exists: every wave waits for at least that one
     }
 
+    // ONE: this lane's slice of the rows its half-wave merges (row s1_row(x) of the unit).
+    const bool s1_lane = l32 < F.Gg;
+    const float2* const s1_base = S.part + ((int64_t)group * F.Gg + (s1_lane ? l32 : 0)) * R;
+    auto s1_row = [&](const int x) { return hw + x * 2 * NW; };
+
     // One iteration; MODE says (at compile time) whether the units one (bit 0) and two (bit 1)
     // steps ahead exist, so that every variant of the loop body has a fixed number of loads in
     // flight behind the hand-off words.
@@ -473,11 +491,11 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
         constexpr bool kNext1 = (decltype(MODE)::value & 1) != 0;
         constexpr bool kNext2 = (decltype(MODE)::value & 2) != 0;
         const bool has_p1 = it < nu;
-        const bool has_l1 = it >= 1 && it - 1 < nu;
-        const bool has_p2 = it >= 2;
+        const bool has_l1 = !ONE && it >= 1 && it - 1 < nu;
+        const bool has_p2 = it >= BACK;
         const int unit = group + it * F.NG;
         const int unit_l1 = unit - F.NG;
-        const int unit_p2 = unit - 2 * F.NG;
+        const int unit_p2 = unit - BACK * F.NG;
         const int64_t kstep = kNext1 ? kstep_to(it + 1) : 0;   // to the next unit's keys
 
         // ---- A. request this iteration's hand-off words at the very top: they are needed after
@@ -487,11 +505,17 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
         // The loads are unconditional (lanes and iterations without a word re-read a valid one and
         // ignore it) so that their number is the same on every path.
         const float2* const l1_src = l1_base + (int64_t)(has_l1 ? it - 1 : 0) * l1_step;
-        const unsigned long long l1_bits = load_pair_bits(l1_src);
-        const float2* const p2_src = p2_base + (int64_t)(has_p2 ? it - 2 : 0) * p2_step;
-        unsigned long long p2_bits[L2PT];
+        const float2* const p2_src = p2_base + (int64_t)(has_p2 && !ONE ? it - 2 : 0) * p2_step;
+        const float2* const s1_src = s1_base + (int64_t)(has_p2 && ONE ? it - 1 : 0) * l1_step;
+        unsigned long long l1_bits = 0, p2_bits[ONE ? 1 : L2PT], s1_bits[ONE ? ROWS1 : 1];
+        if constexpr (ONE) {
 #pragma unroll
-        for (int x = 0; x < L2PT; ++x) p2_bits[x] = load_pair_bits(p2_src + p2_at[x]);
+            for (int x = 0; x < ROWS1; ++x) s1_bits[x] = load_pair_bits(s1_src + s1_row(x));
+        } else {
+            l1_bits = load_pair_bits(l1_src);
+#pragma unroll
+            for (int x = 0; x < L2PT; ++x) p2_bits[x] = load_pair_bits(p2_src + p2_at[x]);
+        }
         __builtin_amdgcn_sched_barrier(0);
 
         // ---- B. logits of the upper tiles of the slice (waits for their K; the lower tiles were
@@ -563,7 +587,28 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
         }
         // ---- E. step P2 of the unit two back: level-1 words of a row sit in 16 neighbouring
         // lanes; merge them in a fixed tree into (max, 1/sum)
-        if (has_p2) {
+        auto leave_fin = [&](const int row, const float mm, const float zz) __attribute__((always_inline)) {
+            const int ru = row >> 4;
+            const int i = (ru % F.UH) * 16 + (row & 15);
+            const bool real = ru < F.RU && i < G.W && zz > 0.f;
+            sm_fin[it % 3][row] = real ? make_float2(mm, 1.0f / zz) : make_float2(0.f, 0.f);
+            if (S.lse_out && wg == 0 && real)   // for whoever scores further keys of these rows
+                S.lse_out[((int64_t)unit_p2 * F.gs + ru / F.UH) * G.W + i] = (mm + log2f(zz)) * 0.6931471805599453f;
+        };
+        if (ONE && has_p2) {   // the slices of the unit one back: the tree of step L1 (a lane per slice)
+#pragma unroll
+            for (int x = 0; x < ROWS1; ++x) {
+                float m = -INFINITY, z = 0.f;
+                if (s1_lane) unpack_pair(await_pair(s1_src + s1_row(x), s1_bits[x], F.spin_limit, gave_up), m, z);
+                float mm = row16_max(m);
+                mm = fmaxf(mm, __shfl_xor(mm, 16, 64));
+                float zz = m == -INFINITY ? 0.f : z * __builtin_amdgcn_exp2f(m - mm);
+                zz = row16_sum(zz);
+                zz += __shfl_xor(zz, 16, 64);
+                if (l32 == 0) leave_fin(s1_row(x), mm, mm == -INFINITY ? 0.f : zz);
+            }
+        }
+        if (!ONE && has_p2) {
 #pragma unroll
             for (int x = 0; x < L2PT; ++x) {
                 const int idx = tid + x * NT;
@@ -572,14 +617,7 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
                 if (p2_ok[x]) unpack_pair(got, m, z);
                 const float mm = row16_max(m);
                 const float zz = row16_sum(m == -INFINITY ? 0.f : z * __builtin_amdgcn_exp2f(m - mm));
-                if (idx < R * NBP && (idx & (NBP - 1)) == 0) {
-                    const int row = idx / NBP, ru = row >> 4;
-                    const int i = (ru % F.UH) * 16 + (row & 15);
-                    const bool real = ru < F.RU && i < G.W && zz > 0.f;
-                    sm_fin[it % 3][row] = real ? make_float2(mm, 1.0f / zz) : make_float2(0.f, 0.f);
-                    if (S.lse_out && wg == 0 && real)   // for whoever scores further keys of these rows
-                        S.lse_out[((int64_t)unit_p2 * F.gs + ru / F.UH) * G.W + i] = (mm + log2f(zz)) * 0.6931471805599453f;
-                }
+                if (idx < R * NBP && (idx & (NBP - 1)) == 0) leave_fin(idx / NBP, mm, zz);
             }
         }
         if constexpr (kNext1) {   // the next unit's Q chunks
@@ -659,7 +697,7 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
             for (int ru = 0; ru < RUW; ++ru) {
                 const float4* fin4 = reinterpret_cast<const float4*>(&sm_fin[it % 3][ru * 16 + kg * 4]);
                 const float4 a = fin4[0], b = fin4[1];   // (m, 1/Z) of rows kg*4 .. kg*4+3
-                const float4 ms = *reinterpret_cast<const float4*>(&sm_ref[(it + 1) % 3][w][ru * 16 + kg * 4]);
+                const float4 ms = *reinterpret_cast<const float4*>(&sm_ref[(it + 3 - BACK) % 3][w][ru * 16 + kg * 4]);
                 f[ru][0] = (ms.x == -INFINITY || a.y == 0.f) ? 0.f : __builtin_amdgcn_exp2f(ms.x - a.x) * a.y;
                 f[ru][1] = (ms.y == -INFINITY || a.w == 0.f) ? 0.f : __builtin_amdgcn_exp2f(ms.y - a.z) * a.w;
                 f[ru][2] = (ms.z == -INFINITY || b.y == 0.f) ? 0.f : __builtin_amdgcn_exp2f(ms.z - b.x) * b.y;
@@ -677,7 +715,8 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
 #pragma unroll
                 for (int t = 0; t < KT; ++t) {
                     f32x4 ev;
-                    if constexpr (PARK) ev = park[((it & 1) * NSLOT + ru * KT + t) * NT + tid];   // left there at it - 2
+                    if constexpr (PARK) ev = park[(((it - BACK) & 1) * NSLOT + ru * KT + t) * NT + tid];   // left there at it - BACK
+                    else if constexpr (ONE) ev = e1[ru][t];
                     else ev = e2[ru][t];
                     v[t] = fmaf(ev[0], f[ru][0], v[t]);
                     v[t] = fmaf(ev[1], f[ru][1], v[t]);
@@ -732,7 +771,7 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
                 if constexpr (PARK) {
                     if (has_p1) park[((it & 1) * NSLOT + ru * KT + t) * NT + tid] = e[ru][t];
                 } else {
-                    e2[ru][t] = e1[ru][t];
+                    if constexpr (!ONE) e2[ru][t] = e1[ru][t];
                     e1[ru][t] = e[ru][t];
                 }
             }
@@ -750,28 +789,30 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
 
 #undef SNAPKV_ISSUE
     int it = 0;
-    for (; it + 2 < nu; ++it) iteration(std::integral_constant<int, 3>{}, it);
-    for (; it + 1 < nu; ++it) iteration(std::integral_constant<int, 1>{}, it);   // last but one unit
-    for (; it < nu + 2; ++it) iteration(std::integral_constant<int, 0>{}, it);   // last unit, two drain steps
+    if constexpr (!ONE) {
+        for (; it + 2 < nu; ++it) iteration(std::integral_constant<int, 3>{}, it);
+        for (; it + 1 < nu; ++it) iteration(std::integral_constant<int, 1>{}, it);   // last but one unit
+    }
+    for (; it < nu + BACK; ++it) iteration(std::integral_constant<int, 0>{}, it);   // last unit, the drain steps
     if (gave_up) {
         atomicAdd(&g_sync_timeouts, 1u);
         if (S.gave_up_flag) __hip_atomic_store(S.gave_up_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
-template <typename T, int D, int RUW, int KT, int NW>
+template <typename T, int D, int RUW, int KT, int NW, bool ONE>
 __global__ __launch_bounds__(NW * 64) void score_fused(const void* __restrict__ qv,
                                                        const void* __restrict__ kv,
                                                        float* __restrict__ vote, const FusedSync S,
                                                        const ScoreGeom G, const FusedGeom F) {
-    score_fused_body<T, D, RUW, KT, NW>(qv, kv, vote, S, G, F, (int)blockIdx.x);
+    score_fused_body<T, D, RUW, KT, NW, ONE>(qv, kv, vote, S, G, F, (int)blockIdx.x);
 }
 
 template <typename T, int D, int RUW, int KT, int NW>
 __global__ __launch_bounds__(NW * 64) void score_fused_layers(float* __restrict__ vote, const FusedSync S,
                                                               const ScoreGeom G, const FusedGeom F,
                                                               const ScoreLayers SL) {
-    score_fused_body<T, D, RUW, KT, NW, true>(nullptr, nullptr, vote, S, G, F, (int)blockIdx.x, &SL);
+    score_fused_body<T, D, RUW, KT, NW, false, true>(nullptr, nullptr, vote, S, G, F, (int)blockIdx.x, &SL);
 }
 
 // Several prompts of one model in one launch: every prompt has its own groups of workgroups
@@ -799,7 +840,7 @@ __global__ __launch_bounds__(NW * 64) void score_fused_joint(const FusedJoint J)
         if ((int)blockIdx.x >= J.p[i].wg_begin) pi = i;
     const FusedPrompt& P = J.p[pi];
     const int bid = (int)blockIdx.x - P.wg_begin;
-    score_fused_body<T, D, RUW, KT, NW>(P.q, P.k, P.vote, P.S, P.G, P.F, bid);
+    score_fused_body<T, D, RUW, KT, NW, false>(P.q, P.k, P.vote, P.S, P.G, P.F, bid);
 }
 
 
@@ -1319,10 +1360,10 @@ struct FusedCall {
 
 // call == nullptr: returns in *occ how many workgroups of this instance fit one compute unit
 // (asked of the runtime, so that a launch never exceeds what is resident at the same time).
-template <typename T, int D, int RUW, int NW>
+template <typename T, int D, int RUW, int NW, bool ONE>
 static hipError_t fused_instance(const FusedCall* call, int* occ) {
     constexpr int KT = kFusedSlots / RUW;
-    auto kern = score_fused<T, D, RUW, KT, NW>;
+    auto kern = score_fused<T, D, RUW, KT, NW, ONE>;
     constexpr int kQueueBytes = fused_lds_bytes<T, D, RUW, NW>();
     static int cached_occ = -1;
     if (cached_occ < 0) {
@@ -1343,13 +1384,20 @@ static hipError_t fused_instance(const FusedCall* call, int* occ) {
     return hipGetLastError();
 }
 
+// Whether every group has one unit and a row's slices fit one level-1 block (and nothing else is merged with them).
+static bool one_unit(const FusedGeom& F) { return F.units <= F.NG && F.NB == 1 && F.NBX == 1; }
+
 template <typename T, int D, int NW>
 static hipError_t fused_by_rows(int RUW, const FusedCall* call, int* occ) {
+    if (call && RUW <= 2 && one_unit(*call->F)) {   // (plans count the general form's residency; this one asks for its own)
+        const hipError_t e = RUW == 1 ? fused_instance<T, D, 1, NW, true>(call, occ) : fused_instance<T, D, 2, NW, true>(call, occ);
+        if (e != hipErrorCooperativeLaunchTooLarge) return e;
+    }
     switch (RUW) {
-        case 1: return fused_instance<T, D, 1, NW>(call, occ);
-        case 2: return fused_instance<T, D, 2, NW>(call, occ);
-        case 4: return fused_instance<T, D, 4, NW>(call, occ);
-        case 8: return fused_instance<T, D, 8, NW>(call, occ);
+        case 1: return fused_instance<T, D, 1, NW, false>(call, occ);
+        case 2: return fused_instance<T, D, 2, NW, false>(call, occ);
+        case 4: return fused_instance<T, D, 4, NW, false>(call, occ);
+        case 8: return fused_instance<T, D, 8, NW, false>(call, occ);
     }
     return hipErrorInvalidValue;
 }

@@ -174,3 +174,32 @@ def test_random_layer_lists(snapkv, kw):
     torch.cuda.synchronize()
     compare(snapkv, w, [dict(q_win=a, k=b, v=c) for a, b, c in zip(q, k, v)], oks, ovs, ois, oracle_on=(n_layers - 1,))
     assert snapkv.snapkv_sync_timeouts() == 0
+
+
+# single calls in which every group of workgroups has one unit (a short prompt whose units all run side by side) have a form
+# of the single-read kernel of their own; separately allocated layers go through the general one
+ONE_UNIT = {
+    "one_slice": dict(L=512, C=128),
+    "few_keys": dict(L=41, C=36),                                                    # most waves have no key
+    "one_key_in_the_second_slice": dict(L=513, C=128),
+    "chip_full": dict(L=4096, Hq=32, Hkv=32, C=100),                                 # 32 units of 8 slices
+    "one_unit_too_many": dict(L=4097, Hq=32, Hkv=32, C=100),                         # 28 groups: the general form
+    "row_unit": dict(L=8192, Hq=32, Hkv=32, W=16, p=5, C=100),                       # exponentials wait in LDS
+    "row_unit_32_slices": dict(L=32768, Hq=4, Hkv=4, W=16, p=5, C=100),
+    "parts_of_a_head": dict(L=8190, Hq=32, Hkv=8, W=16, pool_kind=1, p=5, C=100),
+    "32_slices": dict(L=16384, Hq=4, Hkv=4, C=100),
+    "33_slices": dict(L=16385, Hq=4, Hkv=4, C=100),                                  # two level-1 blocks: the general form
+    "d64_f16": dict(L=3001, D=64, dtype="f16", W=13, C=100),
+    "f32": dict(L=1500, D=64, dtype="f32", C=100),
+}
+
+
+@pytest.mark.parametrize("name", sorted(ONE_UNIT))
+def test_one_unit_per_group(snapkv, name):
+    w, cases = layer_cases(2, **ONE_UNIT[name])
+    oks, ovs, ois = outputs(w, 2, cases[0]["k"].dtype, stack=False)
+    for _ in range(3):                                                               # (scratch left ready by the call before)
+        snapkv.snapkv_compress_layers(*([c[n] for c in cases] for n in ("q_win", "k", "v")), w.pool_kind, w.p, w.C, oks, ovs, ois)
+        compare(snapkv, w, cases, oks, ovs, ois)
+    compare(snapkv, w, cases, oks, ovs, ois, oracle_on=(1,))
+    assert snapkv.snapkv_sync_timeouts() == 0
