@@ -587,28 +587,25 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
         }
         // ---- E. step P2 of the unit two back: level-1 words of a row sit in 16 neighbouring
         // lanes; merge them in a fixed tree into (max, 1/sum)
-        auto leave_fin = [&](const int row, const float mm, const float zz) __attribute__((always_inline)) {
-            const int ru = row >> 4;
-            const int i = (ru % F.UH) * 16 + (row & 15);
-            const bool real = ru < F.RU && i < G.W && zz > 0.f;
-            sm_fin[it % 3][row] = real ? make_float2(mm, 1.0f / zz) : make_float2(0.f, 0.f);
-            if (S.lse_out && wg == 0 && real)   // for whoever scores further keys of these rows
-                S.lse_out[((int64_t)unit_p2 * F.gs + ru / F.UH) * G.W + i] = (mm + log2f(zz)) * 0.6931471805599453f;
-        };
-        if (ONE && has_p2) {   // the slices of the unit one back: the tree of step L1 (a lane per slice)
+        if constexpr (ONE) {             // the slices of the unit one back: the tree of step L1 (a lane per slice)
+            if (has_p2) {
 #pragma unroll
-            for (int x = 0; x < ROWS1; ++x) {
-                float m = -INFINITY, z = 0.f;
-                if (s1_lane) unpack_pair(await_pair(s1_src + s1_row(x), s1_bits[x], F.spin_limit, gave_up), m, z);
-                float mm = row16_max(m);
-                mm = fmaxf(mm, __shfl_xor(mm, 16, 64));
-                float zz = m == -INFINITY ? 0.f : z * __builtin_amdgcn_exp2f(m - mm);
-                zz = row16_sum(zz);
-                zz += __shfl_xor(zz, 16, 64);
-                if (l32 == 0) leave_fin(s1_row(x), mm, mm == -INFINITY ? 0.f : zz);
+                for (int x = 0; x < ROWS1; ++x) {
+                    float m = -INFINITY, z = 0.f;
+                    if (s1_lane) unpack_pair(await_pair(s1_src + s1_row(x), s1_bits[x], F.spin_limit, gave_up), m, z);
+                    float mm = row16_max(m);
+                    mm = fmaxf(mm, __shfl_xor(mm, 16, 64));
+                    float zz = m == -INFINITY ? 0.f : z * __builtin_amdgcn_exp2f(m - mm);
+                    zz = row16_sum(zz);
+                    zz += __shfl_xor(zz, 16, 64);
+                    if (l32 == 0) {
+                        const int row = s1_row(x), ru = row >> 4;
+                        const bool real = ru < F.RU && (ru % F.UH) * 16 + (row & 15) < G.W && mm != -INFINITY && zz > 0.f;
+                        sm_fin[it % 3][row] = real ? make_float2(mm, 1.0f / zz) : make_float2(0.f, 0.f);
+                    }
+                }
             }
-        }
-        if (!ONE && has_p2) {
+        } else if (has_p2) {
 #pragma unroll
             for (int x = 0; x < L2PT; ++x) {
                 const int idx = tid + x * NT;
@@ -617,7 +614,14 @@ __device__ __forceinline__ void score_fused_body(const void* __restrict__ qv, co
                 if (p2_ok[x]) unpack_pair(got, m, z);
                 const float mm = row16_max(m);
                 const float zz = row16_sum(m == -INFINITY ? 0.f : z * __builtin_amdgcn_exp2f(m - mm));
-                if (idx < R * NBP && (idx & (NBP - 1)) == 0) leave_fin(idx / NBP, mm, zz);
+                if (idx < R * NBP && (idx & (NBP - 1)) == 0) {
+                    const int row = idx / NBP, ru = row >> 4;
+                    const int i = (ru % F.UH) * 16 + (row & 15);
+                    const bool real = ru < F.RU && i < G.W && zz > 0.f;
+                    sm_fin[it % 3][row] = real ? make_float2(mm, 1.0f / zz) : make_float2(0.f, 0.f);
+                    if (S.lse_out && wg == 0 && real)   // for whoever scores further keys of these rows
+                        S.lse_out[((int64_t)unit_p2 * F.gs + ru / F.UH) * G.W + i] = (mm + log2f(zz)) * 0.6931471805599453f;
+                }
             }
         }
         if constexpr (kNext1) {   // the next unit's Q chunks
