@@ -40,11 +40,21 @@
 // against float64 (2-norm, 1e-8; 18461 keys, 32/8 heads, 32 rows), single-read kernel / a reference that stays at the
 // first key's logit / as it is: logits N(0, 1.8 nats) 12.2 / 12.6 / 12.3; with 40 keys 6, 20 and 40 nats above those
 // 12.1 / 11.9 / 10.6, 15.8 / 17.5 / 15.2 and 28.1 / 34.5 / 28.0.  Checking and raising cost 0.8 of 64 us per call at
-// 28471 keys, 0.5 of 67 at 32749 and nothing measurable at 131072.  Blocks of 64 rows, 140001 keys, logits N(0, s) with
-// clusters, mean of four draws, front and rest of the single-read kernel / first four keys / first sixteen: W = 16, four query
-// heads, s = 0.9, 1.8 and 3.6 nats 5.5 / 5.4 / 5.3, 16.4 / 18.3 / 17.4 and 42.6 / 43.0 / 43.1 (of single votes near the
-// selection's threshold 5.4 / 5.4 / 5.3, 12.4 / 12.8 / 12.2, 46.2 / 46.3 / 46.6); W = 64, one query head 23.8 / 5.2 / 5.1,
-// 27.2 / 11.2 / 10.9 and 52.9 / 30.5 / 30.3.
+// 28471 keys, 0.5 of 67 at 32749 and nothing measurable at 131072.
+//
+// The row's origin (blocks of 64 rows).  Most of the error is that of the logits themselves, whose partial sums are rounded four
+// times on the way.  Here they do not start from zero but from minus the row's origin: the first sixteen keys' logits fall into
+// four quads, and the second largest of the quads' maxima is the origin (the largest may be a first token that every row attends
+// to).  The sums of the logits that matter then end nearer to zero.  Reference, maxima and exponents are all counted from the
+// origin, so nothing else changes; wide_stats leaves it behind a unit's slices.  It costs no time (262144 keys, 32/8 heads, W = 16 251 us
+// a call with it and without).  Error of votes within a factor of two of the 1024th largest (2-norm of the relative errors, 1e-8, 32
+// heads), logits N(0, s nats) and clusters, the single-read kernel (and from 262145 keys on or with W = 64: its front and rest) / the
+// two passes without / with the origin, s = 0.45, 0.9, 1.8 and 3.6:
+//   W = 16, four query heads, 140001 keys: 4.5 / 4.4 / 4.4, 5.6 / 5.4 / 5.2, 14.1 / 14.1 / 10.1 and 52.6 / 52.9 / 30.4;
+//     380000 keys: 29.6 / 4.5 / 4.5, 28.5 / 5.7 / 5.5, 35.1 / 15.9 / 11.5 and 77.7 / 57.3 / 34.2;
+//   W = 64, one query head, 140001 keys: 25.6 / 4.6 / 4.6, 26.5 / 5.3 / 5.1, 22.7 / 8.6 / 6.9 and 51.4 / 35.9 / 21.4.
+// With the first key 8, 20 and 40 nats above the rest (W = 16, s = 1.8): 14.7 / 14.7 / 10.1, 41 / 41 / 31 and 206 / 205 / 140.  Started
+// from minus the reference instead: 0.61 to 0.71 of the first figure without such a key, but 1.2 to 1.8 of it with one.
 //
 // MFMA layout: that of snapkv_fused.hip (16x16x32, lane l: row / column l % 16, contraction slice l / 16;
 // accumulator register r is row (l / 16) * 4 + r, column l % 16; the 16-byte pieces 4p + l / 16 of a row).
@@ -106,12 +116,22 @@ __device__ __forceinline__ wf32x4 mma16(w_f16, uint4 a, uint4 b, wf32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(wf16x8, a), __builtin_bit_cast(wf16x8, b), c, 0, 0, 0);
 }
 template <typename T, int D>
-__device__ __forceinline__ wf32x4 logits16(const KFrag<D>& q, const KFrag<D>& k) {
-    wf32x4 acc = {0.f, 0.f, 0.f, 0.f};
+__device__ __forceinline__ wf32x4 logits16(const KFrag<D>& q, const KFrag<D>& k, wf32x4 acc = {0.f, 0.f, 0.f, 0.f}) {
 #pragma unroll
     for (int p = 0; p < KFrag<D>::NP; ++p) acc = mma16(T{}, q.v[p], k.v[p], acc);
     return acc;
 }
+
+// Blocks of 64 rows: logits are counted from an origin of the row (see "The row reference").
+template <int RUW> constexpr bool kOrigin = RUW == 4;
+template <int RUW> constexpr int kExtra = kOrigin<RUW> ? 1 : 0;
+template <int RUW> struct Origins {
+    wf32x4 neg[kOrigin<RUW> ? kWaveRows : 1];
+    template <typename T, int D> __device__ __forceinline__ wf32x4 logits(const KFrag<D>& q, const KFrag<D>& k, int i) const {
+        if constexpr (kOrigin<RUW>) return logits16<T, D>(q, k, neg[i]);
+        else return logits16<T, D>(q, k);
+    }
+};
 
 template <int CTRL> __device__ __forceinline__ float wdpp(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
@@ -141,7 +161,8 @@ struct WideEntry {
     const char* q;
     const char* k;
     float* vote;
-    float2* part;        // [units][NS][RUW * 16] per slice and row: (reference, sum of 2^(s - reference))
+    float2* part;        // [units][NS + kExtra][RUW * 16] per slice and row: (reference, sum of 2^(s - reference));
+                         //   behind a unit's slices, RUW = 4: (-origin, 0) per row
     int64_t k_hs;        // bytes between the K rows of consecutive KV heads
     int64_t vpitch;      // floats between vote rows
     unsigned round_begin; // rounds of the entries before this one
@@ -178,6 +199,11 @@ template <int N> __device__ __forceinline__ void enter(const WideArgs<N>& A, Cur
     c.NS = E.NS;
     c.units = E.units;
     c.kb = E.k + (int64_t)c.kv * E.k_hs;
+}
+
+// Where the statistics of the cursor's unit begin.
+template <int RUW, int N> __device__ __forceinline__ int64_t unit_part(const WideArgs<N>& A, const Cursor& c) {
+    return ((int64_t)c.kv * A.nblk + c.blk) * (c.NS + kExtra<RUW>) * (RUW * 16);
 }
 
 // First round at or after `r` at which a slice begins.
@@ -357,8 +383,8 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     constexpr int R = Wv::R, TILES = Wv::TILES, PARTS = Wv::PARTS;
     __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];                      // K of two rounds as MFMA fragments
     constexpr int kFirst = RUW == 8 ? 4 : 16;
-    enum { kBase, kRef, kSum = kRef + 2, kStatArrays = kSum + 2 };        // per part and row: the references at a slice's
-    __shared__ __attribute__((aligned(16))) float sm_st[kStatArrays][PARTS][R];   // start, two slices' references and their sums
+    enum { kBase, kRef, kSum = kRef + 2, kOrg = kSum + 2, kStatArrays = kOrg + 2 * kExtra<RUW> };   // per part and row: the references at a slice's
+    __shared__ __attribute__((aligned(16))) float sm_st[kStatArrays][PARTS][R];   // start, two slices' references, their sums and the origins
     Wv W(A);
     {
         const int64_t wg = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, all = (int64_t)gridDim.x * gridDim.y * gridDim.z * kThreads;
@@ -370,8 +396,9 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     if (rounds <= 0) return;
     KFrag<D> q[kWaveRows], S;
     float z[kWaveRows][4], ref[kWaveRows][4];
+    Origins<RUW> org;
 
-    // A unit begins: the wave's Q rows, and the rows' references from the prompt's first kFirst keys (or fewer: those that
+    // A unit begins: the wave's Q rows, and the rows' origins and references from the prompt's first kFirst keys (or fewer: those that
     // every row sees; each quad, or row, of lanes brings all of them).  They depend on the unit alone, and every slice starts from
     // them, so a slice's result does not depend on which slices its workgroup had before.
     float* const my = &sm_st[kBase][W.kp][W.rg * kWaveRows * 16 + W.kg * 4];   // from the lane's first row on
@@ -386,12 +413,14 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
             const wf32x4 a = logits16<T, D>(q[i], f);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                float m = a[r];
-                if constexpr (kFirst == 16) {
-                    m = lanes16_max(m);
-                } else {
-                    m = fmaxf(m, wdpp<0xB1>(m));
-                    m = fmaxf(m, wdpp<0x4E>(m));
+                float m = fmaxf(a[r], wdpp<0xB1>(a[r]));
+                m = fmaxf(m, wdpp<0x4E>(m));
+                if constexpr (kOrigin<RUW>) {   // of the four quads' maxima the second largest is the origin
+                    const float m2 = wdpp<0x141>(m), hi = fmaxf(m, m2), lo = fminf(m, m2), hi2 = wdpp<0x140>(hi), lo2 = wdpp<0x140>(lo);
+                    float o = fmaxf(fminf(hi, hi2), fmaxf(lo, lo2));
+                    o = fabsf(o) < 0x1p100f ? o : 0.f;
+                    org.neg[i][r] = -o;
+                    m = fmaxf(hi, hi2) - o;
                 }
                 m *= A.c2;
                 ref[i][r] = m == -INFINITY ? 0.f : m;
@@ -403,7 +432,8 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     };
     bool raised = false;                 // (wave-uniform) a reference was raised since the slice's start
     int par = 0;                         // which half of sm_ref and sm_sum the current slice uses
-    float2* pending = nullptr;           // where the pairs of the slice before go, once all waves have left theirs
+    float2* pending = nullptr;           // where the pairs of the slice before go, once all waves have left theirs,
+    float2* origins = nullptr;           //   and the unit's origins (with its first slice)
     auto store_slice = [&](int half) __attribute__((always_inline)) {
         if (W.tid < R) {                 // fixed order over the parts
             float m = -INFINITY, s = 0.f;
@@ -412,6 +442,8 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
 #pragma unroll
             for (int v = 0; v < PARTS; ++v) s += sm_st[kSum + half][v][W.tid] * __builtin_amdgcn_exp2f(sm_st[kRef + half][v][W.tid] - m);
             pending[W.tid] = make_float2(m, s);
+            if constexpr (kOrigin<RUW>)
+                if (origins) origins[W.tid] = make_float2(sm_st[kOrg + half][0][W.tid], 0.f);
         }
         pending = nullptr;
     };
@@ -439,7 +471,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
             W.tile(f, buf, t);
 #pragma unroll
             for (int i = 0; i < kWaveRows; ++i) {
-                wf32x4 a = logits16<T, D>(q[i], f);
+                wf32x4 a = org.template logits<T, D>(q[i], f, i);
                 if (special) W.mask(a, j0 + t * 16, i, cc);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -463,7 +495,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
                     W.tile(f, buf, t);
 #pragma unroll
                     for (int i = 0; i < kWaveRows; ++i) {
-                        wf32x4 a = logits16<T, D>(q[i], f);
+                        wf32x4 a = org.template logits<T, D>(q[i], f, i);
                         W.mask(a, j0 + t * 16, i, cc);
                         f2(a, i);
                     }
@@ -506,6 +538,8 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
                     *reinterpret_cast<float4*>(my + (kSum + par) * (PARTS * R) + i * 16) = make_float4(y[0], y[1], y[2], y[3]);
                     *reinterpret_cast<float4*>(my + (kRef + par) * (PARTS * R) + i * 16) = make_float4(ref[i][0], ref[i][1], ref[i][2], ref[i][3]);
                 }
+                if constexpr (kOrigin<RUW>)
+                    if (W.n16 == 0) *reinterpret_cast<wf32x4*>(my + (kOrg + par) * (PARTS * R) + i * 16) = org.neg[i];
                 if (raised) {
                     const float4 b = *reinterpret_cast<const float4*>(my + i * 16);
                     ref[i][0] = b.x, ref[i][1] = b.y, ref[i][2] = b.z, ref[i][3] = b.w;
@@ -516,7 +550,8 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
             for (int i = 0; i < kWaveRows; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) z[i][r] = 0.f;
-            pending = A.e[cc.e].part + (((int64_t)cc.kv * A.nblk + cc.blk) * cc.NS + cc.sl) * R;
+            pending = A.e[cc.e].part + unit_part<RUW>(A, cc) + (int64_t)cc.sl * R;
+            if constexpr (kOrigin<RUW>) origins = cc.sl == 0 ? pending + (int64_t)cc.NS * R : nullptr;
             par ^= 1;
         }
         if (left <= 0) break;
@@ -537,6 +572,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
     __shared__ float sm_v[2][RUW][kRound];                            // sums over the rows of a row unit, per key
     __shared__ float2 sm[SUB][R];
     __shared__ __attribute__((aligned(16))) float2 smf[R];
+    __shared__ __attribute__((aligned(16))) float smo[kOrigin<RUW> ? R : 1];
     Wv W(A);
     int rounds;
     Cursor cc = begin_share(A, rounds), pc = cc;
@@ -545,6 +581,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
     W.ask_page(pc);
     S = W.request(pc);
 
+    Origins<RUW> org;
     float mref[kWaveRows][4], wgt[kWaveRows][4];   // the rows' reference and 1 / sum (padding rows: +inf and 0)
     // (reference, sum) pairs merged in a balanced tree (fixed order, few roundings)
     auto fold = [](const auto& y, float& m, float& s) __attribute__((always_inline)) {
@@ -563,7 +600,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
     };
     auto begin_unit = [&]() __attribute__((always_inline)) {            // the unit's slices merged in a fixed order, and the wave's Q rows
         const int row = W.tid % R, sub = W.tid / R;
-        const float2* src = A.e[cc.e].part + ((int64_t)cc.kv * A.nblk + cc.blk) * cc.NS * R + row;
+        const float2* src = A.e[cc.e].part + unit_part<RUW>(A, cc) + row;
         float m = -INFINITY, s = 0.f;
 #pragma clang loop unroll(disable)
         for (int s0 = sub; s0 < cc.NS; s0 += 8 * SUB) {   // eight slices' pairs in flight at a time
@@ -577,6 +614,8 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
             fold(x, m, s);
         }
         sm[sub][row] = make_float2(m, s);
+        if constexpr (kOrigin<RUW>)
+            if (W.tid < R) smo[row] = src[(int64_t)cc.NS * R].x;
         W.load_q(q, cc);
         lds_meet();
         if (W.tid < R) {
@@ -595,6 +634,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
             const float4 a = f4[0], b = f4[1];
             mref[i][0] = a.x, wgt[i][0] = a.y, mref[i][1] = a.z, wgt[i][1] = a.w;
             mref[i][2] = b.x, wgt[i][2] = b.y, mref[i][3] = b.z, wgt[i][3] = b.w;
+            if constexpr (kOrigin<RUW>) org.neg[i] = *reinterpret_cast<const wf32x4*>(&smo[(W.rg * kWaveRows + i) * 16 + W.kg * 4]);
         }
     };
     begin_unit();
@@ -626,7 +666,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
             W.tile(f, kbuf[half], t);
 #pragma unroll
             for (int i = 0; i < kWaveRows; ++i) {
-                const wf32x4 a = logits16<T, D>(q[i], f);
+                const wf32x4 a = org.template logits<T, D>(q[i], f, i);
                 float s = 0.f;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s = fmaf(__builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -mref[i][r])), wgt[i][r], s);
@@ -734,7 +774,7 @@ static bool wide_shape(const ScoreGeom& G, Blocks* b) {
     if (G.n <= 0 || !row_blocks(G, b) || (int64_t)G.g * b->UH * 16 * G.L < (b->ru == 8 ? kMinRowKeys : b->UH == 2 ? kMinRowKeys64of2 : kMinRowKeys64)) return false;
     ScoreGeom one = G;
     one.Hkv = 1;
-    const size_t part = sizeof(float2) * (size_t)b->nblk * slices_of(G, *b) * b->ru * 16;
+    const size_t part = sizeof(float2) * (size_t)b->nblk * (slices_of(G, *b) + (b->ru == 4 ? kExtra<4> : kExtra<8>)) * b->ru * 16;
     return part <= std::max(stream_stat_bytes(one), sizeof(float) * (size_t)G.g * (size_t)G.n);
 }
 
@@ -747,7 +787,7 @@ bool wide_ok(int dtype, int D, const ScoreGeom& G) {
 size_t wide_part_bytes(const ScoreGeom& G) {
     Blocks b;
     if (!wide_shape(G, &b)) return 0;
-    return (sizeof(float2) * (size_t)G.Hkv * b.nblk * slices_of(G, b) * b.ru * 16 + 255) & ~(size_t)255;
+    return (sizeof(float2) * (size_t)G.Hkv * b.nblk * (slices_of(G, b) + (b.ru == 4 ? kExtra<4> : kExtra<8>)) * b.ru * 16 + 255) & ~(size_t)255;
 }
 
 hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st, const WideClear& clear) {

@@ -106,6 +106,45 @@ def test_64_rows_layers_and_batches_equal_single_calls(snapkv):
     assert torch.equal(ok, want[0][1]) and torch.equal(ov, want[0][2])
 
 
+def relative_error(snapkv, q, k, L):
+    """Of the first L keys' votes against float64, over the votes within a factor of two of a head's 1024th (2-norm)."""
+    (Hq, W, D), Hkv = q.shape, k.shape[0]
+    keys = k[:, :L].contiguous()
+    votes = torch.empty((Hkv, L - W), device="cuda")
+    snapkv.snapkv_pooled_scores(q, keys, 0, 1, votes)
+    seen = torch.arange(L, device="cuda") <= torch.arange(L - W, L, device="cuda").unsqueeze(1)
+    errors = []
+    for h in range(Hkv):
+        want = torch.zeros(L - W, dtype=torch.float64, device="cuda")
+        for x in q.view(Hkv, -1, W, D)[h]:
+            logits = (x.double() @ keys[h].double().t()) / D ** 0.5
+            want += torch.softmax(logits.masked_fill(~seen, float("-inf")), 1)[:, :L - W].sum(0)
+        edge = want.topk(1024)[0][-1]
+        near = (want > edge / 2) & (want < edge * 2)
+        errors.append(((votes[h].double() - want)[near] / want[near]).pow(2).mean())
+    return float(torch.stack(errors).mean().sqrt())
+
+
+@pytest.mark.parametrize("W,spread,sink", [(13, 3.6, 0.0), (16, 3.6, 0.0), (16, 1.8, 8.0), (16, 1.8, 20.0)])
+def test_64_rows_are_as_exact_as_the_single_read_kernel(snapkv, W, spread, sink):
+    """Logits N(0, spread nats), and a first key `sink` nats above them.  131073 keys take the two passes, 131072 the single-read kernel:
+    the error of what the two passes score is no larger than that kernel's."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(29)
+    Hkv, g, L, D = 8, 4, 131073, 128
+    q = torch.randn((Hkv * g, W, D), generator=gen, device="cuda") + 1.5 * torch.randn((Hkv * g, 1, D), generator=gen, device="cuda")
+    k = torch.randn((Hkv, L, D), generator=gen, device="cuda")
+    q = q * (spread / q.pow(2).mean().sqrt())
+    if sink:
+        u = torch.nn.functional.normalize(torch.randn(D, generator=gen, device="cuda"), dim=0)
+        q += 8 * u
+        k[:, 0] += sink * D ** 0.5 / 8 * u
+    q, k = q.bfloat16(), k.bfloat16()
+    two, one = relative_error(snapkv, q, k, L), relative_error(snapkv, q, k, L - 1)
+    print(f"relative error {two:.3e}, single-read kernel {one:.3e}")
+    assert two <= one, (two, one)
+
+
 def outputs(w, n, dtype):
     return ([torch.zeros((w.Hkv, w.C, w.D), dtype=dtype, device="cuda") for _ in range(n)],
             [torch.zeros((w.Hkv, w.C, w.D), dtype=dtype, device="cuda") for _ in range(n)],
