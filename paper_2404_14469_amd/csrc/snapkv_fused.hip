@@ -45,8 +45,6 @@
 // pieces 4p + l/16 of its row: the four lanes of a row then read 64 contiguous bytes per load.
 #include "snapkv_internal.h"
 
-#include <algorithm>
-#include <climits>
 #include <cstdlib>
 #include <type_traits>
 
@@ -1582,8 +1580,8 @@ static hipError_t joint_dispatch(int dtype, int D, int RUW, const FusedJoint* J,
 }
 
 // Hands what the chip has left over to the prompts of a joint launch, a step at a time to the one with the most iterations
-// still to run; every prompt starts with one group.  Returns the iterations of the prompt that has most.
-static int joint_spread(FusedGeom* F, const int* take, int taken, int slots) {
+// still to run; every prompt starts with one group.
+static void joint_spread(FusedGeom* F, const int* take, int taken, int slots) {
     // the next number of groups a prompt can have: a divisor of split below it, a multiple of it above
     auto next_groups = [](const FusedGeom& f) {
         if (f.NG >= f.split) return f.NG + f.split;
@@ -1614,66 +1612,29 @@ static int joint_spread(FusedGeom* F, const int* take, int taken, int slots) {
         total += (nx - f.NG) * f.Gg;
         f.NG = nx;
     }
-    int most = 0;
-    for (int t = 0; t < taken; ++t) most = std::max(most, iterations(F[take[t]]));
-    return most;
 }
 
-// Where to cut a batch (longest prompt first) into joint launches.  A launch lasts as long as its prompt with the most
-// iterations, so one more prompt can cost more than it brings: eight prompts of 8500 keys, 32/8 heads fill a launch in which
-// one of them has a single group, 16 iterations; seven have two groups each and take 8, and the eighth by itself 2.  The cuts into runs of neighbours
-// that cost least (iterations, and kJointStart halves of one for a launch's first keys and its drain) are compared with
-// filling launch after launch.  Returns the number of launches and their prompts in cut[], or 0: fill them one by one.
-// Microseconds per call, W = 16, filled / cut: 32/8 heads, eight prompts of 8500 keys 114 / 94, twelve of 8-9K keys 173 / 137,
-// eight of 5-20K keys 114 / 105; where nothing is cut the same.  Reckoned over 2000 batches of 2-12 prompts of 1K-64K keys a
-// third is cut, for 3 to 5 % fewer iterations over all.
-constexpr int kJointStart = 7;
+// Cuts of a batch (longest prompt first) into joint launches; see joint_cuts.  Microseconds per call, W = 16, filled / cut:
+// 32/8 heads, eight prompts of 8500 keys 114 / 94, twelve of 8-9K keys 173 / 137, eight of 5-20K 114 / 105.  Reckoned over 2000
+// batches of 2-12 prompts of 1K-64K keys a third is cut, for 3 to 5 % fewer iterations over all.
 int fused_joint_cuts(int dtype, int D, int count, const ScoreGeom* G, int* cut) {
     if (count < 3 || count > kMaxBatch || (dtype != 0 && dtype != 2)) return 0;
-    FusedGeom F[kMaxBatch];
-    for (int i = 0; i < count; ++i)
-        if (!fused_plan(dtype, D, G[i], &F[i]) || F[i].RUW != F[0].RUW || F[i].split != F[0].split || F[i].NW != F[0].NW) return 0;
+    FusedGeom F0, F;
+    int Gg[kMaxBatch];
+    for (int i = 0; i < count; ++i) {
+        if (!fused_plan(dtype, D, G[i], i == 0 ? &F0 : &F)) return 0;
+        if (i > 0 && (F.RUW != F0.RUW || F.split != F0.split || F.NW != F0.NW || F.units != F0.units)) return 0;
+        Gg[i] = i == 0 ? F0.Gg : F.Gg;
+    }
     int occ = 0;
-    if (joint_dispatch(dtype, D, F[0].RUW, nullptr, 0, nullptr, &occ) != hipSuccess) {
+    if (joint_dispatch(dtype, D, F0.RUW, nullptr, 0, nullptr, &occ) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
     const int slots = cu_count() * occ;
-    int take[kMaxJoint], filled = 0;
-    bool done[kMaxBatch] = {};
-    for (int left = count; left > 0;) {   // launch after launch, as fused_joint_plan fills them
-        int taken = 0, total = 0;
-        for (int i = 0; i < count && taken < kMaxJoint; ++i)
-            if (!done[i] && total + F[i].Gg <= slots) {
-                total += F[i].Gg;
-                done[i] = true;
-                take[taken++] = i;
-            }
-        if (taken == 0) return 0;
-        left -= taken;
-        filled += 2 * joint_spread(F, take, taken, slots) + kJointStart;
-    }
-    int cost[kMaxBatch + 1], from[kMaxBatch + 1];   // of the first i prompts; where their last launch begins
-    cost[0] = 0;
-    for (int i = 1; i <= count; ++i) cost[i] = INT_MAX;
-    for (int i = 0; i < count; ++i) {
-        int total = 0;
-        for (int j = i; j < count && j - i < kMaxJoint; ++j) {
-            total += F[j].Gg;
-            if (total > slots) break;
-            take[j - i] = j;
-            const int c = cost[i] + 2 * joint_spread(F, take, j - i + 1, slots) + kJointStart;
-            if (c < cost[j + 1]) {
-                cost[j + 1] = c;
-                from[j + 1] = i;
-            }
-        }
-    }
-    if (50 * cost[count] > 49 * filled) return 0;   // (no less than 2 %)
-    int launches = 0;
-    for (int i = count; i > 0; i = from[i]) ++launches;
-    for (int i = count, l = launches; i > 0; i = from[i]) cut[--l] = i - from[i];
-    return launches;
+    for (int i = 0; i < count; ++i)
+        if (Gg[i] > slots) return 0;
+    return joint_cuts(JointUnits{F0.units, F0.split}, Gg, count, slots, cut);
 }
 
 // Plans one joint launch over some of the prompts G[0..count), scanned in the order given (the

@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "snapkv_joint.h"
+
 namespace snapkv {
 
 // Geometry of a scoring call.  A "vote row" is one fp32 vector of length n: one per query head, or (windows of
@@ -150,9 +152,7 @@ hipError_t launch_publish_rest(const float2* stat_part, const FusedSync& S, cons
 // (test hook) 0, or the number of workgroups the plans of the single-read kernel may count as resident
 extern int g_fused_slot_cap;
 // Several prompts of one model in one launch of the single-read kernel (snapkv_fused.hip).
-constexpr int kMaxBatch = 32;   // prompts of a batch
-constexpr int kMaxJointPrompts = 8;
-// Cuts a batch into joint launches: the number of launches and how many prompts each takes, or 0 (see its definition).
+// Cuts a batch into joint launches: the number of launches and how many prompts each takes, or 0 (see joint_cuts).
 int fused_joint_cuts(int dtype, int D, int count, const ScoreGeom* G, int* cut);
 int fused_joint_plan(int dtype, int D, int count, const ScoreGeom* G, FusedGeom* F, int* take, int* wg_begin,
                      int* grid);

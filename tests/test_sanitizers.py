@@ -41,3 +41,15 @@ def test_long_prompt_plan_model_under_sanitizers(tmp_path):
     r = build_and_run(tmp_path, "long_plan_model", [os.path.join(ROOT, "tests", "sanitize", "long_plan_model.c")])
     assert r.returncode == 0, r.stdout + r.stderr
     assert "all cases passed" in r.stdout
+
+
+def test_cuts_of_batches_into_joint_launches(tmp_path):
+    """Optimised and without sanitizers: it also bounds the time that a plan takes in front of a launch."""
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    exe = str(tmp_path / "joint_cuts")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-o", exe, os.path.join(ROOT, "tests", "sanitize", "joint_cuts_driver.cpp")],
+                   check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert "all cases passed" in r.stdout
