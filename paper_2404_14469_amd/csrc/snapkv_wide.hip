@@ -792,6 +792,8 @@ size_t wide_part_bytes(const ScoreGeom& G) {
 
 hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st, const WideClear& clear) {
     if (count < 1 || count > kMaxWide) return hipErrorInvalidValue;
+    for (int i = 0; i < count; ++i)
+        if (!P[i].q || !P[i].k || !P[i].vote || !P[i].part) return hipErrorInvalidValue;
     Blocks b;
     if ((dtype != 0 && dtype != 2) || (D != 64 && D != 128) || !row_blocks(*P[0].G, &b)) return hipErrorInvalidValue;
     const ScoreGeom& G0 = *P[0].G;

@@ -3,6 +3,7 @@ host-side argument validation returns the documented codes before any GPU work (
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -115,6 +116,18 @@ def test_workspace_bytes():
     assert 0 < a < b and a % 256 == 0
     # must at least hold the votes and the pooled scores
     assert a >= 2 * 8 * (4096 - 32) * 4
+
+
+def test_two_pass_launcher_refuses_missing_buffers(tmp_path):
+    """A null buffer is an error of the launch, before any GPU work, and not a fault of the kernels."""
+    lib = pkg.load()._name
+    exe = str(tmp_path / "wide_guard")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", rocm + "/include", "-o", exe,
+                    os.path.join(ROOT, "tests", "sanitize", "wide_guard_driver.cpp"), lib, "-L", rocm + "/lib", "-lamdhip64",
+                    "-Wl,-rpath," + os.path.dirname(lib) + ":" + rocm + "/lib"], check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
 
 
 def test_binding_refuses_cpu_tensors():
