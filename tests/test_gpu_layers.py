@@ -9,6 +9,7 @@ import torch
 from paper_2404_14469_amd import workloads
 from paper_2404_14469_amd.workloads import Workload
 from parity import check_against_oracle, run_gpu
+from test_gpu_decode import launched
 
 pytestmark = pytest.mark.gpu
 
@@ -203,3 +204,14 @@ def test_one_unit_per_group(snapkv, name):
         compare(snapkv, w, cases, oks, ovs, ois)
     compare(snapkv, w, cases, oks, ovs, ois, oracle_on=(1,))
     assert snapkv.snapkv_sync_timeouts() == 0
+
+
+GENERAL = {"one_unit_too_many", "33_slices"}
+
+
+@pytest.mark.parametrize("name", sorted(ONE_UNIT))
+def test_which_calls_have_one_unit_per_group(snapkv, name, tmp_path):
+    w, (case,) = layer_cases(1, **{**ONE_UNIT[name], "layers": 1})
+    kernels = launched(lambda: run_gpu(snapkv, case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C), tmp_path)
+    forms = [n for n, _ in kernels if "score_fused<" in n]
+    assert forms and all(("true>" in n) == (name not in GENERAL) for n in forms), forms

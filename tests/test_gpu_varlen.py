@@ -7,6 +7,7 @@ import torch
 from paper_2404_14469_amd import workloads
 from paper_2404_14469_amd.workloads import Workload
 from parity import check_against_oracle, run_gpu
+from test_gpu_decode import launched
 
 pytestmark = pytest.mark.gpu
 
@@ -51,9 +52,10 @@ MIXES = {
     "d64_f16": dict(lengths=[2222, 5555, 3333], D=64, dtype="f16", C=200),
     "wide_window_runs_one_by_one": dict(lengths=[1500, 2100], W=160, C=320, p=5),
     "single_prompt": dict(lengths=[4321]),
-    # filled, one launch gives one of the eight a single group and 16 iterations; cut, seven take 8 and the last 2
-    "cut_into_seven_and_one": dict(lengths=[8500, 8490, 8507, 8501, 8499, 8508, 8493, 8510], Hq=32, Hkv=8, W=16, p=5, C=100),
-    "cut_equal_heads": dict(lengths=[17001, 9000, 16500, 16800, 2000, 16999, 17010, 16600, 900], Hq=16, Hkv=16, W=16, p=5, C=100),
+    # filled, one launch gives one of the eight a single group and 16 iterations; cut, the longest takes 2 by itself and the seven others 8
+    "cut_into_one_and_seven": dict(lengths=[8500, 8490, 8507, 8501, 8499, 8508, 8493, 8510], Hq=32, Hkv=8, W=16, p=5, C=100),
+    # 17 slices of 1024 keys six times, 9, 2 and 1; the selection takes 144 heads of up to 16384 positions
+    "cut_equal_heads": dict(lengths=[16399, 9000, 16385, 16390, 2000, 16398, 16400, 16387, 900], Hq=16, Hkv=16, W=16, p=5, C=100),
     # the gathers move four pieces per thread up to 2048 workgroups of single pieces and one beyond: batch / single calls
     "many_rows": dict(lengths=[6001, 5003, 5500], Hq=8, Hkv=8, C=1501),              # 2256 / 752
     "many_rows_alone": dict(lengths=[6001], Hq=8, Hkv=8, C=5003),                    # - / 2504
@@ -67,6 +69,16 @@ def test_batch_equals_single_calls(snapkv, name):
     cases, oks, ovs, ois, kept = run_batch(snapkv, ws)
     compare_with_single_calls(snapkv, ws, cases, oks, ovs, ois, kept, oracle_on=(0, len(ws) - 1))
     assert snapkv.snapkv_sync_timeouts() == 0
+
+
+@pytest.mark.parametrize("name,launches,least", [("cut_into_one_and_seven", 2, 238), ("cut_equal_heads", 2, 252), ("equal_lengths", 1, 1)])
+def test_cuts_of_joint_launches_are_taken(snapkv, tmp_path, name, launches, least):
+    """The results do not depend on the cuts (above), so the launches are looked at: eight prompts of 17 slices and two parts a head
+    as one of 14 groups and seven of two; nine of 16 heads as three and six (filled: eight, and 16 workgroups for the last)."""
+    kw = dict(MIXES[name])
+    ws = prompts(kw.pop("lengths"), **kw)
+    joint = [groups for n, groups in launched(lambda: run_batch(snapkv, ws), tmp_path) if "score_fused_joint<" in n]
+    assert len(joint) == launches and min(joint) >= least, joint
 
 
 def test_batch_larger_than_one_joint_launch(snapkv):

@@ -1,6 +1,8 @@
 """Prompts whose KV heads are met by 128 window rows or more, long enough for the two-pass scoring kernels
-(csrc/snapkv_wide.hip), or by 64 and longer than the single-read kernel holds: edges of rounds (128 keys), of slices (multiples of 128 keys, at most 64 of them) and of the
+(csrc/snapkv_wide.hip), or by 64 and longer than 131072 keys (163839 with two query heads of W = 32): edges of rounds (128 keys), of slices (multiples of 128 keys, at most 64 of them) and of the
 row blocks (128 rows, whole query heads), every storage type and layout, and rows whose sums leave the fp32 range."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -8,6 +10,7 @@ import torch
 from paper_2404_14469_amd import workloads
 from paper_2404_14469_amd.workloads import Workload
 from parity import check_against_oracle, run_gpu
+from test_gpu_decode import launched
 
 pytestmark = pytest.mark.gpu
 
@@ -73,9 +76,122 @@ def test_64_rows_against_oracle(snapkv, name):
     check_against_oracle(case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C, *res, heads=[w.Hkv - 1])
 
 
-def test_64_rows_layers_and_batches_equal_single_calls(snapkv):
+@pytest.mark.parametrize("L,g,W,two_passes", [(131072, 4, 16, False), (131073, 4, 16, True), (131072, 1, 64, False), (131073, 1, 64, True),
+                                              (163839, 2, 32, False), (163840, 2, 32, True)])
+def test_which_prompts_with_64_rows_take_the_two_passes(snapkv, tmp_path, L, g, W, two_passes):
+    w = half(L, g, W)
+    case = workloads.generate(w, device="cuda")
+    kernels = launched(lambda: run_gpu(snapkv, case["q_win"], case["k"], case["v"], w.pool_kind, w.p, w.C), tmp_path)
+    for name in ("wide_stats", "wide_votes"):
+        assert any(re.search(name + "<.*, 4>", n) for n, _ in kernels) == two_passes, kernels
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("at", [(5,), (60000,), tuple(range(16))])
+def test_64_rows_and_keys_that_are_not_finite(snapkv, at, value):
+    """Rows with an infinite or undefined logit have no votes to give, and that key's votes are undefined: as the single-read kernel
+    (one key less) leaves them, whether the key is among those that the rows' origins come from or not."""
+    w = half(131073, 4, 16)
+    case = workloads.generate(w, device="cuda")
+    q, k = case["q_win"], case["k"].clone()
+    k[0, list(at), 3] = value
+    votes = []
+    for L in (w.L, w.L - 1):
+        out = torch.empty((1, L - w.W), device="cuda")
+        snapkv.snapkv_pooled_scores(q, k[:, :L].contiguous(), 0, 1, out)
+        votes.append(out[0, :w.L - 1 - w.W])
+    two, one = votes
+    assert torch.equal(two.isnan(), one.isnan()) and torch.equal(two == 0, one == 0)
+    real = ~one.isnan()
+    # (the longer prompt has one more key in every row's sum: far less than one part in a thousand here)
+    assert float(((two - one)[real].abs() - 1e-3 * one[real].abs()).max()) <= 1e-30
+
+
+@pytest.mark.parametrize("g,W", [(4, 16), (1, 64)])
+@pytest.mark.parametrize("nats", [10.0, 40.0, 120.0])
+def test_64_rows_whose_reference_is_raised(snapkv, g, W, nats):
+    """As test_score_error_does_not_grow_with_the_logits_range, with blocks of four row units and two tiles a wave: a stretch of keys
+    lies far above the first sixteen.  The logits and their origins are exact here too, so the bound is the same."""
+    L, D = 131099, 128
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(18)
+    q = torch.zeros((g, W, D), device="cuda")
+    q[..., 3], q[..., 7] = 16.0, 1.0 / 8
+    k = torch.zeros((1, L, D), device="cuda")
+    k[0, :, 7] = torch.randint(-256, 257, (L,), generator=gen, device="cuda")
+    k[0, 70000:75000, 3] = round(nats * D ** 0.5 / 16 * 4) / 4
+    q, k = q.bfloat16(), k.bfloat16()
+    sc = torch.empty((1, L - W), device="cuda")
+    snapkv.snapkv_pooled_scores(q, k, 0, 1, sc)
+    logits = (q[0].double() @ k[0].double().t()) / D ** 0.5
+    seen = torch.arange(L, device="cuda") <= torch.arange(L - W, L, device="cuda").unsqueeze(1)
+    want = g * torch.softmax(logits.masked_fill(~seen, float("-inf")), dim=1)[:, :L - W].sum(0)
+    err = float((sc[0].double() - want).norm() / want.norm())
+    print(f"score error at {nats} nats: {err:.2e}")
+    assert err < 4.5e-7, err
+
+
+def test_64_rows_one_cache_per_query_head(snapkv):
+    """One vote row per query head from blocks of four of them: what every head keeps is what it keeps as a KV head of its own
+    (scored by another kernel there: the band decides)."""
+    w = half(131100, 4, 16, Hkv=1)
+    case = workloads.generate(w, device="cuda")
+    q, k, v = case["q_win"], case["k"], case["v"]
+    ok = torch.zeros((w.Hq, w.C, w.D), dtype=k.dtype, device="cuda")
+    ov = torch.zeros_like(ok)
+    oi = torch.full((w.Hq, w.C), -1, dtype=torch.int32, device="cuda")
+    kept = snapkv.snapkv_compress_per_query_head(q, k, v, w.pool_kind, w.p, w.C, ok, ov, oi)
+    kr, vr = (t.repeat_interleave(w.Hq, dim=0).contiguous() for t in (k, v))
+    sc = torch.empty((w.Hq, w.n), device="cuda")
+    snapkv.snapkv_pooled_scores(q, kr, w.pool_kind, w.p, sc)
+    torch.cuda.synchronize()
+    check_against_oracle(q, kr, vr, w.pool_kind, w.p, w.C, sc.cpu().numpy(), ok, ov, oi.cpu().numpy(), kept, heads=[0, 3],
+                         own_topk_exact=False)
+
+
+@pytest.mark.parametrize("g,W", [(4, 16), (1, 64)])
+def test_64_rows_on_a_callers_workspace_and_replayed(snapkv, g, W):
+    """On a workspace full of ones, and replayed from a graph with other calls' remains in it: bit for bit the own-scratch call."""
+    w = half(131101, g, W, Hkv=2)
+    cases = [workloads.generate(w, layer=l, device="cuda") for l in range(2)]
+    want = [run_gpu(snapkv, c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C) for c in cases]
+    q, k, v = (cases[0][n].clone() for n in ("q_win", "k", "v"))
+    ok, ov, oi = (t[0] for t in outputs(w, 1, k.dtype))
+    ws = torch.full((snapkv.snapkv_workspace_bytes(w.L, w.Hq, w.Hkv, w.D, w.W),), 255, dtype=torch.uint8, device="cuda")
+    status = torch.full((1,), -77, dtype=torch.int32, device="cuda")
+    args = (w.pool_kind, w.p, w.C, ok, ov, oi)
+
+    def load(l):
+        for t, n in ((q, "q_win"), (k, "k"), (v, "v")):
+            t.copy_(cases[l][n])
+        ok.zero_(), ov.zero_(), oi.fill_(-1), status.fill_(-77)
+
+    def same(l, what):
+        torch.cuda.synchronize()
+        assert np.array_equal(oi.cpu().numpy(), want[l][3]), (what, l)
+        assert torch.equal(ok, want[l][1]) and torch.equal(ov, want[l][2]), (what, l)
+
+    for l in (0, 1):
+        load(l)
+        snapkv.snapkv_compress(q, k, v, *args, workspace=ws)
+        same(l, "workspace")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        snapkv.snapkv_compress_ws_status(q, k, v, *args, ws, status)
+    for rep in range(4):
+        load(rep % 2)
+        if rep == 2:
+            ws.fill_(255)
+        graph.replay()
+        same(rep % 2, f"replay {rep}")
+        assert int(status.item()) == w.C
+    assert snapkv.snapkv_sync_timeouts() == 0
+
+
+@pytest.mark.parametrize("g,W", [(4, 16), (1, 64)])
+def test_64_rows_layers_and_batches_equal_single_calls(snapkv, g, W):
     """Stacked and separate layers, paged rows and a batch with prompts on both sides of the rule, bit for bit."""
-    w = half(131100, 4, 16, Hkv=2)
+    w = half(131100, g, W, Hkv=2)
     cases = [workloads.generate(w, layer=l, device="cuda") for l in range(2)] + [workloads.generate(w.with_(L=9001), device="cuda")]
     want = [run_gpu(snapkv, c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C) for c in cases]
     lists = [[c[n] for c in cases[:2]] for n in ("q_win", "k", "v")]
