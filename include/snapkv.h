@@ -379,7 +379,7 @@ const char* snapkv_stage_name(int stage);
 
 /*
  * Kernel scheme, a bit set (default 0).  Bit 0 clear: prompts whose KV heads are met by 128 or more window
- * rows, or by 64, in a two-byte type and long enough, are scored by two passes over K that meet all those rows at once;
+ * rows, or by 64 (then longer than 131072 keys), in a two-byte type and long enough, are scored by two passes over K that meet all those rows at once;
  * other prompts whose window logits fit the chip's register files by the single-read kernel (K is
  * streamed once); of a longer prompt that kernel takes the keys that fit and two streaming passes the rest
  * (those keys are streamed twice; the streaming passes hand nothing between workgroups).  Bit 0 set: always

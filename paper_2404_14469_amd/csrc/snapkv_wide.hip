@@ -16,7 +16,8 @@
 //     fewer than four units.  The slice length depends on the prompt's length and its own heads alone, so a head's
 //     result does not depend on which other layers or prompts share the launch.
 //   * A round's keys pass through LDS (landing registers -> two buffers, one barrier a round), where four groups
-//     of waves x two parts of the keys read them as fragments; the next round is on its way meanwhile.
+//     of waves x two parts of the keys (blocks of 64 rows: two groups x four parts) read them as fragments; the next round is on
+//     its way meanwhile.
 //   * A persistent grid of two workgroups per compute unit walks the slices of all units (of all prompts or layers of
 //     the call) in order, a contiguous run of whole slices each; a launch whose slices all find a place at once
 //     has a workgroup per slice.
@@ -31,8 +32,8 @@
 // head): 97 + 103 us against 277 us.
 //
 // The row reference.  Exponentials are taken relative to a reference of the row that is known before its keys are: its
-// largest logit among the prompt's first four keys (sixteen where a block has 64 rows).  The argument s - ref is rounded to fp32, so the terms that matter
-// must not lie far from the reference: a round in which a row's logits exceed it by about 2^kRaiseAt raises the row's
+// largest logit among the prompt's first four keys (sixteen where a block has 64 rows).  The argument s - ref is rounded
+// to fp32, so the terms that matter must not lie far from the reference: a round in which a row's logits exceed it by about 2^kRaiseAt raises the row's
 // reference to its largest logit less kRaiseBelow for the rest of the slice and takes its exponentials again, and
 // wide_votes uses the largest of the slices' references.  Normally distributed logits get there at 4.5 standard
 // deviations where one is 4.6 (base two), and not at all where it is 2.6.  No sum can overflow.  The margin below
@@ -92,15 +93,19 @@ constexpr float kRaiseBelow = 7.f;           //   to that logit less this
 //   2 heads: 27655: 46 / 46 / 42;  131072: 77 / 85 / 66;  32 layers of 1 head, 31337: 196 / 144 / 151
 // (with 512 in all: 1 head, 46087: 55, 131072: 67; 2 heads, 27655: 52)
 constexpr int64_t kMinRowKeys = 9 << 18;
-// With 64 rows the single-read kernel is faster by about a fifth while it holds the prompt (131072 keys); of a longer one it
-// takes the front, the rest is read twice by the streaming kernel.  Microseconds per call, this path / front and rest:
+// With 64 rows the single-read kernel is faster by 12 to 28 % up to 131072 keys, but for lengths that leave it compute units idle
+// (W = 16, 32/8 heads, this path / that kernel: 16384 keys 43 / 34, 40001: 61 / 62, 65536: 80 / 67, 90001: 98 / 103, 131072: 125 / 112;
+// W = 64, 32 heads, 32768: 125 / 103, 131072: 443 / 374).  Beyond that it has W = 16 with one row unit a part, the four parts of a KV head
+// one after another, up to 262144 keys, and everything else, as W = 16 from 262145 keys on, as a front read once and a rest that the
+// streaming kernel reads twice.  Microseconds per call, this path / those:
 //   W = 16, 32/8 heads:  131073 keys 128 / 274;  140001: 150 / 283;  175001: 185 / 287;  262144: 250 / 348;  380000: 356 / 509
 //   W = 64, 32/32 heads: 131073: 463 / 758;  140001: 502 / 782;  175001: 603 / 827;  262144: 848 / 1177;  300001: 981 / 1390
 //   one KV head, W = 16 and 64: 132000: 45 / 58, 48 / 75;  1000001: 144 / 268, 149 / 328
-//   (as far as it holds them: W = 16, 65536: 80 / 67, 131072: 125 / 112;  W = 64, 32768: 125 / 103, 131072: 443 / 374)
-// A window of two row units and two query heads a KV head is streamed better there: W = 32, 32/16 heads
-//   131073: 249 / 239;  150001: 285 / 273;  160001: 298 / 290;  170001: 313 / 344;  262144: 440 / 589;  with four KV heads
-//   131073: 76 / 95,  170001: 89 / 120.
+// A window of two row units and two query heads a KV head: W = 32, 32/16 heads
+//   131073: 249 / 239;  150001: 285 / 273;  160001: 298 / 290;  170001: 313 / 344;  262144: 440 / 589;
+// the line is that of sixteen KV heads, though with four of them this path is the faster one from 131073 keys on (76 / 95; 170001: 89 / 120).
+// Windows of 49 to 63 rows and one query head do not fall into blocks of 32 rows, and the single-read kernel holds 65536 keys of them; from there
+// to 131072 they go as front and rest too (not measured against this path).
 constexpr int64_t kMinRowKeys64 = (1 << 23) + 64, kMinRowKeys64of2 = 5 << 21;
 constexpr int64_t kMaxRounds = 1 << 26;      // rounds of one prompt at most (kMaxWide of them are counted in 32 bits)
 
