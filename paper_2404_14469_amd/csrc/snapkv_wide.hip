@@ -57,6 +57,15 @@
 // With the first key 8, 20 and 40 nats above the rest (W = 16, s = 1.8): 14.7 / 14.7 / 10.1, 41 / 41 / 31 and 206 / 205 / 140.  Started
 // from minus the reference instead: 0.61 to 0.71 of the first figure without such a key, but 1.2 to 1.8 of it with one.
 //
+// wide_stats takes its logits keys x rows (the operands exchanged): a lane has four keys of one row instead of one key of four rows, so
+// that it keeps two references and two sums instead of eight of each, and the sums over keys need an exchange between lanes only
+// once a slice, over four lanes instead of sixteen.  118 registers instead of 127, and microseconds per call, rows x keys / keys x rows: 28471
+// keys, 32/8 heads 56.85 / 56.39; 32749 token-major 59.33 / 58.47; 131072, W = 64 217.0 / 215.8; 32 layers of 31337 1062 / 1056 (two runs of one
+// side differ by 0.1 to 0.3 %).  The registers it frees are not enough for a second set of landing registers (14 to 18 spilled, 44.1 -> 48.0
+// for the two passes at 28471 keys); both rows' products piece by piece, for two chains of MFMAs and fewer registers of keys, change nothing.
+// The error of votes near the selection's threshold against float64 is what it was: over fifteen of the shapes and spreads named above
+// 0.999 of it on average, 0.988 to 1.008 singly.  wide_votes, which sums over rows, stays with rows x keys.
+//
 // MFMA layout: that of snapkv_fused.hip (16x16x32, lane l: row / column l % 16, contraction slice l / 16;
 // accumulator register r is row (l / 16) * 4 + r, column l % 16; the 16-byte pieces 4p + l / 16 of a row).
 #include "snapkv_internal.h"
@@ -138,20 +147,31 @@ template <int RUW> struct Origins {
     }
 };
 
-template <int CTRL> __device__ __forceinline__ float wdpp(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+// Sums and maxima over the lanes of other rows of sixteen: exchanges between the wave's halves and between the two rows of a half.
+struct Two {
+    float a, b;
+};
+__device__ __forceinline__ Two swap32(float a, float b) {
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return {__uint_as_float(x[0]), __uint_as_float(x[1])};
 }
-__device__ __forceinline__ float lanes16_max(float x) {
-    x = fmaxf(x, wdpp<0xB1>(x));
-    x = fmaxf(x, wdpp<0x4E>(x));
-    x = fmaxf(x, wdpp<0x141>(x));
-    return fmaxf(x, wdpp<0x140>(x));
+__device__ __forceinline__ Two swap16(float a, float b) {
+    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return {__uint_as_float(x[0]), __uint_as_float(x[1])};
 }
-__device__ __forceinline__ float lanes16_sum(float x) {
-    x += wdpp<0xB1>(x);
-    x += wdpp<0x4E>(x);
-    x += wdpp<0x141>(x);
-    return x + wdpp<0x140>(x);
+__device__ __forceinline__ float halves(float a, float b) {   // lanes 0-31: a of lane l and l + 32, lanes 32-63: b
+    const Two x = swap32(a, b);
+    return x.a + x.b;
+}
+__device__ __forceinline__ float quarters(float a, float b) {   // even rows of 16 lanes: a of both rows of the half, odd ones: b
+    const Two x = swap16(a, b);
+    return x.a + x.b;
+}
+__device__ __forceinline__ float rows_max(float x) {          // over the four rows of sixteen lanes
+    const Two y = swap32(x, x);
+    x = fmaxf(y.a, y.b);
+    const Two z = swap16(x, x);
+    return fmaxf(z.a, z.b);
 }
 
 // Orders LDS traffic only: the K rounds in flight are not waited for.
@@ -364,13 +384,13 @@ template <typename T, int D, bool PAGED, int N, int RUW> struct WideWave {   // 
             for (int x = 0; x < NP; ++x) q[i].v[x] = *reinterpret_cast<const uint4*>(p + 64 * x);
         }
     }
-    // Prompt-phase causal mask of the 16 keys from j0 on against row unit i of the wave: row x does not see keys
+    // Prompt-phase causal mask of the 16 keys from j0 on (keys x rows) against row unit i of the wave: row x does not see keys
     // after n + x (which for a real row covers the keys past the end; what padding rows hold is ignored).
     __device__ __forceinline__ void mask(wf32x4& a, int j0, int i, const Cursor& c) const {
-        const int ru = rg * kWaveRows + i, d = j0 - c.n + n16 - kg * 4 - (ru - (ru * A.inv_uh >> 8) * A.UH) * 16;
+        const int ru = rg * kWaveRows + i, d = j0 - c.n + kg * 4 - n16 - (ru - (ru * A.inv_uh >> 8) * A.UH) * 16;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            if (d > r) a[r] = -INFINITY;
+            if (d + r > 0) a[r] = -INFINITY;
     }
     __device__ __forceinline__ void keep(uint4* buf, const KFrag<D>& f) const {   // the wave's tile into the round's buffer
 #pragma unroll
@@ -400,13 +420,18 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     Cursor cc = begin_share(A, rounds), pc = cc;
     if (rounds <= 0) return;
     KFrag<D> q[kWaveRows], S;
-    float z[kWaveRows][4], ref[kWaveRows][4];
-    Origins<RUW> org;
+    float z[kWaveRows], ref[kWaveRows], neg[kWaveRows];   // of the lane's two rows; minus the rows' origins (RUW = 4)
 
     // A unit begins: the wave's Q rows, and the rows' origins and references from the prompt's first kFirst keys (or fewer: those that
     // every row sees; each quad, or row, of lanes brings all of them).  They depend on the unit alone, and every slice starts from
     // them, so a slice's result does not depend on which slices its workgroup had before.
-    float* const my = &sm_st[kBase][W.kp][W.rg * kWaveRows * 16 + W.kg * 4];   // from the lane's first row on
+    float* const my = &sm_st[kBase][W.kp][W.rg * kWaveRows * 16 + W.n16];   // the lane's first row
+    // Logits, keys x rows: a lane has four keys (4 * kg + r) of one row, so that the sums over keys need no exchange between lanes but
+    // for the four of a row, once a slice.
+    auto logits = [&](const KFrag<D>& f, int i) __attribute__((always_inline)) {
+        if constexpr (kOrigin<RUW>) return logits16<T, D>(f, q[i], wf32x4{neg[i], neg[i], neg[i], neg[i]});
+        else return logits16<T, D>(f, q[i]);
+    };
     auto ask_unit = [&](KFrag<D>& f) __attribute__((always_inline)) {
         W.load_q(q, cc);
         const int j = W.n16 & (kFirst - 1);
@@ -415,24 +440,21 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     auto begin_unit = [&](const KFrag<D>& f) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < kWaveRows; ++i) {
-            const wf32x4 a = logits16<T, D>(q[i], f);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float m = fmaxf(a[r], wdpp<0xB1>(a[r]));
-                m = fmaxf(m, wdpp<0x4E>(m));
-                if constexpr (kOrigin<RUW>) {   // of the four quads' maxima the second largest is the origin
-                    const float m2 = wdpp<0x141>(m), hi = fmaxf(m, m2), lo = fminf(m, m2), hi2 = wdpp<0x140>(hi), lo2 = wdpp<0x140>(lo);
-                    float o = fmaxf(fminf(hi, hi2), fmaxf(lo, lo2));
-                    o = fabsf(o) < 0x1p100f ? o : 0.f;
-                    org.neg[i][r] = -o;
-                    m = fmaxf(hi, hi2) - o;
-                }
-                m *= A.c2;
-                ref[i][r] = m == -INFINITY ? 0.f : m;
-                z[i][r] = 0.f;
+            const wf32x4 a = logits16<T, D>(f, q[i]);
+            float m = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));   // (four keys: every lane of the row has them)
+            if constexpr (kOrigin<RUW>) {   // of the four quads' maxima the second largest is the origin
+                const Two x = swap32(m, m);
+                const float hi = fmaxf(x.a, x.b), lo = fminf(x.a, x.b);
+                const Two h = swap16(hi, hi), l = swap16(lo, lo);
+                float o = fmaxf(fminf(h.a, h.b), fmaxf(l.a, l.b));
+                o = fabsf(o) < 0x1p100f ? o : 0.f;
+                neg[i] = -o;
+                m = fmaxf(h.a, h.b) - o;
             }
-            // (each lane reads back what it wrote itself)
-            *reinterpret_cast<float4*>(my + i * 16) = make_float4(ref[i][0], ref[i][1], ref[i][2], ref[i][3]);
+            m *= A.c2;
+            ref[i] = m == -INFINITY ? 0.f : m;
+            z[i] = 0.f;
+            my[i * 16] = ref[i];         // (the four lanes of a row hold the same)
         }
     };
     bool raised = false;                 // (wave-uniform) a reference was raised since the slice's start
@@ -469,28 +491,25 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
         if (pending) store_slice(par ^ 1);
         const int j0 = (int)W.round_key(cc) + W.kp * (TILES * 16);   // (prompts have less than 2^31 keys)
         const bool special = j0 + TILES * 16 > cc.n;   // window columns or keys past the end among the wave's
-        float y[kWaveRows][4];           // the round's sums
+        float y[kWaveRows];              // the round's sums
 #pragma unroll
         for (int t = 0; t < TILES; ++t) {
             KFrag<D> f;
             W.tile(f, buf, t);
 #pragma unroll
             for (int i = 0; i < kWaveRows; ++i) {
-                wf32x4 a = org.template logits<T, D>(q[i], f, i);
+                wf32x4 a = logits(f, i);
                 if (special) W.mask(a, j0 + t * 16, i, cc);
+                float x[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float x = __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -ref[i][r]));
-                    y[i][r] = t == 0 ? x : y[i][r] + x;
-                }
+                for (int r = 0; r < 4; ++r) x[r] = __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -ref[i]));
+                const float sum = (x[0] + x[1]) + (x[2] + x[3]);
+                y[i] = t == 0 ? sum : y[i] + sum;
             }
             __builtin_amdgcn_sched_barrier(0);   // (one tile at a time: more do not fit the registers)
         }
-        float top = y[0][0];
-#pragma unroll
-        for (int i = 0; i < kWaveRows; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) top = fmaxf(top, y[i][r]);
+        const float top = fmaxf(y[0], y[1]);
+        static_assert(kWaveRows == 2, "the rows of a lane are written out here and where a slice ends");
         if (__any(top > kRaiseAt)) {     // some row's logits lie far above its reference: first their maxima, then the sums again
             raised = true;
             auto each = [&](auto f2) __attribute__((always_inline)) {
@@ -500,61 +519,44 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
                     W.tile(f, buf, t);
 #pragma unroll
                     for (int i = 0; i < kWaveRows; ++i) {
-                        wf32x4 a = org.template logits<T, D>(q[i], f, i);
+                        wf32x4 a = logits(f, i);
                         W.mask(a, j0 + t * 16, i, cc);
                         f2(a, i);
                     }
                 }
             };
-#pragma unroll
-            for (int i = 0; i < kWaveRows; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) y[i][r] = -INFINITY;
-            each([&](const wf32x4& a, int i) __attribute__((always_inline)) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) y[i][r] = fmaxf(y[i][r], a[r]);
-            });
-#pragma unroll
-            for (int i = 0; i < kWaveRows; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float m = lanes16_max(y[i][r]) * A.c2, to = m > ref[i][r] + kRaiseMin ? m - kRaiseBelow : ref[i][r];
-                    z[i][r] *= __builtin_amdgcn_exp2f(ref[i][r] - to);
-                    ref[i][r] = to;
-                    y[i][r] = 0.f;
-                }
-            each([&](const wf32x4& a, int i) __attribute__((always_inline)) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) y[i][r] += __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -ref[i][r]));
-            });
-        }
-#pragma unroll
-        for (int i = 0; i < kWaveRows; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) z[i][r] += y[i][r];
-        --left;
-        if (cc.rd + 1 == cc.RPS) {       // the slice's last round
+            y[0] = y[1] = -INFINITY;
+            each([&](const wf32x4& a, int i) __attribute__((always_inline)) { y[i] = fmaxf(fmaxf(y[i], fmaxf(a[0], a[1])), fmaxf(a[2], a[3])); });
 #pragma unroll
             for (int i = 0; i < kWaveRows; ++i) {
-                float y[4];
+                const float m = rows_max(y[i]) * A.c2, to = m > ref[i] + kRaiseMin ? m - kRaiseBelow : ref[i];
+                z[i] *= __builtin_amdgcn_exp2f(ref[i] - to);
+                ref[i] = to;
+                y[i] = 0.f;
+            }
+            each([&](const wf32x4& a, int i) __attribute__((always_inline)) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) y[r] = lanes16_sum(z[i][r]);
-                if (W.n16 == 0) {
-                    *reinterpret_cast<float4*>(my + (kSum + par) * (PARTS * R) + i * 16) = make_float4(y[0], y[1], y[2], y[3]);
-                    *reinterpret_cast<float4*>(my + (kRef + par) * (PARTS * R) + i * 16) = make_float4(ref[i][0], ref[i][1], ref[i][2], ref[i][3]);
-                }
-                if constexpr (kOrigin<RUW>)
-                    if (W.n16 == 0) *reinterpret_cast<wf32x4*>(my + (kOrg + par) * (PARTS * R) + i * 16) = org.neg[i];
-                if (raised) {
-                    const float4 b = *reinterpret_cast<const float4*>(my + i * 16);
-                    ref[i][0] = b.x, ref[i][1] = b.y, ref[i][2] = b.z, ref[i][3] = b.w;
-                }
+                for (int r = 0; r < 4; ++r) y[i] += __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -ref[i]));
+            });
+        }
+        z[0] += y[0];
+        z[1] += y[1];
+        --left;
+        if (cc.rd + 1 == cc.RPS) {       // the slice's last round
+            const float sum = halves(z[0], z[1]);   // lanes 0-31: the first row's, of two of its four lanes; 32-63 the second's
+            const float all = quarters(sum, sum);
+            if ((W.kg & 1) == 0) {       // (a lane for each row)
+                const int second = W.kg >> 1;
+                my[(kSum + par) * (PARTS * R) + second * 16] = all;
+                my[(kRef + par) * (PARTS * R) + second * 16] = second ? ref[1] : ref[0];
+                if constexpr (kOrigin<RUW>) my[(kOrg + par) * (PARTS * R) + second * 16] = second ? neg[1] : neg[0];
+            }
+            if (raised) {
+                ref[0] = my[0];
+                ref[1] = my[16];
             }
             raised = false;
-#pragma unroll
-            for (int i = 0; i < kWaveRows; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) z[i][r] = 0.f;
+            z[0] = z[1] = 0.f;
             pending = A.e[cc.e].part + unit_part<RUW>(A, cc) + (int64_t)cc.sl * R;
             if constexpr (kOrigin<RUW>) origins = cc.sl == 0 ? pending + (int64_t)cc.NS * R : nullptr;
             par ^= 1;
@@ -680,14 +682,6 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
             if (t & 1) __builtin_amdgcn_sched_barrier(0);
         }
         // sums over the four lanes of a column: pairs of tiles share the exchanges, so that a lane ends with one tile's
-        auto halves = [](float a, float b) __attribute__((always_inline)) {   // lanes 0-31: a of lane l and l + 32, lanes 32-63: b
-            const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-            return __uint_as_float(x[0]) + __uint_as_float(x[1]);
-        };
-        auto quarters = [](float a, float b) __attribute__((always_inline)) {   // even rows of 16 lanes: a of both rows of the half, odd ones: b
-            const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-            return __uint_as_float(x[0]) + __uint_as_float(x[1]);
-        };
         if constexpr (TILES == 4) {
 #pragma unroll
             for (int i = 0; i < kWaveRows; ++i) {
