@@ -275,16 +275,18 @@ int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGe
     if (split_read) fused_sync_layout(LP.Gf, F, &S, ws.fused);   // F is the front part's plan
     const bool handoff = fused || split_read;
     if (handoff) S.gave_up_flag = ws.status_flag;
-    const bool scoring_clears = path == kPathWide && one_launch_select && !already_prepared;
+    const bool once = path == kPathWide && !layers && wide_once_ok(dtype, D, G);   // the two passes as one launch, with hand-off words too
+    const int64_t nwords = handoff ? fused_sync_pairs(F) : (once ? wide_once_pairs(G) : 0);
+    const bool scoring_clears = path == kPathWide && !once && one_launch_select && !already_prepared;
     if (!already_prepared && !scoring_clears) {
-        if (launch_prepare(handoff ? S.part : nullptr, handoff ? fused_sync_pairs(F) : 0,
+        if (launch_prepare(nwords ? ws.fused : nullptr, nwords,
                            prepare_select ? &ws.sel : nullptr, G.Hkv * G.g, st, ws.status_flag) != hipSuccess)   // scratch is laid out per query head
             return SNAPKV_ERR_HIP;
         stage_done(st, kStagePrepare);
     }
-    if (clean && handoff) {
-        clean->ones = reinterpret_cast<unsigned long long*>(S.part);
-        clean->nones = fused_sync_pairs(F);
+    if (clean && nwords) {
+        clean->ones = reinterpret_cast<unsigned long long*>(ws.fused);
+        clean->nones = nwords;
     }
     if (fused) {   // K is read once; otherwise two passes over K, or over the part of it the chip cannot hold
         if ((layers ? launch_score_fused_layers(dtype, D, *layers, G, F, S, ws.vote, st)
@@ -321,6 +323,11 @@ int run_scores(int dtype, const void* q_win, const void* k, int D, const ScoreGe
                          : launch_score_lse(dtype, D, q_win, k_rest, ws.lse, LP.Gr, LP.Fr, ws.vote + LP.front, st, rl)) != hipSuccess)
             return SNAPKV_ERR_HIP;
         stage_done(st, kStagePass2);
+        Gp.NV = G.g;
+        Gp.VB = 1;
+    } else if (once) {
+        const WidePrompt P{q_win, k, ws.vote, reinterpret_cast<float2*>(ws.fused), &G};
+        if (launch_score_wide_once(dtype, D, P, ws.status_flag, st) != hipSuccess) return SNAPKV_ERR_HIP;
         Gp.NV = G.g;
         Gp.VB = 1;
     } else if (path == kPathWide) {
@@ -493,12 +500,13 @@ int64_t compress_impl(int dtype, const void* q_win, const void* k, const void* v
     }
     if (g_allow_pool_select && pool_select_ok(Gsel, pool_kind, p, C - W)) {   // pooling and selection in one launch
         bool prepared = false;
-        streaming = path == kPathStream || path == kPathWide;
+        const bool once = path == kPathWide && !score_layers && wide_once_ok(dtype, D, G);   // (as run_scores decides)
+        streaming = path == kPathStream || (path == kPathWide && !once);
         if (own_scratch && path != kPathNone) {
             int dev = 0;
             if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) {
                 // the streaming paths do not touch the hand-off words
-                const int64_t nones = streaming ? 0 : fused_sync_pairs(Fp);
+                const int64_t nones = streaming ? 0 : once ? wide_once_pairs(G) : fused_sync_pairs(Fp);
                 now.hkv = Hkv;
                 now.hq = Hq;
                 now.fused_bytes = fused_sync_bytes(G);
@@ -818,7 +826,7 @@ int snapkv_profile_stop(double* stage_ms, int* calls) {
 
 int snapkv_debug_set_wait_limit(long long polls) {
     g_wait_limit.store(polls < 0 ? -1 : (polls > 0x7fffffffLL ? 0x7fffffffLL : polls));
-    if (polls == -2 && (!reset_sync_timeouts() || !reset_select_timeouts())) return SNAPKV_ERR_HIP;
+    if (polls == -2 && (!reset_sync_timeouts() || !reset_wide_timeouts() || !reset_select_timeouts())) return SNAPKV_ERR_HIP;
     return SNAPKV_OK;
 }
 
@@ -831,8 +839,8 @@ int snapkv_set_scoring_scheme(int scheme) {
 }
 
 int64_t snapkv_sync_timeouts(void) {
-    const unsigned v = read_sync_timeouts(), u = read_select_timeouts();
-    return (v == ~0u || u == ~0u) ? (int64_t)SNAPKV_ERR_HIP : (int64_t)v + (int64_t)u;
+    const unsigned v = read_sync_timeouts(), w = read_wide_timeouts(), u = read_select_timeouts();
+    return (v == ~0u || w == ~0u || u == ~0u) ? (int64_t)SNAPKV_ERR_HIP : (int64_t)v + (int64_t)w + (int64_t)u;
 }
 
 int snapkv_num_stages(void) { return kNumStageMarks - 1; }

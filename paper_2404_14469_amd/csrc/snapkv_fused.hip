@@ -44,6 +44,7 @@
 // elements feed which MFMA step is free as long as Q and K agree, so a lane takes the 16-byte
 // pieces 4p + l/16 of its row: the four lanes of a row then read 64 contiguous bytes per load.
 #include "snapkv_internal.h"
+#include "snapkv_handoff.h"
 
 #include <cstdlib>
 #include <type_traits>
@@ -162,39 +163,7 @@ unsigned read_sync_timeouts() {
 }
 
 
-constexpr unsigned long long kInvalidPair = ~0ull;   // a sum-exp is never NaN: no real pair looks like this
-constexpr int kSlicesPerBlock = 32;                  // slices merged by one half-wave in step L1
 constexpr int kL1BlocksPadded = 16;                  // level-1 words per row (Gg <= 512)
-
-__device__ __forceinline__ unsigned long long pack_pair(float m, float z) {
-    return ((unsigned long long)__float_as_uint(z) << 32) | (unsigned long long)__float_as_uint(m);
-}
-__device__ __forceinline__ void unpack_pair(unsigned long long bits, float& m, float& z) {
-    m = __uint_as_float((unsigned)(bits & 0xffffffffull));
-    z = __uint_as_float((unsigned)(bits >> 32));
-}
-__device__ __forceinline__ void publish_pair(float2* p, float m, float z) {
-    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), pack_pair(m, z), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long load_pair_bits(const float2* p) {
-    return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-}
-// Waits (bounded) until the word at p is a published pair; `bits` is what an earlier load saw.
-__device__ __forceinline__ unsigned long long await_pair(const float2* p, unsigned long long bits,
-                                                         unsigned limit, bool& gave_up) {
-    unsigned spins = 0;
-    while (bits == kInvalidPair) {
-        if (gave_up || ++spins > limit) {   // once a wait has given up, later ones do not wait again
-            gave_up = true;
-            return pack_pair(-INFINITY, 0.f);
-        }
-        __builtin_amdgcn_s_sleep(2);
-        bits = load_pair_bits(p);
-    }
-    return bits;
-}
 
 // Hand-offs between the waves of a workgroup go through LDS without a barrier: a wave writes
 // its data, then stamps its flag with the iteration number; a reader waits (bounded) until the
@@ -1211,8 +1180,6 @@ __global__ __launch_bounds__(NW * 64) void score_lse_layers(const float* __restr
 // ---------------------------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------------------------
-constexpr unsigned kSpinLimit = 1u << 15;   // polls before a hand-off wait gives up (tens of ms)
-
 static int g_cu_count[64] = {0};
 int g_fused_slot_cap = 0;
 

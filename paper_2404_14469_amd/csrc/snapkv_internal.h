@@ -187,8 +187,15 @@ struct WideClear {
 };
 hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st,
                              const WideClear& clear = WideClear{});
+// Both passes in one launch, for a call whose slices all find a place at once: the same votes bit for bit.  P.part then is
+// wide_once_pairs(*P.G) hand-off words that hold the "not published" pattern; gave_up (may be null): see FusedSync::gave_up_flag.
+bool wide_once_ok(int dtype, int D, const ScoreGeom& G);
+int64_t wide_once_pairs(const ScoreGeom& G);
+hipError_t launch_score_wide_once(int dtype, int D, const WidePrompt& P, unsigned* gave_up, hipStream_t st);
+unsigned read_wide_timeouts();
+bool reset_wide_timeouts();     // (test hook) both synchronise the device, as these do:
 unsigned read_sync_timeouts();
-bool reset_sync_timeouts();     // (test hook) both synchronise the device
+bool reset_sync_timeouts();
 bool reset_select_timeouts();
 // vote rows are G.vpitch floats apart, score rows score_pitch
 hipError_t launch_pool(const ScoreGeom& G, const float* vote, int pool_kind, int p, float* score,

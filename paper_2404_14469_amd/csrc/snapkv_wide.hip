@@ -18,9 +18,10 @@
 //   * A round's keys pass through LDS (landing registers -> two buffers, one barrier a round), where four groups
 //     of waves x two parts of the keys (blocks of 64 rows: two groups x four parts) read them as fragments; the next round is on
 //     its way meanwhile.
-//   * A persistent grid of two workgroups per compute unit walks the slices of all units (of all prompts or layers of
-//     the call) in order, a contiguous run of whole slices each; a launch whose slices all find a place at once
-//     has a workgroup per slice.
+//   * A single prompt whose slices all find a place at once has both passes in one launch (wide_once).
+//   * Otherwise a persistent grid of two workgroups per compute unit walks the slices of all units (of all prompts or layers of
+//     the call) in order, a contiguous run of whole slices each; a launch of one prompt whose slices all find a place at
+//     once has a workgroup per slice.
 //
 // What bounds it: the stream of keys, and arithmetic that does not hide behind it.  32 layers of 32/8 heads of 31337 keys take
 // 414 + 481 us (back to back 430 + 492; the single-read kernel 1218); the same loops without the arithmetic 384 + 471, with keys
@@ -69,10 +70,25 @@
 // MFMA layout: that of snapkv_fused.hip (16x16x32, lane l: row / column l % 16, contraction slice l / 16;
 // accumulator register r is row (l / 16) * 4 + r, column l % 16; the 16-byte pieces 4p + l / 16 of a row).
 #include "snapkv_internal.h"
+#include "snapkv_handoff.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace snapkv {
+
+__device__ unsigned g_wide_timeouts = 0;
+
+bool reset_wide_timeouts() {
+    const unsigned zero = 0;
+    return hipMemcpyToSymbol(HIP_SYMBOL(g_wide_timeouts), &zero, sizeof zero) == hipSuccess;
+}
+unsigned read_wide_timeouts() {
+    unsigned v = 0;
+    if (hipMemcpyFromSymbol(&v, HIP_SYMBOL(g_wide_timeouts), sizeof v) != hipSuccess) return ~0u;
+    return v;
+}
+
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 wbf16x8;
@@ -203,6 +219,8 @@ template <int N> struct WideArgs {   // N: 1 or kMaxWide (a single prompt's laun
     int64_t pages, row0;
     unsigned rounds;                 // of all entries: each workgroup's share is share rounds, one more for the first `more`
     unsigned share, more;
+    unsigned spin_limit;             // wide_once: polls before a workgroup helps itself,
+    unsigned* gave_up;               //   and null, or a word that is set when one gives up
     unsigned* zeros;                 // words the selection expects to be zero (see WideClear); null: none
     int64_t nzeros;
     unsigned* flag;
@@ -353,9 +371,12 @@ template <typename T, int D, bool PAGED, int N, int RUW> struct WideWave {   // 
     }
     // This wave's tile of the cursor's round, and the cursor moved on.  Unconditional (see row_of).
     __device__ __forceinline__ KFrag<D> request(Cursor& c) {
-        KFrag<D> f;
         const Cursor at = c;
         advance(A, c);
+        return request(at, c);
+    }
+    __device__ __forceinline__ KFrag<D> request(const Cursor& at, const Cursor& c) {   // c: the request after this one
+        KFrag<D> f;
         int64_t row;
         if constexpr (PAGED) {
             row = paged_row(page_id, in_page);
@@ -402,42 +423,29 @@ template <typename T, int D, bool PAGED, int N, int RUW> struct WideWave {   // 
     }
 };
 
-template <typename T, int D, bool PAGED, int N, int RUW>
-__global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
-    using Wv = WideWave<T, D, PAGED, N, RUW>;
-    constexpr int R = Wv::R, TILES = Wv::TILES, PARTS = Wv::PARTS;
-    __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];                      // K of two rounds as MFMA fragments
-    constexpr int kFirst = RUW == 8 ? 4 : 16;
-    enum { kBase, kRef, kSum = kRef + 2, kOrg = kSum + 2, kStatArrays = kOrg + 2 * kExtra<RUW> };   // per part and row: the references at a slice's
-    __shared__ __attribute__((aligned(16))) float sm_st[kStatArrays][PARTS][R];   // start, two slices' references, their sums and the origins
-    Wv W(A);
-    {
-        const int64_t wg = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, all = (int64_t)gridDim.x * gridDim.y * gridDim.z * kThreads;
-        for (int64_t i = wg * kThreads + W.tid; i < A.nzeros; i += all) A.zeros[i] = 0u;
-        if (A.flag && wg == 0 && W.tid == 0) *A.flag = 0u;
-    }
-    int rounds;
-    Cursor cc = begin_share(A, rounds), pc = cc;
-    if (rounds <= 0) return;
-    KFrag<D> q[kWaveRows], S;
-    float z[kWaveRows], ref[kWaveRows], neg[kWaveRows];   // of the lane's two rows; minus the rows' origins (RUW = 4)
+// The sums of exponentials of a lane's two rows (n16 of the wave's two row units) relative to their references.  Logits are taken keys x
+// rows: a lane has four keys (4 * kg + r) of one row, so that the sums over keys need no exchange between lanes but for the four of a
+// row, once a slice.
+template <typename T, int D, int RUW, typename Wv> struct RowSums {
+    static_assert(kWaveRows == 2, "the rows of a lane are written out");
+    static constexpr int kFirst = RUW == 8 ? 4 : 16;    // keys that the references come from
+    const Wv& W;
+    const KFrag<D> (&q)[kWaveRows];
+    float z[kWaveRows], ref[kWaveRows], neg[kWaveRows];  // neg: minus the rows' origins (RUW = 4)
+    bool raised = false;                                // (wave-uniform) a reference was raised since it was last put back
 
-    // A unit begins: the wave's Q rows, and the rows' origins and references from the prompt's first kFirst keys (or fewer: those that
-    // every row sees; each quad, or row, of lanes brings all of them).  They depend on the unit alone, and every slice starts from
-    // them, so a slice's result does not depend on which slices its workgroup had before.
-    float* const my = &sm_st[kBase][W.kp][W.rg * kWaveRows * 16 + W.n16];   // the lane's first row
-    // Logits, keys x rows: a lane has four keys (4 * kg + r) of one row, so that the sums over keys need no exchange between lanes but
-    // for the four of a row, once a slice.
-    auto logits = [&](const KFrag<D>& f, int i) __attribute__((always_inline)) {
-        if constexpr (kOrigin<RUW>) return logits16<T, D>(f, q[i], wf32x4{neg[i], neg[i], neg[i], neg[i]});
-        else return logits16<T, D>(f, q[i]);
-    };
-    auto ask_unit = [&](KFrag<D>& f) __attribute__((always_inline)) {
-        W.load_q(q, cc);
+    __device__ __forceinline__ RowSums(const Wv& w, const KFrag<D> (&q_)[kWaveRows]) : W(w), q(q_) {}
+    __device__ __forceinline__ wf32x4 start(int i) const {
+        const float v = kOrigin<RUW> ? neg[i] : 0.f;
+        return wf32x4{v, v, v, v};
+    }
+    // The rows' origins and references from the prompt's first kFirst keys (or fewer: those that every row sees; each row of lanes
+    // brings all of them).  They depend on the unit alone.
+    __device__ __forceinline__ void ask_first(KFrag<D>& f, const Cursor& c) const {
         const int j = W.n16 & (kFirst - 1);
-        W.load_row(f, cc, W.row_of(cc, j < cc.n ? j : cc.n));
-    };
-    auto begin_unit = [&](const KFrag<D>& f) __attribute__((always_inline)) {
+        W.load_row(f, c, W.row_of(c, j < c.n ? j : c.n));
+    }
+    __device__ __forceinline__ void begin(const KFrag<D>& f) {
 #pragma unroll
         for (int i = 0; i < kWaveRows; ++i) {
             const wf32x4 a = logits16<T, D>(f, q[i]);
@@ -451,26 +459,209 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
                 neg[i] = -o;
                 m = fmaxf(h.a, h.b) - o;
             }
-            m *= A.c2;
+            m *= W.A.c2;
             ref[i] = m == -INFINITY ? 0.f : m;
             z[i] = 0.f;
-            my[i * 16] = ref[i];         // (the four lanes of a row hold the same)
         }
+    }
+    // A round's keys (in buf), which begin with the cursor's.
+    __device__ __forceinline__ void round(const uint4* buf, const Cursor& cc) {
+        constexpr int TILES = Wv::TILES;
+        const float c2 = W.A.c2;
+        const int j0 = (int)W.round_key(cc) + W.kp * (TILES * 16);   // (prompts have less than 2^31 keys)
+        const bool special = j0 + TILES * 16 > cc.n;   // window columns or keys past the end among the wave's
+        float y[kWaveRows];              // the round's sums
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            KFrag<D> f;
+            W.tile(f, buf, t);
+#pragma unroll
+            for (int i = 0; i < kWaveRows; ++i) {
+                wf32x4 a = logits16<T, D>(f, q[i], start(i));
+                if (special) W.mask(a, j0 + t * 16, i, cc);
+                float x[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[r] = __builtin_amdgcn_exp2f(fmaf(a[r], c2, -ref[i]));
+                const float sum = (x[0] + x[1]) + (x[2] + x[3]);
+                y[i] = t == 0 ? sum : y[i] + sum;
+            }
+            __builtin_amdgcn_sched_barrier(0);   // (one tile at a time: more do not fit the registers)
+        }
+        if (__any(fmaxf(y[0], y[1]) > kRaiseAt)) {   // some row's logits lie far above its reference: first their maxima, then the sums again
+            raised = true;
+            auto each = [&](auto f2) __attribute__((always_inline)) {
+#pragma clang loop unroll(disable)
+                for (int t = 0; t < TILES; ++t) {
+                    KFrag<D> f;
+                    W.tile(f, buf, t);
+#pragma unroll
+                    for (int i = 0; i < kWaveRows; ++i) {
+                        wf32x4 a = logits16<T, D>(f, q[i], start(i));
+                        W.mask(a, j0 + t * 16, i, cc);
+                        f2(a, i);
+                    }
+                }
+            };
+            y[0] = y[1] = -INFINITY;
+            each([&](const wf32x4& a, int i) __attribute__((always_inline)) { y[i] = fmaxf(fmaxf(y[i], fmaxf(a[0], a[1])), fmaxf(a[2], a[3])); });
+#pragma unroll
+            for (int i = 0; i < kWaveRows; ++i) {
+                const float m = rows_max(y[i]) * c2, to = m > ref[i] + kRaiseMin ? m - kRaiseBelow : ref[i];
+                z[i] *= __builtin_amdgcn_exp2f(ref[i] - to);
+                ref[i] = to;
+                y[i] = 0.f;
+            }
+            each([&](const wf32x4& a, int i) __attribute__((always_inline)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) y[i] += __builtin_amdgcn_exp2f(fmaf(a[r], c2, -ref[i]));
+            });
+        }
+        z[0] += y[0];
+        z[1] += y[1];
+    }
+    // The sums over the four lanes of a row, and the references: st[0] and st[1], a part's rows one behind the other.
+    __device__ __forceinline__ void leave(float* ref_to, float* sum_to, float* origin_to) const {
+        const float sum = halves(z[0], z[1]);   // lanes 0-31: the first row's, of two of its four lanes; 32-63 the second's
+        const float all = quarters(sum, sum);
+        if ((W.kg & 1) == 0) {           // (a lane for each row)
+            const int second = W.kg >> 1, at = (W.rg * kWaveRows + second) * 16 + W.n16;
+            ref_to[at] = second ? ref[1] : ref[0];
+            sum_to[at] = all;
+            if constexpr (kOrigin<RUW>)
+                if (origin_to) origin_to[at] = second ? neg[1] : neg[0];
+        }
+    }
+};
+
+// The parts' sums of a row added up in a fixed order: (reference, sum).
+template <int PARTS, int R> __device__ __forceinline__ float2 add_parts(const float (&ref)[PARTS][R], const float (&sum)[PARTS][R], int row) {
+    float m = -INFINITY, s = 0.f;
+#pragma unroll
+    for (int v = 0; v < PARTS; ++v) m = fmaxf(m, ref[v][row]);
+#pragma unroll
+    for (int v = 0; v < PARTS; ++v) s += sum[v][row] * __builtin_amdgcn_exp2f(ref[v][row] - m);
+    return make_float2(m, s);
+}
+
+// (reference, sum) pairs merged in a balanced tree (fixed order, few roundings)
+template <int n> __device__ __forceinline__ void fold(const float2 (&y)[n], float& m, float& s) {
+    float t[n];
+    m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < n; ++i) m = fmaxf(m, y[i].y != 0.f ? y[i].x : -INFINITY);
+#pragma unroll
+    for (int i = 0; i < n; ++i) t[i] = y[i].y != 0.f ? y[i].y * __builtin_amdgcn_exp2f(y[i].x - m) : 0.f;
+#pragma unroll
+    for (int d = 1; d < n; d <<= 1)
+#pragma unroll
+        for (int i = 0; i + d < n; i += 2 * d) t[i] += t[i + d];
+    s = t[0];
+}
+
+// Sums over the rows of a row unit of the votes on a round's keys (in buf), into sm_v; logits are taken rows x keys.
+// mref and wgt: the rows' reference and 1 / sum (padding rows: +inf and 0).
+template <typename T, int D, int RUW, typename Wv>
+__device__ __forceinline__ void round_votes(const Wv& W, const KFrag<D> (&q)[kWaveRows], const Origins<RUW>& org, const float (&mref)[kWaveRows][4],
+                                            const float (&wgt)[kWaveRows][4], const uint4* buf, float (&sm_v)[RUW][kRound]) {
+    constexpr int TILES = Wv::TILES;
+    const float c2 = W.A.c2;
+    float v[kWaveRows][TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+        KFrag<D> f;
+        W.tile(f, buf, t);
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i) {
+            const wf32x4 a = org.template logits<T, D>(q[i], f, i);
+            float s = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s = fmaf(__builtin_amdgcn_exp2f(fmaf(a[r], c2, -mref[i][r])), wgt[i][r], s);
+            v[i][t] = s;
+        }
+        if (t & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    // sums over the four lanes of a column: pairs of tiles share the exchanges, so that a lane ends with one tile's
+    if constexpr (TILES == 4) {
+#pragma unroll
+        for (int i = 0; i < kWaveRows; ++i)
+            sm_v[W.rg * kWaveRows + i][W.kp * (TILES * 16) + ((W.kg >> 1) + 2 * (W.kg & 1)) * 16 + W.n16] =
+                quarters(halves(v[i][0], v[i][1]), halves(v[i][2], v[i][3]));
+    } else {                             // the wave's two row units share them too
+        sm_v[W.rg * kWaveRows + (W.kg & 1)][W.kp * (TILES * 16) + (W.kg >> 1) * 16 + W.n16] =
+            quarters(halves(v[0][0], v[0][1]), halves(v[1][0], v[1][1]));
+    }
+}
+// A row's (reference, 1 / sum) from what its slices' merge came to.
+template <int N> __device__ __forceinline__ float2 row_weight(const WideArgs<N>& A, const Cursor& cc, int row, float m, float s) {
+    const int ru = row >> 4, rh = ru * A.inv_uh >> 8;
+    const bool real = rh < A.hb && cc.blk * A.hb + rh < A.g && (ru - rh * A.UH) * 16 + (row & 15) < A.W && s > 0.f;
+    return real ? make_float2(m, 1.0f / s) : make_float2(INFINITY, 0.f);
+}
+// Where a round's votes go: from the round's first key in the block's first query head's vote row on.
+struct VoteRows {
+    float* at = nullptr;
+    int64_t pitch = 0;
+    int keys = 0, heads = 0;
+    template <typename Wv> __device__ __forceinline__ void aim(const Wv& W, const Cursor& cc) {
+        const WideEntry& E = W.A.e[cc.e];
+        const int h0 = cc.blk * W.A.hb;
+        const int64_t k0 = W.round_key(cc);
+        at = E.vote + ((int64_t)cc.kv * W.A.g + h0) * E.vpitch + k0;
+        pitch = E.vpitch;
+        keys = (int)(cc.n - k0 < kRound ? cc.n - k0 : kRound);
+        heads = W.A.g - h0 < W.A.hb ? W.A.g - h0 : W.A.hb;
+    }
+    // The row units of every query head added up and stored.
+    template <int RUW> __device__ __forceinline__ void store(const float (&sm_v)[RUW][kRound], int tid, int UH) const {
+        const int key = tid % kRound;
+        if (key < keys)
+            for (int h = tid / kRound; h < heads; h += kThreads / kRound) {
+                float s = sm_v[h * UH][key];
+                for (int u = 1; u < UH; ++u) s += sm_v[h * UH + u][key];
+                // (device scope: see the vote stores of the single-read kernel)
+                __hip_atomic_store(at + (int64_t)h * pitch + key, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+    }
+};
+
+template <typename T, int D, bool PAGED, int N, int RUW>
+__global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
+    using Wv = WideWave<T, D, PAGED, N, RUW>;
+    constexpr int R = Wv::R, PARTS = Wv::PARTS;
+    __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];                      // K of two rounds as MFMA fragments
+    __shared__ float sm_base[PARTS][R];                                  // the references at a slice's start
+    __shared__ float sm_ref[2][PARTS][R], sm_sum[2][PARTS][R], sm_org[2][kExtra<RUW> ? R : 1];   // two slices' references, sums and origins
+    Wv W(A);
+    {
+        const int64_t wg = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, all = (int64_t)gridDim.x * gridDim.y * gridDim.z * kThreads;
+        for (int64_t i = wg * kThreads + W.tid; i < A.nzeros; i += all) A.zeros[i] = 0u;
+        if (A.flag && wg == 0 && W.tid == 0) *A.flag = 0u;
+    }
+    int rounds;
+    Cursor cc = begin_share(A, rounds), pc = cc;
+    if (rounds <= 0) return;
+    KFrag<D> q[kWaveRows], S;
+    RowSums<T, D, RUW, Wv> rs(W, q);
+
+    // A unit begins; every slice starts from the unit's references, so its result does not depend on which slices its workgroup had before.
+    float* const base = &sm_base[W.kp][W.rg * kWaveRows * 16 + W.n16];   // the lane's first row (its four lanes hold the same)
+    auto ask_unit = [&](KFrag<D>& f) __attribute__((always_inline)) {
+        W.load_q(q, cc);
+        rs.ask_first(f, cc);
     };
-    bool raised = false;                 // (wave-uniform) a reference was raised since the slice's start
+    auto begin_unit = [&](const KFrag<D>& f) __attribute__((always_inline)) {
+        rs.begin(f);
+        base[0] = rs.ref[0];
+        base[16] = rs.ref[1];
+    };
     int par = 0;                         // which half of sm_ref and sm_sum the current slice uses
     float2* pending = nullptr;           // where the pairs of the slice before go, once all waves have left theirs,
     float2* origins = nullptr;           //   and the unit's origins (with its first slice)
     auto store_slice = [&](int half) __attribute__((always_inline)) {
-        if (W.tid < R) {                 // fixed order over the parts
-            float m = -INFINITY, s = 0.f;
-#pragma unroll
-            for (int v = 0; v < PARTS; ++v) m = fmaxf(m, sm_st[kRef + half][v][W.tid]);
-#pragma unroll
-            for (int v = 0; v < PARTS; ++v) s += sm_st[kSum + half][v][W.tid] * __builtin_amdgcn_exp2f(sm_st[kRef + half][v][W.tid] - m);
-            pending[W.tid] = make_float2(m, s);
+        if (W.tid < R) {
+            pending[W.tid] = add_parts<PARTS, R>(sm_ref[half], sm_sum[half], W.tid);
             if constexpr (kOrigin<RUW>)
-                if (origins) origins[W.tid] = make_float2(sm_st[kOrg + half][0][W.tid], 0.f);
+                if (origins) origins[W.tid] = make_float2(sm_org[half][W.tid], 0.f);
         }
         pending = nullptr;
     };
@@ -484,79 +675,20 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
     // A round: its keys go from the landing registers to LDS, the next round is requested, and every wave meets its
     // part of the keys with its rows.
     for (int half = 0;; half ^= 1) {
-        const uint4* const buf = kbuf[half];
         W.keep(kbuf[half], S);
         S = W.request(pc);
         lds_meet();
         if (pending) store_slice(par ^ 1);
-        const int j0 = (int)W.round_key(cc) + W.kp * (TILES * 16);   // (prompts have less than 2^31 keys)
-        const bool special = j0 + TILES * 16 > cc.n;   // window columns or keys past the end among the wave's
-        float y[kWaveRows];              // the round's sums
-#pragma unroll
-        for (int t = 0; t < TILES; ++t) {
-            KFrag<D> f;
-            W.tile(f, buf, t);
-#pragma unroll
-            for (int i = 0; i < kWaveRows; ++i) {
-                wf32x4 a = logits(f, i);
-                if (special) W.mask(a, j0 + t * 16, i, cc);
-                float x[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) x[r] = __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -ref[i]));
-                const float sum = (x[0] + x[1]) + (x[2] + x[3]);
-                y[i] = t == 0 ? sum : y[i] + sum;
-            }
-            __builtin_amdgcn_sched_barrier(0);   // (one tile at a time: more do not fit the registers)
-        }
-        const float top = fmaxf(y[0], y[1]);
-        static_assert(kWaveRows == 2, "the rows of a lane are written out here and where a slice ends");
-        if (__any(top > kRaiseAt)) {     // some row's logits lie far above its reference: first their maxima, then the sums again
-            raised = true;
-            auto each = [&](auto f2) __attribute__((always_inline)) {
-#pragma clang loop unroll(disable)
-                for (int t = 0; t < TILES; ++t) {
-                    KFrag<D> f;
-                    W.tile(f, buf, t);
-#pragma unroll
-                    for (int i = 0; i < kWaveRows; ++i) {
-                        wf32x4 a = logits(f, i);
-                        W.mask(a, j0 + t * 16, i, cc);
-                        f2(a, i);
-                    }
-                }
-            };
-            y[0] = y[1] = -INFINITY;
-            each([&](const wf32x4& a, int i) __attribute__((always_inline)) { y[i] = fmaxf(fmaxf(y[i], fmaxf(a[0], a[1])), fmaxf(a[2], a[3])); });
-#pragma unroll
-            for (int i = 0; i < kWaveRows; ++i) {
-                const float m = rows_max(y[i]) * A.c2, to = m > ref[i] + kRaiseMin ? m - kRaiseBelow : ref[i];
-                z[i] *= __builtin_amdgcn_exp2f(ref[i] - to);
-                ref[i] = to;
-                y[i] = 0.f;
-            }
-            each([&](const wf32x4& a, int i) __attribute__((always_inline)) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) y[i] += __builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -ref[i]));
-            });
-        }
-        z[0] += y[0];
-        z[1] += y[1];
+        rs.round(kbuf[half], cc);
         --left;
         if (cc.rd + 1 == cc.RPS) {       // the slice's last round
-            const float sum = halves(z[0], z[1]);   // lanes 0-31: the first row's, of two of its four lanes; 32-63 the second's
-            const float all = quarters(sum, sum);
-            if ((W.kg & 1) == 0) {       // (a lane for each row)
-                const int second = W.kg >> 1;
-                my[(kSum + par) * (PARTS * R) + second * 16] = all;
-                my[(kRef + par) * (PARTS * R) + second * 16] = second ? ref[1] : ref[0];
-                if constexpr (kOrigin<RUW>) my[(kOrg + par) * (PARTS * R) + second * 16] = second ? neg[1] : neg[0];
+            rs.leave(sm_ref[par][W.kp], sm_sum[par][W.kp], W.kp == 0 ? sm_org[par] : nullptr);
+            if (rs.raised) {
+                rs.ref[0] = base[0];
+                rs.ref[1] = base[16];
             }
-            if (raised) {
-                ref[0] = my[0];
-                ref[1] = my[16];
-            }
-            raised = false;
-            z[0] = z[1] = 0.f;
+            rs.raised = false;
+            rs.z[0] = rs.z[1] = 0.f;
             pending = A.e[cc.e].part + unit_part<RUW>(A, cc) + (int64_t)cc.sl * R;
             if constexpr (kOrigin<RUW>) origins = cc.sl == 0 ? pending + (int64_t)cc.NS * R : nullptr;
             par ^= 1;
@@ -574,7 +706,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
 template <typename T, int D, bool PAGED, int N, int RUW>
 __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
     using Wv = WideWave<T, D, PAGED, N, RUW>;
-    constexpr int R = Wv::R, TILES = Wv::TILES, SUB = kThreads / R;   // SUB threads share a row in the merge of its slices
+    constexpr int R = Wv::R, SUB = kThreads / R;   // SUB threads share a row in the merge of its slices
     __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];
     __shared__ float sm_v[2][RUW][kRound];                            // sums over the rows of a row unit, per key
     __shared__ float2 sm[SUB][R];
@@ -590,21 +722,6 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
 
     Origins<RUW> org;
     float mref[kWaveRows][4], wgt[kWaveRows][4];   // the rows' reference and 1 / sum (padding rows: +inf and 0)
-    // (reference, sum) pairs merged in a balanced tree (fixed order, few roundings)
-    auto fold = [](const auto& y, float& m, float& s) __attribute__((always_inline)) {
-        constexpr int n = sizeof(y) / sizeof(float2);
-        float t[n];
-        m = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < n; ++i) m = fmaxf(m, y[i].y != 0.f ? y[i].x : -INFINITY);
-#pragma unroll
-        for (int i = 0; i < n; ++i) t[i] = y[i].y != 0.f ? y[i].y * __builtin_amdgcn_exp2f(y[i].x - m) : 0.f;
-#pragma unroll
-        for (int d = 1; d < n; d <<= 1)
-#pragma unroll
-            for (int i = 0; i + d < n; i += 2 * d) t[i] += t[i + d];
-        s = t[0];
-    };
     auto begin_unit = [&]() __attribute__((always_inline)) {            // the unit's slices merged in a fixed order, and the wave's Q rows
         const int row = W.tid % R, sub = W.tid / R;
         const float2* src = A.e[cc.e].part + unit_part<RUW>(A, cc) + row;
@@ -630,9 +747,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
 #pragma unroll
             for (int i = 0; i < SUB; ++i) y[i] = sm[i][W.tid];
             fold(y, m, s);
-            const int ru = W.tid >> 4, rh = ru * A.inv_uh >> 8;
-            const bool real = rh < A.hb && cc.blk * A.hb + rh < A.g && (ru - rh * A.UH) * 16 + (W.tid & 15) < A.W && s > 0.f;
-            smf[W.tid] = real ? make_float2(m, 1.0f / s) : make_float2(INFINITY, 0.f);
+            smf[W.tid] = row_weight(A, cc, W.tid, m, s);
         }
         lds_meet();
 #pragma unroll
@@ -646,65 +761,171 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
     };
     begin_unit();
 
-    // The votes of the round before: the row units of every query head added up and stored.
-    float* pending = nullptr;            // its first key in the first query head's vote row
-    int64_t pend_pitch = 0;
-    int pend_keys = 0, pend_heads = 0;
-    auto store_votes = [&](int half) __attribute__((always_inline)) {
-        const int key = W.tid % kRound;
-        if (key < pend_keys)
-            for (int h = W.tid / kRound; h < pend_heads; h += kThreads / kRound) {
-                float s = sm_v[half][h * A.UH][key];
-                for (int u = 1; u < A.UH; ++u) s += sm_v[half][h * A.UH + u][key];
-                // (device scope: see the vote stores of the single-read kernel)
-                __hip_atomic_store(pending + (int64_t)h * pend_pitch + key, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-    };
+    VoteRows last;                       // of the round before
     int left = rounds;
     for (int half = 0;; half ^= 1) {
         W.keep(kbuf[half], S);
         S = W.request(pc);
         lds_meet();
-        if (pending) store_votes(half ^ 1);
-        float v[kWaveRows][TILES];
-#pragma unroll
-        for (int t = 0; t < TILES; ++t) {
-            KFrag<D> f;
-            W.tile(f, kbuf[half], t);
-#pragma unroll
-            for (int i = 0; i < kWaveRows; ++i) {
-                const wf32x4 a = org.template logits<T, D>(q[i], f, i);
-                float s = 0.f;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) s = fmaf(__builtin_amdgcn_exp2f(fmaf(a[r], A.c2, -mref[i][r])), wgt[i][r], s);
-                v[i][t] = s;
-            }
-            if (t & 1) __builtin_amdgcn_sched_barrier(0);
-        }
-        // sums over the four lanes of a column: pairs of tiles share the exchanges, so that a lane ends with one tile's
-        if constexpr (TILES == 4) {
-#pragma unroll
-            for (int i = 0; i < kWaveRows; ++i) {
-                float* dst = &sm_v[half][W.rg * kWaveRows + i][W.kp * (TILES * 16)];
-                dst[((W.kg >> 1) + 2 * (W.kg & 1)) * 16 + W.n16] = quarters(halves(v[i][0], v[i][1]), halves(v[i][2], v[i][3]));
-            }
-        } else {                         // the wave's two row units share them too
-            sm_v[half][W.rg * kWaveRows + (W.kg & 1)][W.kp * (TILES * 16) + (W.kg >> 1) * 16 + W.n16] =
-                quarters(halves(v[0][0], v[0][1]), halves(v[1][0], v[1][1]));
-        }
-        const WideEntry& E = A.e[cc.e];
-        const int h0 = cc.blk * A.hb;
-        const int64_t k0 = W.round_key(cc);
-        pending = E.vote + ((int64_t)cc.kv * A.g + h0) * E.vpitch + k0;
-        pend_pitch = E.vpitch;
-        pend_keys = (int)(cc.n - k0 < kRound ? cc.n - k0 : kRound);
-        pend_heads = A.g - h0 < A.hb ? A.g - h0 : A.hb;
+        last.template store<RUW>(sm_v[half ^ 1], W.tid, A.UH);
+        round_votes<T, D, RUW>(W, q, org, mref, wgt, kbuf[half], sm_v[half]);
+        last.aim(W, cc);
         --left;
         if (left <= 0) break;
         if (advance(A, cc)) begin_unit();
     }
     lds_meet();
-    store_votes((rounds & 1) ^ 1);
+    last.template store<RUW>(sm_v[(rounds & 1) ^ 1], W.tid, A.UH);
+}
+
+// Both passes in one launch, where a call's slices all find a place at once (one prompt, a workgroup per slice): a slice's keys
+// are met twice by its own workgroup, which hands its rows' (reference, sum) to the unit's others in between as
+// words that validate themselves (see snapkv_handoff.h).  The two last rounds' keys are still in LDS then, Q in registers, and the round
+// before those on its way.  The arithmetic and its order are those of the two launches, and so are the votes, bit for bit.
+// A pass of a short call is bound by its start and its end (20 us at 28471 keys, 32/8 heads, of which about 11 are arithmetic and 10 the
+// stream, side by side): the second one's start, its Q and the keys of two of its three or four rounds are saved, for one exchange between workgroups.
+// Microseconds per call, two launches / one (8 KV heads of four query heads, W = 32): 18500 keys 51.3 / 44.6; 24000 52.9 / 45.7; 32768 57.2 / 51.2;
+// 65536 80.2 / 71.2; 131072 128.7 / 114.0; one KV head 18500 35.0 / 32.0, 131072 48.1 / 45.0; on a caller's workspace, whose words a
+// launch before this one has to make ready (the first of two passes cleared the selection's counters on the way), 28471 keys 56.0 / 51.3.
+// Blocks of 64 rows, which begin at 131073 keys, keep the two launches.
+//
+// No workgroup depends on another's being resident: other streams' kernels may hold its place, or wait for ours.  One that has polled for
+// kPatience takes the statistics of the first slice that is missing itself, with the same instructions and so the same words (whose
+// writer is of no consequence), looks again, and in the end takes its own slice once more, so that the votes find LDS as they expect it.
+constexpr unsigned kPatience = 1u << 9;      // polls (about half a millisecond)
+template <typename T, int D, bool PAGED>
+__global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
+    constexpr int RUW = 8;
+    using Wv = WideWave<T, D, PAGED, 1, RUW>;
+    constexpr int R = Wv::R, PARTS = Wv::PARTS, SUB = kThreads / R;
+    __shared__ uint4 kbuf[2][kWaves * Wv::NP * 64];
+    struct Sums {
+        float ref[PARTS][R], sum[PARTS][R];
+    };
+    union Left {                         // (the slice's sums have been read when the first votes are left)
+        Sums sums;
+        float votes[2][RUW][kRound];
+    };
+    __shared__ Left sm;
+    __shared__ float2 sm_part[SUB][R];
+    __shared__ __attribute__((aligned(16))) float2 smf[R];
+    __shared__ int sm_missing;           // the first slice whose words somebody missed
+    Wv W(A);
+    int rounds;
+    Cursor cc = begin_share(A, rounds);
+    const int own = cc.sl;
+    KFrag<D> q[kWaveRows], S;
+    // Requests: the rounds from the first to the last, then back from the one before the last two to the first.
+    Cursor pc = cc;
+    int asked = 0;
+    auto request = [&]() __attribute__((always_inline)) {
+        const Cursor at = pc;
+        ++asked;
+        const int back = 2 * rounds - 3 - asked;
+        pc.rd = asked < rounds ? asked : (back > 0 ? back : 0);
+        return W.request(at, pc);
+    };
+    W.load_q(q, cc);
+    float2* const words = A.e[0].part + ((int64_t)cc.kv * A.nblk + cc.blk) * cc.NS * R;
+    bool gave_up = false;
+    for (int turn = 0;; ++turn) {        // (once, but for workgroups that lost their patience)
+        int none = 0;                    // (what is computed from it is computed in the loop: no register holds it meanwhile)
+        asm volatile("" : "+s"(none));
+        const int tid = W.tid + none;
+        RowSums<T, D, RUW, Wv> rs(W, q);
+        KFrag<D> first;
+        pc = cc;
+        pc.rd = asked = 0;
+        W.ask_page(pc);
+        rs.ask_first(first, cc);
+        S = request();
+        rs.begin(first);
+        for (int r = 0; r < rounds; ++r) {
+            W.keep(kbuf[r & 1], S);
+            S = request();
+            lds_meet();
+            cc.rd = r;
+            rs.round(kbuf[r & 1], cc);
+        }
+        rs.leave(sm.sums.ref[W.kp] + none, sm.sums.sum[W.kp] + none, nullptr);
+        if (tid == 0) sm_missing = cc.NS;
+        lds_meet();
+        if (tid < R) {
+            const float2 x = add_parts<PARTS, R>(sm.sums.ref, sm.sums.sum, tid);
+            publish_pair(words + (int64_t)cc.sl * R + tid, x.x, x.y);
+        }
+        if (turn) {                      // (these words are the next ones to be looked for)
+            __threadfence();
+            lds_meet();
+        }
+        // The unit's slices merged in the order of wide_votes.
+        const int row = tid % R, sub = tid / R;
+        const float2* const src = words + row;
+        float m = -INFINITY, s = 0.f;
+        bool missed = false;
+#pragma clang loop unroll(disable)
+        for (int s0 = sub; s0 < cc.NS; s0 += 8 * SUB) {
+            unsigned long long bits[8];
+            float2 x[9];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) bits[i] = load_pair_bits(src + (int64_t)(s0 + i * SUB < cc.NS ? s0 + i * SUB : 0) * R);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                float pm = -INFINITY, ps = 0.f;
+                if (s0 + i * SUB < cc.NS) {
+                    const bool before = missed;
+                    unpack_pair(await_pair(src + (int64_t)(s0 + i * SUB) * R, bits[i], A.spin_limit, missed), pm, ps);
+                    if (missed != before) atomicMin(&sm_missing, s0 + i * SUB);
+                }
+                x[i] = make_float2(pm, ps);
+            }
+            x[8] = make_float2(m, s);
+            fold(x, m, s);
+        }
+        sm_part[sub][row] = make_float2(m, s);
+        lds_meet();
+        const int missing = __builtin_amdgcn_readfirstlane(sm_missing);
+        gave_up = missing < cc.NS && turn > 2 * cc.NS;   // (every turn leaves the words of one slice: not reached)
+        const int next = missing < cc.NS && !gave_up ? missing : own;
+        if (tid < R) {
+            float2 y[SUB];
+#pragma unroll
+            for (int i = 0; i < SUB; ++i) y[i] = sm_part[i][tid];
+            fold(y, m, s);
+            smf[tid] = row_weight(A, cc, tid, m, s);
+        }
+        lds_meet();
+        if (next == cc.sl && (missing == cc.NS || gave_up)) break;
+        cc.sl = next;
+    }
+    Origins<RUW> org;
+    float mref[kWaveRows][4], wgt[kWaveRows][4];
+#pragma unroll
+    for (int i = 0; i < kWaveRows; ++i) {
+        const float4* f4 = reinterpret_cast<const float4*>(&smf[(W.rg * kWaveRows + i) * 16 + W.kg * 4]);
+        const float4 a = f4[0], b = f4[1];
+        mref[i][0] = a.x, wgt[i][0] = a.y, mref[i][1] = a.z, wgt[i][1] = a.w;
+        mref[i][2] = b.x, wgt[i][2] = b.y, mref[i][3] = b.z, wgt[i][3] = b.w;
+    }
+    VoteRows last;
+    for (int i = 0; i < rounds; ++i) {
+        const int r = rounds - 1 - i;
+        if (i >= 2) {                    // (the last two are in LDS; everybody has left the buffer of the round two before)
+            W.keep(kbuf[r & 1], S);
+            S = request();
+        }
+        lds_meet();
+        last.template store<RUW>(sm.votes[(i & 1) ^ 1], W.tid, A.UH);
+        cc.rd = r;
+        round_votes<T, D, RUW>(W, q, org, mref, wgt, kbuf[r & 1], sm.votes[i & 1]);
+        last.aim(W, cc);
+    }
+    lds_meet();
+    last.template store<RUW>(sm.votes[(rounds & 1) ^ 1], W.tid, A.UH);
+    if (gave_up) {
+        atomicAdd(&g_wide_timeouts, 1u);
+        if (A.gave_up) __hip_atomic_store(A.gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 struct Blocks {
@@ -744,13 +965,28 @@ int wide_cus() {
     return cached[dev];
 }
 
-template <typename T, int D, bool PAGED, int N, int RUW>
-hipError_t launch_both(const WideArgs<kMaxWide>& all, dim3 grid, hipStream_t st) {
+template <int N> WideArgs<N> first_entries(const WideArgs<kMaxWide>& all) {
     WideArgs<N> A;
     A.count = all.count, A.direct = all.direct, A.g = all.g, A.W = all.W, A.UH = all.UH, A.hb = all.hb, A.nblk = all.nblk, A.inv_uh = all.inv_uh;
     A.c2 = all.c2, A.k_rs = all.k_rs, A.table = all.table, A.page = all.page, A.pages = all.pages, A.row0 = all.row0;
     A.rounds = all.rounds, A.share = all.share, A.more = all.more, A.zeros = all.zeros, A.nzeros = all.nzeros, A.flag = all.flag;
+    A.spin_limit = all.spin_limit, A.gave_up = all.gave_up;
     for (int i = 0; i < N; ++i) A.e[i] = all.e[i];
+    return A;
+}
+
+template <typename T, int D>
+hipError_t launch_once(const WideArgs<kMaxWide>& all, bool paged, dim3 grid, hipStream_t st) {
+    const WideArgs<1> A = first_entries<1>(all);
+    if (paged) hipLaunchKernelGGL((wide_once<T, D, true>), grid, dim3(kThreads), 0, st, A);
+    else hipLaunchKernelGGL((wide_once<T, D, false>), grid, dim3(kThreads), 0, st, A);
+    stage_done(st, kStageWide);
+    return hipGetLastError();
+}
+
+template <typename T, int D, bool PAGED, int N, int RUW>
+hipError_t launch_both(const WideArgs<kMaxWide>& all, dim3 grid, hipStream_t st) {
+    const WideArgs<N> A = first_entries<N>(all);
     hipLaunchKernelGGL((wide_stats<T, D, PAGED, N, RUW>), grid, dim3(kThreads), 0, st, A);
     hipLaunchKernelGGL((wide_votes<T, D, PAGED, N, RUW>), grid, dim3(kThreads), 0, st, A);
     stage_done(st, kStageWide);    // (both launches)
@@ -789,7 +1025,7 @@ size_t wide_part_bytes(const ScoreGeom& G) {
     return (sizeof(float2) * (size_t)G.Hkv * b.nblk * (slices_of(G, b) + (b.ru == 4 ? kExtra<4> : kExtra<8>)) * b.ru * 16 + 255) & ~(size_t)255;
 }
 
-hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st, const WideClear& clear) {
+static hipError_t score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st, const WideClear& clear, bool once, unsigned* gave_up) {
     if (count < 1 || count > kMaxWide) return hipErrorInvalidValue;
     for (int i = 0; i < count; ++i)
         if (!P[i].q || !P[i].k || !P[i].vote || !P[i].part) return hipErrorInvalidValue;
@@ -815,6 +1051,8 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
     A.zeros = clear.zeros;
     A.nzeros = clear.zeros ? clear.nzeros : 0;
     A.flag = clear.flag;
+    A.spin_limit = wait_limit(kPatience);
+    A.gave_up = gave_up;
     int64_t slices = 0;
     for (int i = 0; i < count; ++i) {
         const ScoreGeom& G = *P[i].G;
@@ -842,8 +1080,34 @@ hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, h
     const dim3 grid = A.direct ? dim3((unsigned)A.e[0].NS, (unsigned)b.nblk, (unsigned)G0.Hkv) : dim3((unsigned)std::min(slices, places));
     A.share = A.rounds / grid.x;         // (of a launch with a grid of one dimension)
     A.more = A.rounds % grid.x;
+    if (once) {
+        const bool paged = G0.k_table != nullptr;
+        if (!A.direct || b.ru != 8) return hipErrorInvalidValue;
+        if (dtype == 0) return D == 128 ? launch_once<w_bf16, 128>(A, paged, grid, st) : launch_once<w_bf16, 64>(A, paged, grid, st);
+        return D == 128 ? launch_once<w_f16, 128>(A, paged, grid, st) : launch_once<w_f16, 64>(A, paged, grid, st);
+    }
     if (dtype == 0) return D == 128 ? by_rows<w_bf16, 128>(A, b.ru, grid, st) : by_rows<w_bf16, 64>(A, b.ru, grid, st);
     return D == 128 ? by_rows<w_f16, 128>(A, b.ru, grid, st) : by_rows<w_f16, 64>(A, b.ru, grid, st);
+}
+
+hipError_t launch_score_wide(int dtype, int D, int count, const WidePrompt* P, hipStream_t st, const WideClear& clear) {
+    return score_wide(dtype, D, count, P, st, clear, false, nullptr);
+}
+
+int64_t wide_once_pairs(const ScoreGeom& G) {
+    Blocks b;
+    return wide_shape(G, &b) ? (int64_t)G.Hkv * b.nblk * slices_of(G, b) * b.ru * 16 : 0;
+}
+
+// A workgroup per slice, two per compute unit, and words that the hand-off region of the single-read kernel holds.
+bool wide_once_ok(int dtype, int D, const ScoreGeom& G) {
+    Blocks b;
+    return wide_ok(dtype, D, G) && row_blocks(G, &b) && b.ru == 8 && (size_t)wide_once_pairs(G) * sizeof(float2) <= fused_sync_bytes(G) &&
+           (int64_t)G.Hkv * b.nblk * slices_of(G, b) <= 2 * wide_cus();
+}
+
+hipError_t launch_score_wide_once(int dtype, int D, const WidePrompt& P, unsigned* gave_up, hipStream_t st) {
+    return score_wide(dtype, D, 1, &P, st, WideClear{}, true, gave_up);
 }
 
 }  // namespace snapkv
