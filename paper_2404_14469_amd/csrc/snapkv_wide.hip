@@ -12,8 +12,8 @@
 //   * The window rows of a KV head form blocks of whole query heads, at most eight 16-row units each, or four where the
 //     KV head has no more (RUW); a unit of work is one block.  A wave owns 32 of the block's rows, its Q in registers as
 //     MFMA fragments.
-//   * The keys of a unit are cut into at most 64 slices of RPS rounds of 128 keys, or into up to 256 if the prompt has
-//     fewer than four units.  The slice length depends on the prompt's length and its own heads alone, so a head's
+//   * The keys of a unit are cut into at most 64 slices of RPS rounds of 128 keys, into up to 256 if the prompt has
+//     fewer than four units, or into fewer so that all slices of more than eight units find a place at once.  The slice length depends on the prompt's length and its own heads alone, so a head's
 //     result does not depend on which other layers or prompts share the launch.
 //   * A round's keys pass through LDS (landing registers -> two buffers, one barrier a round), where four groups
 //     of waves x two parts of the keys (blocks of 64 rows: two groups x four parts) read them as fragments; the next round is on
@@ -102,7 +102,9 @@ constexpr int kWaves = 8;                    // waves per workgroup, two workgro
 constexpr int kThreads = kWaves * 64;
 constexpr int kRound = kWaves * 16;          // keys of a round: every wave brings one 16-key tile to LDS
 constexpr int kSlices = 64;                  // slices per unit at most,
-constexpr int kPlaces = 256;                 //   or as many as give a prompt of few units this many in all
+constexpr int64_t kPlaces = 256;             //   or as many as give a prompt of few units this many in all,
+constexpr int64_t kPlacesAll = 512;          //   or a prompt of many, up to kMaxOnce, no more than this in all: the places of a chip
+constexpr int64_t kMaxOnce = 32;             //   of 256 compute units (a fixed number, so that results do not depend on the device)
 constexpr int kWaveRows = 2;                 // 16-row units of a wave
 constexpr float kRaiseAt = 0x1p16f;          // exponential (of a lane's sum) from which a row's reference is raised,
 constexpr float kRaiseMin = 8.f;             //   by rows whose largest logit lies this far above it (base two),
@@ -117,7 +119,14 @@ constexpr float kRaiseBelow = 7.f;           //   to that logit less this
 //   1 head: 18439 keys 40 / 41 / 39;  46087: 45 / 50 / 43;  131072: 55 / 80 / 53;  700001: 313 / 292 / 116
 //   2 heads: 27655: 46 / 46 / 42;  131072: 77 / 85 / 66;  32 layers of 1 head, 31337: 196 / 144 / 151
 // (with 512 in all: 1 head, 46087: 55, 131072: 67; 2 heads, 27655: 52)
-constexpr int64_t kMinRowKeys = 9 << 18;
+// Where one launch does it, the line lies lower the more units a prompt has.  Single-read kernel / this path:
+//   1 and 2 units of 128 rows: 14000 keys 29 / 30, -;  16384: 28 / 31, 29 / 32;  18000: 30 / 32, 34 / 33
+//   4 units: 11000: 34 / 37;  14000: 34.3 / 32.4;  16384: 34.5 / 32.8;  18000: 43 / 35
+//   8 units: 8192: 40 / 42;  14000: 43.9 / 41.2;  16384: 44.0 / 42.0;  18000: 59 / 45;  two layers: 14000: 60.5 / 63.5;  16384: 60.7 / 59.0;  four:
+//            14000: 95 / 85;  18000: 157 / 94;  three: 16384: 78 / 82 (as many keys as that kernel takes in one go)
+//   12 units: 12300: 58 / 50;  16 units: 12300: 66 / 53;  of 256 rows a KV head 6200: 50.7 / 45.1, two layers 67.8 / 65.5, three 86 / 74;
+//   32 units: 12300: 101 / 66;  16384: 101 / 72;  two layers 12300: 173 / 121
+constexpr int64_t min_row_keys(int64_t units) { return units > 8 ? 3 << 19 : units >= 4 ? (1 << 21) + 1 : 9 << 18; }
 // With 64 rows the single-read kernel is faster by 12 to 28 % up to 131072 keys, but for lengths that leave it compute units idle
 // (W = 16, 32/8 heads, this path / that kernel: 16384 keys 43 / 34, 40001: 61 / 62, 65536: 80 / 67, 90001: 98 / 103, 131072: 125 / 112;
 // W = 64, 32 heads, 32768: 125 / 103, 131072: 443 / 374).  Beyond that it has W = 16 with one row unit a part, the four parts of a KV head
@@ -943,9 +952,16 @@ bool row_blocks(const ScoreGeom& G, Blocks* b) {
 }
 
 // Rounds per slice and slices per unit.  They depend on the prompt and its own heads only, not on what else the call holds.
+// A prompt of more than kPlacesAll / kSlices units of 128 rows has as many slices per unit as still find a place all at once, so that it takes one
+// launch (wide_once).  Microseconds per call, 64 slices / this: 8 KV heads, W = 64, four query heads (16 units): 6200 keys 50.7 / 45.1;
+// 12300: 63.5 / 52.0;  28000: 79.9 / 61.3;  131072: 191.6 / 180.6;  12 units of W = 32: 20000: 65.9 / 50.7;  131072: 234 / 182;  32 units of
+// W = 128: 20000: 102 / 82;  131072: 459 / 432.  Of more layers than one at once, which walk the slices, only few and short ones see it:
+// 16 units, 28000 keys, 2 layers: 118 / 101, 3: 154 / 149;  12300 keys: 77 / 79, 98 / 105.
 int rounds_per_slice(const ScoreGeom& G, const Blocks& b) {
     auto rounds = [&](int64_t most) { return (G.L + kRound * most - 1) / (kRound * most); };
-    const int64_t usual = rounds(kSlices), few_units = rounds(std::max<int64_t>(kSlices, kPlaces / ((int64_t)G.own_kv * b.nblk)));
+    const int64_t units = (int64_t)G.own_kv * b.nblk;
+    const int64_t most = b.ru == 8 && units * kSlices > kPlacesAll && units <= kMaxOnce ? kPlacesAll / units : kSlices;
+    const int64_t usual = rounds(most), few_units = rounds(std::max(most, kPlaces / units));
     return (int)std::max(few_units, std::min<int64_t>(usual, 2));   // (a slice's end costs half a round)
 }
 int slices_of(const ScoreGeom& G, const Blocks& b) {
@@ -1002,11 +1018,11 @@ template <typename T, int D> hipError_t by_rows(const WideArgs<kMaxWide>& A, int
 
 }  // namespace
 
-// Whether these kernels take the prompt: enough window rows and keys (kMinRowKeys), and statistics that fit what a workspace
+// Whether these kernels take the prompt: enough window rows and keys (min_row_keys), and statistics that fit what a workspace
 // holds anyway (a region of the streaming passes, or the pooled scores that come later), a head at a time so that
 // the answer does not depend on how many heads a call has.
 static bool wide_shape(const ScoreGeom& G, Blocks* b) {
-    if (G.n <= 0 || !row_blocks(G, b) || (int64_t)G.g * b->UH * 16 * G.L < (b->ru == 8 ? kMinRowKeys : b->UH == 2 ? kMinRowKeys64of2 : kMinRowKeys64)) return false;
+    if (G.n <= 0 || !row_blocks(G, b) || (int64_t)G.g * b->UH * 16 * G.L < (b->ru == 8 ? min_row_keys((int64_t)G.own_kv * b->nblk) : b->UH == 2 ? kMinRowKeys64of2 : kMinRowKeys64)) return false;
     ScoreGeom one = G;
     one.Hkv = 1;
     const size_t part = sizeof(float2) * (size_t)b->nblk * (slices_of(G, *b) + (b->ru == 4 ? kExtra<4> : kExtra<8>)) * b->ru * 16;

@@ -7,9 +7,15 @@ import torch
 from paper_2404_14469_amd import workloads
 from parity import check_against_oracle, run_gpu
 from test_gpu_decode import launched
-from test_gpu_wide import outputs, work
+from test_gpu_wide import outputs
 
 pytestmark = pytest.mark.gpu
+
+
+def work(L, g, W, Hkv=2, D=128, dtype="bf16", C=300, p=7, pool_kind=0):
+    return workloads.Workload("wide_once", L=L, Hq=g * Hkv, Hkv=Hkv, D=D, W=W, pool_kind=pool_kind, p=p, C=C, dtype=dtype,
+                              clusters=(5, 5), radius=6, layers=2, seed=5300)
+
 
 # rounds of a slice: 2 (both in LDS when the votes are taken), 3, 4 (one and two are read again), 5 with a last slice of one key
 CASES = {
@@ -17,8 +23,12 @@ CASES = {
     "three_rounds": (dict(L=18500, g=4, W=32, Hkv=8), True),
     "four_rounds": (dict(L=28471, g=4, W=32, Hkv=8, dtype="f16"), True),
     "five_rounds_one_key": (dict(L=64 * 4 * 128 + 1, g=4, W=31, Hkv=4, pool_kind=1, p=5), True),
-    "two_blocks_512_slices": (dict(L=20001, g=4, W=64, Hkv=4, p=13), True),
-    "two_blocks_too_many_slices": (dict(L=20001, g=4, W=64, Hkv=5, p=13), False),     # 10 units: the two launches
+    "two_blocks_512_places": (dict(L=20001, g=4, W=64, Hkv=4, p=13), True),
+    # more than eight units: fewer slices, and all of them find a place
+    "ten_units_51_slices": (dict(L=9300, g=4, W=64, Hkv=5, p=13), True),
+    "sixteen_units_long_slices": (dict(L=70001, g=4, W=64, Hkv=8, p=13, dtype="f16"), True),
+    "32_units_16_slices": (dict(L=18561, g=1, W=128, Hkv=32, C=300), True),
+    "33_units": (dict(L=18561, g=1, W=113, Hkv=33, C=300), False),                    # 64 slices, the two launches
     "d64_padded_rows": (dict(L=16500, g=3, W=48, Hkv=3, D=64), True),
     "one_row_per_head": (dict(L=150001, g=8, W=1, Hkv=2), True),
 }
@@ -30,10 +40,7 @@ def test_one_launch_equals_two(snapkv, tmp_path, name):
     w = work(**kw)
     cases = [workloads.generate(w, layer=l, device="cuda") for l in range(2)]
     got = [run_gpu(snapkv, c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C) for c in cases for _ in range(2)]   # (scratch left by others)
-    kernels = set()
-    for _ in range(3):                   # (the profiler has lost a process's first kernels)
-        if not any("gather_rows" in n for n in kernels):
-            kernels |= {n for n, _ in launched(lambda: run_gpu(snapkv, *(cases[0][n] for n in ("q_win", "k", "v")), w.pool_kind, w.p, w.C), tmp_path)}
+    kernels = {n for n, _ in launched(lambda: run_gpu(snapkv, *(cases[0][n] for n in ("q_win", "k", "v")), w.pool_kind, w.p, w.C), tmp_path)}
     assert any("wide_once" in n for n in kernels) == once and any("wide_stats" in n for n in kernels) != once, kernels
     oks, ovs, ois = outputs(w, 2, cases[0]["k"].dtype)
     snapkv.snapkv_compress_layers(*([c[n] for c in cases] for n in ("q_win", "k", "v")), w.pool_kind, w.p, w.C, oks, ovs, ois)
@@ -42,6 +49,20 @@ def test_one_launch_equals_two(snapkv, tmp_path, name):
             assert np.array_equal(ois[l].cpu().numpy(), r[3]) and torch.equal(oks[l], r[1]) and torch.equal(ovs[l], r[2]), l
         assert np.array_equal(got[2 * l][0], got[2 * l + 1][0])
     check_against_oracle(*(cases[1][n] for n in ("q_win", "k", "v")), w.pool_kind, w.p, w.C, *got[2], heads=[w.Hkv - 1])
+    assert snapkv.snapkv_sync_timeouts() == 0
+
+
+# From which length on a prompt of so many units comes here: one to three, four to eight, more (min_row_keys); 128 and 256 window rows.
+@pytest.mark.parametrize("first,kw", [(18432, dict(g=4, W=32, Hkv=3)), (16385, dict(g=4, W=32, Hkv=4)), (16385, dict(g=4, W=32, Hkv=8)),
+                                      (8193, dict(g=4, W=64, Hkv=4)), (12288, dict(g=4, W=32, Hkv=9)), (6144, dict(g=4, W=64, Hkv=8))])
+def test_where_the_line_stands(snapkv, tmp_path, first, kw):
+    for L in (first - 1, first):
+        w = work(L=L, **kw)
+        c = workloads.generate(w, device="cuda")
+        got = run_gpu(snapkv, c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C)
+        check_against_oracle(c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C, *got, heads=[0, w.Hkv - 1])
+        kernels = {n for n, _ in launched(lambda: run_gpu(snapkv, c["q_win"], c["k"], c["v"], w.pool_kind, w.p, w.C), tmp_path)}
+        assert any("wide_once" in n for n in kernels) == (L == first) and any("score_fused" in n for n in kernels) == (L < first), (L, kernels)
     assert snapkv.snapkv_sync_timeouts() == 0
 
 
