@@ -199,7 +199,7 @@ int static_scratch(void** out) {
 // Which kernels score a prompt: the single-read kernel (its hand-off words are in use; *F is its plan), the
 // single-read kernel on the front part of a prompt too long for it and streaming passes on the rest (the
 // same, *F = LP->Ff), two streaming passes (the hand-off words stay untouched; *F is their plan), or the
-// two passes over all window rows of a KV head at once (neither hand-off words nor a plan: F->BH is 1).
+// two passes over all window rows of a KV head at once (no plan: F->BH is 1; hand-off words where both are one launch).
 enum { kPathNone = 0, kPathFused = 1, kPathStream = 2, kPathLong = 3, kPathWide = 4 };
 // (the test hook that limits the resident workgroups is for the single-read kernel's long prompts)
 bool use_wide(int dtype, int D, const ScoreGeom& G) { return g_allow_fused && g_fused_slot_cap == 0 && wide_ok(dtype, D, G); }

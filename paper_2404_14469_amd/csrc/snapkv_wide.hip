@@ -13,8 +13,9 @@
 //     KV head has no more (RUW); a unit of work is one block.  A wave owns 32 of the block's rows, its Q in registers as
 //     MFMA fragments.
 //   * The keys of a unit are cut into at most 64 slices of RPS rounds of 128 keys, into up to 256 if the prompt has
-//     fewer than four units, or into fewer so that all slices of more than eight units find a place at once.  The slice length depends on the prompt's length and its own heads alone, so a head's
-//     result does not depend on which other layers or prompts share the launch.
+//     fewer than four units, or into fewer so that all slices of more than eight units find a place at once.  The
+//     slice length depends on the prompt's length and its own heads alone, so a head's result does not depend on which
+//     other layers or prompts share the launch.
 //   * A round's keys pass through LDS (landing registers -> two buffers, one barrier a round), where four groups
 //     of waves x two parts of the keys (blocks of 64 rows: two groups x four parts) read them as fragments; the next round is on
 //     its way meanwhile.
@@ -24,7 +25,8 @@
 //     once has a workgroup per slice.
 //
 // What bounds it: the stream of keys, and arithmetic that does not hide behind it.  32 layers of 32/8 heads of 31337 keys take
-// 414 + 481 us (back to back 430 + 492; the single-read kernel 1218); the same loops without the arithmetic 384 + 471, with keys
+// 402 + 481 us; before the statistics took their logits keys x rows 414 + 481, to which what follows belongs (back to back
+// 430 + 492; the single-read kernel 1218); the same loops without the arithmetic 384 + 471, with keys
 // that are always in the cache 334 + 351, and the keys alone 337 at 6.1 TB/s.  The votes' pass also stores 131 MB.  Counters
 // (profiles/sq_counters_gqa_two_pass.txt, 32768 keys): of the 781 thousand cycles of wide_stats a SIMD's matrix unit is busy
 // for 263 and its vector instructions take 436; of the 992 of wide_votes 262 and 443.  Tried on the way: all 128 rows in one
@@ -1022,7 +1024,9 @@ template <typename T, int D> hipError_t by_rows(const WideArgs<kMaxWide>& A, int
 // holds anyway (a region of the streaming passes, or the pooled scores that come later), a head at a time so that
 // the answer does not depend on how many heads a call has.
 static bool wide_shape(const ScoreGeom& G, Blocks* b) {
-    if (G.n <= 0 || !row_blocks(G, b) || (int64_t)G.g * b->UH * 16 * G.L < (b->ru == 8 ? min_row_keys((int64_t)G.own_kv * b->nblk) : b->UH == 2 ? kMinRowKeys64of2 : kMinRowKeys64)) return false;
+    if (G.n <= 0 || !row_blocks(G, b)) return false;
+    const int64_t least = b->ru == 8 ? min_row_keys((int64_t)G.own_kv * b->nblk) : b->UH == 2 ? kMinRowKeys64of2 : kMinRowKeys64;
+    if ((int64_t)G.g * b->UH * 16 * G.L < least) return false;
     ScoreGeom one = G;
     one.Hkv = 1;
     const size_t part = sizeof(float2) * (size_t)b->nblk * (slices_of(G, *b) + (b->ru == 4 ? kExtra<4> : kExtra<8>)) * b->ru * 16;
