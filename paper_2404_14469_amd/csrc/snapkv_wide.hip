@@ -957,8 +957,10 @@ bool row_blocks(const ScoreGeom& G, Blocks* b) {
 // A prompt of more than kPlacesAll / kSlices units of 128 rows has as many slices per unit as still find a place all at once, so that it takes one
 // launch (wide_once).  Microseconds per call, 64 slices / this: 8 KV heads, W = 64, four query heads (16 units): 6200 keys 50.7 / 45.1;
 // 12300: 63.5 / 52.0;  28000: 79.9 / 61.3;  131072: 191.6 / 180.6;  12 units of W = 32: 20000: 65.9 / 50.7;  131072: 234 / 182;  32 units of
-// W = 128: 20000: 102 / 82;  131072: 459 / 432.  Of more layers than one at once, which walk the slices, only few and short ones see it:
-// 16 units, 28000 keys, 2 layers: 118 / 101, 3: 154 / 149;  12300 keys: 77 / 79, 98 / 105.
+// W = 128: 20000: 102 / 82;  131072: 459 / 432.  Layers of one call walk the same slices (a head's result is the same in every call), of which
+// each workgroup then has few and long ones: mostly the same or faster, and slower where few layers leave the last one to a part of the chip.  16 units,
+// 2 layers: 8500 keys 98 / 73;  12300: 76 / 80;  20000: 96 / 88;  32000: 119 / 110;  3: 8500: 131 / 82;  12300: 98 / 105;  17000: 111 / 120;  20000: 124 / 124;
+// 4: 10500: 103 / 108;  15000: 127 / 117;  24000: 171 / 156;  32000: 210 / 195;  6: 10500: 134 / 137;  17000: 184 / 183;  32000: 356 / 347.
 int rounds_per_slice(const ScoreGeom& G, const Blocks& b) {
     auto rounds = [&](int64_t most) { return (G.L + kRound * most - 1) / (kRound * most); };
     const int64_t units = (int64_t)G.own_kv * b.nblk;
