@@ -21,7 +21,7 @@
 //     its way meanwhile.
 //   * A single prompt whose slices all find a place at once has both passes in one launch (wide_once).
 //   * Otherwise a persistent grid of two workgroups per compute unit walks the slices of all units (of all prompts or layers of
-//     the call) in order, a contiguous run of whole slices each; a launch of one prompt whose slices all find a place at
+//     the call) in order, a contiguous run of whole slices each (of the votes: of rounds); a launch of one prompt whose slices all find a place at
 //     once has a workgroup per slice.
 //
 // What bounds it: the stream of keys, and arithmetic that does not hide behind it.  32 layers of 32/8 heads of 31337 keys take
@@ -73,6 +73,7 @@
 // accumulator register r is row (l / 16) * 4 + r, column l % 16; the 16-byte pieces 4p + l / 16 of a row).
 #include "snapkv_internal.h"
 #include "snapkv_handoff.h"
+#include "snapkv_shares.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -267,12 +268,16 @@ template <int N> __device__ __forceinline__ unsigned slice_start(const WideArgs<
     if constexpr (N > 1)
         for (int i = 1; i < A.count; ++i)
             if (r >= A.e[i].round_begin) e = i;
-    const unsigned in = r - A.e[e].round_begin, rps = (unsigned)A.e[e].RPS;
-    return A.e[e].round_begin + (in + rps - 1) / rps * rps;
+    return A.e[e].round_begin + whole_slices(r - A.e[e].round_begin, (unsigned)A.e[e].RPS);
 }
-// Where the workgroup's stretch of rounds begins: equal shares, moved to the next slice's start.
-template <int N> __device__ __forceinline__ unsigned share(const WideArgs<N>& A, unsigned wg) {
-    return slice_start(A, A.share * wg + (wg < A.more ? wg : A.more));
+// Where the workgroup's stretch of rounds begins.  The statistics are of whole slices (WHOLE); the votes, which take a row's weight as it is
+// wherever they begin, are shared out by rounds.  With whole slices in both passes, of which a workgroup of a few layers' launch has two
+// or three, a part of the chip had nothing to do at the end.  Microseconds per call, W = 64, 32/8 heads: 3 layers of 8500 keys 78.1 / 76.3, of 12300
+// 101.1 / 96.2, of 17000 115.7 / 112.5;  4 of 10500 103.5 / 100.3, of 15000 114.5 / 111.3, of 32000 207 / 208;  W = 32: 4 of 28000 138.5 / 134.2, 32 of
+// 31337 1004 / 1005.
+template <bool WHOLE, int N> __device__ __forceinline__ unsigned share(const WideArgs<N>& A, unsigned wg) {
+    const unsigned r = begin_rounds(A.share, A.more, wg);
+    return WHOLE ? slice_start(A, r) : r;
 }
 
 template <int N> __device__ __forceinline__ Cursor cursor_at(const WideArgs<N>& A, unsigned r) {
@@ -282,19 +287,19 @@ template <int N> __device__ __forceinline__ Cursor cursor_at(const WideArgs<N>& 
         for (int i = 1; i < A.count; ++i)
             if (r >= A.e[i].round_begin) c.e = i;
     const WideEntry& E = A.e[c.e];
-    const unsigned in = (r - E.round_begin) / (unsigned)E.RPS;   // r is the start of a slice
-    const int u = (int)(in / (unsigned)E.NS);
-    c.sl = (int)(in % (unsigned)E.NS);
+    const unsigned in = r - E.round_begin, slice = in / (unsigned)E.RPS;
+    const int u = (int)(slice / (unsigned)E.NS);
+    c.sl = (int)(slice % (unsigned)E.NS);
     c.kv = u / A.nblk;
     c.blk = u % A.nblk;
-    c.rd = 0;
+    c.rd = (int)(in % (unsigned)E.RPS);
     enter(A, c);
     return c;
 }
 
 // Where the workgroup starts and how many rounds are its own.  A launch whose slices all find a place at once has a
 // workgroup per slice (grid: slices of a unit x blocks of a KV head x KV heads; no divisions before the first load).
-template <int N> __device__ __forceinline__ Cursor begin_share(const WideArgs<N>& A, int& rounds) {
+template <bool WHOLE, int N> __device__ __forceinline__ Cursor begin_share(const WideArgs<N>& A, int& rounds) {
     if (N == 1 && A.direct) {
         Cursor c;
         c.e = 0;
@@ -306,7 +311,7 @@ template <int N> __device__ __forceinline__ Cursor begin_share(const WideArgs<N>
         rounds = c.RPS;
         return c;
     }
-    const unsigned r0 = share(A, blockIdx.x), r1 = share(A, blockIdx.x + 1);
+    const unsigned r0 = share<WHOLE>(A, blockIdx.x), r1 = share<WHOLE>(A, blockIdx.x + 1);
     rounds = (int)(r1 - r0);
     return cursor_at(A, r0 < A.rounds ? r0 : 0u);
 }
@@ -649,7 +654,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_stats(const WideArgs<N> A) {
         if (A.flag && wg == 0 && W.tid == 0) *A.flag = 0u;
     }
     int rounds;
-    Cursor cc = begin_share(A, rounds), pc = cc;
+    Cursor cc = begin_share<true>(A, rounds), pc = cc;
     if (rounds <= 0) return;
     KFrag<D> q[kWaveRows], S;
     RowSums<T, D, RUW, Wv> rs(W, q);
@@ -725,7 +730,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
     __shared__ __attribute__((aligned(16))) float smo[kOrigin<RUW> ? R : 1];
     Wv W(A);
     int rounds;
-    Cursor cc = begin_share(A, rounds), pc = cc;
+    Cursor cc = begin_share<false>(A, rounds), pc = cc;
     if (rounds <= 0) return;
     KFrag<D> q[kWaveRows], S;
     W.ask_page(pc);
@@ -823,7 +828,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
     __shared__ int sm_missing;           // the first slice whose words somebody missed
     Wv W(A);
     int rounds;
-    Cursor cc = begin_share(A, rounds);
+    Cursor cc = begin_share<true>(A, rounds);
     const int own = cc.sl;
     KFrag<D> q[kWaveRows], S;
     // Requests: the rounds from the first to the last, then back from the one before the last two to the first.
