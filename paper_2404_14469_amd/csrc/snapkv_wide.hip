@@ -231,6 +231,7 @@ template <int N> struct WideArgs {   // N: 1 or kMaxWide (a single prompt's laun
     int64_t pages, row0;
     unsigned rounds;                 // of all entries: each workgroup's share is share rounds, one more for the first `more`
     unsigned share, more;
+    bool reversed;                   // the statistics' shares are handed out as share_of says
     unsigned spin_limit;             // wide_once: polls before a workgroup helps itself,
     unsigned* gave_up;               //   and null, or a word that is set when one gives up
     unsigned* zeros;                 // words the selection expects to be zero (see WideClear); null: none
@@ -311,7 +312,8 @@ template <bool WHOLE, int N> __device__ __forceinline__ Cursor begin_share(const
         rounds = c.RPS;
         return c;
     }
-    const unsigned r0 = share<WHOLE>(A, blockIdx.x), r1 = share<WHOLE>(A, blockIdx.x + 1);
+    const unsigned own = WHOLE ? share_of(blockIdx.x, gridDim.x, A.reversed) : blockIdx.x;
+    const unsigned r0 = share<WHOLE>(A, own), r1 = share<WHOLE>(A, own + 1);
     rounds = (int)(r1 - r0);
     return cursor_at(A, r0 < A.rounds ? r0 : 0u);
 }
@@ -994,7 +996,7 @@ template <int N> WideArgs<N> first_entries(const WideArgs<kMaxWide>& all) {
     WideArgs<N> A;
     A.count = all.count, A.direct = all.direct, A.g = all.g, A.W = all.W, A.UH = all.UH, A.hb = all.hb, A.nblk = all.nblk, A.inv_uh = all.inv_uh;
     A.c2 = all.c2, A.k_rs = all.k_rs, A.table = all.table, A.page = all.page, A.pages = all.pages, A.row0 = all.row0;
-    A.rounds = all.rounds, A.share = all.share, A.more = all.more, A.zeros = all.zeros, A.nzeros = all.nzeros, A.flag = all.flag;
+    A.rounds = all.rounds, A.share = all.share, A.more = all.more, A.reversed = all.reversed, A.zeros = all.zeros, A.nzeros = all.nzeros, A.flag = all.flag;
     A.spin_limit = all.spin_limit, A.gave_up = all.gave_up;
     for (int i = 0; i < N; ++i) A.e[i] = all.e[i];
     return A;
@@ -1081,6 +1083,7 @@ static hipError_t score_wide(int dtype, int D, int count, const WidePrompt* P, h
     A.spin_limit = wait_limit(kPatience);
     A.gave_up = gave_up;
     int64_t slices = 0;
+    bool alike = true;                   // all slices are of the same length, as those of layers are
     for (int i = 0; i < count; ++i) {
         const ScoreGeom& G = *P[i].G;
         if (G.g != G0.g || G.W != G0.W || G.k_rs != G0.k_rs || G.n <= 0 || G.L + G.k_row0 >= (int64_t)1 << 31) return hipErrorInvalidValue;
@@ -1100,6 +1103,7 @@ static hipError_t score_wide(int dtype, int D, int count, const WidePrompt* P, h
         if ((int64_t)E.units * E.NS * E.RPS > kMaxRounds) return hipErrorInvalidValue;
         A.rounds += (unsigned)E.units * E.NS * E.RPS;
         slices += (int64_t)E.units * E.NS;
+        alike = alike && E.RPS == A.e[0].RPS;
     }
     for (int i = count; i < kMaxWide; ++i) A.e[i] = A.e[0];
     const int64_t places = 2 * wide_cus();   // two workgroups per compute unit
@@ -1107,6 +1111,7 @@ static hipError_t score_wide(int dtype, int D, int count, const WidePrompt* P, h
     const dim3 grid = A.direct ? dim3((unsigned)A.e[0].NS, (unsigned)b.nblk, (unsigned)G0.Hkv) : dim3((unsigned)std::min(slices, places));
     A.share = A.rounds / grid.x;         // (of a launch with a grid of one dimension)
     A.more = A.rounds % grid.x;
+    A.reversed = !A.direct && alike && reverse_shares(A.rounds, grid.x, (unsigned)A.e[0].RPS);
     if (once) {
         const bool paged = G0.k_table != nullptr;
         if (!A.direct || b.ru != 8) return hipErrorInvalidValue;
