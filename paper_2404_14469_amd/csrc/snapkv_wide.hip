@@ -73,6 +73,7 @@
 // accumulator register r is row (l / 16) * 4 + r, column l % 16; the 16-byte pieces 4p + l / 16 of a row).
 #include "snapkv_internal.h"
 #include "snapkv_handoff.h"
+#include "snapkv_help.h"
 #include "snapkv_shares.h"
 
 #include <algorithm>
@@ -808,8 +809,10 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
 // Blocks of 64 rows, which begin at 131073 keys, keep the two launches.
 //
 // No workgroup depends on another's being resident: other streams' kernels may hold its place, or wait for ours.  One that has polled for
-// kPatience takes the statistics of the first slice that is missing itself, with the same instructions and so the same words (whose
-// writer is of no consequence), looks again, and in the end takes its own slice once more, so that the votes find LDS as they expect it.
+// kPatience takes the statistics of a missing slice itself, with the same instructions and so the same words (whose
+// writer is of no consequence), looks again without waiting, and in the end takes its own slice once more, so that the votes find LDS as they
+// expect it.  Workgroups take different slices (see snapkv_help.h), so that a unit of which r workgroups have places and m have none is
+// done after kPatience and 2 m / r + 2 slices' statistics at most or so, even if the others' places are not free until then.
 constexpr unsigned kPatience = 1u << 9;      // polls (about half a millisecond)
 template <typename T, int D, bool PAGED>
 __global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
@@ -827,7 +830,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
     __shared__ Left sm;
     __shared__ float2 sm_part[SUB][R];
     __shared__ __attribute__((aligned(16))) float2 smf[R];
-    __shared__ int sm_missing;           // the first slice whose words somebody missed
+    __shared__ int sm_missing;           // of the slices whose words somebody missed the smallest key
     Wv W(A);
     int rounds;
     Cursor cc = begin_share<true>(A, rounds);
@@ -866,7 +869,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
             rs.round(kbuf[r & 1], cc);
         }
         rs.leave(sm.sums.ref[W.kp] + none, sm.sums.sum[W.kp] + none, nullptr);
-        if (tid == 0) sm_missing = cc.NS;
+        if (tid == 0) sm_missing = kNoneMissing;
         lds_meet();
         if (tid < R) {
             const float2 x = add_parts<PARTS, R>(sm.sums.ref, sm.sums.sum, tid);
@@ -879,6 +882,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
         // The unit's slices merged in the order of wide_votes.
         const int row = tid % R, sub = tid / R;
         const float2* const src = words + row;
+        const unsigned limit = patience(turn, A.spin_limit);
         float m = -INFINITY, s = 0.f;
         bool missed = false;
 #pragma clang loop unroll(disable)
@@ -891,9 +895,8 @@ __global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
             for (int i = 0; i < 8; ++i) {
                 float pm = -INFINITY, ps = 0.f;
                 if (s0 + i * SUB < cc.NS) {
-                    const bool before = missed;
-                    unpack_pair(await_pair(src + (int64_t)(s0 + i * SUB) * R, bits[i], A.spin_limit, missed), pm, ps);
-                    if (missed != before) atomicMin(&sm_missing, s0 + i * SUB);
+                    unpack_pair(await_pair(src + (int64_t)(s0 + i * SUB) * R, bits[i], limit, missed), pm, ps);
+                    if (missed && bits[i] == kInvalidPair) atomicMin(&sm_missing, help_key(s0 + i * SUB, own));
                 }
                 x[i] = make_float2(pm, ps);
             }
@@ -902,9 +905,10 @@ __global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
         }
         sm_part[sub][row] = make_float2(m, s);
         lds_meet();
-        const int missing = __builtin_amdgcn_readfirstlane(sm_missing);
-        gave_up = missing < cc.NS && turn > 2 * cc.NS;   // (every turn leaves the words of one slice: not reached)
-        const int next = missing < cc.NS && !gave_up ? missing : own;
+        const int key = __builtin_amdgcn_readfirstlane(sm_missing);
+        const bool none_missing = key == kNoneMissing;
+        gave_up = !none_missing && turn > 2 * cc.NS;     // (a bound only: every turn leaves the words of one slice, so it is not reached)
+        const int next = none_missing || gave_up ? own : help_slice(key, own);
         if (tid < R) {
             float2 y[SUB];
 #pragma unroll
@@ -913,7 +917,7 @@ __global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
             smf[tid] = row_weight(A, cc, tid, m, s);
         }
         lds_meet();
-        if (next == cc.sl && (missing == cc.NS || gave_up)) break;
+        if (next == cc.sl && (none_missing || gave_up)) break;
         cc.sl = next;
     }
     Origins<RUW> org;

@@ -55,12 +55,14 @@ def test_cuts_of_batches_into_joint_launches(tmp_path):
     assert "all cases passed" in r.stdout
 
 
-def test_shares_of_the_two_pass_launches(tmp_path):
+@pytest.mark.parametrize("name", ["shares", "help"])
+def test_plans_of_the_two_pass_launches(tmp_path, name):
+    """Which workgroup takes which rounds, and which missing slices."""
     if shutil.which("g++") is None:
         pytest.skip("no g++")
-    exe = str(tmp_path / "shares")
+    exe = str(tmp_path / name)
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-Wall", "-Werror", "-o", exe,
-                    os.path.join(ROOT, "tests", "sanitize", "shares_driver.cpp")], check=True, capture_output=True, text=True)
+                    os.path.join(ROOT, "tests", "sanitize", name + "_driver.cpp")], check=True, capture_output=True, text=True)
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0:verify_asan_link_order=0")
     r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
