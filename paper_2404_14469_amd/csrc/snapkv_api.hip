@@ -615,6 +615,7 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
     int64_t nmax = 0;
     size_t per_prompt[kMaxBatch], stats = 0, handoff = 0;   // handoff: bytes of hand-off words per prompt
     bool wide[kMaxBatch];   // scored by the two-pass kernels, as in a call of its own
+    int nwide = 0, last_wide = 0;
     for (int i = 0; i < count; ++i) {
         G[i] = make_geom(L[i], Hq, Hkv, D, W);
         G[i].k_rs = row_bytes;
@@ -622,6 +623,7 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
         FusedGeom F;
         if (!lse_plan(dtype, D, G[i], &F)) return 1;   // more window rows than the one-row-per-head kernels take
         wide[i] = use_wide(dtype, D, G[i]);
+        if (wide[i]) ++nwide, last_wide = i;
         if (g_allow_fused && !wide[i] && fused_plan(dtype, D, G[i], &F)) {   // hand-off words this prompt's launch will use
             const size_t words = (size_t)fused_sync_pairs(F) * sizeof(unsigned long long);
             handoff = words > handoff ? words : handoff;
@@ -637,19 +639,27 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
     Gb.VB = 1;
     if (!pool_select_ok(Gb, pool_kind, p, C - W)) return 1;
 
+    // One such prompt takes both passes in one launch where it would by itself (the same votes), with hand-off words behind the others'.
+    // A prompt between the present lines (min_row_keys) and 9 << 18 rows x keys would rather share a joint launch, but has to have the result of
+    // its own call.  Microseconds per call, joint launch / two launches / this: 32/8 heads, W = 32: 17300 and 8192 keys 63 / 71 / 65;  with 12000 and
+    // 5000 92 / 99 / 93;  with three of 5000 71 / 86 / 80;  16500, 16200, 15000, 14000 103 / 126 / 120;  18000 and six of 2000-9000 115 / 113 / 107;
+    // W = 64: 9000 and 4000 84 / 75 / 67;  12 KV heads: 13000, 12000, 11000, 9000 122 / 121 / 114;  17000, 9000, 5000, 4000 109 / 120 / 113.
+    // Several such prompts: four of 16400 keys 143 / 92;  two of 17300 98 / 69;  17300, 17000, 12000, 9000 103 / 116.
+    const bool once = nwide == 1 && wide_once_ok(dtype, D, G[last_wide]);
     const size_t counters = select_counter_bytes(Htot);
     handoff = up(handoff);
+    const size_t words = handoff * count + (once ? up((size_t)wide_once_pairs(G[last_wide]) * sizeof(unsigned long long)) : 0);
     const size_t votes = up(sizeof(float) * (size_t)Hq * count * (size_t)npad);
     const size_t idx_tmp = up(sizeof(int32_t) * (size_t)Htot * (size_t)C);
     const size_t nvalid = up(sizeof(int32_t) * (size_t)Htot);
     const size_t sel = select_layout(Htot, npad, nullptr, nullptr, false, nullptr);
-    const size_t need = counters + handoff * count + votes + stats + idx_tmp + nvalid + sel;
+    const size_t need = counters + words + votes + stats + idx_tmp + nvalid + sel;
     void* base = nullptr;
     int rc = internal_scratch(need, &base);
     if (rc != SNAPKV_OK) return rc;
     char* b = static_cast<char*>(base);
     char* handoff_p = b + counters;
-    float* votes_p = reinterpret_cast<float*>(handoff_p + handoff * count);
+    float* votes_p = reinterpret_cast<float*>(handoff_p + words);
     char* stats_p = reinterpret_cast<char*>(votes_p) + votes;
     int32_t* idx_p = reinterpret_cast<int32_t*>(stats_p + stats);
     int32_t* nvalid_p = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(idx_p) + idx_tmp);
@@ -673,7 +683,7 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
     lengths.Hkv = Hkv;
     lengths.nvalid = nvalid_p;
     for (int i = 0; i < kMaxBatch; ++i) lengths.n[i] = i < count ? (int32_t)G[i].n : 0;
-    if (launch_prepare(handoff_p, (int64_t)(handoff * count / sizeof(unsigned long long)), &Sb, Htot, st, nullptr, &lengths) != hipSuccess)
+    if (launch_prepare(handoff_p, (int64_t)(words / sizeof(unsigned long long)), &Sb, Htot, st, nullptr, &lengths) != hipSuccess)
         return SNAPKV_ERR_HIP;
     stage_done(st, kStagePrepare);
     // scoring: the prompts, longest first, share launches of the single-read kernel as far as they fit
@@ -690,14 +700,15 @@ int compress_batch(int dtype, int count, const void* const* q_win, const void* c
         sp += per_prompt[i];
         G[i].vpitch = npad;
     }
-    int rest[kMaxBatch], nrest = 0, nwide = 0;
+    int rest[kMaxBatch], nrest = 0, wides = 0;
     WidePrompt WP[kMaxBatch];
     static_assert(kMaxBatch <= kMaxWide, "the prompts of a batch that take the two-pass kernels share their launches");
     for (int i = 0; i < count; ++i) {
-        if (wide[i]) WP[nwide++] = WidePrompt{q_win[i], k[i], wsp[i].vote, wsp[i].wide_part, &G[i]};
+        if (wide[i]) WP[wides++] = WidePrompt{q_win[i], k[i], wsp[i].vote, once ? reinterpret_cast<float2*>(handoff_p + handoff * count) : wsp[i].wide_part, &G[i]};
         else rest[nrest++] = i;
     }
-    if (nwide > 0 && launch_score_wide(dtype, D, nwide, WP, st) != hipSuccess) return SNAPKV_ERR_HIP;
+    if (nwide > 0 && (once ? launch_score_wide_once(dtype, D, WP[0], nullptr, st) : launch_score_wide(dtype, D, nwide, WP, st)) != hipSuccess)
+        return SNAPKV_ERR_HIP;
     std::sort(rest, rest + nrest, [&](int a, int b) { return L[a] != L[b] ? L[a] > L[b] : a < b; });
     int cut[kMaxBatch], launches = 0, launch = 0;
     {

@@ -7,6 +7,7 @@ import torch
 from paper_2404_14469_amd import workloads
 from parity import check_against_oracle, run_gpu
 from test_gpu_decode import launched
+from test_gpu_varlen import compare_with_single_calls, run_batch
 from test_gpu_wide import outputs
 
 pytestmark = pytest.mark.gpu
@@ -102,3 +103,17 @@ def test_two_streams_with_workspaces(snapkv):
     torch.cuda.synchronize()
     for g, st, (ok, ov, oi) in zip(good, status, outs):
         assert int(st.item()) == w.C and np.array_equal(oi.cpu().numpy(), g[3]) and torch.equal(ok, g[1]) and torch.equal(ov, g[2])
+
+
+# One prompt of a batch in one launch, more in the two; beside prompts of the joint launches and one that fits the capacity.
+@pytest.mark.parametrize("lengths,once,kw", [([8192, 17300, 5000, 290], True, dict(g=4, W=32, Hkv=8)), ([131072, 600], True, dict(g=4, W=64, Hkv=8, p=13, dtype="f16")),
+                                             ([16385, 16384], True, dict(g=4, W=31, Hkv=5, pool_kind=1, p=5)), ([17300, 16400, 3000], False, dict(g=4, W=32, Hkv=8)),
+                                             ([18561, 2000], False, dict(g=1, W=113, Hkv=33))])
+def test_batches(snapkv, tmp_path, lengths, once, kw):
+    ws = [work(L=L, **kw).with_(seed=5400 + i) for i, L in enumerate(lengths)]
+    for _ in range(2):                   # (the second call's words lie where the first one's were)
+        batch = run_batch(snapkv, ws)
+        compare_with_single_calls(snapkv, ws, *batch)
+    kernels = {n for n, _ in launched(lambda: run_batch(snapkv, ws), tmp_path)}
+    assert any("wide_once" in n for n in kernels) == once and any("wide_stats" in n for n in kernels) != once, kernels
+    assert snapkv.snapkv_sync_timeouts() == 0
