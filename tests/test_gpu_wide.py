@@ -1,5 +1,6 @@
 """Prompts whose KV heads are met by 128 window rows or more, long enough for the two-pass scoring kernels
-(csrc/snapkv_wide.hip), or by 64 and longer than 131072 keys (163839 with two query heads of W = 32): edges of rounds (128 keys), of slices (multiples of 128 keys, at most 64 of them) and of the
+(csrc/snapkv_wide.hip), or by 64 and longer than 131072 keys (163839 with two query heads of W = 32): edges of rounds (128 keys),
+of slices (multiples of 128 keys, at most 64 of them, 256 where a prompt has few units, fewer where it has more than eight) and of the
 row blocks (128 rows, whole query heads), every storage type and layout, and rows whose sums leave the fp32 range."""
 import re
 
@@ -14,7 +15,7 @@ from test_gpu_decode import launched
 
 pytestmark = pytest.mark.gpu
 
-MIN_ROW_KEYS = 9 << 18   # csrc/snapkv_wide.hip: window rows times keys from which these kernels are used
+MIN_ROW_KEYS = 9 << 18   # csrc/snapkv_wide.hip: window rows times keys from which these kernels are used for any number of units (min_row_keys)
 
 
 def work(L, g, W, Hkv=2, D=128, dtype="bf16", C=300, p=7, pool_kind=0):
