@@ -27,7 +27,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0   # MI355X published HBM3E bandwidth
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_long_131k.txt")
-KERNEL_SOURCES = ("snapkv_fused.hip", "snapkv_internal.h")   # what the dominant kernel is built from
+KERNEL_SOURCES = ("snapkv_fused.hip", "snapkv_handoff.h", "snapkv_internal.h")   # what the dominant kernel is built from
 
 
 def kernel_source_digest() -> str:
