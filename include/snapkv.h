@@ -397,16 +397,19 @@ int snapkv_set_scoring_scheme(int scheme);
 /*
  * The single-read scoring kernel and the cooperative pooling + selection kernel hand data
  * between resident workgroups and bound every wait; a wait that gives up is counted here (0 in
- * correct operation; the results of such a call are invalid).  Synchronises the
+ * correct operation; the results of such a call are invalid).  The two scoring passes in one launch hand data between
+ * workgroups too, but need none of the others: one that has waited for about half a millisecond does the work it misses itself, with the same
+ * result, and nothing is counted (a bound on its turns is counted here as well; none reaches it).  Synchronises the
  * device.  Returns the count since the library was loaded, or a negative SNAPKV_ERR_* code.
  */
 int64_t snapkv_sync_timeouts(void);
 
 /*
  * Test hook, not for production: bounds every wait inside the kernels to `polls` polls (0: every wait gives
- * up at once; negative: the kernels' own bounds, tens of milliseconds).  With a bound of 0 all kernels
- * still run to their end and stay inside their buffers, the results are invalid and the condition is
- * reported as described at snapkv_compress_ws_status.  Process-wide.  -2 also sets the count of
+ * up at once; negative: the kernels' own bounds, tens of milliseconds, or half of one for the two scoring passes in one
+ * launch).  With a bound of 0 all kernels still run to their end and stay inside their buffers; where the single-read kernel scored or the
+ * cooperative kernel selected, the results are invalid and the condition is reported as described at
+ * snapkv_compress_ws_status, while scores of the two passes in one launch are as valid as ever.  Process-wide.  -2 also sets the count of
  * snapkv_sync_timeouts back to zero (and synchronises the device for it).
  */
 int snapkv_debug_set_wait_limit(long long polls);

@@ -33,7 +33,7 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The two regions whose contents carry over between calls come first, at offsets that depend on
 // the number of KV heads only: pool_select's counters (zero when idle), then the hand-off words of
-// the single-read scoring kernel (all-ones when idle).  The selection's scratch and the scores are
+// the single-read scoring kernel, or of the two passes in one launch, which fit its region (all-ones when idle).  The selection's scratch and the scores are
 // sized for one selection per query head, which the per-query-head form of the step runs.
 size_t workspace_layout(const ScoreGeom& G, Workspace* ws, void* base) {
     constexpr size_t kHeader = 256;      // the status word (see Workspace::status_flag)

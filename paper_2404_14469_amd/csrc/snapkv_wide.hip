@@ -25,11 +25,11 @@
 //     once has a workgroup per slice.
 //
 // What bounds it: the stream of keys, and arithmetic that does not hide behind it.  32 layers of 32/8 heads of 31337 keys take
-// 402 + 481 us; before the statistics took their logits keys x rows 414 + 481, to which what follows belongs (back to back
-// 430 + 492; the single-read kernel 1218); the same loops without the arithmetic 384 + 471, with keys
-// that are always in the cache 334 + 351, and the keys alone 337 at 6.1 TB/s.  The votes' pass also stores 131 MB.  Counters
-// (profiles/sq_counters_gqa_two_pass.txt, 32768 keys): of the 781 thousand cycles of wide_stats a SIMD's matrix unit is busy
-// for 263 and its vector instructions take 436; of the 992 of wide_votes 262 and 443.  Tried on the way: all 128 rows in one
+// 406 + 480 us (one session differs from another by about ten of each).  What follows was measured when the statistics took their logits rows x
+// keys, in a session with 414 + 481 (back to back 430 + 492; the single-read kernel 1218): the same loops without the arithmetic 384 + 471, with keys
+// that are always in the cache 334 + 351, and the keys alone 337 at 6.1 TB/s.  The votes' pass also stores 131 MB.  Counters of the present
+// kernels (profiles/sq_counters_gqa_two_pass.txt, 32768 keys): of the 778 thousand cycles of wide_stats a SIMD's matrix unit is busy
+// for 263 and its vector instructions take 385 (rows x keys: 436); of the 960 of wide_votes 262 and 444.  Tried on the way: all 128 rows in one
 // wave with Q in LDS (two waves per SIMD, 425 + 512 us, and 240 registers); keys brought to LDS without registers, a ring of four
 // rounds of 64 keys (456 + 522); a second set of landing registers (spills).  At 131072 keys, W = 64 (two blocks per
 // head): 97 + 103 us against 277 us.
@@ -63,8 +63,8 @@
 // wide_stats takes its logits keys x rows (the operands exchanged): a lane has four keys of one row instead of one key of four rows, so
 // that it keeps two references and two sums instead of eight of each, and the sums over keys need an exchange between lanes only
 // once a slice, over four lanes instead of sixteen.  118 registers instead of 127, and microseconds per call, rows x keys / keys x rows: 28471
-// keys, 32/8 heads 56.85 / 56.39; 32749 token-major 59.33 / 58.47; 131072, W = 64 217.0 / 215.8; 32 layers of 31337 1062 / 1056 (two runs of one
-// side differ by 0.1 to 0.3 %).  The registers it frees are not enough for a second set of landing registers (14 to 18 spilled, 44.1 -> 48.0
+// keys, 32/8 heads 56.85 / 56.39; 32749 token-major 59.33 / 58.47; 131072, W = 64 217.0 / 215.8 (two runs of one
+// side differ by 0.1 to 0.3 %); the pass of 32 layers of 31337 keys, both in turn in one session, 409 (404 to 417) / 406 (403 to 411): no more than its runs differ.  The registers it frees are not enough for a second set of landing registers (14 to 18 spilled, 44.1 -> 48.0
 // for the two passes at 28471 keys); both rows' products piece by piece, for two chains of MFMAs and fewer registers of keys, change nothing.
 // The error of votes near the selection's threshold against float64 is what it was: over fifteen of the shapes and spreads named above
 // 0.999 of it on average, 0.988 to 1.008 singly.  wide_votes, which sums over rows, stays with rows x keys.
@@ -81,7 +81,7 @@
 
 namespace snapkv {
 
-__device__ unsigned g_wide_timeouts = 0;
+__device__ unsigned g_wide_timeouts = 0;   // workgroups of wide_once that reached the bound on their turns (none does, see there)
 
 bool reset_wide_timeouts() {
     const unsigned zero = 0;
@@ -130,6 +130,18 @@ constexpr float kRaiseBelow = 7.f;           //   to that logit less this
 //            14000: 95 / 85;  18000: 157 / 94;  three: 16384: 78 / 82 (as many keys as that kernel takes in one go)
 //   12 units: 12300: 58 / 50;  16 units: 12300: 66 / 53;  of 256 rows a KV head 6200: 50.7 / 45.1, two layers 67.8 / 65.5, three 86 / 74;
 //   32 units: 12300: 101 / 66;  16384: 101 / 72;  two layers 12300: 173 / 121
+// More than kMaxOnce units, which have the two launches, gain from the same line where a KV head has 128 rows, where it has 256 but for 8192 keys, and
+// in layers; with 512 rows and slices of one round (no more than 8192 keys) some single prompts lose a little:
+//   128 rows: 33 units: 12300: 99 / 79;  16384: 98 / 87;  40: 12300: 111 / 87;  16384: 112 / 104;  64: 12300: 164 / 118;  16384: 170 / 144;  two layers of 40:
+//            12300: 224 / 144;  16384: 226 / 205;  three of 33: 14000: 286 / 217
+//   256 rows: 34 units: 6200: 66 / 62;  8192: 66 / 63;  40: 6200: 71 / 66;  7680: 75 / 65;  8192: 70 / 75;  48: 6200: 79 / 71;  8192: 79 / 82;  56: 8192: 86 / 88;
+//            64: 6200: 95 / 79;  8192: 94 / 80;  two layers of 40: 6200: 142 / 91;  8192: 142 / 107
+//   512 rows: 36 units: 3100: 50 / 50;  3600: 52 / 55;  4096: 52 / 53;  4590: 67 / 53;  48: 3600: 56 / 59;  4096: 57 / 63;  64: 3600: 65 / 65;  4096: 65 / 58;
+//            two layers of 36: 4096: 104 / 68
+// Few layers from four units on, between these lines and 9 << 18: 4 units: two of 16400 keys 62 / 52, three of 18400 78 / 58;  8 units: two of 16400 99 / 67,
+// three 138 / 79;  12 units: two of 12300 84 / 72, three of 18000 194 / 104;  16 units of 256 rows: two of 6200 90 / 60, four 181 / 80.
+// Prompts of a batch between these lines and 9 << 18, which shared a joint launch before, mostly gain too, and lose where they are few among shorter ones
+// (compress_batch in snapkv_api.hip has the figures).
 constexpr int64_t min_row_keys(int64_t units) { return units > 8 ? 3 << 19 : units >= 4 ? (1 << 21) + 1 : 9 << 18; }
 // With 64 rows the single-read kernel is faster by 12 to 28 % up to 131072 keys, but for lengths that leave it compute units idle
 // (W = 16, 32/8 heads, this path / that kernel: 16384 keys 43 / 34, 40001: 61 / 62, 65536: 80 / 67, 90001: 98 / 103, 131072: 125 / 112;
@@ -806,13 +818,17 @@ __global__ __launch_bounds__(kThreads, 4) void wide_votes(const WideArgs<N> A) {
 // Microseconds per call, two launches / one (8 KV heads of four query heads, W = 32): 18500 keys 51.3 / 44.6; 24000 52.9 / 45.7; 32768 57.2 / 51.2;
 // 65536 80.2 / 71.2; 131072 128.7 / 114.0; one KV head 18500 35.0 / 32.0, 131072 48.1 / 45.0; on a caller's workspace, whose words a
 // launch before this one has to make ready (the first of two passes cleared the selection's counters on the way), 28471 keys 56.0 / 51.3.
-// Blocks of 64 rows, which begin at 131073 keys, keep the two launches.
+// Of keys that no cache holds (a rotation over 2 GB of prompts), before the prompt came here or in two launches / one: 17300 keys 59.5 / 45.9; 28471 59.2 / 52.3;
+// 65536 92.9 / 84.8; W = 64: 12300 59.2 / 47.7; 131072 219 / 199; one KV head 18433 34.2 / 31.4.  Counters (profiles/sq_counters_gqa_two_pass.txt), 32768 keys:
+// of 79 thousand cycles a SIMD's matrix unit is busy for 17 and its vector instructions take 34; 101 MB are read for 67 of keys.
+// Blocks of 64 rows, which begin at 131073 keys, keep the two launches, and so do the prompts of a batch that has two or more of this kind.
 //
 // No workgroup depends on another's being resident: other streams' kernels may hold its place, or wait for ours.  One that has polled for
 // kPatience takes the statistics of a missing slice itself, with the same instructions and so the same words (whose
 // writer is of no consequence), looks again without waiting, and in the end takes its own slice once more, so that the votes find LDS as they
 // expect it.  Workgroups take different slices (see snapkv_help.h), so that a unit of which r workgroups have places and m have none is
-// done after kPatience and 2 m / r + 2 slices' statistics at most or so, even if the others' places are not free until then.
+// done after kPatience and 2 m / r + 2 slices' statistics at most or so, even if the others' places are not free until then: half a millisecond
+// and, in the worst case of one workgroup with a place, the statistics of the whole unit, where two launches would have gone on with what places there are.
 constexpr unsigned kPatience = 1u << 9;      // polls (about half a millisecond)
 template <typename T, int D, bool PAGED>
 __global__ __launch_bounds__(kThreads, 4) void wide_once(const WideArgs<1> A) {
@@ -966,12 +982,14 @@ bool row_blocks(const ScoreGeom& G, Blocks* b) {
 
 // Rounds per slice and slices per unit.  They depend on the prompt and its own heads only, not on what else the call holds.
 // A prompt of more than kPlacesAll / kSlices units of 128 rows has as many slices per unit as still find a place all at once, so that it takes one
-// launch (wide_once).  Microseconds per call, 64 slices / this: 8 KV heads, W = 64, four query heads (16 units): 6200 keys 50.7 / 45.1;
-// 12300: 63.5 / 52.0;  28000: 79.9 / 61.3;  131072: 191.6 / 180.6;  12 units of W = 32: 20000: 65.9 / 50.7;  131072: 234 / 182;  32 units of
-// W = 128: 20000: 102 / 82;  131072: 459 / 432.  Layers of one call walk the same slices (a head's result is the same in every call), of which
-// each workgroup then has few and long ones: mostly the same or faster, and slower where few layers leave the last one to a part of the chip.  16 units,
-// 2 layers: 8500 keys 98 / 73;  12300: 76 / 80;  20000: 96 / 88;  32000: 119 / 110;  3: 8500: 131 / 82;  12300: 98 / 105;  17000: 111 / 120;  20000: 124 / 124;
-// 4: 10500: 103 / 108;  15000: 127 / 117;  24000: 171 / 156;  32000: 210 / 195;  6: 10500: 134 / 137;  17000: 184 / 183;  32000: 356 / 347.
+// launch (wide_once).  Microseconds per call, 64 slices / this: 8 KV heads, W = 64, four query heads (16 units): 6200 keys 50.2 / 38.9;
+// 12300: 56.0 / 46.9;  28000: 77.7 / 60.6;  131072: 192.8 / 179.8;  12 units of W = 32: 20000: 62.1 / 48.9;  131072: 210 / 185;  32 units of
+// W = 128: 20000: 95 / 77;  131072: 453 / 428.  Layers of one call walk the same slices (a head's result is the same in every call), of which
+// each workgroup then has few and long ones; with the votes shared out by rounds and the statistics' shares as share_of says (snapkv_shares.h) that
+// is mostly the same or faster.  16 units, 2 layers: 8500 keys 64 / 67;  12300: 72.9 / 74.7;  20000: 91 / 83;  32000: 122 / 112;  3: 8500: 81 / 79;  12300: 94 / 93;
+// 17000: 113 / 113;  20000: 123 / 122;  4: 10500: 101 / 99;  15000: 122 / 114;  24000: 166 / 153;  32000: 209 / 199;  6: 10500: 134 / 133;  17000: 182 / 181;  32000: 347 / 339;
+// 12 units: 2: 16384: 83 / 79;  3: 28000: 136 / 140.  A lane's sums run over up to four times as many rounds (32 units): the votes' error against float64, over
+// 24 settings, was 1.002 of that with 64 slices on average and at most 1.037, which is what the settings scatter by.
 int rounds_per_slice(const ScoreGeom& G, const Blocks& b) {
     auto rounds = [&](int64_t most) { return (G.L + kRound * most - 1) / (kRound * most); };
     const int64_t units = (int64_t)G.own_kv * b.nblk;
@@ -1034,8 +1052,8 @@ template <typename T, int D> hipError_t by_rows(const WideArgs<kMaxWide>& A, int
 }  // namespace
 
 // Whether these kernels take the prompt: enough window rows and keys (min_row_keys), and statistics that fit what a workspace
-// holds anyway (a region of the streaming passes, or the pooled scores that come later), a head at a time so that
-// the answer does not depend on how many heads a call has.
+// holds anyway (a region of the streaming passes, or the pooled scores that come later).  The answer depends on the prompt and on the KV heads of a
+// layer (own_kv), not on how many layers or prompts a call has: the place is looked at for one head.
 static bool wide_shape(const ScoreGeom& G, Blocks* b) {
     if (G.n <= 0 || !row_blocks(G, b)) return false;
     const int64_t least = b->ru == 8 ? min_row_keys((int64_t)G.own_kv * b->nblk) : b->UH == 2 ? kMinRowKeys64of2 : kMinRowKeys64;
