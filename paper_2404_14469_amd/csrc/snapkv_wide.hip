@@ -19,7 +19,7 @@
 //   * A round's keys pass through LDS (landing registers -> two buffers, one barrier a round), where four groups
 //     of waves x two parts of the keys (blocks of 64 rows: two groups x four parts) read them as fragments; the next round is on
 //     its way meanwhile.
-//   * A single prompt whose slices all find a place at once has both passes in one launch (wide_once).
+//   * A single prompt (or the only one of a batch that comes here) whose slices all find a place at once has both passes in one launch (wide_once).
 //   * Otherwise a persistent grid of two workgroups per compute unit walks the slices of all units (of all prompts or layers of
 //     the call) in order, a contiguous run of whole slices each (of the votes: of rounds); a launch of one prompt whose slices all find a place at
 //     once has a workgroup per slice.
