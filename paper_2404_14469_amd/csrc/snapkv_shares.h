@@ -18,20 +18,28 @@ constexpr unsigned whole_slices(unsigned in, unsigned rps) { return (in + rps - 
 // met in one L2 (4 layers of 15000, W = 64: 112 / 120).
 constexpr unsigned share_of(unsigned wg, unsigned grid, bool reversed) { return reversed && wg >= grid / 2 ? grid / 2 + (grid - 1 - wg) : wg; }
 
-// Whether it does: which order has the smaller largest sum of two such shares, or fewer of that size.  (Many slices a share: it hardly matters.)
+// Whether it does: which order has the smaller largest sum of two such shares, or fewer of that size.  (Many slices a share, or a grid of more workgroups
+// than any chip has places for: it hardly matters, or is not looked at.)  A share's end is the one before moved on by whole slices, not a
+// division: 1.7 us of host time for 512 workgroups, with divisions 3.7.
 inline bool reverse_shares(unsigned rounds, unsigned grid, unsigned rps) {
-    if (grid < 2 || rounds / rps / grid >= 32) return false;
-    const unsigned share = rounds / grid, more = rounds % grid, half = grid / 2;
-    auto length = [&](unsigned wg) { return whole_slices(begin_rounds(share, more, wg + 1), rps) - whole_slices(begin_rounds(share, more, wg), rps); };
+    constexpr unsigned kMost = 1024;
+    if (grid < 2 || grid > kMost || rounds / rps / grid >= 32) return false;
+    const unsigned share = rounds / grid, more = rounds % grid, half = grid / 2, whole = share / rps * rps;
+    unsigned length[kMost], begin = 0, from = 0;
+    for (unsigned wg = 0; wg < grid; ++wg) {
+        begin += share + (wg < more);
+        unsigned to = from + whole;      // (at most whole_slices(begin, rps))
+        while (to < begin) to += rps;
+        length[wg] = to - from;
+        from = to;
+    }
     unsigned most[2] = {0, 0}, times[2] = {0, 0};
-    for (unsigned wg = 0; wg < half; ++wg) {
-        const unsigned first = length(wg);
+    for (unsigned wg = 0; wg < half; ++wg)
         for (int r = 0; r < 2; ++r) {
-            const unsigned sum = first + length(share_of(wg + half, grid, r == 1));
+            const unsigned sum = length[wg] + length[share_of(wg + half, grid, r == 1)];
             if (sum > most[r]) most[r] = sum, times[r] = 0;
             times[r] += sum == most[r];
         }
-    }
     return most[1] < most[0] || (most[1] == most[0] && times[1] < times[0]);
 }
 
